@@ -287,7 +287,11 @@ int lbm_set_open_channel(lbm_ctx* ctx, const lbm_open_channel* oc);
  * for the last step of an odd batch, the library steps with shape 0.  Shapes
  * 21-23 are shape 16 with each strip cut into workgroups of 128, 64 and 32
  * rows (the rows next to a cut are collided by both neighbours).  Shape 20,
- * the default, makes two steps per launch with whole strips when there are
+ * the default, steps periodic channels of up to 1024 columns with the sweep
+ * kernel (any width; up to four steps per launch, the steps in between held
+ * in registers) where the active members are many enough for it to be the
+ * fastest, or whenever row ranges are given (lbm_set_run_rows).  Otherwise it
+ * makes two steps per launch with whole strips when there are
  * at least two per compute unit and with strips cut into the tallest row
  * ranges that give four workgroups per compute unit otherwise (32 rows at
  * the least); it steps with shape 0 while the active members give fewer
@@ -296,8 +300,9 @@ int lbm_set_open_channel(lbm_ctx* ctx, const lbm_open_channel* oc);
  */
 int lbm_set_tile(lbm_ctx* ctx, int32_t tile_id);
 int32_t lbm_tile_count(void);
-/* Lattice steps per launch that the next lbm_step_batch makes (1 or 2), for
-   the shape in use and the members active now. */
+/* Lattice steps per launch that the next lbm_step_batch makes at least (1 or
+   2; the default shape's sweep makes up to 4), for the shape in use and the
+   members active now. */
 int lbm_launch_steps(const lbm_ctx* ctx, int32_t* steps);
 /* Time every tile shape on this ensemble (n_steps each, on the context's
    stream, synchronising it) and keep the fastest.  Writes the chosen id.  If
@@ -312,7 +317,8 @@ int lbm_autotune(lbm_ctx* ctx, int32_t n_steps, int32_t* best_tile);
 /* Runs of consecutive members with one lattice shape: the ensemble's
    segments, each with its own row range in two-step launches. */
 int lbm_run_count(const lbm_ctx* ctx, int32_t* n_runs);
-/* Rows per workgroup of each run in two-step launches: rows[r] = -1 as the
+/* Rows per workgroup of each run in two-step launches, and per unit of the
+   default shape's sweep: rows[r] = -1 as the
    tile shape says (its own policy), 0 whole strips of 256 columns, else row
    ranges of rows[r] rows (a range of ny or more is a whole strip).  n_runs
    must be lbm_run_count's, or 0 (rows may then be NULL) to drop every

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <string.h>
 
 #include <vector>
 
@@ -41,6 +42,13 @@ struct RareScratch {
     int *new_parity_host = nullptr, *n_extra_host = nullptr;
 };
 
+// The sweep launch of a batch (steps 0: another kernel steps it).
+struct SweepPlan {
+    int steps;
+    lbm::SweepArgs args;
+    SweepPlan() { memset((void*)this, 0, sizeof *this); }  // compared byte by byte
+};
+
 // What a captured chunk of lbm_step_batch depends on besides device memory:
 // a replay is valid while all of it is unchanged.
 struct ChunkGraphKey {
@@ -48,12 +56,13 @@ struct ChunkGraphKey {
     int total_blocks, total_blocks2, compact;
     double mu, inv_sigma_dt;
     const void* ghost;
+    SweepPlan sweep;
     bool operator==(const ChunkGraphKey& o) const {
         return tile_id == o.tile_id && one_tile == o.one_tile && two == o.two && waves2 == o.waves2 &&
                table_gen == o.table_gen &&
                model == o.model && open == o.open && chunk == o.chunk && total_blocks == o.total_blocks &&
                total_blocks2 == o.total_blocks2 && compact == o.compact && mu == o.mu &&
-               inv_sigma_dt == o.inv_sigma_dt && ghost == o.ghost;
+               inv_sigma_dt == o.inv_sigma_dt && ghost == o.ghost && memcmp(&sweep, &o.sweep, sizeof sweep) == 0;
     }
 };
 

@@ -66,8 +66,11 @@ struct MemberDev {
     int ring;             // cells around the square that own drag partials: 4 s + 4
     double omega;         // 1 / tau
     double half_fx;       // F / 2 (Guo velocity shift)
-    double gf3, gf9;      // (1 - omega/2) * 3F and (1 - omega/2) * 9F (Guo source)
-    double force;         // F (central-moment collision)
+    double force;         // F
+    // coefficients of the BGK update (bgk_coefficients): the relaxation 1 - omega, and, for
+    // the axes (a, weight 1/9) and the diagonals (q, weight 1/36), the weight times 9/2 omega,
+    // 3 omega and the Guo source's 9 (1 - omega/2) F and 3 (1 - omega/2) F; a1 = omega / 9
+    double keep, a1, a45, a3, a9, ag, q45, q3, q9, qg;
     double sb, s3, s4;    // central-moment rates: trace, third order, fourth order
     int model;            // 0: BGK; 1: central moments; 2: central moments, unit bulk/third/fourth rates
     int open;             // 1: inlet, entrance grid, sponge and outlet instead of periodic x
@@ -83,6 +86,21 @@ struct MemberDev {
     double u_c;           // inlet centre-line velocity
     long long ghost_off;  // first float of the member's outlet ghost column [9][ny]
 };
+
+// The BGK update's coefficients from omega and the force.
+__host__ __device__ inline void bgk_coefficients(MemberDev& m) {
+    const double om = m.omega, g3 = (1.0 - 0.5 * om) * 3.0 * m.force, g9 = (1.0 - 0.5 * om) * 9.0 * m.force;
+    m.keep = 1.0 - om;
+    m.a1 = WD[1] * om;
+    m.a45 = WD[1] * (4.5 * om);
+    m.a3 = WD[1] * (3.0 * om);
+    m.a9 = WD[1] * g9;
+    m.ag = WD[1] * g3;
+    m.q45 = WD[5] * (4.5 * om);
+    m.q3 = WD[5] * (3.0 * om);
+    m.q9 = WD[5] * g9;
+    m.qg = WD[5] * g3;
+}
 
 // True if (x, y) is a cell of the member's square.
 __device__ __forceinline__ bool in_square(const MemberDev& m, int x, int y) {

@@ -41,6 +41,40 @@ struct StepArgs {
     const float* ghost;
 };
 
+constexpr int SWEEP_WAVES = 8;  // waves of a sweep workgroup at most
+constexpr int SWEEP_CELLS = 2;  // cells per lane (four: 172 registers of the four-step kernel spill, 2.2 x the time)
+
+// Members of one lattice shape in a sweep launch: a unit is the row range
+// `rows` of one member, `waves` waves wide; a workgroup holds units_per_block.
+struct SweepSegment {
+    int block_begin;
+    int member_begin;
+    int units;            // members x ranges
+    int ranges;           // row ranges per member
+    int rows;             // rows per range (the last may be shorter)
+    int waves;            // waves per unit, spanning the width
+    int lanes;            // lanes used of each wave (the last wave: what is left)
+    int units_per_block;
+};
+
+struct SweepArgs {
+    const MemberDev* members;
+    const int* parity;
+    const int* active;
+    const int* active_list;  // as StepArgs::active_list
+    float* pop0;
+    float* pop1;
+    double* partial;
+    int slot;                // chunk step of the launch's first step
+    int flip;
+    int xcd;
+    int total_blocks;
+    int block_waves;         // waves per workgroup
+    int width;               // 0: every width is a multiple of 64 SWEEP_CELLS
+    int nseg;
+    SweepSegment seg[MAX_SEGMENTS];
+};
+
 struct GhostArgs {
     const MemberDev* members;
     const int* parity;
@@ -82,7 +116,7 @@ struct TileShape {
     int r;      // rows per wave (a tile is 256 columns by tyt * r rows); 1 for two-step shapes
     int xcd;    // 1: remap workgroups so each XCD gets a contiguous range of tiles
     int steps;  // lattice steps per launch: 1, or 2 (a strip of 256 columns swept bottom to top)
-    int adaptive;  // two-step shape used only while the active members give a strip per CU
+    int adaptive;  // chooses between the sweep, the two-step kernel and shape 0 by the active members
     int seg_rows;  // two-step shapes: rows per workgroup (0: whole strips; -1: split only when
                    // the strips alone leave workgroup slots empty)
 };
@@ -95,6 +129,8 @@ hipError_t launch_step(int tile_id, const StepArgs& a, int model, hipStream_t st
 // two steps per launch, `waves` rows per iteration; the segment table must
 // describe strips of 256 columns (tiles_per_member = tiles_x = nx / 256)
 hipError_t launch_step2(int waves, const StepArgs& a, int model, hipStream_t st);
+// up to four steps per launch
+hipError_t launch_sweep(int steps, const SweepArgs& a, int model, hipStream_t st);
 hipError_t launch_init(const InitArgs& a, int n_members, long long max_cells, hipStream_t st);
 // the outlet ghost columns of the open-channel members for the next one-step launch
 hipError_t launch_outlet_ghost(const GhostArgs& a, int n_members, int max_ny, hipStream_t st);

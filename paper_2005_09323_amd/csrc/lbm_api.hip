@@ -203,6 +203,117 @@ static bool two_step_now(const lbm_ctx* c) {
     return 2 * groups >= 3LL * c->cu_count;
 }
 
+// Rows per unit of a sweep: the run's own choice (lbm_set_run_rows) or `rows`.
+static int sweep_rows(const lbm_ctx* c, int run, int ny, int rows) {
+    const int own = run < (int)c->run_rows.size() ? c->run_rows[run] : -1;
+    return std::max(1, std::min(own < 0 ? rows : own == 0 ? ny : own, ny));
+}
+
+// Estimated us of one sweep launch of `steps` steps with about `rows` rows per
+// unit.  A unit takes rows + 2 (steps - 1) iterations (the rows beside its own
+// that the later stages pull from, and the pipeline's fill) and about three
+// iterations' time to start; with two waves per SIMD (the registers allow no
+// more) an iteration takes 1.2 us plus 0.8 us per stage, alone on its SIMD
+// 0.6 of that; a memory pass is bounded by 4.8 TB/s (measured, MI355X:
+// 1 x 128 x 512 for a lone wave, 256 x 1024 x 128 for a full device).
+static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int rows, const int* members) {
+    const double slots = (double)c->cu_count * (SWEEP_WAVES / p.args.block_waves);
+    double load = 0.0, longest = 0.0, blocks = 0.0, bytes = 0.0;
+    for (int s = 0; s < c->nseg; ++s) {
+        const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
+        const int h = sweep_rows(c, s, d.ny, rows), ranges = (d.ny + h - 1) / h;
+        const double len = h + 2.0 * (p.steps - 1) + 3.0;
+        const int per = p.args.block_waves / p.args.seg[s].waves;
+        const double nb = std::ceil((double)members[s] * ranges / per);
+        blocks += nb;
+        load += nb * len;
+        longest = std::max(longest, len);
+        bytes += (double)members[s] * d.nx * (72.0 * d.ny + 72.0 * (p.steps - 1) * (ranges - 1));
+    }
+    const double rounds = c->nseg == 1 ? std::ceil(blocks / slots) * longest : std::max(longest, load / slots + 0.5 * longest);
+    const double fill = std::min(1.0, blocks / slots);
+    const double iteration = (1.2 + 0.8 * p.steps) * (fill > 0.5 ? 0.2 + 0.8 * fill : 0.6);
+    return std::max(rounds * iteration, bytes / 4.8e6) + 4.0;
+}
+
+// The sweep launch of the next batch (steps per launch and the table of units); false if another kernel should step it.  The sweep takes
+// lattices of up to 64 SWEEP_WAVES SWEEP_CELLS = 1024 columns in periodic channels; the
+// adaptive shape chooses it where its estimated time per step is below that of
+// the kernels it would use otherwise.
+static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
+    if (!TILE_SHAPES[c->tile_id].adaptive || c->open) return false;
+    const bool listed = !every_member && c->n_active < c->n && c->uniform_shape;
+    p = SweepPlan();
+    SweepArgs& a = p.args;
+    a.nseg = c->nseg;
+    a.block_waves = 1;
+    int members[MAX_SEGMENTS], tallest = 0;
+    double cells = 0.0;
+    for (int s = 0; s < c->nseg; ++s) {
+        const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
+        if (36LL * d.nx * d.ny >= (1LL << 31)) return false;
+        const int end = s + 1 < c->nseg ? c->seg[s + 1].member_begin : c->n;
+        const int lanes = (d.nx + SWEEP_CELLS - 1) / SWEEP_CELLS;
+        SweepSegment& g = a.seg[s];
+        g.member_begin = c->seg[s].member_begin;
+        g.waves = (lanes + 63) / 64;
+        g.lanes = (lanes + g.waves - 1) / g.waves;
+        if (g.waves > SWEEP_WAVES) return false;
+        a.block_waves = std::max(a.block_waves, g.waves);
+        if (d.nx % (64 * SWEEP_CELLS)) a.width = 1;
+        members[s] = listed ? c->n_active : end - g.member_begin;
+        tallest = std::max(tallest, d.ny);
+        cells += (double)members[s] * d.nx * d.ny;
+    }
+    double best = 1e300;
+    int rows = tallest;
+    for (int steps : {4, 2})
+        for (int parts = 1; parts <= tallest; ++parts) {
+            const int h = (tallest + parts - 1) / parts;
+            if (parts > 1 && h == (tallest + parts - 2) / (parts - 1)) continue;  // seen
+            SweepPlan q = p;
+            q.steps = steps;
+            const double t = sweep_cost(c, q, h, members) / steps;
+            if (t < best) {
+                best = t;
+                rows = h;
+                p.steps = steps;
+            }
+        }
+    bool chosen = false;  // row ranges given by the caller: sweep them
+    for (int r : c->run_rows) chosen = chosen || r >= 0;
+    if (!chosen) {
+        // the other kernels: two steps per launch at 130 G updates/s, or one per launch at 80 (rows of
+        // four cells per lane) or 50 (one cell per lane), and 6 us per launch
+        bool four = true;
+        for (int s = 0; s < c->nseg; ++s) four = four && c->seg[s].vec;
+        const double other = two_step_now(c) ? cells / 130e3 + 3.5 : cells / (four ? 80e3 : 50e3) + 6.0;
+        if (cells < 3e6 || best >= other) return false;
+    }
+    int blocks = 0;
+    for (int s = 0; s < c->nseg; ++s) {
+        const int ny = c->desc[c->seg[s].member_begin].ny;
+        SweepSegment& g = a.seg[s];
+        g.rows = sweep_rows(c, s, ny, rows);
+        g.ranges = (ny + g.rows - 1) / g.rows;
+        g.units_per_block = a.block_waves / g.waves;
+        if ((long long)members[s] * g.ranges + blocks > (1LL << 30)) return false;
+        g.units = members[s] * g.ranges;
+        g.block_begin = blocks;
+        blocks += (g.units + g.units_per_block - 1) / g.units_per_block;
+    }
+    a.total_blocks = blocks;
+    a.xcd = 1;
+    a.members = c->d_members;
+    a.parity = c->d_parity;
+    a.active = c->d_active;
+    a.active_list = listed ? c->d_active_list : nullptr;
+    a.pop0 = c->pop[0];
+    a.pop1 = c->pop[1];
+    a.partial = c->d_partial;
+    return true;
+}
+
 // Tables of the current tile shape.  A two-step shape applies when every
 // member's width is a multiple of 256 and its block fits 32-bit byte
 // offsets; otherwise (and for the last step of an odd chunk) the library
@@ -276,9 +387,8 @@ extern "C" int lbm_create(lbm_ctx** out, const lbm_member_desc* members, int32_t
         const double omega = 1.0 / d.tau;
         m.omega = omega;
         m.half_fx = 0.5 * d.force_x;
-        m.gf3 = (1.0 - 0.5 * omega) * 3.0 * d.force_x;
-        m.gf9 = (1.0 - 0.5 * omega) * 9.0 * d.force_x;
         m.force = d.force_x;
+        bgk_coefficients(m);
         m.sb = m.s3 = m.s4 = 1.0;
         m.model = 0;
         m.open = 0;
@@ -468,6 +578,8 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     }
     const int waves2 = TILE_SHAPES[c->tile_id].tyt;
     const bool two = two_step_now(c);
+    SweepPlan sweep;
+    const bool swept = plan_sweep(c, sweep, false);
     a.active_list = nullptr;
     a2.active_list = nullptr;
     a.ghost = c->open ? c->d_ghost : nullptr;
@@ -496,6 +608,13 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
         hipError_t e;
         int s = 0;
         launches = 0;
+        if (swept)
+            for (int t; s < chunk; s += t, ++launches) {
+                t = std::min(sweep.steps, chunk - s);
+                sweep.args.slot = s;
+                sweep.args.flip = launches & 1;
+                if ((e = launch_sweep(t, sweep.args, c->model, st)) != hipSuccess) return e;
+            }
         if (two)
             for (; s + 1 < chunk; s += 2, ++launches) {
                 a2.slot = s;
@@ -526,6 +645,10 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
             ChunkGraphKey key{c->tile_id, c->one_tile, two ? 1 : 0, waves2, c->model, c->open ? 1 : 0, chunk,
                               c->table_gen, a.total_blocks, a2.total_blocks, a.active_list ? 1 : 0, c->mu, c->dt / c->sigma,
                               (const void*)c->d_ghost};
+            if (swept) {
+                sweep.args.slot = sweep.args.flip = 0;
+                key.sweep = sweep;
+            }
             if (!c->graph_exec || !(key == c->graph_key)) {
                 free_chunk_graph(c);
                 if (!c->cap_stream && (e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking)) != hipSuccess)
@@ -814,8 +937,10 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         ms = -1.0f;
         if (build_segments(c) != LBM_OK) return LBM_OK;
         const TileShape ts = TILE_SHAPES[t];
-        if (ts.steps == 2 && !c->two_step) return LBM_OK;  // it would run shape 0
-        if (ts.adaptive) return LBM_OK;                    // a policy over shapes 16 and 0, not a shape
+        if (ts.steps == 2 && !ts.adaptive && !c->two_step) return LBM_OK;  // it would run shape 0
+        SweepPlan sweep;
+        // the adaptive shape: where it sweeps (it runs shape 16 or 0 otherwise)
+        if (ts.adaptive && !plan_sweep(c, sweep, true)) return LBM_OK;
         const bool two = ts.steps == 2;
         a.total_blocks = two ? c->total_blocks2 : c->total_blocks;
         a.split = two && c->split2 ? 1 : 0;
@@ -830,8 +955,13 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
                 hipError_t ge = launch_outlet_ghost(g, c->n, c->max_ny, c->stream);
                 if (ge != hipSuccess) return ge;
             }
+            if (ts.adaptive) {
+                sweep.args.flip = flip;
+                return launch_sweep(sweep.steps, sweep.args, c->model, c->stream);
+            }
             return two ? launch_step2(ts.tyt, a, c->model, c->stream) : launch_step(t, a, c->model, c->stream);
         };
+        const int steps_per_launch = ts.adaptive ? sweep.steps : ts.steps;
         // warm-up pair
         launch(0);
         launch(1);
@@ -845,7 +975,7 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         if (err != hipSuccess) return lbm_hip_fail(err, "autotune timing");
         float t_ms = 0;
         hipEventElapsedTime(&t_ms, e0, e1);
-        ms = t_ms / (float)(2 * pairs * ts.steps);
+        ms = t_ms / (float)(2 * pairs * steps_per_launch);
         return LBM_OK;
     };
     int rc = LBM_OK;
@@ -863,7 +993,7 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
     // workgroup), keeping whatever times best for the whole ensemble.
     c->tile_id = best;
     const int runs = count_runs(c);
-    if (rc == LBM_OK && TILE_SHAPES[best].steps == 2 && runs > 1 && build_segments(c) == LBM_OK && c->two_step) {
+    if (rc == LBM_OK && TILE_SHAPES[best].steps == 2 && !TILE_SHAPES[best].adaptive && runs > 1 && build_segments(c) == LBM_OK && c->two_step) {
         c->run_rows.assign(runs, -1);
         for (int r = 0; r < runs; ++r) c->run_rows[r] = c->seg2[r].rows >= c->desc[c->seg2[r].member_begin].ny ? 0 : c->seg2[r].rows;
         rc = time_shape(best, best_ms);  // the reference, timed next to the variants

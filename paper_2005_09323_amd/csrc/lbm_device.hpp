@@ -12,6 +12,20 @@
 
 namespace lbm {
 
+// The momentum that a cell's links hand to the square: 2 c_ix f_i^out over the
+// directions set in links (from the results before their rounding to FP32).
+__device__ __forceinline__ double link_momentum(unsigned links, double o1, double o3, double o5, double o6, double o7,
+                                                double o8) {
+    double drag = 0.0;
+    if ((links >> 1) & 1u) drag += 2.0 * o1;
+    if ((links >> 3) & 1u) drag -= 2.0 * o3;
+    if ((links >> 5) & 1u) drag += 2.0 * o5;
+    if ((links >> 6) & 1u) drag -= 2.0 * o6;
+    if ((links >> 7) & 1u) drag -= 2.0 * o7;
+    if ((links >> 8) & 1u) drag += 2.0 * o8;
+    return drag;
+}
+
 // BGK relaxation with Guo forcing of one cell, in deviation form:
 //   rho = 1 + sum d_i,  J = sum c_i d_i + F/2 = rho u,
 //   d_i^eq = w_i [(rho - 1) + 3 c.J + 4.5 (c.J)(c.u) - 1.5 J.u],
@@ -37,46 +51,42 @@ namespace lbm {
 // written in one expression may become one FMA, nothing across statements),
 // so that every kernel that inlines this function computes the same bits
 // whatever the optimizer does around it.
-__device__ __forceinline__ double bgk_guo(const MemberDev& m, float d[9], unsigned links) {
+__device__ __forceinline__ double bgk_guo(const MemberDev& m, float d[9], unsigned links, bool ring) {
 #pragma clang fp contract(on)
     const double d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3], d4 = d[4];
     const double d5 = d[5], d6 = d[6], d7 = d[7], d8 = d[8];
-    const double drho = ((d0 + d1) + (d2 + d3)) + ((d4 + d5) + (d6 + d7)) + d8;
-    const double jx = (((d1 - d3) + (d5 - d6)) + (d8 - d7)) + m.half_fx;
-    const double jy = ((d2 - d4) + (d5 - d7)) + (d6 - d8);
+    // sums and differences of opposite directions (8 - 6 as the second diagonal)
+    const double s13 = d1 + d3, s24 = d2 + d4, s57 = d5 + d7, s86 = d8 + d6;
+    const double e57 = d5 - d7, e86 = d8 - d6;
+    const double drho = d0 + ((s13 + s24) + (s57 + s86));
+    const double jx = ((d1 - d3) + (e57 + e86)) + m.half_fx;
+    const double jy = (d2 - d4) + (e57 - e86);
     const double rho = 1.0 + drho;
     // 1/rho: hardware FP32 reciprocal of rho rounded to FP32 (relative error
     // below 2e-7 together) refined by one Newton step in FP64, which squares
     // it: below 4e-14, far under the FP32 storage rounding
     double inv = (double)__builtin_amdgcn_rcpf((float)rho);
-    inv = inv * (2.0 - rho * inv);
+    inv = inv * fma(-rho, inv, 2.0);
     const double ux = jx * inv;
     const double uy = jy * inv;
-    const double om = m.omega;
-    const double keep = 1.0 - om;
-    const double c3 = 3.0 * om, c45 = 4.5 * om;
-    const double b = om * (drho - 1.5 * (jx * ux + jy * uy)) - m.gf3 * ux;
-    double drag = 0.0;
-    d[0] = (float)(keep * d0 + WD[0] * b);
-    // pair (ip, im) with c_ip = -c_im; e = c_ip.J, v = c_ip.u; xmove: c_ip,x = +1 (else 0)
-    auto pair = [&](int ip, int im, double dp, double dm, double e, double v, bool xmove) {
-#pragma clang fp contract(on)
-        const double even = xmove ? fma(c45 * e, v, fma(m.gf9, v, b)) : fma(c45 * e, v, b);
-        const double odd = xmove ? fma(c3, e, m.gf3) : c3 * e;
-        const double op = fma(keep, dp, WD[ip] * (even + odd));
-        const double on = fma(keep, dm, WD[im] * (even - odd));
-        if (xmove) {
-            if ((links >> ip) & 1u) drag += 2.0 * op;
-            if ((links >> im) & 1u) drag -= 2.0 * on;
-        }
+    const double keep = m.keep;
+    const double ba = fma(m.a1, fma(-1.5, fma(jy, uy, jx * ux), drho), -(m.ag * ux));  // b / 9
+    const double bq = 0.25 * ba;                                                        // b / 36
+    // e = c.J, v = c.u of the positive direction of a pair
+    auto pair = [&](int ip, int im, double dp, double dm, double even, double odd, double& op, double& on) {
+        op = fma(keep, dp, even + odd);
+        on = fma(keep, dm, even - odd);
         d[ip] = (float)op;
         d[im] = (float)on;
     };
-    pair(1, 3, d1, d3, jx, ux, true);
-    pair(2, 4, d2, d4, jy, uy, false);
-    pair(5, 7, d5, d7, jx + jy, ux + uy, true);
-    pair(8, 6, d8, d6, jx - jy, ux - uy, true);
-    return drag;
+    double o1, o3, o2, o4, o5, o7, o8, o6;
+    d[0] = (float)fma(4.0, ba, keep * d0);
+    pair(1, 3, d1, d3, fma(fma(m.a45, jx, m.a9), ux, ba), fma(m.a3, jx, m.ag), o1, o3);
+    pair(2, 4, d2, d4, fma(m.a45 * jy, uy, ba), m.a3 * jy, o2, o4);
+    const double ep = jx + jy, em = jx - jy;
+    pair(5, 7, d5, d7, fma(fma(m.q45, ep, m.q9), ux + uy, bq), fma(m.q3, ep, m.qg), o5, o7);
+    pair(8, 6, d8, d6, fma(fma(m.q45, em, m.q9), ux - uy, bq), fma(m.q3, em, m.qg), o8, o6);
+    return ring ? link_momentum(links, o1, o3, o5, o6, o7, o8) : 0.0;
 }
 
 // Central-moment multiple-relaxation-time collision with Guo forcing of one
@@ -97,7 +107,7 @@ __device__ __forceinline__ double bgk_guo(const MemberDev& m, float d[9], unsign
 //   population increments by the inverse of the D2Q9 raw-moment matrix.
 // With every rate equal to omega this is the BGK + Guo update.  Contraction
 // is pinned per source expression, as in bgk_guo.
-__device__ __forceinline__ double cm_guo(const MemberDev& m, float d[9], unsigned links) {
+__device__ __forceinline__ double cm_guo(const MemberDev& m, float d[9], unsigned links, bool ring) {
 #pragma clang fp contract(on)
     const double d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3], d4 = d[4];
     const double d5 = d[5], d6 = d[6], d7 = d[7], d8 = d[8];
@@ -154,18 +164,9 @@ __device__ __forceinline__ double cm_guo(const MemberDev& m, float d[9], unsigne
     const double o6 = d6 + 0.25 * ((M21 - M11) + (M22 - M12));
     const double o7 = d7 + 0.25 * ((M11 - M21) + (M22 - M12));
     const double o8 = d8 + 0.25 * ((M12 - M11) + (M22 - M21));
-    double drag = 0.0;
-    if (links) {
-        if ((links >> 1) & 1u) drag += 2.0 * o1;
-        if ((links >> 3) & 1u) drag -= 2.0 * o3;
-        if ((links >> 5) & 1u) drag += 2.0 * o5;
-        if ((links >> 6) & 1u) drag -= 2.0 * o6;
-        if ((links >> 7) & 1u) drag -= 2.0 * o7;
-        if ((links >> 8) & 1u) drag += 2.0 * o8;
-    }
     d[0] = (float)o0; d[1] = (float)o1; d[2] = (float)o2; d[3] = (float)o3; d[4] = (float)o4;
     d[5] = (float)o5; d[6] = (float)o6; d[7] = (float)o7; d[8] = (float)o8;
-    return drag;
+    return ring ? link_momentum(links, o1, o3, o5, o6, o7, o8) : 0.0;
 }
 
 // The central-moment collision above when the bulk, third- and fourth-order
@@ -181,76 +182,75 @@ __device__ __forceinline__ double cm_guo(const MemberDev& m, float d[9], unsigne
 // pre-collision second moments about u use j_x = rho u_x - F/2, j_y = rho u_y,
 // so each raw moment is a short sum.  Equal to cm_guo with those rates up to
 // FP64 rounding; contraction pinned as there.
-__device__ __forceinline__ double cm1_guo(const MemberDev& m, float d[9], unsigned links) {
+__device__ __forceinline__ double cm1_guo(const MemberDev& m, float d[9], unsigned links, bool ring) {
 #pragma clang fp contract(on)
     const double d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3], d4 = d[4];
     const double d5 = d[5], d6 = d[6], d7 = d[7], d8 = d[8];
-    const double dr = ((d0 + d1) + (d2 + d3)) + ((d4 + d5) + (d6 + d7)) + d8;  // rho - 1
+    // sums and differences of opposite directions (8 - 6 as the second diagonal)
+    const double s13 = d1 + d3, s24 = d2 + d4, s57 = d5 + d7, s86 = d8 + d6;
+    const double e57 = d5 - d7, e86 = d8 - d6;
+    const double dr = d0 + ((s13 + s24) + (s57 + s86));  // rho - 1
     const double rho = 1.0 + dr;
-    const double jx = ((d1 - d3) + (d5 - d6)) + (d8 - d7);
-    const double jy = ((d2 - d4) + (d5 - d7)) + (d6 - d8);
-    const double m11 = (d5 - d6) + (d7 - d8);
+    const double jx = (d1 - d3) + (e57 + e86);
+    const double jy = (d2 - d4) + (e57 - e86);
+    const double m11 = s57 - s86;
     double inv = (double)__builtin_amdgcn_rcpf((float)rho);
-    inv = inv * (2.0 - rho * inv);
+    inv = inv * fma(-rho, inv, 2.0);
     const double F = m.force;
     const double ux = (jx + m.half_fx) * inv, uy = jy * inv;
     const double uxx = ux * ux, uyy = uy * uy, uxy = ux * uy;
+    const double om1 = 1.0 - m.omega;
     // second order: k20 - k02 and k11 relax at omega, k20 + k02 goes to 2 rho / 3
     // (m20 - m02 = (d1 + d3) - (d2 + d4): the diagonal directions and the weights cancel)
-    const double kd = (((d1 + d3) - (d2 + d4)) - rho * (uxx - uyy)) + ux * F;
-    const double k11 = (m11 - rho * uxy) + 0.5 * F * uy;
-    const double om1 = 1.0 - m.omega;
-    const double a = 0.5 * om1 * kd;
+    const double uxf = ux * F, ruxx = rho * uxx, ruyy = rho * uyy, ruxy = rho * uxy;
+    const double kd = ((s13 - s24) - (ruxx - ruyy)) + uxf;
+    const double k11 = fma(m.half_fx, uy, m11 - ruxy);
+    const double a = (0.5 * om1) * kd;
     const double k11s = om1 * k11;
-    const double k20s = rho * (1.0 / 3.0) + a, k02s = rho * (1.0 / 3.0) - a;
+    const double k20s = fma(rho, 1.0 / 3.0, a), k02s = fma(rho, 1.0 / 3.0, -a);
     // post-collision raw moments (k10* = F/2, k01* = 0), as deviations from rest; the third
     // and fourth central moments (equilibrium plus half the source's) enter only through
     // what survives the shift
     const double m10s = jx + F;
-    const double dm20s = dr * (1.0 / 3.0) + a + ux * F + uxx * rho;
-    const double dm02s = dr * (1.0 / 3.0) - a + uyy * rho;
-    const double m11s = k11s + 0.5 * uy * F + uxy * rho;
-    const double m21s = 2.0 * ux * k11s + uy * k20s;
-    const double m12s = F * (1.0 / 6.0) + 2.0 * uy * k11s + ux * k02s;
-    const double dm22s = (dr * (1.0 / 9.0) + ux * F * (1.0 / 3.0)) + (uxx * k02s + uyy * k20s + 4.0 * uxy * k11s);
+    const double dm20s = (fma(dr, 1.0 / 3.0, a) + uxf) + ruxx;
+    const double dm02s = fma(dr, 1.0 / 3.0, -a) + ruyy;
+    const double m11s = fma(m.half_fx, uy, k11s) + ruxy;
+    const double k2 = 2.0 * k11s;
+    const double m21s = fma(ux, k2, uy * k20s);
+    const double m12s = fma(uy, k2, fma(ux, k02s, F * (1.0 / 6.0)));
+    const double dm22s = fma(dr, 1.0 / 9.0, uxf * (1.0 / 3.0)) + fma(2.0 * uxy, k2, fma(uyy, k20s, uxx * k02s));
     // populations (inverse of the raw-moment matrix), opposite directions as sum and
-    // difference of shared terms
-    const double ax = dm20s - dm22s, bx = m10s - m12s;  // f1 + f3 and f1 - f3 (deviations)
-    const double ay = dm02s - dm22s, by = jy - m21s;    // f2 + f4 and f2 - f4
-    const double t1 = dm22s + m12s, t2 = dm22s - m12s, t3 = m11s + m21s, t4 = m21s - m11s;
+    // difference of shared terms, each carrying its factor 1/2 or 1/4
+    const double ax = dm20s - dm22s, ay = dm02s - dm22s;
+    const double bx = 0.5 * (m10s - m12s), by = 0.5 * (jy - m21s);
+    const double t1 = dm22s + m12s, t2 = dm22s - m12s;
+    const double t3 = 0.25 * (m11s + m21s), t4 = 0.25 * (m21s - m11s);
     const double o0 = (dr - dm20s) - ay;
-    const double o1 = 0.5 * (ax + bx), o3 = 0.5 * (ax - bx);
-    const double o2 = 0.5 * (ay + by), o4 = 0.5 * (ay - by);
-    const double o5 = 0.25 * (t1 + t3), o8 = 0.25 * (t1 - t3);
-    const double o6 = 0.25 * (t2 + t4), o7 = 0.25 * (t2 - t4);
-    double drag = 0.0;
-    if (links) {
-        if ((links >> 1) & 1u) drag += 2.0 * o1;
-        if ((links >> 3) & 1u) drag -= 2.0 * o3;
-        if ((links >> 5) & 1u) drag += 2.0 * o5;
-        if ((links >> 6) & 1u) drag -= 2.0 * o6;
-        if ((links >> 7) & 1u) drag -= 2.0 * o7;
-        if ((links >> 8) & 1u) drag += 2.0 * o8;
-    }
+    const double o1 = fma(0.5, ax, bx), o3 = fma(0.5, ax, -bx);
+    const double o2 = fma(0.5, ay, by), o4 = fma(0.5, ay, -by);
+    const double o5 = fma(0.25, t1, t3), o8 = fma(0.25, t1, -t3);
+    const double o6 = fma(0.25, t2, t4), o7 = fma(0.25, t2, -t4);
     d[0] = (float)o0; d[1] = (float)o1; d[2] = (float)o2; d[3] = (float)o3; d[4] = (float)o4;
     d[5] = (float)o5; d[6] = (float)o6; d[7] = (float)o7; d[8] = (float)o8;
-    return drag;
+    return ring ? link_momentum(links, o1, o3, o5, o6, o7, o8) : 0.0;
 }
 
 // The collision of a kernel instantiated for one model (0: BGK, 1: central
 // moments, 2: central moments with unit bulk, third- and fourth-order rates);
 // the step kernels are compiled once per model so that each keeps its own
 // register allocation.
+// ring: whether any cell of the wave's row has links (wave-uniform; the drag
+// is not formed otherwise).
 template <int MODEL>
-__device__ __forceinline__ double collide_cell(const MemberDev& m, float d[9], unsigned links) {
-    if constexpr (MODEL == 2) return cm1_guo(m, d, links);
-    else if constexpr (MODEL == 1) return cm_guo(m, d, links);
-    else return bgk_guo(m, d, links);
+__device__ __forceinline__ double collide_cell(const MemberDev& m, float d[9], unsigned links, bool ring) {
+    if constexpr (MODEL == 2) return cm1_guo(m, d, links, ring);
+    else if constexpr (MODEL == 1) return cm_guo(m, d, links, ring);
+    else return bgk_guo(m, d, links, ring);
 }
 
 // The member's own model, decided at run time (the one-off initial step).
 __device__ __forceinline__ double collide_member(const MemberDev& m, float d[9], unsigned links) {
-    return m.model == 2 ? cm1_guo(m, d, links) : (m.model ? cm_guo(m, d, links) : bgk_guo(m, d, links));
+    return m.model == 2 ? cm1_guo(m, d, links, true) : (m.model ? cm_guo(m, d, links, true) : bgk_guo(m, d, links, true));
 }
 
 // The nine pulled populations of one cell (x, y) from the state at t, with
@@ -294,8 +294,7 @@ __device__ __forceinline__ void sponge_at(MemberDev& m, int x) {
     om = om * (2.0 - tau * om);
     om = om * (2.0 - tau * om);
     m.omega = om;
-    m.gf3 = (1.0 - 0.5 * om) * 3.0 * m.force;
-    m.gf9 = (1.0 - 0.5 * om) * 9.0 * m.force;
+    bgk_coefficients(m);
 }
 
 // Open channel inlet: the ghost column x = -1 holds the equilibrium of

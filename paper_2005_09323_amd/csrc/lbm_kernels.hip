@@ -43,9 +43,9 @@ __device__ __forceinline__ void scalar_cell(const MemberDev& m, const float* __r
     if (OPEN) {
         MemberDev mc = m;
         sponge_at(mc, x);
-        drag = collide_cell<MODEL>(mc, dl, links);
+        drag = collide_cell<MODEL>(mc, dl, links, ri >= 0);
     } else {
-        drag = collide_cell<MODEL>(m, dl, links);
+        drag = collide_cell<MODEL>(m, dl, links, ri >= 0);
     }
     const long long cell = (long long)y * nx + x;
 #pragma unroll
@@ -170,9 +170,9 @@ __device__ __forceinline__ void vec_row(const MemberDev& m, const float* __restr
         if (OPEN) {
             MemberDev mc = m;
             if (sponge_wave) sponge_at(mc, x0 + k);
-            drag = collide_cell<MODEL>(mc, dl, links);
+            drag = collide_cell<MODEL>(mc, dl, links, near_sq);
         } else {
-            drag = collide_cell<MODEL>(m, dl, links);
+            drag = collide_cell<MODEL>(m, dl, links, near_sq);
         }
 #pragma unroll
         for (int i = 0; i < 9; ++i) p[i][k] = dl[i];
@@ -395,7 +395,8 @@ static hipError_t launch_step_t(const StepArgs& a, int model, hipStream_t st) {
 // wave, whether workgroups are remapped so each XCD gets contiguous tiles,
 // and steps per launch.  Ids 0-15 are one-step shapes (launch_step switches
 // on id % 8); ids 16-19 are the two-step kernel with TYT rows per iteration;
-// id 20 is shape 16 while the active members fill the device, shape 0 otherwise.
+// ids 21-23 are shape 16 with shorter strips, and id 20 takes the sweep kernel (up to four steps
+// per launch), shape 16 or shape 0 by what the active members give.
 const TileShape TILE_SHAPES[] = {
     {4, 1, 1, 1, 0}, {4, 2, 1, 1, 0}, {8, 1, 1, 1, 0}, {2, 2, 1, 1, 0},
     {16, 1, 1, 1, 0}, {1, 4, 1, 1, 0}, {4, 4, 1, 1, 0}, {8, 2, 1, 1, 0},

@@ -114,9 +114,9 @@ __device__ __forceinline__ void collide_row(const MemberDev& m, f4 p[9], double*
         if (OPEN) {
             MemberDev mc = m;
             if (sponge) sponge_at(mc, x0 + k);
-            drag = collide_cell<MODEL>(mc, dl, links);
+            drag = collide_cell<MODEL>(mc, dl, links, near_sq);
         } else {
-            drag = collide_cell<MODEL>(m, dl, links);
+            drag = collide_cell<MODEL>(m, dl, links, near_sq);
         }
 #pragma unroll
         for (int i = 0; i < 9; ++i) p[i][k] = dl[i];
@@ -371,9 +371,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 if (OPEN) {
                     MemberDev mc = m;
                     if (sponge || base + 256 > m.sp_x0) sponge_at(mc, xh);
-                    collide_cell<MODEL>(mc, hv, 0u);
+                    collide_cell<MODEL>(mc, hv, 0u, false);
                 } else {
-                    collide_cell<MODEL>(m, hv, 0u);
+                    collide_cell<MODEL>(m, hv, 0u, false);
                 }
             }
             if (lane < 2) {
