@@ -34,58 +34,73 @@ __global__ __launch_bounds__(256) void ams_maxima_kernel(const float* series, in
     if (threadIdx.x == 0) maxima[m] = sbad[0] ? -INFINITY : smax[0];
 }
 
-// Exclusive scan of flags[0..n) into out[0..n) (slot order), returns the total.
+// Exclusive scan of flags[0..n) into out[0..n) (slot order), returns the total:
+// each thread adds a run of slots, the threads' totals are scanned within the
+// waves by shuffles and over the waves through sh.
 __device__ int block_exclusive_scan(const int* flags, int* out, int n, int* sh) {
-    const int t = (int)threadIdx.x, nt = (int)blockDim.x;
-    // each thread owns a contiguous run of slots
+    const int t = (int)threadIdx.x, nt = (int)blockDim.x, lane = t & 63, wave = t >> 6;
     const int per = (n + nt - 1) / nt;
     const int lo = min(n, t * per), hi = min(n, lo + per);
     int local = 0;
     for (int m = lo; m < hi; ++m) local += flags[m];
-    sh[t] = local;
-    __syncthreads();
-    if (t == 0) {
-        int acc = 0;
-        for (int k = 0; k < nt; ++k) {
-            const int v = sh[k];
-            sh[k] = acc;
-            acc += v;
-        }
-        sh[nt] = acc;
+    int inc = local;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += v;
     }
+    if (lane == 63) sh[wave] = inc;
     __syncthreads();
-    int run = sh[t];
+    int run = inc - local, total = 0;
+    for (int w = 0; w < nt / 64; ++w) {
+        if (w < wave) run += sh[w];
+        total += sh[w];
+    }
     for (int m = lo; m < hi; ++m) {
         out[m] = run;
         run += flags[m];
     }
-    const int total = sh[nt];
     __syncthreads();
     return total;
 }
 
+// One workgroup; its lists live in LDS.  512 members: 37.7 us while one thread
+// ran through the 1024 totals of each scan and every member counted its rank
+// over all others; 14.2 with the totals scanned by the waves and the level
+// searched bit by bit.
 __global__ __launch_bounds__(1024) void ams_select_kernel(AmsArgs a) {
     __shared__ float q[MAX_AMS];
     __shared__ int flag[MAX_AMS];
     __shared__ int pos[MAX_AMS];
     __shared__ int surv[MAX_AMS];
-    __shared__ int sh[1025];
-    __shared__ float level_sh;
+    __shared__ int sh[16];
+    __shared__ int below[32];
     const int t = (int)threadIdx.x, nt = (int)blockDim.x, n = a.n;
-    for (int m = t; m < n; m += nt) q[m] = a.maxima[m];
-    if (t == 0) level_sh = INFINITY;
-    __syncthreads();
-    // the n_kill-th lowest maximum: the value v with #{q < v} < n_kill <= #{q <= v}
-    for (int m = t; m < n; m += nt) {
-        int lt = 0, le = 0;
-        for (int j = 0; j < n; ++j) {
-            lt += q[j] < q[m];
-            le += q[j] <= q[m];
-        }
-        if (lt < a.n_kill && a.n_kill <= le) level_sh = q[m];  // every writer stores the same value
+    // the n_kill-th lowest maximum, bit by bit from the top of the values' order-preserving keys: the
+    // largest key with fewer than n_kill keys below it (a count over the block per bit)
+    constexpr int PER = MAX_AMS / 1024;
+    unsigned key[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int m = t + i * nt;
+        const float v = m < n ? a.maxima[m] : INFINITY;
+        if (m < n) q[m] = v;
+        const unsigned u = __float_as_uint(v + 0.0f);  // -0 and 0 are one value
+        key[i] = m < n ? (u >> 31 ? ~u : u | 0x80000000u) : 0xFFFFFFFFu;
     }
+    if (t < 32) below[t] = 0;
     __syncthreads();
-    const float level = level_sh;
+    unsigned found = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+        const unsigned cand = found | (1u << bit);
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) c += __popcll(__ballot(key[i] < cand));
+        if ((t & 63) == 0 && c) atomicAdd(&below[bit], c);
+        __syncthreads();
+        if (below[bit] < a.n_kill) found = cand;
+    }
+    const float level = __uint_as_float(found >> 31 ? found & 0x7FFFFFFFu : ~found);
     // killed: at or below the level (ties together), in slot order
     for (int m = t; m < n; m += nt) flag[m] = q[m] <= level ? 1 : 0;
     __syncthreads();

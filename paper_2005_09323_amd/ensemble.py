@@ -342,16 +342,17 @@ def ams_score_kill_branch(series: torch.Tensor, n_kill: int, key: int, iteration
     killed = torch.empty(n, dtype=torch.int32, device=dev)
     parent = torch.empty(n, dtype=torch.int32, device=dev)
     branch_t = torch.empty(n, dtype=torch.int32, device=dev)
-    n_killed = torch.empty(1, dtype=torch.int32, device=dev)
-    level = torch.empty(1, dtype=torch.float32, device=dev)
+    found = torch.empty(2, dtype=torch.int32, device=dev)  # the count and the level, read back together
+    n_killed, level = found[:1], found[1:].view(torch.float32)
     maxima = torch.empty(n, dtype=torch.float32, device=dev)
     native.check(native.lib().ams_score_kill_branch(_ptr(series), n, t_len, n_kill, key, iteration,
                                                     _ptr(killed), _ptr(parent), _ptr(branch_t),
                                                     _ptr(n_killed), _ptr(level), _ptr(maxima),
                                                     _stream_handle(None)))
-    k = int(n_killed.item())
-    return dict(killed=killed[:k], parents=parent[:k], branch_t=branch_t[:k], level=float(level.item()),
-                maxima=maxima, n_killed=k)
+    host = found.cpu()
+    k = int(host[0])
+    return dict(killed=killed[:k], parents=parent[:k], branch_t=branch_t[:k],
+                level=float(host[1:].view(torch.float32)[0]), maxima=maxima, n_killed=k)
 
 
 class ScoreNet:

@@ -109,30 +109,46 @@ def window_maxima(series: torch.Tensor, window: int) -> torch.Tensor:
     return fmax
 
 
-def tail_probability(fmax: torch.Tensor, log_weight: torch.Tensor, levels: Sequence[float]) -> np.ndarray:
-    """(1/N) sum_j exp(log_weight_j) [fmax_j >= a] for each level (device, FP64)."""
+def _tail_probability(fmax: torch.Tensor, log_weight: torch.Tensor, levels: Sequence[float]) -> torch.Tensor:
     lev = torch.tensor(list(levels), dtype=torch.float64, device=fmax.device)
     prob = torch.empty(len(lev), dtype=torch.float64, device=fmax.device)
     native.check(native.lib().tail_probability(_ptr(fmax), _ptr(log_weight.contiguous()), int(fmax.numel()),
                                                _ptr(lev), len(lev), _ptr(prob), _stream_handle(None)))
-    return prob.cpu().numpy()
+    return prob
+
+
+def tail_probability(fmax: torch.Tensor, log_weight: torch.Tensor, levels: Sequence[float]) -> np.ndarray:
+    """(1/N) sum_j exp(log_weight_j) [fmax_j >= a] for each level (device, FP64)."""
+    return _tail_probability(fmax, log_weight, levels).cpu().numpy()
+
+
+def _return_time(p: torch.Tensor, block: float, window: float) -> torch.Tensor:
+    r = torch.empty_like(p)
+    native.check(native.lib().return_times(_ptr(p), int(p.numel()), float(block), float(window), _ptr(r),
+                                           _stream_handle(None)))
+    return r
 
 
 def return_time(prob: np.ndarray, block: float, window: float) -> np.ndarray:
     """r(a) = -(T_a - T) / ln(1 - P(a)) (paper Appendix C.2); inf where P = 0 (device, FP64)."""
     p = torch.as_tensor(np.asarray(prob, dtype=np.float64)).reshape(-1).to("cuda").contiguous()
-    r = torch.empty_like(p)
-    native.check(native.lib().return_times(_ptr(p), int(p.numel()), float(block), float(window), _ptr(r),
-                                           _stream_handle(None)))
-    return r.cpu().numpy().reshape(np.shape(prob))
+    return _return_time(p, block, window).cpu().numpy().reshape(np.shape(prob))
+
+
+def _probability_and_time(fmax: torch.Tensor, log_weight: torch.Tensor, levels: Sequence[float], block: float,
+                          window: float):
+    """tail_probability and return_time of its result, read back together."""
+    p = _tail_probability(fmax, log_weight, levels)
+    both = torch.stack((p, _return_time(p, block, window))).cpu().numpy()
+    return both[0], both[1]
 
 
 def gktl_return_times(run: GktlRun, ens: Ensemble, window: int, levels: Sequence[float]):
     """Reweighted tail probability of the time-averaged drag and its return time (steps)."""
     tr = rebuild(run, ens)
     fmax = window_maxima(tr.series, window)
-    prob = tail_probability(fmax, tr.log_weight, levels)
-    return prob, return_time(prob, run.t_a, window), tr, fmax
+    prob, times = _probability_and_time(fmax, tr.log_weight, levels, run.t_a, window)
+    return prob, times, tr, fmax
 
 
 def direct_return_times(series: torch.Tensor, block: int, window: int, levels: Sequence[float]):
@@ -142,8 +158,8 @@ def direct_return_times(series: torch.Tensor, block: int, window: int, levels: S
     nb = length // block
     blocks = series[:, :nb * block].reshape(rows * nb, block)
     fmax = window_maxima(blocks, window)
-    prob = tail_probability(fmax, torch.zeros_like(fmax), levels)
-    return prob, return_time(prob, block, window), fmax
+    prob, times = _probability_and_time(fmax, torch.zeros_like(fmax), levels, block, window)
+    return prob, times, fmax
 
 
 # ---------------------------------------------------------------------------
