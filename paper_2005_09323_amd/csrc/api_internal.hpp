@@ -30,16 +30,17 @@ hipError_t fill_iota(int* p, int n, hipStream_t st);  // p[i] = i
 struct RareScratch {
     bool ready = false;
     int blocks_per_state = 0;
-    double *prefix = nullptr, *alpha = nullptr, *alpha_sum = nullptr, *scale = nullptr, *coef_w = nullptr;
+    double *alpha = nullptr, *alpha_sum = nullptr, *scale = nullptr, *coef_w = nullptr;
     double* mass_partial = nullptr;
     int *mode = nullptr, *src = nullptr, *need_mass = nullptr, *flags_new = nullptr, *status = nullptr;
     int* status_host = nullptr;
     // relabelling clone: new block and buffer of every slot, the slots written
     long long* new_off = nullptr;
     int *new_parity = nullptr, *extra = nullptr, *n_extra = nullptr;
-    // pinned read-back of the tables above (the host mirrors follow them)
+    // pinned copies of the tables above, written by the selection (the host mirrors follow them)
     long long* new_off_host = nullptr;
-    int *new_parity_host = nullptr, *n_extra_host = nullptr;
+    int* new_parity_host = nullptr;
+    hipEvent_t selected = nullptr;  // the selection of the last clone has run
 };
 
 // The sweep launch of a batch (steps 0: another kernel steps it).

@@ -13,57 +13,92 @@ namespace lbm {
 
 typedef float f4g __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ double block_max(double v, double* sh) {
-    const int t = (int)threadIdx.x, nt = (int)blockDim.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int s = nt / 2; s > 0; s >>= 1) {
-        if (t < s) sh[t] = fmax(sh[t], sh[t + s]);
-        __syncthreads();
+// The perturbation coefficients of member m and their sum (four words per
+// Philox block).
+__device__ __forceinline__ double draw_alphas(double* __restrict__ alpha, int m, int period, uint64_t key, int n_snap) {
+    double psum = 0.0;
+    for (int q0 = 0; q0 < n_snap; q0 += 4) {
+        const U64x4 w = philox4x64_10((uint64_t)m, (uint64_t)period, (uint64_t)(q0 / 4), 0, key, PURPOSE_PRTB);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (q0 + j >= n_snap) break;
+            const double al = uniform53(w.v[j]);
+            alpha[(long long)m * MAX_SNAP + q0 + j] = al;
+            psum += al;
+        }
     }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
+    return psum;
 }
 
-// One workgroup of 1024 threads; N <= MAX_SELECT.
+// One workgroup of 1024 threads; N <= MAX_SELECT.  The weights, the running
+// sum and every table the decisions need sit in LDS; one thread forms the
+// running sum in slot order, eight slots at a time (from memory, 256 members
+// took 50 of the kernel's 65 us; the kernel takes 17 now).  What the host needs of the result
+// goes straight to its pinned tables.
 __global__ __launch_bounds__(1024) void gktl_select_kernel(SelectArgs a) {
-    __shared__ double sh[1024];
+    __shared__ double prefix[MAX_SELECT];
     __shared__ int first_slot[MAX_SELECT];
-    __shared__ int n_live;
-    const int t = (int)threadIdx.x, nt = (int)blockDim.x, n = a.n;
+    __shared__ int anc_of[MAX_SELECT];
+    __shared__ int dead_state[MAX_SELECT];
+    __shared__ double wave_max[16];
+    __shared__ int wave_live[16], wave_dead[16], wave_extra[16];
+    const int t = (int)threadIdx.x, nt = (int)blockDim.x, n = a.n, lane = t & 63, wave = t >> 6;
     double mx = -INFINITY;
+    int live = 0;  // the last slot with a finite weight: the ancestor if u * total rounds up to total
     for (int m = t; m < n; m += nt) {
         const double s = a.k * a.accum[m];
-        if (isfinite(s)) mx = fmax(mx, s);
+        if (isfinite(s)) {
+            mx = fmax(mx, s);
+            live = m;
+        }
+        prefix[m] = s;
         first_slot[m] = 0x7fffffff;
     }
-    if (t == 0) n_live = 0;
-    mx = block_max(mx, sh);  // max is exact and order-free
-    if (!isfinite(mx)) {     // every weight non-finite: report and change nothing
-        if (t == 0) *a.status = 1;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {  // maxima are exact and order-free
+        mx = fmax(mx, __shfl_xor(mx, off, 64));
+        live = max(live, __shfl_xor(live, off, 64));
+    }
+    if (lane == 0) {
+        wave_max[wave] = mx;
+        wave_live[wave] = live;
+    }
+    __syncthreads();
+    for (int w = 0; w < 16; ++w) {
+        mx = fmax(mx, wave_max[w]);
+        live = max(live, wave_live[w]);
+    }
+    if (!isfinite(mx)) {  // every weight non-finite: report and change nothing
+        if (t == 0) {
+            *a.status = 1;
+            *a.status_host = 1;
+            if (a.relabel) *a.n_extra = 0;
+        }
         return;
     }
     // weights relative to the largest, then the running sum in slot order
     for (int m = t; m < n; m += nt) {
-        const double s = a.k * a.accum[m];
-        a.prefix[m] = isfinite(s) ? exp(s - mx) : 0.0;
+        const double s = prefix[m];
+        prefix[m] = isfinite(s) ? exp(s - mx) : 0.0;
     }
     __syncthreads();
     if (t == 0) {
         double acc = 0.0;
-        int last_live = 0;
-        for (int m = 0; m < n; ++m) {
-            if (isfinite(a.k * a.accum[m])) last_live = m;  // fallback ancestor if u * total rounds up to total
-            acc += a.prefix[m];
-            a.prefix[m] = acc;
+        int m = 0;
+        for (; m + 8 <= n; m += 8) {
+            double v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = prefix[m + j];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) prefix[m + j] = acc += v[j];
         }
-        n_live = last_live;
+        for (; m < n; ++m) prefix[m] = acc += prefix[m];
         *a.ln_r = mx + log(acc) - log((double)n);
         *a.status = 0;
+        *a.status_host = 0;
     }
     __syncthreads();
-    const double total = a.prefix[n - 1];
+    const double total = prefix[n - 1];
     for (int m = t; m < n; m += nt) {
         const U64x4 w = philox4x64_10((uint64_t)m, (uint64_t)a.period, 0, 0, a.key, PURPOSE_GKTS);
         const double target = uniform53(w.v[0]) * total;
@@ -71,65 +106,66 @@ __global__ __launch_bounds__(1024) void gktl_select_kernel(SelectArgs a) {
         int lo = 0, hi = n;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (a.prefix[mid] > target) hi = mid; else lo = mid + 1;
+            if (prefix[mid] > target) hi = mid; else lo = mid + 1;
         }
-        const int anc = lo < n ? lo : n_live;
+        const int anc = lo < n ? lo : live;
         a.ancestors[m] = anc;
+        anc_of[m] = anc;
+        a.need_mass[m] = 0;
         atomicMin(&first_slot[anc], m);  // lowest slot taking each ancestor: order-free
     }
     __syncthreads();
     for (int m = t; m < n; m += nt) {
-        const int anc = a.ancestors[m];
+        const int anc = anc_of[m];
         const int pert = (a.n_snap > 0 && a.eps != 0.0 && first_slot[anc] != m) ? 1 : 0;
         a.mode[m] = pert ? MODE_PERTURB : MODE_COPY;
         a.src[m] = anc;
         if (pert) {
-            double psum = 0.0;
-            for (int q = 0; q < a.n_snap; ++q) {
-                const U64x4 w = philox4x64_10((uint64_t)m, (uint64_t)a.period, (uint64_t)(q / 4), 0, a.key, PURPOSE_PRTB);
-                const double al = uniform53(w.v[q % 4]);
-                a.alpha[(long long)m * MAX_SNAP + q] = al;
-                psum += al;
-            }
-            a.alpha_sum[m] = psum;
+            a.need_mass[anc] = 1;  // parents of perturbed copies need their mass
+            a.alpha_sum[m] = draw_alphas(a.alpha, m, a.period, a.key, a.n_snap);
         }
     }
-    __syncthreads();
-    // parents of perturbed copies need their mass
-    for (int m = t; m < n; m += nt) a.need_mass[m] = 0;
-    __syncthreads();
-    for (int m = t; m < n; m += nt)
-        if (a.mode[m] == MODE_PERTURB) a.need_mass[a.src[m]] = 1;
     if (!a.relabel) return;
     // Relabelling: the first copy of each ancestor keeps the ancestor's block
     // and buffer; the k-th further copy (in slot order) takes the block of the
     // k-th state (in slot order) that left no descendant.  There are as many
     // such states as further copies, and no copy reads them.  Ranks by a
     // block-wide exclusive prefix count over slot order (each thread counts
-    // PER consecutive slots, then a scan over the threads).
+    // PER consecutive slots, then scans within and over the waves).
     constexpr int PER = MAX_SELECT / 1024;
-    __shared__ int scan_dead[1024], scan_extra[1024];
-    __shared__ int dead_state[MAX_SELECT];
     const int b0 = t * PER;
     int cd = 0, ce = 0;
     for (int j = 0; j < PER; ++j) {
         const int m = b0 + j;
         if (m < n) {
             cd += first_slot[m] == 0x7fffffff ? 1 : 0;
-            ce += first_slot[a.ancestors[m]] != m ? 1 : 0;
+            ce += first_slot[anc_of[m]] != m ? 1 : 0;
         }
     }
-    scan_dead[t] = cd;
-    scan_extra[t] = ce;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {  // inclusive scan (Hillis-Steele)
-        const int vd = t >= off ? scan_dead[t - off] : 0, ve = t >= off ? scan_extra[t - off] : 0;
-        __syncthreads();
-        scan_dead[t] += vd;
-        scan_extra[t] += ve;
-        __syncthreads();
+    int rd = cd, re = ce;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int vd = __shfl_up(rd, off, 64), ve = __shfl_up(re, off, 64);
+        if (lane >= off) {
+            rd += vd;
+            re += ve;
+        }
     }
-    int rd = scan_dead[t] - cd, re = scan_extra[t] - ce;  // exclusive ranks of this thread's first slot
+    if (lane == 63) {
+        wave_dead[wave] = rd;
+        wave_extra[wave] = re;
+    }
+    __syncthreads();
+    rd -= cd;
+    re -= ce;  // exclusive ranks of this thread's first slot
+    int total_extra = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) {
+            rd += wave_dead[w];
+            re += wave_extra[w];
+        }
+        total_extra += wave_extra[w];
+    }
     for (int j = 0; j < PER; ++j) {
         const int m = b0 + j;
         if (m < n && first_slot[m] == 0x7fffffff) dead_state[rd++] = m;
@@ -138,16 +174,18 @@ __global__ __launch_bounds__(1024) void gktl_select_kernel(SelectArgs a) {
     for (int j = 0; j < PER; ++j) {
         const int m = b0 + j;
         if (m >= n) break;
-        const int anc = a.ancestors[m];
-        a.new_parity[m] = a.parity[anc];
-        if (first_slot[anc] == m) {
-            a.new_off[m] = a.members[anc].off;
-        } else {
-            a.new_off[m] = a.members[dead_state[re]].off;
+        const int anc = anc_of[m], par = a.parity[anc];
+        long long off = a.members[anc].off;
+        if (first_slot[anc] != m) {
+            off = a.members[dead_state[re]].off;
             a.extra[re++] = m;
         }
+        a.new_parity[m] = par;
+        a.new_off[m] = off;
+        a.new_parity_host[m] = par;
+        a.new_off_host[m] = off;
     }
-    if (t == 1023) *a.n_extra = scan_extra[1023];
+    if (t == 0) *a.n_extra = total_extra;
 }
 
 // Host-chosen modes (in-place perturbation of selected members): fill the
@@ -159,16 +197,7 @@ __global__ void perturb_plan_kernel(PlanArgs a) {
     a.mode[m] = pert ? MODE_PERTURB : MODE_SKIP;
     a.src[m] = m;
     a.need_mass[m] = pert;
-    if (pert) {
-        double psum = 0.0;
-        for (int q = 0; q < a.n_snap; ++q) {
-            const U64x4 w = philox4x64_10((uint64_t)m, (uint64_t)a.period, (uint64_t)(q / 4), 0, a.key, PURPOSE_PRTB);
-            const double al = uniform53(w.v[q % 4]);
-            a.alpha[(long long)m * MAX_SNAP + q] = al;
-            psum += al;
-        }
-        a.alpha_sum[m] = psum;
-    }
+    if (pert) a.alpha_sum[m] = draw_alphas(a.alpha, m, a.period, a.key, a.n_snap);
 }
 
 // Sum of deviations over the fluid cells of one state, as fixed per-block
@@ -178,6 +207,7 @@ __global__ void perturb_plan_kernel(PlanArgs a) {
 __global__ __launch_bounds__(256) void mass_partial_kernel(MassArgs a) {
     const int j = (int)blockIdx.y;
     const bool snap = j >= a.n;
+    if (a.status && *a.status) return;  // the selection changed nothing
     if (!snap && !a.need_mass[j]) return;
     const MemberDev m = a.members[snap ? 0 : j];
     const long long plane = (long long)m.nx * m.ny;
@@ -227,21 +257,30 @@ __global__ __launch_bounds__(256) void mass_partial_kernel(MassArgs a) {
 // coefficient of the rest weights, c_w = s (1 + eps sum alpha) - 1.
 //   M_parent = N_fluid + sum d_parent,  M_n = N_fluid + sum d^(n),
 //   M_after = M_parent + eps sum_n alpha_n M_n,  s = M_parent / M_after.
-__global__ void mass_scale_kernel(ScaleArgs a) {
-    const int m = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (m >= a.n || a.mode[m] != MODE_PERTURB) return;
-    const double nf = a.n_fluid;
-    auto mass = [&](int j) {
+// One wave per member: lane 0 adds the parent's partials, lane 1 + q those of
+// snapshot q, each in block order (one thread doing all of it took 25 us for
+// 10 snapshots of 36 partials, 6 so).
+__global__ __launch_bounds__(64) void mass_scale_kernel(ScaleArgs a) {
+    const int m = (int)blockIdx.x, lane = (int)threadIdx.x;
+    if (a.status && *a.status) return;
+    if (a.mode[m] != MODE_PERTURB) return;
+    double mass = 0.0, al = 0.0;
+    if (lane <= a.n_snap) {
+        const double* p = a.partial + (long long)(lane == 0 ? a.src[m] : a.n + lane - 1) * a.blocks_per_state;
         double s = 0.0;
-        for (int b = 0; b < a.blocks_per_state; ++b) s += a.partial[(long long)j * a.blocks_per_state + b];
-        return nf + s;
-    };
-    const double mp = mass(a.src[m]);
+#pragma unroll 12
+        for (int b = 0; b < a.blocks_per_state; ++b) s += p[b];
+        mass = a.n_fluid + s;
+        if (lane > 0) al = a.alpha[(long long)m * MAX_SNAP + lane - 1];
+    }
+    const double mp = __shfl(mass, 0, 64);
     double add = 0.0;
-    for (int q = 0; q < a.n_snap; ++q) add += a.alpha[(long long)m * MAX_SNAP + q] * mass(a.n + q);
-    const double s = mp / (mp + a.eps * add);
-    a.scale[m] = s;
-    a.coef_w[m] = s * (1.0 + a.eps * a.alpha_sum[m]) - 1.0;
+    for (int q = 0; q < a.n_snap; ++q) add += __shfl(al, q + 1, 64) * __shfl(mass, q + 1, 64);
+    if (lane == 0) {
+        const double s = mp / (mp + a.eps * add);
+        a.scale[m] = s;
+        a.coef_w[m] = s * (1.0 + a.eps * a.alpha_sum[m]) - 1.0;
+    }
 }
 
 // New state of every member with mode != SKIP, written to the buffer that
@@ -333,109 +372,130 @@ __global__ void clone_commit_kernel(FinishArgs a) {
 // Relabelling clone: the further copies extra[PLACE_GROUP * blockIdx.y + g]
 // get their ancestor's state (copy) or its perturbation (the arithmetic of
 // clone_gather_kernel), written into their new blocks in the ancestor's
-// buffer.  A workgroup serves a group of copies over one stretch of cells, so
-// that each snapshot word is read once for the whole group.  Sources are
-// blocks of ancestors, destinations blocks of states without descendant:
-// never the same block.
-constexpr int PLACE_GROUP = 8;
+// buffer.  Sources are blocks of ancestors, destinations blocks of states
+// without descendant: never the same block.
+//
+// Bound by memory: a workgroup takes one stretch of 1024 values, holds it of
+// every snapshot in registers (FP64, NS >= n_snap of them, zeros beyond), and
+// runs through up to 32 copies, the next copy's source in flight while one is
+// formed; the copies' pointers and coefficients are gathered into LDS first.
+// 92 copies of 1024 x 256 from 10 snapshots: 756 us with groups of 8 copies
+// (the snapshots then cross the fabric 12 times, 1.1 of 2.8 GB, and every
+// stretch waited for the chain of small reads that gives a copy's pointers),
+// 468 us here (1.7 GB in and out: 3.7 TB/s).
+constexpr int PLACE_GROUP = 32;
 
+template <int NS>
 __global__ __launch_bounds__(256) void clone_place_kernel(PlaceArgs a) {
     const int g0 = (int)blockIdx.y * PLACE_GROUP;
-    const int ng = min(PLACE_GROUP, a.n_extra - g0);
-    const MemberDev m0 = a.members[a.src[a.extra[g0]]];
+    const int ng = min(PLACE_GROUP, *a.n_extra - g0);  // the count is 0 where the selection changed nothing
+    if (ng <= 0) return;
+    const int t = (int)threadIdx.x;
+    __shared__ const float* from[PLACE_GROUP];
+    __shared__ float* to[PLACE_GROUP];
+    __shared__ double al[PLACE_GROUP][NS > 0 ? NS : 1], sc[PLACE_GROUP], cw[PLACE_GROUP];
+    if (t < ng) {
+        const int m = a.extra[g0 + t], src = a.src[m];
+        float* const buf = a.parity[src] ? a.pop1 : a.pop0;
+        from[t] = buf + a.members[src].off;
+        to[t] = buf + a.new_off[m];
+        if (NS > 0) {
+            sc[t] = a.scale[m];
+            cw[t] = a.coef_w[m];
+        }
+    }
+    if constexpr (NS > 0)
+        for (int i = t; i < ng * NS; i += 256) {
+            const int g = i / NS, q = i - g * NS;
+            al[g][q] = q < a.n_snap ? a.alpha[(long long)a.extra[g0 + g] * MAX_SNAP + q] : 0.0;
+        }
+    const MemberDev& m0 = a.members[0];  // every member has one lattice shape
     const long long plane = (long long)m0.nx * m0.ny;
     const long long total = 9 * plane;
-    const long long e0 = 4 * ((long long)blockIdx.x * 256 + threadIdx.x);
+    const long long e0 = 4 * ((long long)blockIdx.x * 256 + t);
+    __syncthreads();
     if (e0 >= total) return;
-    const bool pert = a.n_snap > 0 && a.mode[a.extra[g0]] == MODE_PERTURB;  // all copies alike
+    const double eps = a.eps;
     if ((plane & 3) == 0) {
-        double ad[PLACE_GROUP][4];
+        double sn[NS > 0 ? NS : 1][4];
+        if constexpr (NS > 0)
 #pragma unroll
-        for (int g = 0; g < PLACE_GROUP; ++g)
+            for (int q = 0; q < NS; ++q) {
+                const f4g v = q < a.n_snap ? *(const f4g*)(a.snapshots + (long long)q * total + e0) : f4g{0, 0, 0, 0};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) ad[g][k] = 0.0;
-        if (pert) {
-            for (int q = 0; q < a.n_snap; ++q) {
-                const f4g sv = *(const f4g*)(a.snapshots + (long long)q * total + e0);
-#pragma unroll
-                for (int g = 0; g < PLACE_GROUP; ++g) {
-                    if (g >= ng) break;
-                    const double al = a.alpha[(long long)a.extra[g0 + g] * MAX_SNAP + q];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) ad[g][k] = perturb_acc(ad[g][k], al, sv[k]);
-                }
+                for (int k = 0; k < 4; ++k) sn[q][k] = (double)v[k];
             }
-        }
-        const int i = (int)(e0 / plane);
-        // the group's source words first: the stores below may alias them as far as
-        // the compiler knows, so loads after a store would wait for it
-        f4g vs[PLACE_GROUP];
-#pragma unroll
-        for (int g = 0; g < PLACE_GROUP; ++g) {
-            if (g >= ng) break;
-            const int src = a.src[a.extra[g0 + g]];
-            vs[g] = *(const f4g*)((a.parity[src] ? a.pop1 : a.pop0) + a.members[src].off + e0);
-        }
-#pragma unroll
-        for (int g = 0; g < PLACE_GROUP; ++g) {
-            if (g >= ng) break;
-            const int m = a.extra[g0 + g];
-            float* const buf = a.parity[a.src[m]] ? a.pop1 : a.pop0;
-            const f4g v = vs[g];
+        const double wi = WD[(int)(e0 / plane)];
+        f4g next = *(const f4g*)(from[0] + e0);
+#pragma unroll 1
+        for (int g = 0; g < ng; ++g) {
+            const f4g v = next;
+            if (g + 1 < ng) next = *(const f4g*)(from[g + 1] + e0);
             f4g out = v;
-            if (pert) {
-                const double s = a.scale[m], cw = a.coef_w[m] * WD[i], eps = a.eps;
+            if constexpr (NS > 0) {
+                double ad[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int k = 0; k < 4; ++k) out[k] = perturb_out(v[k], ad[g][k], s, eps, cw);
+                for (int q = 0; q < NS; ++q)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) ad[k] = fma(al[g][q], sn[q][k], ad[k]);
+                const double s = sc[g], c = cw[g] * wi;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) out[k] = perturb_out(v[k], ad[k], s, eps, c);
             }
-            __builtin_nontemporal_store(out, (f4g*)(buf + a.new_off[m] + e0));
+            __builtin_nontemporal_store(out, (f4g*)(to[g] + e0));
         }
         return;
     }
     const int cnt = (int)min((long long)4, total - e0);
-    for (int g = 0; g < ng; ++g) {
-        const int m = a.extra[g0 + g];
-        const int src = a.src[m];
-        float* const buf = a.parity[src] ? a.pop1 : a.pop0;
-        const float* sp = buf + a.members[src].off;
-        float* dp = buf + a.new_off[m];
+    for (int g = 0; g < ng; ++g)
         for (int k = 0; k < cnt; ++k) {
             const long long e = e0 + k;
-            if (!pert) {
-                dp[e] = sp[e];
-                continue;
+            if constexpr (NS == 0) {
+                to[g][e] = from[g][e];
+            } else {
+                double ad = 0.0;
+                for (int q = 0; q < a.n_snap; ++q) ad = perturb_acc(ad, al[g][q], a.snapshots[(long long)q * total + e]);
+                to[g][e] = perturb_out(from[g][e], ad, sc[g], eps, cw[g] * WD[(int)(e / plane)]);
             }
-            const int i = (int)(e / plane);
-            double ad = 0.0;
-            for (int q = 0; q < a.n_snap; ++q)
-                ad = perturb_acc(ad, a.alpha[(long long)m * MAX_SNAP + q], a.snapshots[(long long)q * total + e]);
-            dp[e] = perturb_out(sp[e], ad, a.scale[m], a.eps, a.coef_w[m] * WD[i]);
         }
+}
+
+// After the relabelling clone: every slot's block, buffer and flag (its
+// ancestor's, read before any is written: one workgroup).
+__global__ __launch_bounds__(1024) void clone_relabel_commit_kernel(CommitArgs a) {
+    if (*a.status) return;
+    constexpr int PER = MAX_SELECT / 1024;
+    const int t = (int)threadIdx.x;
+    int flag[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int m = t + 1024 * j;
+        flag[j] = m < a.n ? a.flags[a.src[m]] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int m = t + 1024 * j;
+        if (m >= a.n) break;
+        a.members[m].off = a.new_off[m];
+        a.parity[m] = a.new_parity[m];
+        a.accum[m] = 0.0;
+        a.flags[m] = flag[j];
     }
 }
 
-// After the relabelling clone: every slot's block, buffer and flag.
-__global__ void clone_relabel_commit_kernel(CommitArgs a) {
-    const int m = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (m >= a.n) return;
-    a.members[m].off = a.new_off[m];
-    a.parity[m] = a.new_parity[m];
-    a.accum[m] = 0.0;
-    a.flags[m] = a.flags_new[m];
-}
-
-hipError_t launch_place(const PlaceArgs& a, long long floats_per_member, hipStream_t st) {
-    if (a.n_extra == 0) return hipSuccess;
-    const unsigned gx = (unsigned)((floats_per_member / 4 + 255) / 256 + 1);
-    hipLaunchKernelGGL(clone_place_kernel, dim3(gx, (a.n_extra + PLACE_GROUP - 1) / PLACE_GROUP), dim3(256), 0, st, a);
+hipError_t launch_place(const PlaceArgs& a, int n, long long floats_per_member, hipStream_t st) {
+    if (n < 2) return hipSuccess;  // at most n - 1 further copies
+    const dim3 grid((unsigned)((floats_per_member + 1023) / 1024), (n - 1 + PLACE_GROUP - 1) / PLACE_GROUP), block(256);
+    if (a.n_snap == 0) hipLaunchKernelGGL(clone_place_kernel<0>, grid, block, 0, st, a);
+    else if (a.n_snap <= 4) hipLaunchKernelGGL(clone_place_kernel<4>, grid, block, 0, st, a);
+    else if (a.n_snap <= 10) hipLaunchKernelGGL(clone_place_kernel<10>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(clone_place_kernel<MAX_SNAP>, grid, block, 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_relabel_commit(const FinishArgs& f, const CommitArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(clone_finish_kernel, dim3((f.n + 255) / 256), dim3(256), 0, st, f);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(clone_relabel_commit_kernel, dim3((a.n + 255) / 256), dim3(256), 0, st, a);
+hipError_t launch_relabel_commit(const CommitArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(clone_relabel_commit_kernel, dim3(1), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 
@@ -452,7 +512,7 @@ hipError_t launch_mass(const MassArgs& a, int n_states, hipStream_t st) {
     return hipGetLastError();
 }
 hipError_t launch_scale(const ScaleArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(mass_scale_kernel, dim3((a.n + 255) / 256), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(mass_scale_kernel, dim3(a.n), dim3(64), 0, st, a);
     return hipGetLastError();
 }
 hipError_t launch_gather(const GatherArgs& a, long long floats_per_member, hipStream_t st) {

@@ -19,8 +19,7 @@ static int ensure_rare_scratch(lbm_ctx* c) {
     c->rare.blocks_per_state = (int)((floats + MASS_CHUNK - 1) / MASS_CHUNK);
     hipError_t e;
     RareScratch& r = c->rare;
-    if ((e = hipMalloc(&r.prefix, sizeof(double) * n)) != hipSuccess ||
-        (e = hipMalloc(&r.alpha, sizeof(double) * (size_t)n * MAX_SNAP)) != hipSuccess ||
+    if ((e = hipMalloc(&r.alpha, sizeof(double) * (size_t)n * MAX_SNAP)) != hipSuccess ||
         (e = hipMalloc(&r.alpha_sum, sizeof(double) * n)) != hipSuccess ||
         (e = hipMalloc(&r.scale, sizeof(double) * n)) != hipSuccess ||
         (e = hipMalloc(&r.coef_w, sizeof(double) * n)) != hipSuccess ||
@@ -37,7 +36,7 @@ static int ensure_rare_scratch(lbm_ctx* c) {
         (e = hipMalloc(&r.n_extra, sizeof(int))) != hipSuccess ||
         (e = hipHostMalloc(&r.new_off_host, sizeof(long long) * n)) != hipSuccess ||
         (e = hipHostMalloc(&r.new_parity_host, sizeof(int) * n)) != hipSuccess ||
-        (e = hipHostMalloc(&r.n_extra_host, sizeof(int))) != hipSuccess)
+        (e = hipEventCreateWithFlags(&r.selected, hipEventDisableTiming)) != hipSuccess)
         return lbm_hip_fail(e, "allocation of cloning scratch");
     r.ready = true;
     return LBM_OK;
@@ -45,7 +44,6 @@ static int ensure_rare_scratch(lbm_ctx* c) {
 
 void free_rare_scratch(lbm_ctx* c) {
     RareScratch& r = c->rare;
-    hipFree(r.prefix);
     hipFree(r.alpha);
     hipFree(r.alpha_sum);
     hipFree(r.scale);
@@ -63,13 +61,13 @@ void free_rare_scratch(lbm_ctx* c) {
     if (r.status_host) hipHostFree(r.status_host);
     if (r.new_off_host) hipHostFree(r.new_off_host);
     if (r.new_parity_host) hipHostFree(r.new_parity_host);
-    if (r.n_extra_host) hipHostFree(r.n_extra_host);
+    if (r.selected) hipEventDestroy(r.selected);
     r = RareScratch();
 }
 
 // Mass partials of the perturbed copies' parents and of the snapshots, and
 // each perturbed copy's scale, for the modes already in r.mode/r.src.
-static int run_mass_scale(lbm_ctx* c, double eps, const float* snapshots, int n_snap) {
+static int run_mass_scale(lbm_ctx* c, double eps, const float* snapshots, int n_snap, const int* status) {
     RareScratch& r = c->rare;
     hipError_t e;
     if (n_snap > 0 && eps != 0.0) {
@@ -77,6 +75,7 @@ static int run_mass_scale(lbm_ctx* c, double eps, const float* snapshots, int n_
         ma.members = c->d_members;
         ma.parity = c->d_parity;
         ma.need_mass = r.need_mass;
+        ma.status = status;
         ma.pop0 = c->pop[0];
         ma.pop1 = c->pop[1];
         ma.snapshots = snapshots;
@@ -85,6 +84,7 @@ static int run_mass_scale(lbm_ctx* c, double eps, const float* snapshots, int n_
         ma.blocks_per_state = r.blocks_per_state;
         if ((e = launch_mass(ma, c->n + n_snap, c->stream)) != hipSuccess) return lbm_hip_fail(e, "mass kernel");
         ScaleArgs sa;
+        sa.status = status;
         sa.mode = r.mode;
         sa.src = r.src;
         sa.partial = r.mass_partial;
@@ -111,7 +111,7 @@ static int run_mass_scale(lbm_ctx* c, double eps, const float* snapshots, int n_
 static int run_gather(lbm_ctx* c, double eps, const float* snapshots, int n_snap, int reset_accum) {
     RareScratch& r = c->rare;
     hipError_t e;
-    int rc = run_mass_scale(c, eps, snapshots, n_snap);
+    int rc = run_mass_scale(c, eps, snapshots, n_snap, nullptr);
     if (rc) return rc;
     GatherArgs ga;
     ga.members = c->d_members;
@@ -168,7 +168,6 @@ extern "C" int gktl_select_clone(lbm_ctx* c, double k, uint64_t key, int32_t per
     sa.n = c->n;
     sa.n_snap = n_snap;
     sa.eps = eps;
-    sa.prefix = r.prefix;
     sa.ln_r = ln_r_dev;
     sa.ancestors = ancestors_dev;
     sa.status = r.status;
@@ -184,69 +183,58 @@ extern "C" int gktl_select_clone(lbm_ctx* c, double k, uint64_t key, int32_t per
     sa.new_parity = r.new_parity;
     sa.extra = r.extra;
     sa.n_extra = r.n_extra;
+    sa.status_host = r.status_host;
+    sa.new_off_host = r.new_off_host;
+    sa.new_parity_host = r.new_parity_host;
     hipError_t e;
     if ((e = launch_select(sa, c->stream)) != hipSuccess) return lbm_hip_fail(e, "selection kernel");
-    // the all-non-finite case must leave the ensemble untouched: read the status (synchronises);
-    // relabelling also reads back where every slot's state goes (the host mirrors follow it)
+    // The all-non-finite case must leave the ensemble untouched: the gather waits for the selection's
+    // status, the relabelling's kernels read it themselves, so that they follow the selection without
+    // a gap and the host waits for the selection only (it writes the status and where every slot's
+    // state goes into pinned memory; the host mirrors follow).
     const int n = c->n;
-    if ((e = hipMemcpyAsync(r.status_host, r.status, sizeof(int), hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
-        return lbm_hip_fail(e, "selection status");
-    if (c->relabel &&
-        ((e = hipMemcpyAsync(r.n_extra_host, r.n_extra, sizeof(int), hipMemcpyDeviceToHost, c->stream)) != hipSuccess ||
-         (e = hipMemcpyAsync(r.new_off_host, r.new_off, sizeof(long long) * n, hipMemcpyDeviceToHost, c->stream)) !=
-             hipSuccess ||
-         (e = hipMemcpyAsync(r.new_parity_host, r.new_parity, sizeof(int) * n, hipMemcpyDeviceToHost, c->stream)) !=
-             hipSuccess))
-        return lbm_hip_fail(e, "selection tables");
-    if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return lbm_hip_fail(e, "selection status");
+    if ((e = hipEventRecord(r.selected, c->stream)) != hipSuccess) return lbm_hip_fail(e, "selection event");
+    if (c->relabel) {
+        // the first copy of every ancestor keeps its block; the other copies are written into blocks
+        // whose states left no descendant
+        if ((rc = run_mass_scale(c, eps, snapshots, n_snap, r.status))) return rc;
+        PlaceArgs pa;
+        pa.members = c->d_members;
+        pa.parity = c->d_parity;
+        pa.extra = r.extra;
+        pa.src = r.src;
+        pa.mode = r.mode;
+        pa.new_off = r.new_off;
+        pa.pop0 = c->pop[0];
+        pa.pop1 = c->pop[1];
+        pa.snapshots = snapshots;
+        pa.alpha = r.alpha;
+        pa.scale = r.scale;
+        pa.coef_w = r.coef_w;
+        pa.eps = eps;
+        pa.n_snap = (eps != 0.0) ? n_snap : 0;
+        pa.n_extra = r.n_extra;
+        if ((e = launch_place(pa, n, 9LL * c->h_members[0].nx * c->h_members[0].ny, c->stream)) != hipSuccess)
+            return lbm_hip_fail(e, "placement kernel");
+        CommitArgs ca;
+        ca.members = c->d_members;
+        ca.parity = c->d_parity;
+        ca.new_off = r.new_off;
+        ca.new_parity = r.new_parity;
+        ca.accum = c->accum;
+        ca.flags = c->d_flags;
+        ca.src = r.src;
+        ca.status = r.status;
+        ca.n = n;
+        if ((e = launch_relabel_commit(ca, c->stream)) != hipSuccess) return lbm_hip_fail(e, "relabelling commit");
+    }
+    if ((e = hipEventSynchronize(r.selected)) != hipSuccess) return lbm_hip_fail(e, "selection status");
     if (*r.status_host != 0) return lbm_fail(LBM_ENONFINITE, "every trajectory has a non-finite weight");
     if (!c->relabel) {
         if ((rc = run_gather(c, eps, snapshots, n_snap, 1))) return rc;
         for (int m = 0; m < n; ++m) c->h_parity[m] ^= 1;
         return LBM_OK;
     }
-    // relabelling: the first copy of every ancestor keeps its block; the other
-    // copies are written into blocks whose states left no descendant
-    if ((rc = run_mass_scale(c, eps, snapshots, n_snap))) return rc;
-    PlaceArgs pa;
-    pa.members = c->d_members;
-    pa.parity = c->d_parity;
-    pa.extra = r.extra;
-    pa.src = r.src;
-    pa.mode = r.mode;
-    pa.new_off = r.new_off;
-    pa.pop0 = c->pop[0];
-    pa.pop1 = c->pop[1];
-    pa.snapshots = snapshots;
-    pa.alpha = r.alpha;
-    pa.scale = r.scale;
-    pa.coef_w = r.coef_w;
-    pa.eps = eps;
-    pa.n_snap = (eps != 0.0) ? n_snap : 0;
-    pa.n_extra = *r.n_extra_host;
-    if (pa.n_extra < 0 || pa.n_extra > n)
-        return lbm_fail(LBM_EHIP, "selection reported %d further copies of %d", pa.n_extra, n);
-    if ((e = launch_place(pa, 9LL * c->h_members[0].nx * c->h_members[0].ny, c->stream)) != hipSuccess)
-        return lbm_hip_fail(e, "placement kernel");
-    FinishArgs fa;
-    fa.mode = r.mode;
-    fa.src = r.src;
-    fa.parity = c->d_parity;
-    fa.accum = c->accum;
-    fa.flags = c->d_flags;
-    fa.flags_new = r.flags_new;
-    fa.n = n;
-    fa.reset_accum = 1;
-    CommitArgs ca;
-    ca.members = c->d_members;
-    ca.parity = c->d_parity;
-    ca.new_off = r.new_off;
-    ca.new_parity = r.new_parity;
-    ca.accum = c->accum;
-    ca.flags = c->d_flags;
-    ca.flags_new = r.flags_new;
-    ca.n = n;
-    if ((e = launch_relabel_commit(fa, ca, c->stream)) != hipSuccess) return lbm_hip_fail(e, "relabelling commit");
     for (int m = 0; m < n; ++m) {
         c->h_members[m].off = r.new_off_host[m];
         c->h_parity[m] = r.new_parity_host[m];

@@ -23,6 +23,10 @@ struct SelectArgs {
     int* new_parity;    // [n] out (relabel): its buffer
     int* extra;         // [n] out (relabel): slots whose state is written (copies beyond the first), in order
     int* n_extra;       // [1] out (relabel)
+    // the host's pinned copies of status and of the two tables above
+    int* status_host;
+    long long* new_off_host;
+    int* new_parity_host;
     const double* accum;
     double k;
     uint64_t key;
@@ -30,7 +34,6 @@ struct SelectArgs {
     int n;
     int n_snap;
     double eps;
-    double* prefix;     // [n] scratch
     double* ln_r;       // [1] out
     int* ancestors;     // [n] out
     int* status;        // [1] out: 1 if every weight is non-finite
@@ -58,6 +61,7 @@ struct MassArgs {
     const MemberDev* members;
     const int* parity;
     const int* need_mass;
+    const int* status;       // null, or nonzero where the selection changed nothing
     const float* pop0;
     const float* pop1;
     const float* snapshots;  // [n_snap][9][ny][nx]
@@ -67,6 +71,7 @@ struct MassArgs {
 };
 
 struct ScaleArgs {
+    const int* status;  // as MassArgs::status
     const int* mode;
     const int* src;
     const double* partial;
@@ -115,7 +120,7 @@ struct PlaceArgs {
     const double* coef_w;
     double eps;
     int n_snap;
-    int n_extra;  // entries of extra
+    const int* n_extra;  // [1] entries of extra
 };
 
 struct CommitArgs {
@@ -125,7 +130,8 @@ struct CommitArgs {
     const int* new_parity;
     double* accum;
     int* flags;
-    const int* flags_new;
+    const int* src;     // [n] ancestor of each slot
+    const int* status;  // nonzero: the selection changed nothing
     int n;
 };
 
@@ -146,8 +152,8 @@ hipError_t launch_mass(const MassArgs& a, int n_states, hipStream_t st);
 hipError_t launch_scale(const ScaleArgs& a, hipStream_t st);
 hipError_t launch_gather(const GatherArgs& a, long long floats_per_member, hipStream_t st);
 hipError_t launch_finish(const FinishArgs& a, hipStream_t st);
-hipError_t launch_place(const PlaceArgs& a, long long floats_per_member, hipStream_t st);
-// flags_new[m] = flags[src[m]] (before any flag changes), then the commit
-hipError_t launch_relabel_commit(const FinishArgs& f, const CommitArgs& a, hipStream_t st);
+// (n members: at most n - 1 further copies)
+hipError_t launch_place(const PlaceArgs& a, int n, long long floats_per_member, hipStream_t st);
+hipError_t launch_relabel_commit(const CommitArgs& a, hipStream_t st);
 
 }  // namespace lbm
