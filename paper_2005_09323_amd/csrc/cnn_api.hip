@@ -79,6 +79,32 @@ extern "C" int32_t score_net_params(void) { return CNN_N_PARAMS; }
 
 extern "C" size_t score_net_workspace_bytes(int32_t batch) { return batch < 1 ? 0 : layout(batch).total; }
 
+namespace {
+// The pictures of n members (from m0 on, or the active ones), enqueued.
+int pictures(const lbm_ctx* c, int m0, const int* list, int n, int px0, int py0, int patch, int pool, double u_scale,
+             double rho_scale, float* out) {
+    FeatureArgs a;
+    a.members = c->d_members;
+    a.parity = c->d_parity;
+    a.pop0 = c->pop[0];
+    a.pop1 = c->pop[1];
+    a.m0 = m0;
+    a.list = list;
+    a.px0 = px0;
+    a.py0 = py0;
+    a.patch = patch;
+    a.pool = pool;
+    a.u_scale = u_scale;
+    a.rho_scale = rho_scale;
+    a.out = out;
+    // 16-byte loads of four cells: blocks, rows and the patch's first column all on 16 bytes
+    a.vec4 = pool == 4 && px0 % 4 == 0;
+    for (int m = 0; m < c->n && a.vec4; ++m) a.vec4 = c->desc[m].nx % 4 == 0 && c->h_members[m].off % 4 == 0;
+    hipError_t e = launch_features(a, n, c->stream);
+    return e == hipSuccess ? LBM_OK : lbm_hip_fail(e, "feature kernel");
+}
+}  // namespace
+
 extern "C" int score_features(const lbm_ctx* c, int32_t m0, int32_t n, int32_t px0, int32_t py0, int32_t patch,
                               int32_t pool, double u_scale, double rho_scale, float* out_dev) {
     if (!c || !out_dev) return lbm_fail(LBM_EINVAL, "NULL argument");
@@ -91,22 +117,7 @@ extern "C" int score_features(const lbm_ctx* c, int32_t m0, int32_t n, int32_t p
             return lbm_fail(LBM_EINVAL, "patch outside member %d", m);
     }
     if (n == 0) return LBM_OK;
-    FeatureArgs a;
-    a.members = c->d_members;
-    a.parity = c->d_parity;
-    a.pop0 = c->pop[0];
-    a.pop1 = c->pop[1];
-    a.m0 = m0;
-    a.list = nullptr;
-    a.px0 = px0;
-    a.py0 = py0;
-    a.patch = patch;
-    a.pool = pool;
-    a.u_scale = u_scale;
-    a.rho_scale = rho_scale;
-    a.out = out_dev;
-    hipError_t e = launch_features(a, n, c->stream);
-    return e == hipSuccess ? LBM_OK : lbm_hip_fail(e, "feature kernel");
+    return pictures(c, m0, nullptr, n, px0, py0, patch, pool, u_scale, rho_scale, out_dev);
 }
 
 extern "C" int score_features_active(const lbm_ctx* c, int32_t px0, int32_t py0, int32_t patch, int32_t pool,
@@ -126,22 +137,7 @@ extern "C" int score_features_active(const lbm_ctx* c, int32_t px0, int32_t py0,
             return lbm_fail(LBM_EINVAL, "patch outside member %d", m);
     }
     if (c->n_active == 0) return LBM_OK;
-    FeatureArgs a;
-    a.members = c->d_members;
-    a.parity = c->d_parity;
-    a.pop0 = c->pop[0];
-    a.pop1 = c->pop[1];
-    a.m0 = 0;
-    a.list = c->d_active_list;
-    a.px0 = px0;
-    a.py0 = py0;
-    a.patch = patch;
-    a.pool = pool;
-    a.u_scale = u_scale;
-    a.rho_scale = rho_scale;
-    a.out = out_dev;
-    hipError_t e = launch_features(a, c->n_active, c->stream);
-    return e == hipSuccess ? LBM_OK : lbm_hip_fail(e, "feature kernel");
+    return pictures(c, 0, c->d_active_list, c->n_active, px0, py0, patch, pool, u_scale, rho_scale, out_dev);
 }
 
 extern "C" int score_net_forward(const float* params_dev, const float* x_dev, int32_t batch, float* y_dev,

@@ -86,6 +86,7 @@ struct FeatureArgs {
     int m0;
     const int* list;  // member of output row b: list[b], or m0 + b where null
     int px0, py0, patch, pool;
+    int vec4;         // 1: pool 4, and every row of a patch starts on 16 bytes
     double u_scale, rho_scale;
     float* out;  // [n][3][patch/pool][patch/pool]
 };
