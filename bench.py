@@ -149,7 +149,7 @@ def _timed(fn, reps=1):
     return e0.elapsed_time(e1) / reps
 
 
-KERNEL_SOURCES = ("common.hpp", "kernels.hpp", "lbm_device.hpp", "lbm_kernels.hip", "lbm_step2.hip", "lbm_sweep.hip")
+KERNEL_SOURCES = ("common.hpp", "kernels.hpp", "lbm_device.hpp", "lbm_kernels.hip", "lbm_step2.hip", "lbm_sweep.hip", "lbm_resident.hip")
 
 
 def kernel_sources_sha256() -> str:

@@ -150,13 +150,26 @@ int lbm_set_active(lbm_ctx* ctx, const int32_t* active_host);
  * private stream) and replayed on the context's stream until the launch
  * configuration changes (tile shape, collision, open channel, number of
  * active members, observable), so that the host submits one graph per 64
- * steps instead of 33 to 129 kernel launches.
+ * steps instead of 17 to 129 kernel launches.  Where the default shape keeps
+ * the populations in registers for a whole chunk, a chunk is one launch for
+ * every 2048 x 128 x (1 to 6 rows) cells or so, and nothing is captured;
+ * batches of one or two steps, calls under a stream capture of the caller's and
+ * open channels are stepped by the other kernels.
  */
 int lbm_step_batch(lbm_ctx* ctx, int32_t n_steps);
 
 /* Replay captured chunks in lbm_step_batch (on = 1, the default) or launch
    every kernel of every chunk (on = 0).  Both give bit-identical results. */
 int lbm_set_graphs(lbm_ctx* ctx, int32_t on);
+
+/*
+ * Bound, in microseconds, of the waits between workgroups while the default
+ * shape keeps a small ensemble's populations in registers for a whole chunk of
+ * steps (20 000 unless set; below 0: no wait).  A chunk whose workgroups wait
+ * longer for one another (kernels of other streams hold part of the device) is
+ * stepped again by a kernel that waits for nothing: slower, the same results.
+ */
+int lbm_set_wait_limit(lbm_ctx* ctx, int32_t us);
 
 /* The drag on the square (paper Section 2.1: the x-force the flow exerts on
    the obstacle; here by momentum exchange, see the conventions above) of steps
@@ -287,10 +300,12 @@ int lbm_set_open_channel(lbm_ctx* ctx, const lbm_open_channel* oc);
  * for the last step of an odd batch, the library steps with shape 0.  Shapes
  * 21-23 are shape 16 with each strip cut into workgroups of 128, 64 and 32
  * rows (the rows next to a cut are collided by both neighbours).  Shape 20,
- * the default, steps periodic channels of up to 1024 columns with the sweep
- * kernel (any width; up to four steps per launch, the steps in between held
- * in registers) where the active members are many enough for it to be the
- * fastest, or whenever row ranges are given (lbm_set_run_rows).  Otherwise it
+ * the default, steps periodic channels of up to 1024 columns (any width) with
+ * the populations in registers for a whole chunk of steps (lbm_step_batch)
+ * where the active members fit in a few such launches, and with the sweep
+ * kernel (up to four steps per launch, the steps in between held in registers)
+ * where they are many enough for it to be the faster, or whenever row ranges
+ * are given (lbm_set_run_rows).  Otherwise it
  * makes two steps per launch with whole strips when there are
  * at least two per compute unit and with strips cut into the tallest row
  * ranges that give four workgroups per compute unit otherwise (32 rows at
@@ -301,7 +316,8 @@ int lbm_set_open_channel(lbm_ctx* ctx, const lbm_open_channel* oc);
 int lbm_set_tile(lbm_ctx* ctx, int32_t tile_id);
 int32_t lbm_tile_count(void);
 /* Lattice steps per launch that the next lbm_step_batch makes at least (1 or
-   2; the default shape's sweep makes up to 4), for the shape in use and the
+   2; the default shape's sweep makes up to 4, and a batch kept in registers
+   makes more than this says), for the shape in use and the
    members active now. */
 int lbm_launch_steps(const lbm_ctx* ctx, int32_t* steps);
 /* Time every tile shape on this ensemble (n_steps each, on the context's

@@ -21,6 +21,7 @@ struct MaskBits {
 hipError_t fill_int(int* p, int n, int v, hipStream_t st);
 hipError_t fill_double(double* p, int n, double v, hipStream_t st);
 hipError_t set_int(int* p, int v, hipStream_t st);
+hipError_t add_int(int* p, int n, int v, hipStream_t st);  // p[i] += v
 // p[m] = bit m; list (if non-null) = the set members in increasing order
 hipError_t set_bits(int* p, int* list, int n, const MaskBits& bits, hipStream_t st);
 hipError_t fill_iota(int* p, int n, hipStream_t st);  // p[i] = i
@@ -46,8 +47,21 @@ struct RareScratch {
 // The sweep launch of a batch (steps 0: another kernel steps it).
 struct SweepPlan {
     int steps;
+    double us;  // estimated time per step of the sweep, or of the kernels used instead
     lbm::SweepArgs args;
     SweepPlan() { memset((void*)this, 0, sizeof *this); }  // compared byte by byte
+};
+
+// The resident launches of a batch: each holds some of the members (all of
+// their rows) for the whole chunk.
+constexpr int RESIDENT_PASSES = 1 << lbm::RESIDENT_PASS_BITS;
+struct ResidentPlan {
+    int rows = 0;  // rows per wave
+    int passes = 0;
+    double us = 0.0;        // estimated time per step
+    double bytes = 0.0;     // of the state, read and written once
+    size_t halo_words = 0;  // of all passes
+    lbm::ResidentArgs args[RESIDENT_PASSES];
 };
 
 // What a captured chunk of lbm_step_batch depends on besides device memory:
@@ -86,6 +100,17 @@ struct lbm_ctx {
     int* d_active_list = nullptr;  // the n_active active members in ascending order
     int n_active = 0;
     int* d_flags = nullptr;
+    // resident chunks: words between workgroups (allocated when first needed), per member the chunks
+    // stepped so far and the one given up, the bound of a wait; the last batch's workgroups, how many of
+    // them a compute unit holds and the batch's end
+    unsigned long long* d_halo = nullptr;
+    size_t halo_words = 0;
+    int* d_epoch = nullptr;
+    int* d_given_up = nullptr;
+    long long wait_ticks = 2000000;  // 20 ms
+    int resident_blocks = 0, resident_places = 1, resident_chunks = 0;
+    hipEvent_t resident_done = nullptr;
+    int device = 0;
     std::vector<int> h_parity, h_cursor, h_active;
     double* d_partial = nullptr;
     long long partial_floats = 0;

@@ -75,6 +75,43 @@ struct SweepArgs {
     SweepSegment seg[MAX_SEGMENTS];
 };
 
+// Members of one lattice shape in a resident launch: a workgroup (unit) holds
+// `groups` groups of the launch's rows per wave of one member, `waves` waves
+// wide; `ranges` workgroups share a member.
+struct ResidentSegment {
+    int block_begin;
+    int member_begin;
+    int ranges;
+    int waves, lanes;      // as SweepSegment
+    int groups;
+    long long halo_begin;  // first halo word of the segment: [unit][side 2][slot 2][6][(nx + 1) / 2]
+};
+
+// A word's tag: the launch's number (below RESIDENT_EPOCHS), its pass and the step it is for.
+constexpr int RESIDENT_STEP_BITS = 7, RESIDENT_PASS_BITS = 4;
+constexpr int RESIDENT_EPOCHS = 1 << (32 - RESIDENT_STEP_BITS - RESIDENT_PASS_BITS);
+
+struct ResidentArgs {
+    const MemberDev* members;
+    const int* parity;
+    const int* active;
+    const int* active_list;  // as StepArgs::active_list (member_begin counts in it then)
+    float* pop0;
+    float* pop1;
+    double* partial;
+    unsigned long long* halo;
+    const int* epoch;        // per member: the launch's number (all alike; finalize counts it)
+    int* given_up;           // per member: the epoch whose chunk was given up
+    long long wait_ticks;    // bound of a wait (100 MHz clock); below 0: give up at the first
+    int n_steps;
+    int flip;                // as StepArgs::flip
+    int pass;
+    int total_blocks;
+    int block_waves;
+    int nseg;
+    ResidentSegment seg[MAX_SEGMENTS];
+};
+
 struct GhostArgs {
     const MemberDev* members;
     const int* parity;
@@ -109,6 +146,13 @@ struct FinalizeArgs {
     int swap_parity;     // parity of the number of buffer swaps in this chunk (one per kernel launch)
     double mu;
     double inv_sigma_dt; // dt / sigma
+    // resident chunks: per member the launch's number (counted here) and that of a chunk given up,
+    // which is stepped again here first, from the buffers below
+    int* epoch;
+    const int* given_up; // null: the chunk was not a resident one
+    float* pop0;
+    float* pop1;
+    double* redo_partial;
 };
 
 struct TileShape {
@@ -131,6 +175,8 @@ hipError_t launch_step(int tile_id, const StepArgs& a, int model, hipStream_t st
 hipError_t launch_step2(int waves, const StepArgs& a, int model, hipStream_t st);
 // up to four steps per launch
 hipError_t launch_sweep(int steps, const SweepArgs& a, int model, hipStream_t st);
+// a chunk of steps in one launch, `rows` (1, 2, 3, 4 or 6) rows per wave
+hipError_t launch_resident(int rows, const ResidentArgs& a, int model, hipStream_t st);
 hipError_t launch_init(const InitArgs& a, int n_members, long long max_cells, hipStream_t st);
 // the outlet ghost columns of the open-channel members for the next one-step launch
 hipError_t launch_outlet_ghost(const GhostArgs& a, int n_members, int max_ny, hipStream_t st);

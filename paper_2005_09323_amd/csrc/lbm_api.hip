@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <fstream>
+#include <mutex>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -48,6 +49,10 @@ __global__ void fill_double_kernel(double* p, int n, double v) {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (i < n) p[i] = v;
 }
+__global__ void add_int_kernel(int* p, int n, int v) {
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < n) p[i] += v;
+}
 __global__ void set_int_kernel(int* p, int v) { *p = v; }
 __global__ void iota_kernel(int* p, int n) {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -68,6 +73,10 @@ __global__ void set_bits_kernel(int* p, int* list, int n, MaskBits bits) {
 hipError_t fill_int(int* p, int n, int v, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_int_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n, v);
+    return hipGetLastError();
+}
+hipError_t add_int(int* p, int n, int v, hipStream_t st) {
+    hipLaunchKernelGGL(add_int_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n, v);
     return hipGetLastError();
 }
 hipError_t fill_double(double* p, int n, double v, hipStream_t st) {
@@ -203,6 +212,219 @@ static bool two_step_now(const lbm_ctx* c) {
     return 2 * groups >= 3LL * c->cu_count;
 }
 
+// Estimated us of one step of a resident launch with `rows` rows per wave: the
+// rows' time, with waves alone on their SIMD or two on each, or that of the
+// words between workgroups (`sides` rows of a wave handed to another
+// workgroup) if they take longer.  Measured, MI355X, one step: 1 x 256 x 64
+// with 1, 2, 3, 4, 6 rows 2.3, 3.3, 4.1, 5.0, 6.5 (lone waves, 512 columns 10 %
+// more); per launch of 64 x 512 x 128 with 2, 3, 4, 6 rows in workgroups of
+// eight waves 4.0, 5.2, 6.6, 8.9; the words: 4 x 512 x 128, one row, 4096 sides
+// 6.3 us, 2048 sides 3.6.
+static double resident_cost(int rows, bool two, double sides) {
+    static const double lone[] = {0, 2.4, 3.4, 4.3, 5.4, 0, 7.0}, both[] = {0, 3.0, 3.8, 5.0, 6.3, 0, 8.4};
+    return std::max((two ? both : lone)[rows], 1.5e-3 * sides) + 1.5e-4 * sides;
+}
+
+// The resident launches of the next batch, if the adaptive shape may have any: a
+// whole chunk of steps per launch with the populations in registers (periodic
+// channels of up to 1024 columns, all workgroups of a launch side by side on
+// the device: two waves per SIMD at most), as many launches as the members
+// need.  Rows per wave and waves per workgroup (four, two of them on a compute
+// unit, or eight) with the least estimated time: more rows per wave are fewer
+// launches, fewer rows a shorter step; eight waves hand half as many rows to
+// other workgroups as two times four (16 x 512 x 128: 7.0 us per step instead
+// of 7.7), four leave small ensembles a SIMD per wave (1 x 256 x 64: 2.3
+// instead of 2.5).
+static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) {
+    if (!TILE_SHAPES[c->tile_id].adaptive || c->open) return false;
+    for (int r : c->run_rows)
+        if (r >= 0) return false;  // row ranges given by the caller: the sweep's
+    hipStreamCaptureStatus captured;  // a replay would not be known to the other contexts' launches
+    if (hipStreamIsCapturing(c->stream, &captured) != hipSuccess || captured != hipStreamCaptureStatusNone) return false;
+    const bool listed = !every_member && c->n_active < c->n && c->uniform_shape;
+    double cells = 0.0;
+    int widest = 0;
+    for (int s = 0; s < c->nseg; ++s) {
+        const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
+        if (36LL * d.nx * d.ny >= (1LL << 31)) return false;
+        widest = std::max(widest, d.nx);
+        const int end = s + 1 < c->nseg ? c->seg[s + 1].member_begin : c->n;
+        cells += (double)(listed ? c->n_active : end - c->seg[s].member_begin) * d.nx * d.ny;
+    }
+    if (widest > 64 * SWEEP_WAVES * SWEEP_CELLS || cells > RESIDENT_PASSES * 1.6e6) return false;
+    // the launches with `rows` rows per wave and workgroups of `waves` waves (or one row of the lattice, if wider)
+    auto cut = [&](int rows, int waves, ResidentPlan& q) {
+        q.rows = rows;
+        q.passes = 0;
+        q.us = 0.0;
+        q.halo_words = 0;
+        int block_waves = 1;
+        for (int s = 0; s < c->nseg; ++s) {
+            const int w = (c->desc[c->seg[s].member_begin].nx + 64 * SWEEP_CELLS - 1) / (64 * SWEEP_CELLS);
+            block_waves = std::max(block_waves, w * std::max(1, waves / w));
+        }
+        const long long slots = (long long)c->cu_count * (SWEEP_WAVES / block_waves);
+        long long blocks = slots, sides = 0, words = 0;  // (no pass yet)
+        auto close = [&] {
+            if (!q.passes) return;
+            q.args[q.passes - 1].total_blocks = (int)blocks;
+            q.us += resident_cost(rows, blocks * block_waves > 4LL * c->cu_count, (double)sides);
+        };
+        for (int s = 0; s < c->nseg; ++s) {
+            const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
+            ResidentSegment g;
+            const int lanes = (d.nx + SWEEP_CELLS - 1) / SWEEP_CELLS;
+            g.waves = (lanes + 63) / 64;
+            g.lanes = (lanes + g.waves - 1) / g.waves;
+            g.groups = std::max(1, waves / g.waves);
+            g.ranges = (d.ny + g.groups * rows - 1) / (g.groups * rows);
+            if (g.ranges > slots) return false;
+            int m = listed ? 0 : c->seg[s].member_begin;
+            const int end = listed ? c->n_active : s + 1 < c->nseg ? c->seg[s + 1].member_begin : c->n;
+            while (m < end) {
+                if (slots - blocks < g.ranges) {  // another pass
+                    close();
+                    if (q.passes == RESIDENT_PASSES) return false;
+                    q.args[q.passes++].nseg = 0;
+                    blocks = sides = words = 0;
+                }
+                ResidentArgs& a = q.args[q.passes - 1];
+                const int here = (int)std::min<long long>(end - m, (slots - blocks) / g.ranges);
+                g.block_begin = (int)blocks;
+                g.member_begin = m;
+                g.halo_begin = words;
+                a.seg[a.nseg++] = g;
+                a.block_waves = block_waves;
+                blocks += (long long)here * g.ranges;
+                sides += 2LL * here * (g.ranges - 1) * g.waves;
+                words += (long long)here * g.ranges * 24 * ((d.nx + 1) / 2);
+                q.halo_words = std::max(q.halo_words, (size_t)words);
+                m += here;
+            }
+        }
+        close();
+        return q.passes > 0;
+    };
+    p.us = 1e300;
+    p.bytes = 72.0 * cells;
+    ResidentPlan q;
+    int best_rows = 0, best_waves = 0;
+    for (int waves : {4, 8}) {
+        for (int rows : {1, 2, 3, 4, 6}) {
+            if (cut(rows, waves, q) && q.us < p.us) {
+                p.us = q.us;
+                best_rows = rows;
+                best_waves = waves;
+            }
+        }
+    }
+    if (!best_rows || !cut(best_rows, best_waves, p)) return false;
+    for (int k = 0; k < p.passes; ++k) {
+        ResidentArgs& a = p.args[k];
+        a.members = c->d_members;
+        a.parity = c->d_parity;
+        a.active = c->d_active;
+        a.active_list = listed ? c->d_active_list : nullptr;
+        a.pop0 = c->pop[0];
+        a.pop1 = c->pop[1];
+        a.partial = c->d_partial;
+        a.halo = c->d_halo;
+        a.epoch = c->d_epoch;
+        a.given_up = c->d_given_up;
+        a.wait_ticks = c->wait_ticks;
+        a.flip = 0;
+        a.pass = k;
+    }
+    return true;
+}
+
+static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps, int flip, hipStream_t st) {
+    if (++c->resident_chunks >= RESIDENT_EPOCHS) {  // the words' tags would repeat: from the start again
+        hipError_t e;
+        if ((e = fill_int(c->d_epoch, c->n, 1, st)) != hipSuccess || (e = fill_int(c->d_given_up, c->n, 0, st)) != hipSuccess ||
+            (e = fill_int((int*)c->d_halo, (int)(2 * c->halo_words), 0, st)) != hipSuccess)
+            return e;
+        c->resident_chunks = 0;
+    }
+    for (int k = 0; k < p.passes; ++k) {
+        p.args[k].n_steps = steps;
+        p.args[k].flip = flip;
+        const hipError_t e = launch_resident(p.rows, p.args[k], c->model, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Another thread may be capturing a stream of its own: allocations and event
+// queries here are no part of that.
+struct OutsideCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// The words between workgroups, grown to the plan's need and cleared (no
+// launch's).  Later launches find older launches' words, whoever wrote them:
+// the members' epochs advance together, so no old word passes for a new one.
+// False if there is no memory for them (another kernel steps the batch then).
+static bool ensure_halo(lbm_ctx* c, ResidentPlan& p) {
+    const OutsideCapture outside;
+    if (p.halo_words > c->halo_words) {
+        if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
+        hipFree(c->d_halo);
+        c->d_halo = nullptr;
+        c->halo_words = 0;
+        if (hipMalloc(&c->d_halo, sizeof(unsigned long long) * p.halo_words) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (fill_int((int*)c->d_halo, (int)(2 * p.halo_words), 0, c->stream) != hipSuccess) return false;
+        c->halo_words = p.halo_words;
+    }
+    for (int k = 0; k < p.passes; ++k) p.args[k].halo = c->d_halo;
+    return true;
+}
+
+// The contexts of this process that have made resident launches.  Workgroups
+// of a resident launch wait for one another, so two launches that do not fit
+// on the device together must not run together: each could hold the places
+// that the other's missing workgroups need, until a wait reaches its limit.
+struct ResidentUsers {
+    std::mutex lock;
+    std::vector<lbm_ctx*> users;
+};
+static ResidentUsers& resident_users() {
+    static ResidentUsers* const u = new ResidentUsers;  // (contexts may outlive static destructors)
+    return *u;
+}
+
+// Before a resident launch of `c` (under the lock): its stream waits for the
+// other contexts' launches that are still running, if all of them together
+// are more than the device holds.
+static hipError_t admit_resident(lbm_ctx* c, ResidentUsers& u, const ResidentPlan& p) {
+    const OutsideCapture outside;
+    hipError_t e;
+    if (!c->resident_done) {
+        if ((e = hipEventCreateWithFlags(&c->resident_done, hipEventDisableTiming)) != hipSuccess) return e;
+        u.users.push_back(c);
+    }
+    c->resident_places = SWEEP_WAVES / p.args[0].block_waves;
+    c->resident_blocks = 0;
+    for (int k = 0; k < p.passes; ++k) c->resident_blocks = std::max(c->resident_blocks, p.args[k].total_blocks);
+    long long blocks = c->resident_blocks;
+    bool fit = true;
+    for (const lbm_ctx* o : u.users)
+        if (o != c && o->device == c->device && hipEventQuery(o->resident_done) == hipErrorNotReady) {
+            blocks += o->resident_blocks;
+            fit = fit && o->resident_places == c->resident_places;
+        }
+    (void)hipGetLastError();  // (not ready)
+    if (fit && blocks <= (long long)c->cu_count * c->resident_places) return hipSuccess;
+    for (const lbm_ctx* o : u.users)
+        if (o != c && o->device == c->device && (e = hipStreamWaitEvent(c->stream, o->resident_done, 0)) != hipSuccess) return e;
+    return hipSuccess;
+}
+
 // Rows per unit of a sweep: the run's own choice (lbm_set_run_rows) or `rows`.
 static int sweep_rows(const lbm_ctx* c, int run, int ny, int rows) {
     const int own = run < (int)c->run_rows.size() ? c->run_rows[run] : -1;
@@ -215,7 +437,10 @@ static int sweep_rows(const lbm_ctx* c, int run, int ny, int rows) {
 // iterations' time to start; with two waves per SIMD (the registers allow no
 // more) an iteration takes 1.2 us plus 0.8 us per stage, alone on its SIMD
 // 0.6 of that; a memory pass is bounded by 4.8 TB/s (measured, MI355X:
-// 1 x 128 x 512 for a lone wave, 256 x 1024 x 128 for a full device).
+// 1 x 128 x 512 for a lone wave, 256 x 1024 x 128 for a full device).  Units of
+// fewer than 32 rows take longer than that (us per launch of four steps, 12, 20
+// and 32 x 1024 x 256 in units of 13, 22 and 32 rows: 148, 194 and 204, without
+// the last factor 92, 130 and 184).
 static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int rows, const int* members) {
     const double slots = (double)c->cu_count * (SWEEP_WAVES / p.args.block_waves);
     double load = 0.0, longest = 0.0, blocks = 0.0, bytes = 0.0;
@@ -233,7 +458,7 @@ static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int rows, const i
     const double rounds = c->nseg == 1 ? std::ceil(blocks / slots) * longest : std::max(longest, load / slots + 0.5 * longest);
     const double fill = std::min(1.0, blocks / slots);
     const double iteration = (1.2 + 0.8 * p.steps) * (fill > 0.5 ? 0.2 + 0.8 * fill : 0.6);
-    return std::max(rounds * iteration, bytes / 4.8e6) + 4.0;
+    return std::max(rounds * iteration, bytes / 4.8e6) * (1.0 + 0.03 * std::max(0, 32 - rows)) + 4.0;
 }
 
 // The sweep launch of the next batch (steps per launch and the table of units); false if another kernel should step it.  The sweep takes
@@ -282,12 +507,15 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
         }
     bool chosen = false;  // row ranges given by the caller: sweep them
     for (int r : c->run_rows) chosen = chosen || r >= 0;
+    p.us = best;
     if (!chosen) {
         // the other kernels: two steps per launch at 130 G updates/s, or one per launch at 80 (rows of
         // four cells per lane) or 50 (one cell per lane), and 6 us per launch
         bool four = true;
         for (int s = 0; s < c->nseg; ++s) four = four && c->seg[s].vec;
         const double other = two_step_now(c) ? cells / 130e3 + 3.5 : cells / (four ? 80e3 : 50e3) + 6.0;
+        p.us = std::min(best, other);
+        if (cells < 3e6) p.us = other;
         if (cells < 3e6 || best >= other) return false;
     }
     int blocks = 0;
@@ -311,6 +539,30 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     a.pop0 = c->pop[0];
     a.pop1 = c->pop[1];
     a.partial = c->d_partial;
+    return true;
+}
+
+// Which kernel steps the next batch of n_steps with the adaptive shape:
+// resident launches (true), sweeps (`swept`) or neither, by the estimated
+// times.  us per step in long batches, resident launches and the others:
+// 1 x 256 x 64 2.3 and 6.8, 16 x 512 x 128 7.0 and 15.6, 64 x 512 x 128 26.5 and
+// 44, 20 x 1024 x 256 31.6 and 48.5, 32 x 1024 x 256 52.1 and 51.0, 256 x 512 x
+// 128 106 and 80 (the sweep's estimate is 10 % low where the two are close).  A
+// resident launch also takes 8 us and a copy of the state to begin and end:
+// calls of one step 19.5 and 14.9, 37 and 24, of two 21 and 22, 43 and 41, of
+// four 26 and 38, 55 and 75 for the first two sizes.
+static bool plan_batch(const lbm_ctx* c, int n_steps, ResidentPlan& resident, SweepPlan& sweep, bool& swept, bool every_member) {
+    const bool stays = plan_resident(c, resident, every_member);
+    swept = false;
+    if (stays && resident.passes == 1 && n_steps >= 4) return true;
+    swept = plan_sweep(c, sweep, every_member);
+    bool chosen = false;  // row ranges given by the caller: sweep them
+    for (int r : c->run_rows) chosen = chosen || r >= 0;
+    if (swept && n_steps < 4 && !chosen) swept = false;  // (64 x 512 x 128, calls of one step 93 and 66 us, of two 115 and 92)
+    if (!stays) return false;
+    const double start = n_steps < c->chunk ? 8.0 * resident.passes + resident.bytes / 5.2e6 : 0.0;  // (part of us, over a chunk)
+    if (start + resident.us * n_steps >= (swept ? 1.1 : 1.0) * sweep.us * n_steps) return false;
+    swept = false;
     return true;
 }
 
@@ -414,6 +666,7 @@ extern "C" int lbm_create(lbm_ctx** out, const lbm_member_desc* members, int32_t
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
             c->cu_count = cus;
+        c->device = dev;
     }
     int rc = build_segments(c);
     if (rc) {
@@ -428,6 +681,8 @@ extern "C" int lbm_create(lbm_ctx** out, const lbm_member_desc* members, int32_t
         (e = hipMalloc(&c->d_active, sizeof(int) * n_members)) != hipSuccess ||
         (e = hipMalloc(&c->d_active_list, sizeof(int) * n_members)) != hipSuccess ||
         (e = hipMalloc(&c->d_flags, sizeof(int) * n_members)) != hipSuccess ||
+        (e = hipMalloc(&c->d_epoch, sizeof(int) * n_members)) != hipSuccess ||
+        (e = hipMalloc(&c->d_given_up, sizeof(int) * n_members)) != hipSuccess ||
         (e = hipMalloc(&c->d_partial, sizeof(double) * c->partial_floats)) != hipSuccess ||
         (e = hipMalloc(&c->d_scratch, sizeof(double) * (4 * (size_t)n_members + 64))) != hipSuccess ||
         (e = hipMalloc(&c->d_iscratch, sizeof(int) * (4 * (size_t)n_members + 64))) != hipSuccess) {
@@ -443,6 +698,8 @@ extern "C" int lbm_create(lbm_ctx** out, const lbm_member_desc* members, int32_t
         (e = fill_int(c->d_cursor, n_members, 0, c->stream)) != hipSuccess ||
         (e = fill_int(c->d_active, n_members, 1, c->stream)) != hipSuccess ||
         (e = fill_iota(c->d_active_list, n_members, c->stream)) != hipSuccess ||
+        (e = fill_int(c->d_epoch, n_members, 1, c->stream)) != hipSuccess ||
+        (e = fill_int(c->d_given_up, n_members, 0, c->stream)) != hipSuccess ||
         (e = fill_int(c->d_flags, n_members, 0, c->stream)) != hipSuccess) {
         lbm_destroy(c);
         return lbm_hip_fail(e, "initialising bookkeeping");
@@ -461,6 +718,15 @@ extern "C" int lbm_destroy(lbm_ctx* c) {
     hipFree(c->d_active);
     hipFree(c->d_active_list);
     hipFree(c->d_flags);
+    hipFree(c->d_epoch);
+    hipFree(c->d_given_up);
+    hipFree(c->d_halo);
+    if (c->resident_done) {
+        ResidentUsers& u = resident_users();
+        const std::lock_guard<std::mutex> hold(u.lock);
+        u.users.erase(std::find(u.users.begin(), u.users.end(), c));
+        hipEventDestroy(c->resident_done);
+    }
     hipFree(c->d_partial);
     hipFree(c->d_scratch);
     hipFree(c->d_iscratch);
@@ -488,6 +754,11 @@ static FinalizeArgs finalize_args(lbm_ctx* c, int n, int accumulate, int swap_pa
     f.swap_parity = swap_parity;
     f.mu = c->mu;
     f.inv_sigma_dt = c->dt / c->sigma;
+    f.epoch = c->d_epoch;
+    f.given_up = nullptr;
+    f.pop0 = c->pop[0];
+    f.pop1 = c->pop[1];
+    f.redo_partial = c->d_partial;
     return f;
 }
 
@@ -578,8 +849,14 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     }
     const int waves2 = TILE_SHAPES[c->tile_id].tyt;
     const bool two = two_step_now(c);
+    ResidentPlan resident;
     SweepPlan sweep;
-    const bool swept = plan_sweep(c, sweep, false);
+    bool swept;
+    bool stays = plan_batch(c, n_steps, resident, sweep, swept, false);
+    if (stays && !ensure_halo(c, resident)) {
+        stays = false;
+        swept = plan_sweep(c, sweep, false);
+    }
     a.active_list = nullptr;
     a2.active_list = nullptr;
     a.ghost = c->open ? c->d_ghost : nullptr;
@@ -608,6 +885,13 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
         hipError_t e;
         int s = 0;
         launches = 0;
+        if (stays) {
+            launches = 1;  // every member's buffers swap once
+            if ((e = launch_resident_passes(c, resident, chunk, 0, st)) != hipSuccess) return e;
+            FinalizeArgs f = finalize_args(c, chunk, 1, 1);
+            f.given_up = c->d_given_up;
+            return launch_finalize(f, c->n, st);
+        }
         if (swept)
             for (int t; s < chunk; s += t, ++launches) {
                 t = std::min(sweep.steps, chunk - s);
@@ -638,10 +922,16 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     };
     hipError_t e;
     int done = 0;
+    std::unique_lock<std::mutex> hold;
+    if (stays) {
+        ResidentUsers& u = resident_users();
+        hold = std::unique_lock<std::mutex>(u.lock);
+        if ((e = admit_resident(c, u, resident)) != hipSuccess) return lbm_hip_fail(e, "resident launch");
+    }
     while (done < n_steps) {
         const int chunk = std::min(n_steps - done, c->chunk);
         int launches = 0;
-        if (c->graphs && chunk == c->chunk) {
+        if (c->graphs && chunk == c->chunk && !stays) {  // (a resident chunk is two launches)
             ChunkGraphKey key{c->tile_id, c->one_tile, two ? 1 : 0, waves2, c->model, c->open ? 1 : 0, chunk,
                               c->table_gen, a.total_blocks, a2.total_blocks, a.active_list ? 1 : 0, c->mu, c->dt / c->sigma,
                               (const void*)c->d_ghost};
@@ -684,6 +974,7 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
             }
         done += chunk;
     }
+    if (stays && (e = hipEventRecord(c->resident_done, c->stream)) != hipSuccess) return lbm_hip_fail(e, "resident launch");
     return LBM_OK;
 }
 
@@ -697,6 +988,12 @@ void free_chunk_graph(lbm_ctx* c) {
 extern "C" int lbm_set_graphs(lbm_ctx* c, int32_t on) {
     if (!c) return lbm_fail(LBM_EINVAL, "NULL context");
     c->graphs = on != 0;
+    return LBM_OK;
+}
+
+extern "C" int lbm_set_wait_limit(lbm_ctx* c, int32_t us) {
+    if (!c) return lbm_fail(LBM_EINVAL, "NULL context");
+    c->wait_ticks = us < 0 ? -1 : 100LL * us;
     return LBM_OK;
 }
 
@@ -939,8 +1236,11 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         const TileShape ts = TILE_SHAPES[t];
         if (ts.steps == 2 && !ts.adaptive && !c->two_step) return LBM_OK;  // it would run shape 0
         SweepPlan sweep;
-        // the adaptive shape: where it sweeps (it runs shape 16 or 0 otherwise)
-        if (ts.adaptive && !plan_sweep(c, sweep, true)) return LBM_OK;
+        // the adaptive shape: where it stays in registers or sweeps (it runs shape 16 or 0 otherwise)
+        ResidentPlan resident;
+        bool swept = false;
+        const bool stays = ts.adaptive && plan_batch(c, c->chunk, resident, sweep, swept, true) && ensure_halo(c, resident);
+        if (ts.adaptive && !stays && !swept) return LBM_OK;
         const bool two = ts.steps == 2;
         a.total_blocks = two ? c->total_blocks2 : c->total_blocks;
         a.split = two && c->split2 ? 1 : 0;
@@ -955,13 +1255,23 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
                 hipError_t ge = launch_outlet_ghost(g, c->n, c->max_ny, c->stream);
                 if (ge != hipSuccess) return ge;
             }
+            if (stays) {
+                const hipError_t re = launch_resident_passes(c, resident, c->chunk, flip, c->stream);
+                return re == hipSuccess ? add_int(c->d_epoch, c->n, 1, c->stream) : re;
+            }
             if (ts.adaptive) {
                 sweep.args.flip = flip;
                 return launch_sweep(sweep.steps, sweep.args, c->model, c->stream);
             }
             return two ? launch_step2(ts.tyt, a, c->model, c->stream) : launch_step(t, a, c->model, c->stream);
         };
-        const int steps_per_launch = ts.adaptive ? sweep.steps : ts.steps;
+        std::unique_lock<std::mutex> hold;  // until the timing has ended
+        if (stays) {
+            ResidentUsers& u = resident_users();
+            hold = std::unique_lock<std::mutex>(u.lock);
+            if (admit_resident(c, u, resident) != hipSuccess) return lbm_fail(LBM_EHIP, "resident launch");
+        }
+        const int steps_per_launch = stays ? c->chunk : ts.adaptive ? sweep.steps : ts.steps;
         // warm-up pair
         launch(0);
         launch(1);

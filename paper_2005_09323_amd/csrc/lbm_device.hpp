@@ -388,6 +388,31 @@ __device__ __forceinline__ unsigned square_links(const MemberDev& m, int x, int 
     return mask;
 }
 
+// Barrier that orders LDS accesses only (populations and words in flight to or
+// from memory stay in flight across it).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The value of the lane before (after) in the wave; the first (last) lane gets `in`.
+__device__ __forceinline__ float wave_shr1_in(float v, float in) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(in), __float_as_int(v), 0x138, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_shl1_in(float v, float in) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(in), __float_as_int(v), 0x130, 0xF, 0xF, false));
+}
+
+// A value the optimizer cannot see through: a row's two forms (the general one
+// beside walls and the square, the plain one elsewhere) share most of their
+// code, and merging it across their branch holds whole rows in FP64 there (72
+// registers more in the sweep kernel).
+__device__ __forceinline__ float pinned(float v) {
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+
 // Workgroup -> (member, tile): members are grouped in segments of equal
 // lattice shape; within a segment tiles run x-fastest, then y, then member.
 __device__ __forceinline__ int block_to_member(const StepArgs& a, int b, int& tx, int& ty, int& vec, int& rows) {

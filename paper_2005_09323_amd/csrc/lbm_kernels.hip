@@ -335,6 +335,34 @@ __global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
     if (ri >= 0) a.partial[m.part_off + ri] = drag;
 }
 
+// A resident chunk that was given up (lbm_resident.hip), stepped again by the
+// member's workgroup alone, cell by cell, from the source buffer that the
+// resident kernel only read; the last step's state ends in the other buffer.
+__device__ __noinline__ void resident_redo(const FinalizeArgs& a, const MemberDev& m, int par) {
+    float* const from = (par ? a.pop1 : a.pop0) + m.off;
+    float* const to = (par ? a.pop0 : a.pop1) + m.off;
+    const int cells = m.nx * m.ny;
+    for (int t = 0; t < a.n; ++t) {
+        const float* src = t & 1 ? to : from;
+        float* dst = t & 1 ? from : to;
+        double* part = a.redo_partial + m.part_off + (long long)t * m.ring;
+        for (int c = (int)threadIdx.x; c < cells; c += (int)blockDim.x) {
+            const int y = c / m.nx, x = c - y * m.nx;
+            if (m.model == 2) scalar_cell<2, false>(m, src, dst, part, nullptr, x, y);
+            else if (m.model == 1) scalar_cell<1, false>(m, src, dst, part, nullptr, x, y);
+            else scalar_cell<0, false>(m, src, dst, part, nullptr, x, y);
+        }
+        __syncthreads();
+    }
+    if (a.n % 2 == 0)
+        for (int c = (int)threadIdx.x; c < cells; c += (int)blockDim.x) {
+            const int y = c / m.nx, x = c - y * m.nx;
+            if (in_solid(m, x, y)) continue;
+            for (int i = 0; i < 9; ++i) to[(long long)i * cells + c] = from[(long long)i * cells + c];
+        }
+    __syncthreads();
+}
+
 // Reduce the drag partials of a chunk of n steps for one member per block:
 // f_d(s) = sum of ring partials in ring order (FP64), written to the series at
 // the member's cursor; then, in step order, accum += (f_d - mu)/sigma * dt.
@@ -342,15 +370,22 @@ __global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
 // place) and its cursor advances by n.
 __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
     const int mi = (int)blockIdx.x;
-    if (!a.active[mi]) return;
+    const int s = (int)threadIdx.x;
+    const bool on = a.active[mi];
     const MemberDev m = a.members[mi];
     __shared__ double fd[256];
-    const int s = (int)threadIdx.x;
+    if (a.given_up) {
+        if (on && a.given_up[mi] == a.epoch[mi]) resident_redo(a, m, a.parity[mi]);
+        __syncthreads();
+        if (s == 0) a.epoch[mi] += 1;  // every member's: the epochs advance together
+    }
+    if (!on) return;
     const int cur = a.cursor[mi];
     if (s < a.n) {
         double acc = 0.0;
         const double* p = a.partial + m.part_off + (long long)s * m.ring;
-        for (int r = 0; r < m.ring; ++r) acc += p[r];
+#pragma unroll 16
+        for (int r = 0; r < m.ring; ++r) acc += p[r];  // loads in flight, sums in order
         fd[s] = acc;
         a.series[(long long)mi * a.ld + cur + s] = (float)acc;
     }

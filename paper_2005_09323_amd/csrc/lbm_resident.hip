@@ -1,0 +1,402 @@
+// A whole chunk of lattice steps in one launch, with the populations in the
+// registers of the device.
+//
+// A wave holds R rows of up to 128 columns (two cells per lane), all nine
+// populations, from the first step of the chunk to the last; the waves of a
+// workgroup span one member's width and a few groups of R rows, and the
+// workgroups of a member share its height.  In a step a row pulls from the
+// rows and columns around it and is collided in place.  What leaves a wave
+// sideways passes through LDS (one 3-value exchange per row and side), what
+// leaves it up or down through LDS within the workgroup and through memory
+// between workgroups, as 8-byte words that carry their step beside the value:
+// a reader takes a word once its step is the one it waits for, so there is no
+// flag to order and no fence.  Two slots alternate; a workgroup can be at most
+// one step ahead of its neighbour.  The rows inside a wave come first in a
+// step, the lowest and the highest last: the words travel meanwhile.
+//
+// The wait for a neighbour is bounded: workgroups of a member run side by side
+// when the device is free (the host launches at most as many as fit), but
+// kernels of other streams may hold part of it.  A wave that waits longer than
+// its limit (lbm_set_wait_limit) gives the member's chunk up: it marks it and
+// leaves, every other wave of the member that waits leaves too, and the
+// chunk's drag reduction steps the member again from the untouched source
+// buffer, by itself (resident_redo).  So every wave ends, and the result never
+// depends on what ran beside.
+//
+// What bounds it: with few waves, a step's chain: a row's collision by a lone
+// wave (0.8 us) and the words' way to memory and back (1 x 256 x 64: 2.3 us
+// per step, 6.8 with one launch per step); with the registers full, the FP64
+// units (16 x 512 x 128, four rows per wave, two waves per SIMD: 7.0 us, 3.5 of
+// them the 204 FP64 instructions of a wave's row at 5.2 cycles of 2.4 GHz; 15.6
+// us with one launch per step).  Six rows are the most that 256 registers hold (eight
+// spill 73).  Rows in the order from the bottom up, waiting first: 9.3 us;
+// walls and square links worked out in each step instead of once: 8.7.
+#include "lbm_device.hpp"
+
+namespace lbm {
+
+constexpr int RC = 2;  // cells per lane
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+
+// (by value: a choice between two places would keep the populations in memory)
+__device__ __forceinline__ float pick(bool c, float a, float b) { return c ? a : b; }
+
+__device__ __forceinline__ void put_word(unsigned long long* p, float v, unsigned tag) {
+    __hip_atomic_store(p, ((unsigned long long)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long get_word(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int R, int MODEL>
+__global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void resident_kernel(ResidentArgs a) {
+    // columns beside a wave: [slot][wave][row][side]: side 0 its first cell (3, 6, 7), side 1 its last (1, 5, 8)
+    __shared__ f4 xe[2][SWEEP_WAVES][R][2];
+    // rows beside a wave of the workgroup: [slot][side][direction x cell of the lane][row group x lanes]:
+    // side 0 the group's lowest row (4, 7, 8), side 1 its highest (2, 5, 6)
+    __shared__ float yh[2][2][6 * 512];
+    // the lane's cells of a row beside a wall or the square: bits 0-7 the directions 1-8 that come from a wall or
+    // the square, bits 8-15 those that go to the square, from bit 16 the cell's place in the ring + 1
+    __shared__ u2 marks[SWEEP_WAVES][R][64];
+    const int b = (int)blockIdx.x;
+    int s = 0;
+#pragma unroll 1
+    while (s + 1 < a.nseg && b >= a.seg[s + 1].block_begin) ++s;
+    const ResidentSegment sg = a.seg[s];
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int W = sg.waves, g = wave / W, w = wave - g * W;  // row group and column wave
+    if (g >= sg.groups) return;
+    const int unit = b - sg.block_begin;
+    const int mloc = unit / sg.ranges, range = unit - mloc * sg.ranges;
+    const int mi = a.active_list ? a.active_list[sg.member_begin + mloc] : sg.member_begin + mloc;
+    const int on = a.active[mi];
+    const MemberDev m = a.members[mi];
+    const int par = a.parity[mi] ^ a.flip;
+    const int epoch = a.epoch[mi];
+    const unsigned tag0 = ((unsigned)epoch << RESIDENT_PASS_BITS | (unsigned)a.pass) << RESIDENT_STEP_BITS;  // tag of step t: + t + 1
+    if (!on) return;
+    const float* __restrict__ src = (par ? a.pop1 : a.pop0) + m.off;
+    float* __restrict__ dst = (par ? a.pop0 : a.pop1) + m.off;
+    const int nx = m.nx, ny = m.ny;
+    const unsigned plane = (unsigned)nx * (unsigned)ny;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, (int)(36u * plane), BUFFER_RSRC_WORD3);
+    const int base = w * sg.lanes * RC;
+    const int x0 = base + RC * lane;
+    const bool last_wave = w == W - 1;
+    const int lastl = last_wave ? (nx - base + RC - 1) / RC - 1 : sg.lanes - 1;
+    const bool one = last_wave && nx - base - RC * lastl == 1;  // the last lane has one cell
+    const int ys = (range * sg.groups + g) * R;                 // the wave's lowest row
+    const int rows = min(R, ny - ys);                           // <= 0: no row (it only meets the barriers)
+    const bool below = rows > 0 && ys > 0, above = rows == R && ys + R < ny;
+    const bool low_mem = below && g == 0, high_mem = above && g == sg.groups - 1;
+    const bool sq_cols = m.ss > 0 && base <= m.sx0 + m.ss && base + sg.lanes * RC - 1 >= m.sx0 - 1;
+    unsigned sqc = 0;  // bit j: column x0 - 1 + j crosses the square
+    if (sq_cols)
+#pragma unroll
+        for (int j = 0; j < RC + 2; ++j) sqc |= ((unsigned)(x0 - 1 + j - m.sx0) < (unsigned)m.ss ? 1u : 0u) << j;
+    // bit j: row ys - 1 + j is a wall, or crosses the square in the wave's columns; bit r: row ys + r is beside
+    // such a row, or may hold cells beside the square
+    unsigned wall_rows = 0, solid_rows = 0, near_rows = 0, ring_rows = 0;
+#pragma unroll
+    for (int j = 0; j < R + 2; ++j) {
+        const int y = ys - 1 + j;
+        wall_rows |= (y < 0 || y >= ny ? 1u : 0u) << j;
+        solid_rows |= (sq_cols && (unsigned)(y - m.sy0) < (unsigned)m.ss ? 1u : 0u) << j;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int y = ys + r;
+        near_rows |= (((wall_rows | solid_rows) >> r) & 7u ? 1u : 0u) << r;
+        ring_rows |= (r < rows && sq_cols && y >= m.sy0 - 1 && y <= m.sy0 + m.ss ? 1u : 0u) << r;
+    }
+#pragma unroll 1
+    for (int r = 0; r < R; ++r) {
+        if (!((near_rows >> r) & 1u)) continue;
+        const int y = ys + r;
+        unsigned word[RC];
+#pragma unroll
+        for (int k = 0; k < RC; ++k) {
+            word[k] = 0;
+#pragma unroll
+            for (int i = 1; i < 9; ++i) {
+                const int j = r + 1 - CY[i];
+                const bool back = ((wall_rows >> j) & 1u) || (((solid_rows >> j) & 1u) && ((sqc >> (1 - CX[i] + k)) & 1u));
+                word[k] |= (back ? 1u : 0u) << (i - 1);
+            }
+            // (a lane beyond the wave's columns is in no ring)
+            if (((ring_rows >> r) & 1u) && lane <= lastl && !in_square(m, x0 + k, y) && ring_index(m, x0 + k, y) >= 0)
+                word[k] |= square_links(m, x0 + k, y) << 7 | (unsigned)(ring_index(m, x0 + k, y) + 1) << 16;
+        }
+        marks[wave][r][lane] = u2{word[0], word[1]};
+    }
+    // Words and floats of a row beside a wave are laid out [direction 3][cell of the lane 2][lane of the member's
+    // width]; a lane reads its own columns and shifts, and the first and the last lane read the column beside the
+    // wave: of the direction that moves right (d 1 from below: 5, d 2 from above: 8), and left (6 and 7).
+    const int hp = (nx + 1) / 2;
+    const int lc = min(w * sg.lanes + lane, hp - 1);
+    const int left_k = w == 0 ? (nx - 1) & 1 : 1;
+    const int beside = lane == 0 ? (w == 0 ? hp - 1 : w * sg.lanes - 1) : lane == lastl ? (last_wave ? 0 : (w + 1) * sg.lanes) : lc;
+    const int beside_low = lane == 0 ? 2 + left_k : lane == lastl ? 4 : 0;
+    const int beside_high = lane == 0 ? 4 + left_k : lane == lastl ? 2 : 0;
+    const long long hs = 6LL * hp;  // words of a row: [unit][side][slot]
+    unsigned long long* const mine = a.halo + sg.halo_begin + (long long)unit * 4 * hs;
+    const int wl = g * W + (w == 0 ? W - 1 : w - 1), wr = g * W + (last_wave ? 0 : w + 1);
+
+    float f[R][9][RC];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned row = (unsigned)max(min(ys + r, ny - 1), 0) * (unsigned)nx;
+        const unsigned voff = 4u * (unsigned)min(x0, nx - RC);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const u2 q = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, 4u * ((unsigned)i * plane + row), 0);
+            const float q0 = __uint_as_float(q.x), q1 = __uint_as_float(q.y);
+            f[r][i][0] = pick(one && lane == lastl, q1, q0);  // the short last lane loaded the row's last two cells
+            f[r][i][1] = q1;
+        }
+    }
+
+    // hand out the populations of row r that leave the wave sideways, for the step with slot n
+    auto publish_row = [&](int r, int n) {
+        if (lane == 0) xe[n][wave][r][0] = f4{f[r][3][0], f[r][6][0], f[r][7][0], 0.0f};
+        if (lane == lastl)
+            xe[n][wave][r][1] = f4{pick(one, f[r][1][0], f[r][1][1]), pick(one, f[r][5][0], f[r][5][1]), pick(one, f[r][8][0], f[r][8][1]), 0.0f};
+    };
+    // those of the lowest (side 0: 4, 7, 8) or highest row (side 1: 2, 5, 6); tag: the step they are for
+    auto publish_side = [&](int side, int r, int i0, int i1, int i2, int n, unsigned tag) {
+        if (!(side ? above : below)) return;
+        const float v[6] = {f[r][i0][0], f[r][i0][1], f[r][i1][0], f[r][i1][1], f[r][i2][0], f[r][i2][1]};
+        if (side ? high_mem : low_mem) {
+            if (lane <= lastl) {
+                unsigned long long* const p = mine + (side * 2 + n) * hs;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) put_word(p + (q * hp + lc), v[q], tag);
+            }
+        } else if (lane <= lastl) {
+#pragma unroll
+            for (int q = 0; q < 6; ++q) yh[n][side][q * 512 + g * hp + lc] = v[q];
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r) publish_row(r, 0);
+    publish_side(0, 0, 4, 7, 8, 0, tag0 + 1u);
+    publish_side(1, R - 1, 2, 5, 6, 0, tag0 + 1u);
+    if (a.wait_ticks < 0 && (low_mem || high_mem)) {  // no wait at all (the giving up is tested so)
+        __hip_atomic_store(&a.given_up[mi], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    lds_barrier();
+
+    auto right = [&](const float (&v)[RC], float in, float (&o)[RC]) {  // +x movers: one cell to the right
+        o[0] = wave_shr1_in(v[1], in);
+        o[1] = v[0];
+    };
+    auto left = [&](const float (&v)[RC], float in, float (&o)[RC]) {  // -x movers
+        const float sh = wave_shl1_in(v[0], in);
+        o[0] = pick(one && lane == lastl, in, v[1]);
+        o[1] = pick(lane == lastl, in, sh);
+    };
+#pragma unroll 1
+    for (int t = 0; t < a.n_steps; ++t) {
+        // looked at afresh each step: the tests made from these are the same in every step, and the compiler would
+        // keep all of them (two scalars each) through the loop
+        unsigned nears = (unsigned)__builtin_amdgcn_readfirstlane((int)near_rows);
+        unsigned rings = (unsigned)__builtin_amdgcn_readfirstlane((int)ring_rows);
+        int hq = __builtin_amdgcn_readfirstlane(hp);
+        __asm__ volatile("" : "+s"(nears), "+s"(rings), "+s"(hq));
+        const int n = t & 1;
+        const unsigned tag = tag0 + (unsigned)t + 1u;
+        double* const ps = a.partial + m.part_off + (long long)t * m.ring;
+
+        // row r of the step, given what arrives from the rows below (2, 5, 6) and above (4, 7, 8) and the columns beside
+        auto collide_row = [&](int r, const float (&up)[3][RC], const float (&dn)[3][RC], float el, float er) {
+            float p[9][RC];
+#pragma unroll
+            for (int k = 0; k < RC; ++k) {
+                p[0][k] = f[r][0][k];
+                p[2][k] = up[0][k];
+                p[5][k] = up[1][k];
+                p[6][k] = up[2][k];
+                p[4][k] = dn[0][k];
+                p[7][k] = dn[1][k];
+                p[8][k] = dn[2][k];
+            }
+            right(f[r][1], el, p[1]);
+            left(f[r][3], er, p[3]);
+            u2 mark{0u, 0u};
+            if ((nears >> r) & 1u) {  // halfway bounce-back: the cell's own opposite population
+                mark = marks[wave][r][lane];
+#pragma unroll
+                for (int i = 1; i < 9; ++i)
+#pragma unroll
+                    for (int k = 0; k < RC; ++k) {
+                        const unsigned back = (unsigned)((int)(mark[k] << (32 - i)) >> 31);  // all ones or zero
+                        p[i][k] = pinned(__uint_as_float((back & __float_as_uint(f[r][OPP[i]][k])) | (~back & __float_as_uint(p[i][k]))));
+                    }
+            }
+            if ((rings >> r) & 1u) {
+#pragma unroll
+                for (int k = 0; k < RC; ++k) {
+                    float dl[9];
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) dl[i] = pinned(p[i][k]);
+                    const double drag = collide_cell<MODEL>(m, dl, mark[k] >> 7 & 0x1FEu, true);
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) f[r][i][k] = pinned(dl[i]);
+                    if (mark[k] >> 16) ps[(int)(mark[k] >> 16) - 1] = drag;
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < RC; ++k) {
+                    float dl[9];
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) dl[i] = pinned(p[i][k]);
+                    collide_cell<MODEL>(m, dl, 0u, false);
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) f[r][i][k] = pinned(dl[i]);
+                }
+            }
+            publish_row(r, n ^ 1);
+        };
+        // what row r sends to the row above it, and to the row below
+        auto send_up = [&](int r, const f4& el, const f4& er, float (&o)[3][RC]) {
+            o[0][0] = f[r][2][0];
+            o[0][1] = f[r][2][1];
+            right(f[r][5], el.y, o[1]);
+            left(f[r][6], er.y, o[2]);
+        };
+        auto send_down = [&](int r, const f4& el, const f4& er, float (&o)[3][RC]) {
+            o[0][0] = f[r][4][0];
+            o[0][1] = f[r][4][1];
+            left(f[r][7], er.z, o[1]);
+            right(f[r][8], el.z, o[2]);
+        };
+        // what arrives from the row below the wave (side 0) or above it; false: given up
+        auto arrive = [&](int side, float (&o)[3][RC]) -> bool {
+            float v[3][RC], e = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) v[q / 2][q & 1] = 0.0f;
+            if (side ? high_mem : low_mem) {
+                // the unit below's side 1, or the unit above's side 0
+                const unsigned long long* const p = mine + (side ? 4 + n : n - 2) * hs;
+                unsigned long long u[7];
+                long long began = 0;
+                for (int spin = 0;; ++spin) {
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) u[q] = get_word(p + (q * hq + lc));
+                    u[6] = get_word(p + ((side ? beside_high : beside_low) * hq + beside));
+                    bool ok = true;
+#pragma unroll
+                    for (int q = 0; q < 7; ++q) ok = ok && (unsigned)(u[q] >> 32) == tag;
+                    if (__all(ok)) break;
+                    if ((spin & 63) == 63) {  // bounded: see the top of the file
+                        const long long now = wall_clock64();
+                        if (!began) began = now;
+                        const bool late = now - began > a.wait_ticks;
+                        if (late) __hip_atomic_store(&a.given_up[mi], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (late || __hip_atomic_load(&a.given_up[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == epoch) return false;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 6; ++q) v[q / 2][q & 1] = __uint_as_float((unsigned)u[q]);
+                e = __uint_as_float((unsigned)u[6]);
+            } else if (side ? above : below) {
+                const float* const q = &yh[n][side ^ 1][(side ? g + 1 : g - 1) * hp];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) v[j / 2][j & 1] = q[j * 512 + lc];
+                e = q[(side ? beside_high : beside_low) * 512 + beside];
+            }
+            o[0][0] = v[0][0];
+            o[0][1] = v[0][1];
+            if (side) {
+                left(v[1], e, o[1]);
+                right(v[2], e, o[2]);
+            } else {
+                right(v[1], e, o[1]);
+                left(v[2], e, o[2]);
+            }
+            return true;
+        };
+
+        if constexpr (R == 1) {
+            const f4 el = xe[n][wl][0][1], er = xe[n][wr][0][0];
+            float up[3][RC], dn[3][RC];
+            if (!arrive(0, up) || !arrive(1, dn)) return;
+            collide_row(0, up, dn, el.x, er.x);
+            publish_side(0, 0, 4, 7, 8, n ^ 1, tag + 1u);
+            publish_side(1, 0, 2, 5, 6, n ^ 1, tag + 1u);
+        } else {
+            // the rows that wait for nothing first: the words from the workgroups beside travel meanwhile
+            float below0[3][RC], nu[3][RC];  // what row 1 sends down to row 0; what arrives at the next row from below
+            f4 el = xe[n][wl][0][1], er = xe[n][wr][0][0];
+            send_up(0, el, er, nu);
+            el = xe[n][wl][1][1];
+            er = xe[n][wr][1][0];
+            send_down(1, el, er, below0);
+#pragma unroll
+            for (int r = 1; r + 1 < R; ++r) {
+                const f4 eln = xe[n][wl][r + 1][1], ern = xe[n][wr][r + 1][0];
+                float nn[3][RC], dn[3][RC];
+                send_up(r, el, er, nn);
+                send_down(r + 1, eln, ern, dn);
+                collide_row(r, nu, dn, el.x, er.x);
+#pragma unroll
+                for (int q = 0; q < 6; ++q) nu[q / 2][q & 1] = nn[q / 2][q & 1];
+                el = eln;
+                er = ern;
+            }
+            {
+                float up[3][RC];
+                if (!arrive(0, up)) return;
+                const f4 e0 = xe[n][wl][0][1], e1 = xe[n][wr][0][0];
+                collide_row(0, up, below0, e0.x, e1.x);
+                publish_side(0, 0, 4, 7, 8, n ^ 1, tag + 1u);
+            }
+            {
+                float dn[3][RC];
+                if (!arrive(1, dn)) return;
+                collide_row(R - 1, nu, dn, el.x, er.x);
+                publish_side(1, R - 1, 2, 5, 6, n ^ 1, tag + 1u);
+            }
+        }
+        lds_barrier();
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r < rows) {
+            unsigned skip = (solid_rows >> (r + 1)) & 1u ? (sqc >> 1) & 3u : 0u;
+            if (lane >= lastl) skip |= lane > lastl ? 3u : one ? 2u : 0u;
+            const unsigned cell = (unsigned)(ys + r) * (unsigned)nx + (unsigned)x0;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                float* const q = dst + ((unsigned)i * plane + cell);
+                if (!(skip & 1u)) q[0] = f[r][i][0];
+                if (!(skip & 2u)) q[1] = f[r][i][1];
+            }
+        }
+    }
+}
+
+template <int R>
+static hipError_t launch_resident_r(const ResidentArgs& a, int model, hipStream_t st) {
+    const dim3 grid(a.total_blocks), block(64 * a.block_waves);
+    if (model == 2) hipLaunchKernelGGL((resident_kernel<R, 2>), grid, block, 0, st, a);
+    else if (model == 1) hipLaunchKernelGGL((resident_kernel<R, 1>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((resident_kernel<R, 0>), grid, block, 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident(int rows, const ResidentArgs& a, int model, hipStream_t st) {
+    switch (rows) {
+        case 1: return launch_resident_r<1>(a, model, st);
+        case 2: return launch_resident_r<2>(a, model, st);
+        case 3: return launch_resident_r<3>(a, model, st);
+        case 4: return launch_resident_r<4>(a, model, st);
+        case 6: return launch_resident_r<6>(a, model, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace lbm

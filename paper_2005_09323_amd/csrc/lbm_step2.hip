@@ -46,12 +46,6 @@ struct RowLoads {
     float e[9];  // the word beyond the strip's edge for the +x / -x movers
 };
 
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Row loads of row y from the state at t: direction i comes from row y - c_iy
 // (or, next to a wall, from the row's own opposite population).  The loads go
 // through L2 (not non-temporal): the neighbouring strip, on the same XCD and

@@ -73,30 +73,6 @@ __device__ __forceinline__ void store_cells(__amdgpu_buffer_rsrc_t rd, unsigned 
     }
 }
 
-// Barrier of the unit's waves that orders their LDS accesses only (loads of
-// populations stay in flight across it).
-__device__ __forceinline__ void sweep_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// The value of the lane before (after) in the wave; the first (last) lane gets `in`.
-__device__ __forceinline__ float wave_shr1_in(float v, float in) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(in), __float_as_int(v), 0x138, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_shl1_in(float v, float in) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(in), __float_as_int(v), 0x130, 0xF, 0xF, false));
-}
-
-// A value the optimizer cannot see through: an iteration's two forms (below)
-// share most of their code, and merging it across their branch holds whole
-// rows in FP64 there (72 registers more).
-__device__ __forceinline__ float pinned(float v) {
-    __asm__ volatile("" : "+v"(v));
-    return v;
-}
-
 // WIDTH: 0 a multiple of 64 C (every lane has its cells), 2 any (lanes beyond
 // the width, and the row's last lane may have fewer cells).
 // An iteration has two forms: `plain` while no row of the wave touches a wall
@@ -377,7 +353,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                 f4* const ed = &edge[y & 1][q][0][0];
                 if (lane == 0) ed[2 * wg_wave] = f4{p[3][0], p[6][0], p[7][0], 0.0f};
                 if (lane == lastl) ed[2 * wg_wave + 1] = f4{last_cell(p[1]), last_cell(p[5]), last_cell(p[8]), 0.0f};
-                if (W > 1) sweep_barrier();
+                if (W > 1) lds_barrier();
                 else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
                 const f4 el = ed[2 * wl + 1], er = ed[2 * wr];
                 float n1[C], n3[C], n5[C], n6[C], n7[C], n8[C];

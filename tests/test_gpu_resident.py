@@ -1,0 +1,101 @@
+"""The resident kernel (the default shape on an ensemble that fits in the device's registers: a chunk
+of steps per launch) against the one-step shape 0.
+
+Both collide every cell with the same arithmetic on the same FP32 inputs, so states and drag are
+equal bit for bit: the tolerance is zero.  Sizes sit where the cutting can go wrong: widths around the
+128 columns of a wave and odd ones (a last lane with one cell), one to eight waves per row, heights
+that end inside a wave's rows, workgroups beside one another within and across members, squares across
+wave and row seams and beside the walls and the periodic edge, every number of rows per wave, more
+members than one launch holds, chunks of one step up to the longest, and inactive members.  With a wait limit below zero every member of more
+than one workgroup is given up and stepped by the kernel that waits for nothing.
+"""
+import pytest
+import torch
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _m(nx, ny, square):
+    return workloads.Member(nx, ny, 0.56, 2e-5, square)
+
+
+LATTICES = {
+    "wave_seams": [_m(256, 24, (124, 8, 8)), _m(256, 24, (1, 1, 3)), _m(256, 24, (250, 18, 5))],
+    "widths": [_m(1024, 11, (127, 3, 4)), _m(600, 10, (594, 4, 3)), _m(330, 9, (128, 3, 4))],
+    "ragged": [_m(201, 33, (60, 12, 6)), _m(257, 11, (125, 4, 4)), _m(130, 21, (1, 1, 3)), _m(127, 6, None)],
+    "smallest": [_m(4, 4, (1, 1, 2)), _m(5, 7, (2, 2, 2)), _m(128, 4, (60, 1, 2)), _m(129, 5, None)],
+    "two_rows": [_m(384, 61, (127, 30, 9))] * 12,
+    "three_rows": [_m(384, 61, (250, 30, 9))] * 17,
+    "four_rows": [_m(512, 131, (250, 60, 9))] * 12,
+    "several_launches": [_m(512, 128, (250, 60, 9))] * 25 + [_m(130, 40, (124, 20, 5))] * 3,
+    "six_rows": [_m(256, 203, (124, 100, 13))] * 28,
+}
+
+
+def _run(members, tile, collision, wait=None):
+    from paper_2005_09323_amd import native
+    from paper_2005_09323_amd.ensemble import Ensemble
+    ens = Ensemble(members, series_capacity=90)
+    ens.pop_a.zero_()  # solid cells are never written
+    ens.pop_b.zero_()
+    ens.set_tile(tile)
+    if collision is not None:
+        ens.set_collision("central", *collision)
+    if wait is not None:
+        native.check(ens.lib.lbm_set_wait_limit(ens._ctx, wait))
+    ens.init(7, 1e-2)
+    ens.step(13)
+    ens.set_active([j % 2 == 0 for j in range(len(members))])
+    ens.step(7)
+    ens.set_active([j % 2 == 1 or j == 2 for j in range(len(members))])
+    ens.step(2)
+    ens.set_active(None)
+    ens.step(65)                      # a whole chunk and one step
+    torch.cuda.synchronize()
+    out = ens.series.clone(), [ens.state(i).clone() for i in range(len(members))], ens.accum.clone()
+    ens.close()
+    return out
+
+
+@pytest.mark.parametrize("collision", [None, (1.0, 1.0, 1.0), (1.2, 0.9, 1.4)])
+@pytest.mark.parametrize("lattices", sorted(LATTICES))
+def test_resident_bit_identical_to_one_step(lattices, collision):
+    members = LATTICES[lattices]
+    drag0, states0, accum0 = _run(members, 0, collision)
+    for wait in (None, -1) if len(members) < 8 else (None,):
+        drag, states, accum = _run(members, 20, collision, wait)
+        assert torch.equal(drag, drag0) and torch.equal(accum, accum0), wait
+        for i, (a, b) in enumerate(zip(states, states0)):
+            assert torch.equal(a, b), (wait, i)
+
+
+def test_contexts_on_two_streams():
+    """Two contexts that do not fit on the device together, stepped from two streams in turn."""
+    from paper_2005_09323_amd.ensemble import Ensemble
+    members = LATTICES["six_rows"]
+    _, states0, _ = _run(members, 0, None)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    ens = []
+    for st in streams:
+        with torch.cuda.stream(st):
+            e = Ensemble(members, series_capacity=90)
+            e.pop_a.zero_()
+            e.pop_b.zero_()
+            e.init(7, 1e-2)
+            ens.append(e)
+    half = [j % 2 == 0 for j in range(len(members))]
+    other = [j % 2 == 1 or j == 2 for j in range(len(members))]
+    for mask, n in ((None, 13), (half, 7), (other, 2), (None, 65)):
+        for st, e in zip(streams, ens):
+            with torch.cuda.stream(st):
+                e.set_active(mask)
+                e.step(n)
+    torch.cuda.synchronize()
+    for st, e in zip(streams, ens):
+        with torch.cuda.stream(st):
+            for i, b in enumerate(states0):
+                assert torch.equal(e.state(i), b), i
+        e.close()
