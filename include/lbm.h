@@ -153,8 +153,8 @@ int lbm_set_active(lbm_ctx* ctx, const int32_t* active_host);
  * steps instead of 17 to 129 kernel launches.  Where the default shape keeps
  * the populations in registers for a whole chunk, a chunk is one launch for
  * every 2048 x 128 x (1 to 6 rows) cells or so, and nothing is captured;
- * batches of one or two steps, calls under a stream capture of the caller's and
- * open channels are stepped by the other kernels.
+ * short batches (of one to three steps or so) and calls under a stream capture
+ * of the caller's are stepped by the other kernels.
  */
 int lbm_step_batch(lbm_ctx* ctx, int32_t n_steps);
 
@@ -271,7 +271,7 @@ int lbm_set_collision(lbm_ctx* ctx, int32_t model, double s_bulk, double s_third
  * (sq_x0 + s <= nx - 3); 0 <= u_c <= 0.3; sponge_tau > 1/2; ny <= 2048
  * (LBM_EUNSUPPORTED beyond: the ghost kernel keeps a column in LDS).  The body
  * force of the members still applies.  A small kernel rebuilds the ghost
- * columns before every launch; the two-step shapes build the outlet column
+ * columns before every launch that does not form them itself; the two-step shapes build the outlet column
  * of their second step themselves.  lbm_init then starts every member
  * from the inlet profile (lbm_init_flow requires ux0 = 0).  oc = NULL
  * restores periodic channels.  Call before lbm_init; synchronises the
@@ -300,10 +300,10 @@ int lbm_set_open_channel(lbm_ctx* ctx, const lbm_open_channel* oc);
  * for the last step of an odd batch, the library steps with shape 0.  Shapes
  * 21-23 are shape 16 with each strip cut into workgroups of 128, 64 and 32
  * rows (the rows next to a cut are collided by both neighbours).  Shape 20,
- * the default, steps periodic channels of up to 1024 columns (any width) with
- * the populations in registers for a whole chunk of steps (lbm_step_batch)
- * where the active members fit in a few such launches, and with the sweep
- * kernel (up to four steps per launch, the steps in between held in registers)
+ * the default, steps channels of up to 1024 columns (any width) with the
+ * populations in registers for a whole chunk of steps (lbm_step_batch) where
+ * the active members fit in a few such launches, and periodic ones with the
+ * sweep kernel (up to four steps per launch, the steps in between held in registers)
  * where they are many enough for it to be the faster, or whenever row ranges
  * are given (lbm_set_run_rows).  Otherwise it
  * makes two steps per launch with whole strips when there are

@@ -87,8 +87,11 @@ struct MemberDev {
     long long ghost_off;  // first float of the member's outlet ghost column [9][ny]
 };
 
-// The BGK update's coefficients from omega and the force.
+// The BGK update's coefficients from omega and the force (contraction off: in
+// the sponge every kernel forms them, and 1 - omega must not become part of
+// omega's own last step in some of them).
 __host__ __device__ inline void bgk_coefficients(MemberDev& m) {
+#pragma clang fp contract(off)
     const double om = m.omega, g3 = (1.0 - 0.5 * om) * 3.0 * m.force, g9 = (1.0 - 0.5 * om) * 9.0 * m.force;
     m.keep = 1.0 - om;
     m.a1 = WD[1] * om;

@@ -219,15 +219,18 @@ static bool two_step_now(const lbm_ctx* c) {
 // with 1, 2, 3, 4, 6 rows 2.3, 3.3, 4.1, 5.0, 6.5 (lone waves, 512 columns 10 %
 // more); per launch of 64 x 512 x 128 with 2, 3, 4, 6 rows in workgroups of
 // eight waves 4.0, 5.2, 6.6, 8.9; the words: 4 x 512 x 128, one row, 4096 sides
-// 6.3 us, 2048 sides 3.6.
-static double resident_cost(int rows, bool two, double sides) {
-    static const double lone[] = {0, 2.4, 3.4, 4.3, 5.4, 0, 7.0}, both[] = {0, 3.0, 3.8, 5.0, 6.3, 0, 8.4};
-    return std::max((two ? both : lone)[rows], 1.5e-3 * sides) + 1.5e-4 * sides;
+// 6.3 us, 2048 sides 3.6.  Open channels (the outlet's waves first wait for the
+// last columns beside them and form its populations): 8 x 512 x 128 with 2, 3,
+// 4, 6 rows 5.4, 6.1, 7.2, 10.5.
+static double resident_cost(int rows, bool two, bool open, double sides) {
+    static const double lone[] = {0, 2.4, 3.4, 4.3, 5.4, 0, 7.0}, both[] = {0, 3.0, 3.8, 5.0, 6.3, 0, 8.4},
+                        opened[] = {0, 0, 5.1, 6.0, 7.2, 0, 10.3};
+    return std::max((open ? opened : two ? both : lone)[rows], 1.5e-3 * sides) + 1.5e-4 * sides;
 }
 
 // The resident launches of the next batch, if the adaptive shape may have any: a
-// whole chunk of steps per launch with the populations in registers (periodic
-// channels of up to 1024 columns, all workgroups of a launch side by side on
+// whole chunk of steps per launch with the populations in registers (channels
+// of up to 1024 columns, all workgroups of a launch side by side on
 // the device: two waves per SIMD at most), as many launches as the members
 // need.  Rows per wave and waves per workgroup (four, two of them on a compute
 // unit, or eight) with the least estimated time: more rows per wave are fewer
@@ -236,7 +239,7 @@ static double resident_cost(int rows, bool two, double sides) {
 // of 7.7), four leave small ensembles a SIMD per wave (1 x 256 x 64: 2.3
 // instead of 2.5).
 static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) {
-    if (!TILE_SHAPES[c->tile_id].adaptive || c->open) return false;
+    if (!TILE_SHAPES[c->tile_id].adaptive) return false;
     for (int r : c->run_rows)
         if (r >= 0) return false;  // row ranges given by the caller: the sweep's
     hipStreamCaptureStatus captured;  // a replay would not be known to the other contexts' launches
@@ -268,7 +271,7 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
         auto close = [&] {
             if (!q.passes) return;
             q.args[q.passes - 1].total_blocks = (int)blocks;
-            q.us += resident_cost(rows, blocks * block_waves > 4LL * c->cu_count, (double)sides);
+            q.us += resident_cost(rows, blocks * block_waves > 4LL * c->cu_count, c->open, (double)sides);
         };
         for (int s = 0; s < c->nseg; ++s) {
             const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
@@ -297,7 +300,7 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
                 a.block_waves = block_waves;
                 blocks += (long long)here * g.ranges;
                 sides += 2LL * here * (g.ranges - 1) * g.waves;
-                words += (long long)here * g.ranges * 24 * ((d.nx + 1) / 2);
+                words += (long long)here * g.ranges * (24 * ((d.nx + 1) / 2) + (c->open ? 4 * RESIDENT_OUTLET_WORDS : 0));
                 q.halo_words = std::max(q.halo_words, (size_t)words);
                 m += here;
             }
@@ -310,7 +313,9 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
     ResidentPlan q;
     int best_rows = 0, best_waves = 0;
     for (int waves : {4, 8}) {
+        if (c->open && waves < 8) continue;  // (its LDS fits once on a compute unit)
         for (int rows : {1, 2, 3, 4, 6}) {
+            if (c->open && rows < 2) continue;  // (the outlet looks two rows away)
             if (cut(rows, waves, q) && q.us < p.us) {
                 p.us = q.us;
                 best_rows = rows;
@@ -349,7 +354,7 @@ static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps,
     for (int k = 0; k < p.passes; ++k) {
         p.args[k].n_steps = steps;
         p.args[k].flip = flip;
-        const hipError_t e = launch_resident(p.rows, p.args[k], c->model, st);
+        const hipError_t e = launch_resident(p.rows, c->open, p.args[k], c->model, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -461,6 +466,17 @@ static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int rows, const i
     return std::max(rounds * iteration, bytes / 4.8e6) * (1.0 + 0.03 * std::max(0, 32 - rows)) + 4.0;
 }
 
+// Estimated us per step of the other kernels: two steps per launch at 130 G
+// updates/s (105 in open channels), or one per launch at 80 (rows of four
+// cells per lane) or 50 (one cell per lane), and 6 us per launch (open: and 7
+// for the outlet's).
+static double others_cost(const lbm_ctx* c, double cells) {
+    bool four = true;
+    for (int s = 0; s < c->nseg; ++s) four = four && c->seg[s].vec;
+    if (two_step_now(c)) return c->open ? cells / 105e3 + 7.0 : cells / 130e3 + 3.5;
+    return cells / (four ? 80e3 : 50e3) + (c->open ? 13.0 : 6.0);
+}
+
 // The sweep launch of the next batch (steps per launch and the table of units); false if another kernel should step it.  The sweep takes
 // lattices of up to 64 SWEEP_WAVES SWEEP_CELLS = 1024 columns in periodic channels; the
 // adaptive shape chooses it where its estimated time per step is below that of
@@ -509,11 +525,7 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     for (int r : c->run_rows) chosen = chosen || r >= 0;
     p.us = best;
     if (!chosen) {
-        // the other kernels: two steps per launch at 130 G updates/s, or one per launch at 80 (rows of
-        // four cells per lane) or 50 (one cell per lane), and 6 us per launch
-        bool four = true;
-        for (int s = 0; s < c->nseg; ++s) four = four && c->seg[s].vec;
-        const double other = two_step_now(c) ? cells / 130e3 + 3.5 : cells / (four ? 80e3 : 50e3) + 6.0;
+        const double other = others_cost(c, cells);
         p.us = std::min(best, other);
         if (cells < 3e6) p.us = other;
         if (cells < 3e6 || best >= other) return false;
@@ -547,8 +559,9 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
 // times.  us per step in long batches, resident launches and the others:
 // 1 x 256 x 64 2.3 and 6.8, 16 x 512 x 128 7.0 and 15.6, 64 x 512 x 128 26.5 and
 // 44, 20 x 1024 x 256 31.6 and 48.5, 32 x 1024 x 256 52.1 and 51.0, 256 x 512 x
-// 128 106 and 80 (the sweep's estimate is 10 % low where the two are close).  A
-// resident launch also takes 8 us and a copy of the state to begin and end:
+// 128 106 and 80 (the sweep's estimate is 10 % low where the two are close); open
+// channels of 16, 64 and 512 x 512 x 128 7.4 and 25.4, 28.5 and 51, 226 and 321.
+// A resident launch also takes 8 us and a copy of the state to begin and end:
 // calls of one step 19.5 and 14.9, 37 and 24, of two 21 and 22, 43 and 41, of
 // four 26 and 38, 55 and 75 for the first two sizes.
 static bool plan_batch(const lbm_ctx* c, int n_steps, ResidentPlan& resident, SweepPlan& sweep, bool& swept, bool every_member) {
@@ -556,6 +569,7 @@ static bool plan_batch(const lbm_ctx* c, int n_steps, ResidentPlan& resident, Sw
     swept = false;
     if (stays && resident.passes == 1 && n_steps >= 4) return true;
     swept = plan_sweep(c, sweep, every_member);
+    if (c->open && stays) sweep.us = others_cost(c, resident.bytes / 72.0);
     bool chosen = false;  // row ranges given by the caller: sweep them
     for (int r : c->run_rows) chosen = chosen || r >= 0;
     if (swept && n_steps < 4 && !chosen) swept = false;  // (64 x 512 x 128, calls of one step 93 and 66 us, of two 115 and 92)
@@ -759,6 +773,7 @@ static FinalizeArgs finalize_args(lbm_ctx* c, int n, int accumulate, int swap_pa
     f.pop0 = c->pop[0];
     f.pop1 = c->pop[1];
     f.redo_partial = c->d_partial;
+    f.ghost = c->d_ghost;
     return f;
 }
 

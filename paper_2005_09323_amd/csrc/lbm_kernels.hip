@@ -335,9 +335,50 @@ __global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
     if (ri >= 0) a.partial[m.part_off + ri] = drag;
 }
 
+// The velocities of the last two columns of row y.
+__device__ __forceinline__ OutletVel outlet_velocities(const MemberDev& m, const float* __restrict__ src, int y, float d1[9], float d2[9]) {
+    const unsigned plane = (unsigned)m.nx * (unsigned)m.ny;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        const unsigned row = (unsigned)i * plane + (unsigned)y * (unsigned)m.nx;
+        d1[i] = src[row + (unsigned)(m.nx - 1)];
+        d2[i] = src[row + (unsigned)(m.nx - 2)];
+    }
+    OutletVel v;
+    stored_velocity(d1, v.ux1, v.uy1);
+    stored_velocity(d2, v.ux2, v.uy2);
+    return v;
+}
+
 // A resident chunk that was given up (lbm_resident.hip), stepped again by the
 // member's workgroup alone, cell by cell, from the source buffer that the
 // resident kernel only read; the last step's state ends in the other buffer.
+template <bool OPEN>
+__device__ __forceinline__ void redo_step(const MemberDev& m, const float* src, float* dst, double* part, float* g) {
+    if (OPEN) {  // the ghost columns first (every row's neighbours anew: no table of ny rows)
+        for (int y = (int)threadIdx.x; y < m.ny; y += (int)blockDim.x) {
+            float d1[9], d2[9];
+            const OutletVel va = outlet_velocities(m, src, y > 0 ? y - 1 : 0, d1, d2);
+            const OutletVel vb = outlet_velocities(m, src, y + 1 < m.ny ? y + 1 : m.ny - 1, d1, d2);
+            const OutletVel v0 = outlet_velocities(m, src, y, d1, d2);
+            const double rho_g = outlet_density(m, d1, d2);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                if (CX[i] == 1) g[i * m.ny + y] = inlet_dev(m, i, y);
+                else if (CX[i] == -1) g[i * m.ny + y] = outlet_ghost_value(m, CX[i], CY[i], WD[i], y, va, v0, vb, rho_g);
+            }
+        }
+        __syncthreads();
+    }
+    for (int c = (int)threadIdx.x; c < m.nx * m.ny; c += (int)blockDim.x) {
+        const int y = c / m.nx, x = c - y * m.nx;
+        if (m.model == 2) scalar_cell<2, OPEN>(m, src, dst, part, g, x, y);
+        else if (m.model == 1) scalar_cell<1, OPEN>(m, src, dst, part, g, x, y);
+        else scalar_cell<0, OPEN>(m, src, dst, part, g, x, y);
+    }
+    __syncthreads();
+}
+
 __device__ __noinline__ void resident_redo(const FinalizeArgs& a, const MemberDev& m, int par) {
     float* const from = (par ? a.pop1 : a.pop0) + m.off;
     float* const to = (par ? a.pop0 : a.pop1) + m.off;
@@ -346,13 +387,8 @@ __device__ __noinline__ void resident_redo(const FinalizeArgs& a, const MemberDe
         const float* src = t & 1 ? to : from;
         float* dst = t & 1 ? from : to;
         double* part = a.redo_partial + m.part_off + (long long)t * m.ring;
-        for (int c = (int)threadIdx.x; c < cells; c += (int)blockDim.x) {
-            const int y = c / m.nx, x = c - y * m.nx;
-            if (m.model == 2) scalar_cell<2, false>(m, src, dst, part, nullptr, x, y);
-            else if (m.model == 1) scalar_cell<1, false>(m, src, dst, part, nullptr, x, y);
-            else scalar_cell<0, false>(m, src, dst, part, nullptr, x, y);
-        }
-        __syncthreads();
+        if (m.open) redo_step<true>(m, src, dst, part, a.ghost + m.ghost_off);
+        else redo_step<false>(m, src, dst, part, nullptr);
     }
     if (a.n % 2 == 0)
         for (int c = (int)threadIdx.x; c < cells; c += (int)blockDim.x) {

@@ -14,6 +14,11 @@
 // one step ahead of its neighbour.  The rows inside a wave come first in a
 // step, the lowest and the highest last: the words travel meanwhile.
 //
+// Open channels: what enters from the inlet is constant; what enters from the
+// outlet is formed by the waves of the last columns before each step
+// (outlet_ghost_value), from the last two columns of their rows and of two rows
+// on either side, which their neighbours hand out beside the rows above.
+//
 // The wait for a neighbour is bounded: workgroups of a member run side by side
 // when the device is free (the host launches at most as many as fit), but
 // kernels of other streams may hold part of it.  A wave that waits longer than
@@ -49,7 +54,7 @@ __device__ __forceinline__ unsigned long long get_word(const unsigned long long*
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int R, int MODEL>
+template <int R, int MODEL, bool OPEN>
 __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void resident_kernel(ResidentArgs a) {
     // columns beside a wave: [slot][wave][row][side]: side 0 its first cell (3, 6, 7), side 1 its last (1, 5, 8)
     __shared__ f4 xe[2][SWEEP_WAVES][R][2];
@@ -59,6 +64,13 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     // the lane's cells of a row beside a wall or the square: bits 0-7 the directions 1-8 that come from a wall or
     // the square, bits 8-15 those that go to the square, from bit 16 the cell's place in the ring + 1
     __shared__ u2 marks[SWEEP_WAVES][R][64];
+    // open channels: what enters from the inlet (1, 5, 8) and the outlet (3, 6, 7) column, rows -1 .. R of a row
+    // group; the last two columns (nx - 1 and nx - 2, nine populations each) of rows -2 .. groups R + 1 of the
+    // workgroup, [slot]; their velocities, rows -2 .. R + 1 of a row group
+    constexpr int OG = OPEN ? SWEEP_WAVES : 1;
+    __shared__ f4 inlet[OG][R + 2], outlet[OG][R + 2];
+    __shared__ __attribute__((aligned(16))) float last2[OPEN ? 2 : 1][OG * R + 4][24];
+    __shared__ OutletVel vel[OG][R + 4];
     const int b = (int)blockIdx.x;
     int s = 0;
 #pragma unroll 1
@@ -66,7 +78,10 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const ResidentSegment sg = a.seg[s];
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int W = sg.waves, g = wave / W, w = wave - g * W;  // row group and column wave
+    // row group and column wave; every other group from the right, so that a SIMD's two waves (four apart) are not
+    // both at one end of their rows
+    const int W = sg.waves, g = wave / W, wn = wave - g * W, w = g & 1 ? W - 1 - wn : wn;
+    auto wave_at = [&](int cw) { return g * W + (g & 1 ? W - 1 - cw : cw); };
     if (g >= sg.groups) return;
     const int unit = b - sg.block_begin;
     const int mloc = unit / sg.ranges, range = unit - mloc * sg.ranges;
@@ -91,24 +106,31 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const int rows = min(R, ny - ys);                           // <= 0: no row (it only meets the barriers)
     const bool below = rows > 0 && ys > 0, above = rows == R && ys + R < ny;
     const bool low_mem = below && g == 0, high_mem = above && g == sg.groups - 1;
+    const bool outlet_wave = OPEN && last_wave, inlet_wave = OPEN && w == 0;
     const bool sq_cols = m.ss > 0 && base <= m.sx0 + m.ss && base + sg.lanes * RC - 1 >= m.sx0 - 1;
     unsigned sqc = 0;  // bit j: column x0 - 1 + j crosses the square
     if (sq_cols)
 #pragma unroll
         for (int j = 0; j < RC + 2; ++j) sqc |= ((unsigned)(x0 - 1 + j - m.sx0) < (unsigned)m.ss ? 1u : 0u) << j;
-    // bit j: row ys - 1 + j is a wall, or crosses the square in the wave's columns; bit r: row ys + r is beside
-    // such a row, or may hold cells beside the square
-    unsigned wall_rows = 0, solid_rows = 0, near_rows = 0, ring_rows = 0;
+    const bool grid_cols = OPEN && m.bar > 0 && base <= m.gx0 + m.bar && base + sg.lanes * RC - 1 >= m.gx0 - 1;
+    unsigned gridc = 0;  // likewise for the grid's columns
+    if (grid_cols)
+#pragma unroll
+        for (int j = 0; j < RC + 2; ++j) gridc |= ((unsigned)(x0 - 1 + j - m.gx0) < (unsigned)m.bar ? 1u : 0u) << j;
+    // bit j: row ys - 1 + j is a wall, or crosses the square or the grid's bars in the wave's columns; bit r: row
+    // ys + r is beside such a row, or may hold cells beside the square
+    unsigned wall_rows = 0, solid_rows = 0, grid_rows = 0, near_rows = 0, ring_rows = 0;
 #pragma unroll
     for (int j = 0; j < R + 2; ++j) {
         const int y = ys - 1 + j;
         wall_rows |= (y < 0 || y >= ny ? 1u : 0u) << j;
         solid_rows |= (sq_cols && (unsigned)(y - m.sy0) < (unsigned)m.ss ? 1u : 0u) << j;
+        if (OPEN) grid_rows |= (grid_cols && y >= 0 && y < ny && grid_row(m, y) ? 1u : 0u) << j;
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int y = ys + r;
-        near_rows |= (((wall_rows | solid_rows) >> r) & 7u ? 1u : 0u) << r;
+        near_rows |= (((wall_rows | solid_rows | grid_rows) >> r) & 7u ? 1u : 0u) << r;
         ring_rows |= (r < rows && sq_cols && y >= m.sy0 - 1 && y <= m.sy0 + m.ss ? 1u : 0u) << r;
     }
 #pragma unroll 1
@@ -122,7 +144,8 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
 #pragma unroll
             for (int i = 1; i < 9; ++i) {
                 const int j = r + 1 - CY[i];
-                const bool back = ((wall_rows >> j) & 1u) || (((solid_rows >> j) & 1u) && ((sqc >> (1 - CX[i] + k)) & 1u));
+                const bool back = ((wall_rows >> j) & 1u) || (((solid_rows >> j) & 1u) && ((sqc >> (1 - CX[i] + k)) & 1u)) ||
+                                  (OPEN && ((grid_rows >> j) & 1u) && ((gridc >> (1 - CX[i] + k)) & 1u));
                 word[k] |= (back ? 1u : 0u) << (i - 1);
             }
             // (a lane beyond the wave's columns is in no ring)
@@ -140,9 +163,23 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const int beside = lane == 0 ? (w == 0 ? hp - 1 : w * sg.lanes - 1) : lane == lastl ? (last_wave ? 0 : (w + 1) * sg.lanes) : lc;
     const int beside_low = lane == 0 ? 2 + left_k : lane == lastl ? 4 : 0;
     const int beside_high = lane == 0 ? 4 + left_k : lane == lastl ? 2 : 0;
-    const long long hs = 6LL * hp;  // words of a row: [unit][side][slot]
-    unsigned long long* const mine = a.halo + sg.halo_begin + (long long)unit * 4 * hs;
-    const int wl = g * W + (w == 0 ? W - 1 : w - 1), wr = g * W + (last_wave ? 0 : w + 1);
+    const long long hs = 6LL * hp;  // words of a row: [unit][side][slot]; then, in open channels, of the last columns
+    const long long unit_words = 4 * hs + (OPEN ? 4 * RESIDENT_OUTLET_WORDS : 0);
+    unsigned long long* const mine = a.halo + sg.halo_begin + unit * unit_words;
+    const int wl = wave_at(w == 0 ? W - 1 : w - 1), wr = wave_at(last_wave ? 0 : w + 1);
+    double om[RC];  // open channels: the relaxation rate of the lane's columns (the sponge's rises to the outlet)
+    if constexpr (OPEN) {
+#pragma unroll
+        for (int k = 0; k < RC; ++k) {
+            MemberDev mc = m;
+            sponge_at(mc, x0 + k);
+            om[k] = mc.omega;
+        }
+        if (inlet_wave && lane < R + 2) {
+            const int y = ys - 1 + lane;
+            inlet[g][lane] = f4{inlet_dev(m, 1, y), inlet_dev(m, 5, y), inlet_dev(m, 8, y), 0.0f};
+        }
+    }
 
     float f[R][9][RC];
 #pragma unroll
@@ -163,6 +200,26 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
         if (lane == 0) xe[n][wave][r][0] = f4{f[r][3][0], f[r][6][0], f[r][7][0], 0.0f};
         if (lane == lastl)
             xe[n][wave][r][1] = f4{pick(one, f[r][1][0], f[r][1][1]), pick(one, f[r][5][0], f[r][5][1]), pick(one, f[r][8][0], f[r][8][1]), 0.0f};
+        if (OPEN && outlet_wave) {
+            float* const q = last2[n][g * R + r + 2];
+            if (lane == lastl)
+#pragma unroll
+                for (int i = 0; i < 9; ++i) q[i] = pick(one, f[r][i][0], f[r][i][1]);
+            if (lane == (one ? lastl - 1 : lastl))
+#pragma unroll
+                for (int i = 0; i < 9; ++i) q[12 + i] = pick(one, f[r][i][1], f[r][i][0]);
+        }
+    };
+    // a word of the last columns: lane 0-17 the first of two rows, 18-35 the second
+    const int last_row = lane < 18 ? 0 : 1, last_at = lane - 18 * last_row < 9 ? lane - 18 * last_row : lane - 18 * last_row + 3;
+    auto publish_outlet = [&](int n, unsigned tag) {
+        if (!OPEN || !outlet_wave) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");  // (written by other lanes of the wave)
+        if (lane < RESIDENT_OUTLET_WORDS) {
+            unsigned long long* const p = mine + 4 * hs + lane;
+            if (low_mem) put_word(p + n * RESIDENT_OUTLET_WORDS, last2[n][2 + last_row][last_at], tag);
+            if (high_mem) put_word(p + (2 + n) * RESIDENT_OUTLET_WORDS, last2[n][g * R + R + last_row][last_at], tag);
+        }
     };
     // those of the lowest (side 0: 4, 7, 8) or highest row (side 1: 2, 5, 6); tag: the step they are for
     auto publish_side = [&](int side, int r, int i0, int i1, int i2, int n, unsigned tag) {
@@ -183,6 +240,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     for (int r = 0; r < R; ++r) publish_row(r, 0);
     publish_side(0, 0, 4, 7, 8, 0, tag0 + 1u);
     publish_side(1, R - 1, 2, 5, 6, 0, tag0 + 1u);
+    publish_outlet(0, tag0 + 1u);
     if (a.wait_ticks < 0 && (low_mem || high_mem)) {  // no wait at all (the giving up is tested so)
         __hip_atomic_store(&a.given_up[mi], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
@@ -210,6 +268,20 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
         const unsigned tag = tag0 + (unsigned)t + 1u;
         double* const ps = a.partial + m.part_off + (long long)t * m.ring;
 
+        auto collide = [&](float (&dl)[9], int k, unsigned links, bool ring) -> double {
+            if constexpr (OPEN) {
+                MemberDev mc = m;
+                if (MODEL != 0) {
+                    mc.omega = om[k];
+                } else if (x0 + k > m.sp_x0) {
+                    mc.omega = om[k];
+                    bgk_coefficients(mc);
+                }
+                return collide_cell<MODEL>(mc, dl, links, ring);
+            } else {
+                return collide_cell<MODEL>(m, dl, links, ring);
+            }
+        };
         // row r of the step, given what arrives from the rows below (2, 5, 6) and above (4, 7, 8) and the columns beside
         auto collide_row = [&](int r, const float (&up)[3][RC], const float (&dn)[3][RC], float el, float er) {
             float p[9][RC];
@@ -242,7 +314,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                     float dl[9];
 #pragma unroll
                     for (int i = 0; i < 9; ++i) dl[i] = pinned(p[i][k]);
-                    const double drag = collide_cell<MODEL>(m, dl, mark[k] >> 7 & 0x1FEu, true);
+                    const double drag = collide(dl, k, mark[k] >> 7 & 0x1FEu, true);
 #pragma unroll
                     for (int i = 0; i < 9; ++i) f[r][i][k] = pinned(dl[i]);
                     if (mark[k] >> 16) ps[(int)(mark[k] >> 16) - 1] = drag;
@@ -253,7 +325,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                     float dl[9];
 #pragma unroll
                     for (int i = 0; i < 9; ++i) dl[i] = pinned(p[i][k]);
-                    collide_cell<MODEL>(m, dl, 0u, false);
+                    collide(dl, k, 0u, false);
 #pragma unroll
                     for (int i = 0; i < 9; ++i) f[r][i][k] = pinned(dl[i]);
                 }
@@ -273,6 +345,21 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             left(f[r][7], er.z, o[1]);
             right(f[r][8], el.z, o[2]);
         };
+        // until every lane's words are there; false: given up (bounded: see the top of the file)
+        auto wait = [&](auto&& words) -> bool {
+            long long began = 0;
+            for (int spin = 0;; ++spin) {
+                const bool ok = words();
+                if (__all(ok)) return true;
+                if ((spin & 63) == 63) {
+                    const long long now = wall_clock64();
+                    if (!began) began = now;
+                    const bool late = now - began > a.wait_ticks;
+                    if (late) __hip_atomic_store(&a.given_up[mi], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (late || __hip_atomic_load(&a.given_up[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == epoch) return false;
+                }
+            }
+        };
         // what arrives from the row below the wave (side 0) or above it; false: given up
         auto arrive = [&](int side, float (&o)[3][RC]) -> bool {
             float v[3][RC], e = 0.0f;
@@ -280,25 +367,18 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             for (int q = 0; q < 6; ++q) v[q / 2][q & 1] = 0.0f;
             if (side ? high_mem : low_mem) {
                 // the unit below's side 1, or the unit above's side 0
-                const unsigned long long* const p = mine + (side ? 4 + n : n - 2) * hs;
+                const unsigned long long* const p = mine + (side ? unit_words + n * hs : (2 + n) * hs - unit_words);
                 unsigned long long u[7];
-                long long began = 0;
-                for (int spin = 0;; ++spin) {
+                if (!wait([&] {
 #pragma unroll
-                    for (int q = 0; q < 6; ++q) u[q] = get_word(p + (q * hq + lc));
-                    u[6] = get_word(p + ((side ? beside_high : beside_low) * hq + beside));
-                    bool ok = true;
+                        for (int q = 0; q < 6; ++q) u[q] = get_word(p + (q * hq + lc));
+                        u[6] = get_word(p + ((side ? beside_high : beside_low) * hq + beside));
+                        bool ok = true;
 #pragma unroll
-                    for (int q = 0; q < 7; ++q) ok = ok && (unsigned)(u[q] >> 32) == tag;
-                    if (__all(ok)) break;
-                    if ((spin & 63) == 63) {  // bounded: see the top of the file
-                        const long long now = wall_clock64();
-                        if (!began) began = now;
-                        const bool late = now - began > a.wait_ticks;
-                        if (late) __hip_atomic_store(&a.given_up[mi], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if (late || __hip_atomic_load(&a.given_up[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == epoch) return false;
-                    }
-                }
+                        for (int q = 0; q < 7; ++q) ok = ok && (unsigned)(u[q] >> 32) == tag;
+                        return ok;
+                    }))
+                    return false;
 #pragma unroll
                 for (int q = 0; q < 6; ++q) v[q / 2][q & 1] = __uint_as_float((unsigned)u[q]);
                 e = __uint_as_float((unsigned)u[6]);
@@ -307,6 +387,10 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
 #pragma unroll
                 for (int j = 0; j < 6; ++j) v[j / 2][j & 1] = q[j * 512 + lc];
                 e = q[(side ? beside_high : beside_low) * 512 + beside];
+            }
+            if (OPEN) {  // beside the first and the last column
+                if (inlet_wave) e = pick(lane == 0, side ? inlet[g][R + 1].z : inlet[g][0].y, e);
+                if (outlet_wave) e = pick(lane == lastl, side ? outlet[g][R + 1].z : outlet[g][0].y, e);
             }
             o[0][0] = v[0][0];
             o[0][1] = v[0][1];
@@ -320,8 +404,63 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             return true;
         };
 
+        // Open channels: what enters from the outlet column (outlet_ghost_value) needs the last two columns of the
+        // rows up to two above and below: lanes form the velocities, then the populations, one each.
+        if (OPEN && outlet_wave) {
+            if (low_mem || high_mem) {
+                const unsigned long long* const pl = mine - unit_words + 4 * hs + (2 + n) * RESIDENT_OUTLET_WORDS + lane;
+                const unsigned long long* const ph = mine + unit_words + 4 * hs + n * RESIDENT_OUTLET_WORDS + lane;
+                unsigned long long ul = 0, uh = 0;
+                if (!wait([&] {
+                        bool ok = true;
+                        if (lane < RESIDENT_OUTLET_WORDS) {
+                            if (low_mem) ul = get_word(pl);
+                            if (high_mem) uh = get_word(ph);
+                            ok = (!low_mem || (unsigned)(ul >> 32) == tag) && (!high_mem || (unsigned)(uh >> 32) == tag);
+                        }
+                        return ok;
+                    }))
+                    return;
+                if (lane < RESIDENT_OUTLET_WORDS) {
+                    if (low_mem) last2[n][last_row][last_at] = __uint_as_float((unsigned)ul);
+                    if (high_mem) last2[n][g * R + R + 2 + last_row][last_at] = __uint_as_float((unsigned)uh);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
+            }
+            if (lane < 2 * (R + 4)) {
+                float dl[9];
+#pragma unroll
+                for (int i = 0; i < 9; ++i) dl[i] = last2[n][g * R + (lane >> 1)][12 * (lane & 1) + i];
+                double ux, uy;
+                stored_velocity(dl, ux, uy);
+                double* const q = &vel[g][lane >> 1].ux1 + 2 * (lane & 1);
+                q[0] = ux;
+                q[1] = uy;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
+            if (lane < 3 * (R + 2)) {
+                const int r = lane / 3, d = lane - 3 * r, y = ys - 1 + r;  // directions 3, 6, 7
+                const OutletVel va = vel[g][y > 0 ? r : r + 1], v0 = vel[g][r + 1], vb = vel[g][y + 1 < ny ? r + 2 : r + 1];
+                double rho_g = 1.0;
+                if (m.out_rho) {
+                    float d1[9], d2[9];
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) {
+                        d1[i] = last2[n][g * R + r + 1][i];
+                        d2[i] = last2[n][g * R + r + 1][12 + i];
+                    }
+                    rho_g = outlet_density(m, d1, d2);
+                }
+                ((float*)&outlet[g][r])[d] =
+                    outlet_ghost_value(m, -1.0, d == 0 ? 0.0 : d == 1 ? 1.0 : -1.0, d == 0 ? WD[3] : WD[6], y, va, v0, vb, rho_g);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
+        }
+        auto beside_left = [&](int r) { return OPEN && inlet_wave ? inlet[g][r + 1] : xe[n][wl][r][1]; };
+        auto beside_right = [&](int r) { return OPEN && outlet_wave ? outlet[g][r + 1] : xe[n][wr][r][0]; };
+
         if constexpr (R == 1) {
-            const f4 el = xe[n][wl][0][1], er = xe[n][wr][0][0];
+            const f4 el = beside_left(0), er = beside_right(0);
             float up[3][RC], dn[3][RC];
             if (!arrive(0, up) || !arrive(1, dn)) return;
             collide_row(0, up, dn, el.x, er.x);
@@ -330,14 +469,14 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
         } else {
             // the rows that wait for nothing first: the words from the workgroups beside travel meanwhile
             float below0[3][RC], nu[3][RC];  // what row 1 sends down to row 0; what arrives at the next row from below
-            f4 el = xe[n][wl][0][1], er = xe[n][wr][0][0];
+            f4 el = beside_left(0), er = beside_right(0);
             send_up(0, el, er, nu);
-            el = xe[n][wl][1][1];
-            er = xe[n][wr][1][0];
+            el = beside_left(1);
+            er = beside_right(1);
             send_down(1, el, er, below0);
 #pragma unroll
             for (int r = 1; r + 1 < R; ++r) {
-                const f4 eln = xe[n][wl][r + 1][1], ern = xe[n][wr][r + 1][0];
+                const f4 eln = beside_left(r + 1), ern = beside_right(r + 1);
                 float nn[3][RC], dn[3][RC];
                 send_up(r, el, er, nn);
                 send_down(r + 1, eln, ern, dn);
@@ -350,8 +489,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             {
                 float up[3][RC];
                 if (!arrive(0, up)) return;
-                const f4 e0 = xe[n][wl][0][1], e1 = xe[n][wr][0][0];
-                collide_row(0, up, below0, e0.x, e1.x);
+                collide_row(0, up, below0, beside_left(0).x, beside_right(0).x);
                 publish_side(0, 0, 4, 7, 8, n ^ 1, tag + 1u);
             }
             {
@@ -361,12 +499,14 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                 publish_side(1, R - 1, 2, 5, 6, n ^ 1, tag + 1u);
             }
         }
+        publish_outlet(n ^ 1, tag + 1u);
         lds_barrier();
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (r < rows) {
             unsigned skip = (solid_rows >> (r + 1)) & 1u ? (sqc >> 1) & 3u : 0u;
+            if (OPEN && ((grid_rows >> (r + 1)) & 1u)) skip |= (gridc >> 1) & 3u;
             if (lane >= lastl) skip |= lane > lastl ? 3u : one ? 2u : 0u;
             const unsigned cell = (unsigned)(ys + r) * (unsigned)nx + (unsigned)x0;
 #pragma unroll
@@ -379,22 +519,22 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     }
 }
 
-template <int R>
+template <int R, bool OPEN>
 static hipError_t launch_resident_r(const ResidentArgs& a, int model, hipStream_t st) {
     const dim3 grid(a.total_blocks), block(64 * a.block_waves);
-    if (model == 2) hipLaunchKernelGGL((resident_kernel<R, 2>), grid, block, 0, st, a);
-    else if (model == 1) hipLaunchKernelGGL((resident_kernel<R, 1>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((resident_kernel<R, 0>), grid, block, 0, st, a);
+    if (model == 2) hipLaunchKernelGGL((resident_kernel<R, 2, OPEN>), grid, block, 0, st, a);
+    else if (model == 1) hipLaunchKernelGGL((resident_kernel<R, 1, OPEN>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((resident_kernel<R, 0, OPEN>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_resident(int rows, const ResidentArgs& a, int model, hipStream_t st) {
+hipError_t launch_resident(int rows, bool open, const ResidentArgs& a, int model, hipStream_t st) {
     switch (rows) {
-        case 1: return launch_resident_r<1>(a, model, st);
-        case 2: return launch_resident_r<2>(a, model, st);
-        case 3: return launch_resident_r<3>(a, model, st);
-        case 4: return launch_resident_r<4>(a, model, st);
-        case 6: return launch_resident_r<6>(a, model, st);
+        case 1: return open ? hipErrorInvalidValue : launch_resident_r<1, false>(a, model, st);
+        case 2: return open ? launch_resident_r<2, true>(a, model, st) : launch_resident_r<2, false>(a, model, st);
+        case 3: return open ? launch_resident_r<3, true>(a, model, st) : launch_resident_r<3, false>(a, model, st);
+        case 4: return open ? launch_resident_r<4, true>(a, model, st) : launch_resident_r<4, false>(a, model, st);
+        case 6: return open ? launch_resident_r<6, true>(a, model, st) : launch_resident_r<6, false>(a, model, st);
         default: return hipErrorInvalidValue;
     }
 }

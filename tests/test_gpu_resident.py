@@ -34,7 +34,20 @@ LATTICES = {
 }
 
 
-def _run(members, tile, collision, wait=None):
+# open channels: (members, grid column and bar, sponge column, outlet density)
+OPEN = {
+    "one_wave": ([_m(128, 21, (60, 8, 4)), _m(67, 9, None), _m(9, 4, None)], (1, 1, 40, 0)),
+    "odd_widths": ([_m(201, 33, (120, 12, 6)), _m(129, 30, (100, 13, 5)), _m(257, 14, (250, 4, 4))], (20, 3, 96, 1)),
+    "eight_waves": ([_m(1024, 37, (130, 10, 9)), _m(769, 19, (600, 4, 3))], (64, 4, 500, 0)),
+    "no_sponge": ([_m(330, 50, (80, 20, 8))] * 3, (0, 0, 1 << 30, 1)),
+    "three_rows": ([_m(512, 81, (250, 30, 9))] * 18, (31, 5, 300, 1)),
+    "four_rows": ([_m(513, 129, (250, 60, 9))] * 8, (31, 5, 300, 0)),
+    "six_rows": ([_m(256, 203, (124, 100, 13))] * 28, (100, 7, 200, 1)),
+    "several_launches": ([_m(512, 128, (250, 60, 9))] * 25 + [_m(130, 40, (122, 20, 5))] * 3, (9, 4, 100, 0)),
+}
+
+
+def _run(members, tile, collision, wait=None, opened=None):
     from paper_2005_09323_amd import native
     from paper_2005_09323_amd.ensemble import Ensemble
     ens = Ensemble(members, series_capacity=90)
@@ -43,6 +56,9 @@ def _run(members, tile, collision, wait=None):
     ens.set_tile(tile)
     if collision is not None:
         ens.set_collision("central", *collision)
+    if opened is not None:
+        grid, bar, sponge, outlet = opened
+        ens.set_open_channel(0.05, grid, bar, sponge, 0.9, outlet_density=outlet)
     if wait is not None:
         native.check(ens.lib.lbm_set_wait_limit(ens._ctx, wait))
     ens.init(7, 1e-2)
@@ -66,6 +82,18 @@ def test_resident_bit_identical_to_one_step(lattices, collision):
     drag0, states0, accum0 = _run(members, 0, collision)
     for wait in (None, -1) if len(members) < 8 else (None,):
         drag, states, accum = _run(members, 20, collision, wait)
+        assert torch.equal(drag, drag0) and torch.equal(accum, accum0), wait
+        for i, (a, b) in enumerate(zip(states, states0)):
+            assert torch.equal(a, b), (wait, i)
+
+
+@pytest.mark.parametrize("collision", [None, (1.0, 1.0, 1.0), (1.2, 0.9, 1.4)])
+@pytest.mark.parametrize("lattices", sorted(OPEN))
+def test_open_resident_bit_identical_to_one_step(lattices, collision):
+    members, opened = OPEN[lattices]
+    drag0, states0, accum0 = _run(members, 0, collision, None, opened)
+    for wait in (None, -1) if len(members) < 8 else (None,):
+        drag, states, accum = _run(members, 20, collision, wait, opened)
         assert torch.equal(drag, drag0) and torch.equal(accum, accum0), wait
         for i, (a, b) in enumerate(zip(states, states0)):
             assert torch.equal(a, b), (wait, i)
