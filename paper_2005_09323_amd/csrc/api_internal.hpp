@@ -55,13 +55,16 @@ struct SweepPlan {
 // The resident launches of a batch: each holds some of the members (all of
 // their rows) for the whole chunk.
 constexpr int RESIDENT_PASSES = 1 << lbm::RESIDENT_PASS_BITS;
+struct ResidentPass {
+    int cells = 0, rows = 0;  // columns per lane, rows per wave
+    lbm::ResidentArgs args;
+};
 struct ResidentPlan {
-    int rows = 0;  // rows per wave
     int passes = 0;
     double us = 0.0;        // estimated time per step
     double bytes = 0.0;     // of the state, read and written once
-    size_t halo_words = 0;  // of all passes
-    lbm::ResidentArgs args[RESIDENT_PASSES];
+    size_t halo_words = 0;  // the most of a pass
+    ResidentPass pass[RESIDENT_PASSES];
 };
 
 // What a captured chunk of lbm_step_batch depends on besides device memory:

@@ -84,13 +84,14 @@ struct ResidentSegment {
     int ranges;
     int waves, lanes;      // as SweepSegment
     int groups;
-    long long halo_begin;  // first halo word of the segment: [unit]{[side 2][slot 2][6][(nx + 1) / 2], open: [side][slot][36]}
+    long long halo_begin;  // first halo word of the segment: [unit]{[side 2][slot 2][3 cells][lanes of the width], open: [side][slot][36]}
 };
 
 // A word's tag: the launch's number (below RESIDENT_EPOCHS), its pass and the step it is for.
 constexpr int RESIDENT_STEP_BITS = 7, RESIDENT_PASS_BITS = 5;
 constexpr int RESIDENT_EPOCHS = 1 << (32 - RESIDENT_STEP_BITS - RESIDENT_PASS_BITS);
 
+constexpr int RESIDENT_WIDEST = 1024;         // columns
 constexpr int RESIDENT_OUTLET_WORDS = 36;  // open channels: two rows of the last two columns
 
 struct ResidentArgs {
@@ -178,8 +179,8 @@ hipError_t launch_step(int tile_id, const StepArgs& a, int model, hipStream_t st
 hipError_t launch_step2(int waves, const StepArgs& a, int model, hipStream_t st);
 // up to four steps per launch
 hipError_t launch_sweep(int steps, const SweepArgs& a, int model, hipStream_t st);
-// a chunk of steps in one launch, `rows` (1, periodic channels only, 2, 3, 4 or 6) rows per wave
-hipError_t launch_resident(int rows, bool open, const ResidentArgs& a, int model, hipStream_t st);
+// a chunk of steps in one launch, `cells` columns per lane and `rows` rows per wave (the host's table of cuts)
+hipError_t launch_resident(int cells, int rows, bool open, const ResidentArgs& a, int model, hipStream_t st);
 hipError_t launch_init(const InitArgs& a, int n_members, long long max_cells, hipStream_t st);
 // the outlet ghost columns of the open-channel members for the next one-step launch
 hipError_t launch_outlet_ghost(const GhostArgs& a, int n_members, int max_ny, hipStream_t st);

@@ -212,28 +212,40 @@ static bool two_step_now(const lbm_ctx* c) {
     return 2 * groups >= 3LL * c->cu_count;
 }
 
-// Estimated us of one step of a resident launch with `rows` rows per wave: the
-// rows' time, with waves alone on their SIMD or two on each, or that of the
-// words between workgroups (`sides` rows of a wave handed to another
-// workgroup) if they take longer.  Measured, MI355X, one step: 1 x 256 x 64
-// with 1, 2, 3, 4, 6 rows 2.3, 3.3, 4.1, 5.0, 6.5 (lone waves, 512 columns 10 %
-// more); per launch of 64 x 512 x 128 with 2, 3, 4, 6 rows in workgroups of
-// eight waves 4.0, 5.2, 6.6, 8.9; the words: 4 x 512 x 128, one row, 4096 sides
-// 6.3 us, 2048 sides 3.6.  Open channels (the outlet's waves first wait for the
-// last columns beside them and form its populations): 8 x 512 x 128 with 2, 3,
-// 4, 6 rows 5.4, 6.1, 7.2, 10.5.
-static double resident_cost(int rows, bool two, bool open, double sides) {
-    static const double lone[] = {0, 2.4, 3.4, 4.3, 5.4, 0, 7.0}, both[] = {0, 3.0, 3.8, 5.0, 6.3, 0, 8.4},
-                        opened[] = {0, 0, 5.1, 6.0, 7.2, 0, 10.3};
-    return std::max((open ? opened : two ? both : lone)[rows], 1.5e-3 * sides) + 1.5e-4 * sides;
+// The resident kernel's cuts, with the us of a step of a full launch (waves
+// alone on their SIMD, two on each, and open channels, whose outlet's waves
+// first wait for the last columns beside them).  Measured, MI355X, us per
+// step: 1 x 256 x 64 with two columns per lane and 1, 2, 3, 4, 6 rows 2.2, 3.0,
+// 3.9, 4.5, 6.0 (lone waves); 64 x 512 x 128, per launch, in workgroups of eight
+// waves, with 2, 3, 4, 6 rows 4.0, 5.2, 6.6, 8.9, and with three columns and 2,
+// 3, 4 rows 5.0, 6.3, 7.8.  Two columns fill eight waves in lattices of 113-128,
+// 225-256, 449-512 or 897-1024 columns, three in 169-192, 337-384 or 673-768:
+// 24 x 330 x 110 8.4 with two columns, 6.8 with three, open 64 x 513 x 129 71 and
+// 46.  (One column per lane: 2.4 for 1 x 256 x 64; five: 21 for 24 x 330 x 110,
+// its registers spill.)  Open: 8 x 512 x 128 with 2, 3, 4, 6 rows 5.4, 6.1, 7.2,
+// 10.5, 10 x 640 x 100 with three columns and 2, 3 rows 6.6, 7.6.  Central
+// moments with three rates take 1.3 times as long.
+struct ResidentCut {
+    int cells, rows;            // columns per lane, rows per wave
+    double lone, both, opened;  // us per step (0: not made)
+};
+constexpr ResidentCut RESIDENT_CUTS[] = {
+    {2, 1, 2.2, 3.0, 0.0}, {2, 2, 3.1, 3.8, 4.8}, {2, 3, 4.1, 5.0, 5.8}, {2, 4, 4.9, 6.2, 7.1},
+    {2, 6, 6.5, 8.2, 10.2}, {3, 2, 4.5, 5.0, 6.1}, {3, 3, 5.8, 6.5, 7.7}, {3, 4, 7.0, 7.8, 0.0},
+};
+// One step: the rows' time, or that of the words between workgroups (`sides`
+// rows of a wave handed to another workgroup) if they take longer (4 x 512 x
+// 128, one row of two columns per lane: 4096 sides 6.3 us, 2048 sides 3.6).
+static double resident_cost(const ResidentCut& cut, bool two, bool open, double sides) {
+    return std::max(open ? cut.opened : two ? cut.both : cut.lone, 0.75e-3 * cut.cells * sides) + 0.75e-4 * cut.cells * sides;
 }
 
 // The resident launches of the next batch, if the adaptive shape may have any: a
 // whole chunk of steps per launch with the populations in registers (channels
 // of up to 1024 columns, all workgroups of a launch side by side on
 // the device: two waves per SIMD at most), as many launches as the members
-// need.  Rows per wave and waves per workgroup (four, two of them on a compute
-// unit, or eight) with the least estimated time: more rows per wave are fewer
+// need.  The cut, and the waves per workgroup (four, two of them on a compute
+// unit, or eight), with the least estimated time: more rows per wave are fewer
 // launches, fewer rows a shorter step; eight waves hand half as many rows to
 // other workgroups as two times four (16 x 512 x 128: 7.0 us per step instead
 // of 7.7), four leave small ensembles a SIMD per wave (1 x 256 x 64: 2.3
@@ -254,33 +266,32 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
         const int end = s + 1 < c->nseg ? c->seg[s + 1].member_begin : c->n;
         cells += (double)(listed ? c->n_active : end - c->seg[s].member_begin) * d.nx * d.ny;
     }
-    if (widest > 64 * SWEEP_WAVES * SWEEP_CELLS || cells > RESIDENT_PASSES * 1.6e6) return false;
-    // the launches with `rows` rows per wave and workgroups of `waves` waves (or one row of the lattice, if wider)
-    auto cut = [&](int rows, int waves, ResidentPlan& q) {
-        q.rows = rows;
-        q.passes = 0;
-        q.us = 0.0;
-        q.halo_words = 0;
+    if (widest > RESIDENT_WIDEST || cells > RESIDENT_PASSES * 1.6e6) return false;
+    // adds the launches of the runs s0 .. s1 - 1 with a cut and workgroups of `waves` waves (or one row of the lattice,
+    // if wider) to a plan
+    auto cut = [&](const ResidentCut& rc, int waves, int s0, int s1, ResidentPlan& q) {
         int block_waves = 1;
-        for (int s = 0; s < c->nseg; ++s) {
-            const int w = (c->desc[c->seg[s].member_begin].nx + 64 * SWEEP_CELLS - 1) / (64 * SWEEP_CELLS);
+        for (int s = s0; s < s1; ++s) {
+            const int w = (c->desc[c->seg[s].member_begin].nx + 64 * rc.cells - 1) / (64 * rc.cells);
+            if (w > SWEEP_WAVES) return false;
             block_waves = std::max(block_waves, w * std::max(1, waves / w));
         }
         const long long slots = (long long)c->cu_count * (SWEEP_WAVES / block_waves);
+        const int first = q.passes;
         long long blocks = slots, sides = 0, words = 0;  // (no pass yet)
         auto close = [&] {
-            if (!q.passes) return;
-            q.args[q.passes - 1].total_blocks = (int)blocks;
-            q.us += resident_cost(rows, blocks * block_waves > 4LL * c->cu_count, c->open, (double)sides);
+            if (q.passes == first) return;
+            q.pass[q.passes - 1].args.total_blocks = (int)blocks;
+            q.us += (c->model == 1 ? 1.3 : 1.0) * resident_cost(rc, blocks * block_waves > 4LL * c->cu_count, c->open, (double)sides);
         };
-        for (int s = 0; s < c->nseg; ++s) {
+        for (int s = s0; s < s1; ++s) {
             const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
             ResidentSegment g;
-            const int lanes = (d.nx + SWEEP_CELLS - 1) / SWEEP_CELLS;
+            const int lanes = (d.nx + rc.cells - 1) / rc.cells;
             g.waves = (lanes + 63) / 64;
             g.lanes = (lanes + g.waves - 1) / g.waves;
             g.groups = std::max(1, waves / g.waves);
-            g.ranges = (d.ny + g.groups * rows - 1) / (g.groups * rows);
+            g.ranges = (d.ny + g.groups * rc.rows - 1) / (g.groups * rc.rows);
             if (g.ranges > slots) return false;
             int m = listed ? 0 : c->seg[s].member_begin;
             const int end = listed ? c->n_active : s + 1 < c->nseg ? c->seg[s + 1].member_begin : c->n;
@@ -288,44 +299,68 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
                 if (slots - blocks < g.ranges) {  // another pass
                     close();
                     if (q.passes == RESIDENT_PASSES) return false;
-                    q.args[q.passes++].nseg = 0;
+                    ResidentPass& p = q.pass[q.passes++];
+                    p.cells = rc.cells;
+                    p.rows = rc.rows;
+                    p.args.nseg = 0;
+                    p.args.block_waves = block_waves;
                     blocks = sides = words = 0;
                 }
-                ResidentArgs& a = q.args[q.passes - 1];
+                ResidentArgs& a = q.pass[q.passes - 1].args;
                 const int here = (int)std::min<long long>(end - m, (slots - blocks) / g.ranges);
                 g.block_begin = (int)blocks;
                 g.member_begin = m;
                 g.halo_begin = words;
                 a.seg[a.nseg++] = g;
-                a.block_waves = block_waves;
                 blocks += (long long)here * g.ranges;
                 sides += 2LL * here * (g.ranges - 1) * g.waves;
-                words += (long long)here * g.ranges * (24 * ((d.nx + 1) / 2) + (c->open ? 4 * RESIDENT_OUTLET_WORDS : 0));
+                words += (long long)here * g.ranges * (12LL * rc.cells * lanes + (c->open ? 4 * RESIDENT_OUTLET_WORDS : 0));
                 q.halo_words = std::max(q.halo_words, (size_t)words);
                 m += here;
             }
         }
         close();
-        return q.passes > 0;
+        return q.passes > first;
     };
-    p.us = 1e300;
-    p.bytes = 72.0 * cells;
+    // the best cut of the runs s0 .. s1 - 1 (null: none fits); us: its estimate
     ResidentPlan q;
-    int best_rows = 0, best_waves = 0;
-    for (int waves : {4, 8}) {
-        if (c->open && waves < 8) continue;  // (its LDS fits once on a compute unit)
-        for (int rows : {1, 2, 3, 4, 6}) {
-            if (c->open && rows < 2) continue;  // (the outlet looks two rows away)
-            if (cut(rows, waves, q) && q.us < p.us) {
-                p.us = q.us;
-                best_rows = rows;
-                best_waves = waves;
+    auto best_cut = [&](int s0, int s1, int& best_waves, double& us) {
+        const ResidentCut* best = nullptr;
+        for (int waves : {4, 8})
+            for (const ResidentCut& rc : RESIDENT_CUTS) {
+                if (c->open ? waves < 8 || rc.opened == 0.0 : waves < 8 && rc.cells > 2) continue;  // (their LDS fits once on a compute unit)
+                q.passes = 0;
+                q.us = 0.0;
+                if (cut(rc, waves, s0, s1, q) && (!best || q.us < us)) {
+                    us = q.us;
+                    best = &rc;
+                    best_waves = waves;
+                }
             }
-        }
+        return best;
+    };
+    // all runs with one cut, or each run with its own (24 x 330 x 110 with 40 x 201 x 75: 14.0 and 11.8 us per step)
+    int waves[MAX_SEGMENTS + 1];
+    const ResidentCut* own[MAX_SEGMENTS + 1];
+    double all = 1e300, each = 0.0, us = 0.0;
+    own[c->nseg] = best_cut(0, c->nseg, waves[c->nseg], us);
+    if (own[c->nseg]) all = us;
+    for (int s = 0; s < c->nseg && c->nseg > 1 && each < all; ++s) {
+        own[s] = best_cut(s, s + 1, waves[s], us);
+        each += own[s] ? us : 1e300;
     }
-    if (!best_rows || !cut(best_rows, best_waves, p)) return false;
+    p.passes = 0;
+    p.us = 0.0;
+    p.bytes = 72.0 * cells;
+    p.halo_words = 0;
+    if (c->nseg > 1 && each < all) {
+        for (int s = 0; s < c->nseg; ++s)
+            if (!cut(*own[s], waves[s], s, s + 1, p)) return false;
+    } else if (!own[c->nseg] || !cut(*own[c->nseg], waves[c->nseg], 0, c->nseg, p)) {
+        return false;
+    }
     for (int k = 0; k < p.passes; ++k) {
-        ResidentArgs& a = p.args[k];
+        ResidentArgs& a = p.pass[k].args;
         a.members = c->d_members;
         a.parity = c->d_parity;
         a.active = c->d_active;
@@ -352,9 +387,11 @@ static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps,
         c->resident_chunks = 0;
     }
     for (int k = 0; k < p.passes; ++k) {
-        p.args[k].n_steps = steps;
-        p.args[k].flip = flip;
-        const hipError_t e = launch_resident(p.rows, c->open, p.args[k], c->model, st);
+        ResidentArgs& a = p.pass[k].args;
+
+        a.n_steps = steps;
+        a.flip = flip;
+        const hipError_t e = launch_resident(p.pass[k].cells, p.pass[k].rows, c->open, a, c->model, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -386,7 +423,7 @@ static bool ensure_halo(lbm_ctx* c, ResidentPlan& p) {
         if (fill_int((int*)c->d_halo, (int)(2 * p.halo_words), 0, c->stream) != hipSuccess) return false;
         c->halo_words = p.halo_words;
     }
-    for (int k = 0; k < p.passes; ++k) p.args[k].halo = c->d_halo;
+    for (int k = 0; k < p.passes; ++k) p.pass[k].args.halo = c->d_halo;
     return true;
 }
 
@@ -413,18 +450,25 @@ static hipError_t admit_resident(lbm_ctx* c, ResidentUsers& u, const ResidentPla
         if ((e = hipEventCreateWithFlags(&c->resident_done, hipEventDisableTiming)) != hipSuccess) return e;
         u.users.push_back(c);
     }
-    c->resident_places = SWEEP_WAVES / p.args[0].block_waves;
+    c->resident_places = 0;  // (its launches differ: beside no other's)
     c->resident_blocks = 0;
-    for (int k = 0; k < p.passes; ++k) c->resident_blocks = std::max(c->resident_blocks, p.args[k].total_blocks);
-    long long blocks = c->resident_blocks;
     bool fit = true;
+    for (int k = 0; k < p.passes; ++k) {
+        const ResidentArgs& a = p.pass[k].args;
+        fit = fit && a.block_waves == p.pass[0].args.block_waves;
+        c->resident_blocks = std::max(c->resident_blocks, a.total_blocks);
+    }
+    if (fit) c->resident_places = SWEEP_WAVES / p.pass[0].args.block_waves;
+    int others = 0;
+    long long blocks = c->resident_blocks;
     for (const lbm_ctx* o : u.users)
         if (o != c && o->device == c->device && hipEventQuery(o->resident_done) == hipErrorNotReady) {
+            ++others;
             blocks += o->resident_blocks;
             fit = fit && o->resident_places == c->resident_places;
         }
     (void)hipGetLastError();  // (not ready)
-    if (fit && blocks <= (long long)c->cu_count * c->resident_places) return hipSuccess;
+    if (!others || (fit && blocks <= (long long)c->cu_count * c->resident_places)) return hipSuccess;
     for (const lbm_ctx* o : u.users)
         if (o != c && o->device == c->device && (e = hipStreamWaitEvent(c->stream, o->resident_done, 0)) != hipSuccess) return e;
     return hipSuccess;

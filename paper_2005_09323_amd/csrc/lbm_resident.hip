@@ -1,7 +1,7 @@
 // A whole chunk of lattice steps in one launch, with the populations in the
 // registers of the device.
 //
-// A wave holds R rows of up to 128 columns (two cells per lane), all nine
+// A wave holds R rows of up to 64 C columns (C cells per lane), all nine
 // populations, from the first step of the chunk to the last; the waves of a
 // workgroup span one member's width and a few groups of R rows, and the
 // workgroups of a member share its height.  In a step a row pulls from the
@@ -33,14 +33,14 @@
 // per step, 6.8 with one launch per step); with the registers full, the FP64
 // units (16 x 512 x 128, four rows per wave, two waves per SIMD: 7.0 us, 3.5 of
 // them the 204 FP64 instructions of a wave's row at 5.2 cycles of 2.4 GHz; 15.6
-// us with one launch per step).  Six rows are the most that 256 registers hold (eight
-// spill 73).  Rows in the order from the bottom up, waiting first: 9.3 us;
+// us with one launch per step).  Six rows of two cells per lane, or four
+// of three, are the most that 256 registers hold (eight spill 73, two of five
+// 20).  Rows in the order from the bottom up, waiting first: 9.3 us;
 // walls and square links worked out in each step instead of once: 8.7.
 #include "lbm_device.hpp"
 
 namespace lbm {
 
-constexpr int RC = 2;  // cells per lane
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef unsigned u2 __attribute__((ext_vector_type(2)));
 
@@ -54,16 +54,16 @@ __device__ __forceinline__ unsigned long long get_word(const unsigned long long*
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int R, int MODEL, bool OPEN>
+template <int C, int R, int MODEL, bool OPEN>
 __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void resident_kernel(ResidentArgs a) {
     // columns beside a wave: [slot][wave][row][side]: side 0 its first cell (3, 6, 7), side 1 its last (1, 5, 8)
     __shared__ f4 xe[2][SWEEP_WAVES][R][2];
     // rows beside a wave of the workgroup: [slot][side][direction x cell of the lane][row group x lanes]:
     // side 0 the group's lowest row (4, 7, 8), side 1 its highest (2, 5, 6)
-    __shared__ float yh[2][2][6 * 512];
+    __shared__ float yh[2][2][3 * C * 512];
     // the lane's cells of a row beside a wall or the square: bits 0-7 the directions 1-8 that come from a wall or
     // the square, bits 8-15 those that go to the square, from bit 16 the cell's place in the ring + 1
-    __shared__ u2 marks[SWEEP_WAVES][R][64];
+    __shared__ __attribute__((aligned(16))) unsigned marks[SWEEP_WAVES][R][64][C];
     // open channels: what enters from the inlet (1, 5, 8) and the outlet (3, 6, 7) column, rows -1 .. R of a row
     // group; the last two columns (nx - 1 and nx - 2, nine populations each) of rows -2 .. groups R + 1 of the
     // workgroup, [slot]; their velocities, rows -2 .. R + 1 of a row group
@@ -97,26 +97,32 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const int nx = m.nx, ny = m.ny;
     const unsigned plane = (unsigned)nx * (unsigned)ny;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, (int)(36u * plane), BUFFER_RSRC_WORD3);
-    const int base = w * sg.lanes * RC;
-    const int x0 = base + RC * lane;
+    const int base = w * sg.lanes * C;
+    const int x0 = base + C * lane;
     const bool last_wave = w == W - 1;
-    const int lastl = last_wave ? (nx - base + RC - 1) / RC - 1 : sg.lanes - 1;
-    const bool one = last_wave && nx - base - RC * lastl == 1;  // the last lane has one cell
+    const int lastl = last_wave ? (nx - base + C - 1) / C - 1 : sg.lanes - 1;
+    const int lastk = last_wave ? nx - base - C * lastl - 1 : C - 1;  // the last cell of the wave's last lane
+    auto last_cell = [&](const float (&v)[C]) {
+        float e = v[C - 1];
+#pragma unroll
+        for (int k = 0; k < C - 1; ++k) e = pick(lastk == k, v[k], e);
+        return e;
+    };
     const int ys = (range * sg.groups + g) * R;                 // the wave's lowest row
     const int rows = min(R, ny - ys);                           // <= 0: no row (it only meets the barriers)
     const bool below = rows > 0 && ys > 0, above = rows == R && ys + R < ny;
     const bool low_mem = below && g == 0, high_mem = above && g == sg.groups - 1;
     const bool outlet_wave = OPEN && last_wave, inlet_wave = OPEN && w == 0;
-    const bool sq_cols = m.ss > 0 && base <= m.sx0 + m.ss && base + sg.lanes * RC - 1 >= m.sx0 - 1;
+    const bool sq_cols = m.ss > 0 && base <= m.sx0 + m.ss && base + sg.lanes * C - 1 >= m.sx0 - 1;
     unsigned sqc = 0;  // bit j: column x0 - 1 + j crosses the square
     if (sq_cols)
 #pragma unroll
-        for (int j = 0; j < RC + 2; ++j) sqc |= ((unsigned)(x0 - 1 + j - m.sx0) < (unsigned)m.ss ? 1u : 0u) << j;
-    const bool grid_cols = OPEN && m.bar > 0 && base <= m.gx0 + m.bar && base + sg.lanes * RC - 1 >= m.gx0 - 1;
+        for (int j = 0; j < C + 2; ++j) sqc |= ((unsigned)(x0 - 1 + j - m.sx0) < (unsigned)m.ss ? 1u : 0u) << j;
+    const bool grid_cols = OPEN && m.bar > 0 && base <= m.gx0 + m.bar && base + sg.lanes * C - 1 >= m.gx0 - 1;
     unsigned gridc = 0;  // likewise for the grid's columns
     if (grid_cols)
 #pragma unroll
-        for (int j = 0; j < RC + 2; ++j) gridc |= ((unsigned)(x0 - 1 + j - m.gx0) < (unsigned)m.bar ? 1u : 0u) << j;
+        for (int j = 0; j < C + 2; ++j) gridc |= ((unsigned)(x0 - 1 + j - m.gx0) < (unsigned)m.bar ? 1u : 0u) << j;
     // bit j: row ys - 1 + j is a wall, or crosses the square or the grid's bars in the wave's columns; bit r: row
     // ys + r is beside such a row, or may hold cells beside the square
     unsigned wall_rows = 0, solid_rows = 0, grid_rows = 0, near_rows = 0, ring_rows = 0;
@@ -137,9 +143,9 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     for (int r = 0; r < R; ++r) {
         if (!((near_rows >> r) & 1u)) continue;
         const int y = ys + r;
-        unsigned word[RC];
+        unsigned word[C];
 #pragma unroll
-        for (int k = 0; k < RC; ++k) {
+        for (int k = 0; k < C; ++k) {
             word[k] = 0;
 #pragma unroll
             for (int i = 1; i < 9; ++i) {
@@ -152,25 +158,26 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             if (((ring_rows >> r) & 1u) && lane <= lastl && !in_square(m, x0 + k, y) && ring_index(m, x0 + k, y) >= 0)
                 word[k] |= square_links(m, x0 + k, y) << 7 | (unsigned)(ring_index(m, x0 + k, y) + 1) << 16;
         }
-        marks[wave][r][lane] = u2{word[0], word[1]};
+#pragma unroll
+        for (int k = 0; k < C; ++k) marks[wave][r][lane][k] = word[k];
     }
-    // Words and floats of a row beside a wave are laid out [direction 3][cell of the lane 2][lane of the member's
-    // width]; a lane reads its own columns and shifts, and the first and the last lane read the column beside the
+    // Words and floats of a row beside a wave are laid out [direction 3][cell of the lane C][lane of the
+    // member's width]; a lane reads its own columns and shifts, and the first and the last lane read the column beside the
     // wave: of the direction that moves right (d 1 from below: 5, d 2 from above: 8), and left (6 and 7).
-    const int hp = (nx + 1) / 2;
+    const int hp = (nx + C - 1) / C;
     const int lc = min(w * sg.lanes + lane, hp - 1);
-    const int left_k = w == 0 ? (nx - 1) & 1 : 1;
+    const int left_k = w == 0 ? (nx - 1) % C : C - 1;
     const int beside = lane == 0 ? (w == 0 ? hp - 1 : w * sg.lanes - 1) : lane == lastl ? (last_wave ? 0 : (w + 1) * sg.lanes) : lc;
-    const int beside_low = lane == 0 ? 2 + left_k : lane == lastl ? 4 : 0;
-    const int beside_high = lane == 0 ? 4 + left_k : lane == lastl ? 2 : 0;
-    const long long hs = 6LL * hp;  // words of a row: [unit][side][slot]; then, in open channels, of the last columns
+    const int beside_low = lane == 0 ? C + left_k : lane == lastl ? 2 * C : 0;
+    const int beside_high = lane == 0 ? 2 * C + left_k : lane == lastl ? C : 0;
+    const long long hs = 3LL * C * hp;  // words of a row: [unit][side][slot]; then, in open channels, of the last columns
     const long long unit_words = 4 * hs + (OPEN ? 4 * RESIDENT_OUTLET_WORDS : 0);
     unsigned long long* const mine = a.halo + sg.halo_begin + unit * unit_words;
     const int wl = wave_at(w == 0 ? W - 1 : w - 1), wr = wave_at(last_wave ? 0 : w + 1);
-    double om[RC];  // open channels: the relaxation rate of the lane's columns (the sponge's rises to the outlet)
+    double om[C];  // open channels: the relaxation rate of the lane's columns (the sponge's rises to the outlet)
     if constexpr (OPEN) {
 #pragma unroll
-        for (int k = 0; k < RC; ++k) {
+        for (int k = 0; k < C; ++k) {
             MemberDev mc = m;
             sponge_at(mc, x0 + k);
             om[k] = mc.omega;
@@ -181,33 +188,31 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
         }
     }
 
-    float f[R][9][RC];
+    float f[R][9][C];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const unsigned row = (unsigned)max(min(ys + r, ny - 1), 0) * (unsigned)nx;
-        const unsigned voff = 4u * (unsigned)min(x0, nx - RC);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const u2 q = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, 4u * ((unsigned)i * plane + row), 0);
-            const float q0 = __uint_as_float(q.x), q1 = __uint_as_float(q.y);
-            f[r][i][0] = pick(one && lane == lastl, q1, q0);  // the short last lane loaded the row's last two cells
-            f[r][i][1] = q1;
-        }
+        for (int i = 0; i < 9; ++i) load_cells<C>(rs, 4u * (unsigned)x0, 4u * ((unsigned)i * plane + row), f[r][i]);  // (dead cells: any value)
     }
 
     // hand out the populations of row r that leave the wave sideways, for the step with slot n
     auto publish_row = [&](int r, int n) {
         if (lane == 0) xe[n][wave][r][0] = f4{f[r][3][0], f[r][6][0], f[r][7][0], 0.0f};
-        if (lane == lastl)
-            xe[n][wave][r][1] = f4{pick(one, f[r][1][0], f[r][1][1]), pick(one, f[r][5][0], f[r][5][1]), pick(one, f[r][8][0], f[r][8][1]), 0.0f};
+        if (lane == lastl) xe[n][wave][r][1] = f4{last_cell(f[r][1]), last_cell(f[r][5]), last_cell(f[r][8]), 0.0f};
         if (OPEN && outlet_wave) {
             float* const q = last2[n][g * R + r + 2];
             if (lane == lastl)
 #pragma unroll
-                for (int i = 0; i < 9; ++i) q[i] = pick(one, f[r][i][0], f[r][i][1]);
-            if (lane == (one ? lastl - 1 : lastl))
+                for (int i = 0; i < 9; ++i) q[i] = last_cell(f[r][i]);
+            if (lane == (lastk ? lastl : lastl - 1))
 #pragma unroll
-                for (int i = 0; i < 9; ++i) q[12 + i] = pick(one, f[r][i][1], f[r][i][0]);
+                for (int i = 0; i < 9; ++i) {
+                    float e = f[r][i][C - 1];
+#pragma unroll
+                    for (int k = 0; k < C - 1; ++k) e = pick(lastk == k + 1, f[r][i][k], e);
+                    q[12 + i] = e;
+                }
         }
     };
     // a word of the last columns: lane 0-17 the first of two rows, 18-35 the second
@@ -224,16 +229,22 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     // those of the lowest (side 0: 4, 7, 8) or highest row (side 1: 2, 5, 6); tag: the step they are for
     auto publish_side = [&](int side, int r, int i0, int i1, int i2, int n, unsigned tag) {
         if (!(side ? above : below)) return;
-        const float v[6] = {f[r][i0][0], f[r][i0][1], f[r][i1][0], f[r][i1][1], f[r][i2][0], f[r][i2][1]};
+        float v[3 * C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            v[k] = f[r][i0][k];
+            v[C + k] = f[r][i1][k];
+            v[2 * C + k] = f[r][i2][k];
+        }
         if (side ? high_mem : low_mem) {
             if (lane <= lastl) {
                 unsigned long long* const p = mine + (side * 2 + n) * hs;
 #pragma unroll
-                for (int q = 0; q < 6; ++q) put_word(p + (q * hp + lc), v[q], tag);
+                for (int q = 0; q < 3 * C; ++q) put_word(p + (q * hp + lc), v[q], tag);
             }
         } else if (lane <= lastl) {
 #pragma unroll
-            for (int q = 0; q < 6; ++q) yh[n][side][q * 512 + g * hp + lc] = v[q];
+            for (int q = 0; q < 3 * C; ++q) yh[n][side][q * 512 + g * hp + lc] = v[q];
         }
     };
 #pragma unroll
@@ -247,14 +258,16 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     }
     lds_barrier();
 
-    auto right = [&](const float (&v)[RC], float in, float (&o)[RC]) {  // +x movers: one cell to the right
-        o[0] = wave_shr1_in(v[1], in);
-        o[1] = v[0];
+    auto right = [&](const float (&v)[C], float in, float (&o)[C]) {  // +x movers: one cell to the right
+        const float sh = wave_shr1_in(v[C - 1], in);
+#pragma unroll
+        for (int k = C - 1; k > 0; --k) o[k] = v[k - 1];
+        o[0] = sh;
     };
-    auto left = [&](const float (&v)[RC], float in, float (&o)[RC]) {  // -x movers
+    auto left = [&](const float (&v)[C], float in, float (&o)[C]) {  // -x movers
         const float sh = wave_shl1_in(v[0], in);
-        o[0] = pick(one && lane == lastl, in, v[1]);
-        o[1] = pick(lane == lastl, in, sh);
+#pragma unroll
+        for (int k = 0; k < C; ++k) o[k] = pick(lane == lastl && lastk == k, in, k + 1 < C ? v[k + 1 < C ? k + 1 : k] : sh);
     };
 #pragma unroll 1
     for (int t = 0; t < a.n_steps; ++t) {
@@ -271,22 +284,19 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
         auto collide = [&](float (&dl)[9], int k, unsigned links, bool ring) -> double {
             if constexpr (OPEN) {
                 MemberDev mc = m;
-                if (MODEL != 0) {
-                    mc.omega = om[k];
-                } else if (x0 + k > m.sp_x0) {
-                    mc.omega = om[k];
-                    bgk_coefficients(mc);
-                }
+                mc.omega = om[k];
+                __asm__ volatile("" : "+v"(mc.omega));  // (what follows from it would fill the registers otherwise)
+                if (MODEL == 0) bgk_coefficients(mc);
                 return collide_cell<MODEL>(mc, dl, links, ring);
             } else {
                 return collide_cell<MODEL>(m, dl, links, ring);
             }
         };
         // row r of the step, given what arrives from the rows below (2, 5, 6) and above (4, 7, 8) and the columns beside
-        auto collide_row = [&](int r, const float (&up)[3][RC], const float (&dn)[3][RC], float el, float er) {
-            float p[9][RC];
+        auto collide_row = [&](int r, const float (&up)[3][C], const float (&dn)[3][C], float el, float er) {
+            float p[9][C];
 #pragma unroll
-            for (int k = 0; k < RC; ++k) {
+            for (int k = 0; k < C; ++k) {
                 p[0][k] = f[r][0][k];
                 p[2][k] = up[0][k];
                 p[5][k] = up[1][k];
@@ -297,20 +307,21 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             }
             right(f[r][1], el, p[1]);
             left(f[r][3], er, p[3]);
-            u2 mark{0u, 0u};
+            unsigned mark[C] = {};
             if ((nears >> r) & 1u) {  // halfway bounce-back: the cell's own opposite population
-                mark = marks[wave][r][lane];
+#pragma unroll
+                for (int k = 0; k < C; ++k) mark[k] = marks[wave][r][lane][k];
 #pragma unroll
                 for (int i = 1; i < 9; ++i)
 #pragma unroll
-                    for (int k = 0; k < RC; ++k) {
+                    for (int k = 0; k < C; ++k) {
                         const unsigned back = (unsigned)((int)(mark[k] << (32 - i)) >> 31);  // all ones or zero
                         p[i][k] = pinned(__uint_as_float((back & __float_as_uint(f[r][OPP[i]][k])) | (~back & __float_as_uint(p[i][k]))));
                     }
             }
             if ((rings >> r) & 1u) {
 #pragma unroll
-                for (int k = 0; k < RC; ++k) {
+                for (int k = 0; k < C; ++k) {
                     float dl[9];
 #pragma unroll
                     for (int i = 0; i < 9; ++i) dl[i] = pinned(p[i][k]);
@@ -321,7 +332,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                 }
             } else {
 #pragma unroll
-                for (int k = 0; k < RC; ++k) {
+                for (int k = 0; k < C; ++k) {
                     float dl[9];
 #pragma unroll
                     for (int i = 0; i < 9; ++i) dl[i] = pinned(p[i][k]);
@@ -333,15 +344,15 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             publish_row(r, n ^ 1);
         };
         // what row r sends to the row above it, and to the row below
-        auto send_up = [&](int r, const f4& el, const f4& er, float (&o)[3][RC]) {
-            o[0][0] = f[r][2][0];
-            o[0][1] = f[r][2][1];
+        auto send_up = [&](int r, const f4& el, const f4& er, float (&o)[3][C]) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) o[0][k] = f[r][2][k];
             right(f[r][5], el.y, o[1]);
             left(f[r][6], er.y, o[2]);
         };
-        auto send_down = [&](int r, const f4& el, const f4& er, float (&o)[3][RC]) {
-            o[0][0] = f[r][4][0];
-            o[0][1] = f[r][4][1];
+        auto send_down = [&](int r, const f4& el, const f4& er, float (&o)[3][C]) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) o[0][k] = f[r][4][k];
             left(f[r][7], er.z, o[1]);
             right(f[r][8], el.z, o[2]);
         };
@@ -361,39 +372,39 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
             }
         };
         // what arrives from the row below the wave (side 0) or above it; false: given up
-        auto arrive = [&](int side, float (&o)[3][RC]) -> bool {
-            float v[3][RC], e = 0.0f;
+        auto arrive = [&](int side, float (&o)[3][C]) -> bool {
+            float v[3][C], e = 0.0f;
 #pragma unroll
-            for (int q = 0; q < 6; ++q) v[q / 2][q & 1] = 0.0f;
+            for (int q = 0; q < 3 * C; ++q) v[q / C][q % C] = 0.0f;
             if (side ? high_mem : low_mem) {
                 // the unit below's side 1, or the unit above's side 0
                 const unsigned long long* const p = mine + (side ? unit_words + n * hs : (2 + n) * hs - unit_words);
-                unsigned long long u[7];
+                unsigned long long u[3 * C + 1];
                 if (!wait([&] {
 #pragma unroll
-                        for (int q = 0; q < 6; ++q) u[q] = get_word(p + (q * hq + lc));
-                        u[6] = get_word(p + ((side ? beside_high : beside_low) * hq + beside));
+                        for (int q = 0; q < 3 * C; ++q) u[q] = get_word(p + (q * hq + lc));
+                        u[3 * C] = get_word(p + ((side ? beside_high : beside_low) * hq + beside));
                         bool ok = true;
 #pragma unroll
-                        for (int q = 0; q < 7; ++q) ok = ok && (unsigned)(u[q] >> 32) == tag;
+                        for (int q = 0; q <= 3 * C; ++q) ok = ok && (unsigned)(u[q] >> 32) == tag;
                         return ok;
                     }))
                     return false;
 #pragma unroll
-                for (int q = 0; q < 6; ++q) v[q / 2][q & 1] = __uint_as_float((unsigned)u[q]);
-                e = __uint_as_float((unsigned)u[6]);
+                for (int q = 0; q < 3 * C; ++q) v[q / C][q % C] = __uint_as_float((unsigned)u[q]);
+                e = __uint_as_float((unsigned)u[3 * C]);
             } else if (side ? above : below) {
                 const float* const q = &yh[n][side ^ 1][(side ? g + 1 : g - 1) * hp];
 #pragma unroll
-                for (int j = 0; j < 6; ++j) v[j / 2][j & 1] = q[j * 512 + lc];
+                for (int j = 0; j < 3 * C; ++j) v[j / C][j % C] = q[j * 512 + lc];
                 e = q[(side ? beside_high : beside_low) * 512 + beside];
             }
             if (OPEN) {  // beside the first and the last column
                 if (inlet_wave) e = pick(lane == 0, side ? inlet[g][R + 1].z : inlet[g][0].y, e);
                 if (outlet_wave) e = pick(lane == lastl, side ? outlet[g][R + 1].z : outlet[g][0].y, e);
             }
-            o[0][0] = v[0][0];
-            o[0][1] = v[0][1];
+#pragma unroll
+            for (int k = 0; k < C; ++k) o[0][k] = v[0][k];
             if (side) {
                 left(v[1], e, o[1]);
                 right(v[2], e, o[2]);
@@ -461,14 +472,14 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
 
         if constexpr (R == 1) {
             const f4 el = beside_left(0), er = beside_right(0);
-            float up[3][RC], dn[3][RC];
+            float up[3][C], dn[3][C];
             if (!arrive(0, up) || !arrive(1, dn)) return;
             collide_row(0, up, dn, el.x, er.x);
             publish_side(0, 0, 4, 7, 8, n ^ 1, tag + 1u);
             publish_side(1, 0, 2, 5, 6, n ^ 1, tag + 1u);
         } else {
             // the rows that wait for nothing first: the words from the workgroups beside travel meanwhile
-            float below0[3][RC], nu[3][RC];  // what row 1 sends down to row 0; what arrives at the next row from below
+            float below0[3][C], nu[3][C];  // what row 1 sends down to row 0; what arrives at the next row from below
             f4 el = beside_left(0), er = beside_right(0);
             send_up(0, el, er, nu);
             el = beside_left(1);
@@ -477,23 +488,23 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
 #pragma unroll
             for (int r = 1; r + 1 < R; ++r) {
                 const f4 eln = beside_left(r + 1), ern = beside_right(r + 1);
-                float nn[3][RC], dn[3][RC];
+                float nn[3][C], dn[3][C];
                 send_up(r, el, er, nn);
                 send_down(r + 1, eln, ern, dn);
                 collide_row(r, nu, dn, el.x, er.x);
 #pragma unroll
-                for (int q = 0; q < 6; ++q) nu[q / 2][q & 1] = nn[q / 2][q & 1];
+                for (int q = 0; q < 3 * C; ++q) nu[q / C][q % C] = nn[q / C][q % C];
                 el = eln;
                 er = ern;
             }
             {
-                float up[3][RC];
+                float up[3][C];
                 if (!arrive(0, up)) return;
                 collide_row(0, up, below0, beside_left(0).x, beside_right(0).x);
                 publish_side(0, 0, 4, 7, 8, n ^ 1, tag + 1u);
             }
             {
-                float dn[3][RC];
+                float dn[3][C];
                 if (!arrive(1, dn)) return;
                 collide_row(R - 1, nu, dn, el.x, er.x);
                 publish_side(1, R - 1, 2, 5, 6, n ^ 1, tag + 1u);
@@ -505,36 +516,40 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (r < rows) {
-            unsigned skip = (solid_rows >> (r + 1)) & 1u ? (sqc >> 1) & 3u : 0u;
-            if (OPEN && ((grid_rows >> (r + 1)) & 1u)) skip |= (gridc >> 1) & 3u;
-            if (lane >= lastl) skip |= lane > lastl ? 3u : one ? 2u : 0u;
+            unsigned skip = (solid_rows >> (r + 1)) & 1u ? sqc >> 1 : 0u;  // bit k: not written
+            if (OPEN && ((grid_rows >> (r + 1)) & 1u)) skip |= gridc >> 1;
+            if (lane >= lastl) skip |= lane > lastl ? ~0u : ~0u << (lastk + 1);
             const unsigned cell = (unsigned)(ys + r) * (unsigned)nx + (unsigned)x0;
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
                 float* const q = dst + ((unsigned)i * plane + cell);
-                if (!(skip & 1u)) q[0] = f[r][i][0];
-                if (!(skip & 2u)) q[1] = f[r][i][1];
+#pragma unroll
+                for (int k = 0; k < C; ++k)
+                    if (!((skip >> k) & 1u)) q[k] = f[r][i][k];
             }
         }
     }
 }
 
-template <int R, bool OPEN>
+template <int C, int R, bool OPEN>
 static hipError_t launch_resident_r(const ResidentArgs& a, int model, hipStream_t st) {
     const dim3 grid(a.total_blocks), block(64 * a.block_waves);
-    if (model == 2) hipLaunchKernelGGL((resident_kernel<R, 2, OPEN>), grid, block, 0, st, a);
-    else if (model == 1) hipLaunchKernelGGL((resident_kernel<R, 1, OPEN>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((resident_kernel<R, 0, OPEN>), grid, block, 0, st, a);
+    if (model == 2) hipLaunchKernelGGL((resident_kernel<C, R, 2, OPEN>), grid, block, 0, st, a);
+    else if (model == 1) hipLaunchKernelGGL((resident_kernel<C, R, 1, OPEN>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((resident_kernel<C, R, 0, OPEN>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_resident(int rows, bool open, const ResidentArgs& a, int model, hipStream_t st) {
-    switch (rows) {
-        case 1: return open ? hipErrorInvalidValue : launch_resident_r<1, false>(a, model, st);
-        case 2: return open ? launch_resident_r<2, true>(a, model, st) : launch_resident_r<2, false>(a, model, st);
-        case 3: return open ? launch_resident_r<3, true>(a, model, st) : launch_resident_r<3, false>(a, model, st);
-        case 4: return open ? launch_resident_r<4, true>(a, model, st) : launch_resident_r<4, false>(a, model, st);
-        case 6: return open ? launch_resident_r<6, true>(a, model, st) : launch_resident_r<6, false>(a, model, st);
+hipError_t launch_resident(int cells, int rows, bool open, const ResidentArgs& a, int model, hipStream_t st) {
+    switch (10 * cells + rows) {
+        case 21: return open ? hipErrorInvalidValue : launch_resident_r<2, 1, false>(a, model, st);
+        case 22: return open ? launch_resident_r<2, 2, true>(a, model, st) : launch_resident_r<2, 2, false>(a, model, st);
+        case 23: return open ? launch_resident_r<2, 3, true>(a, model, st) : launch_resident_r<2, 3, false>(a, model, st);
+        case 24: return open ? launch_resident_r<2, 4, true>(a, model, st) : launch_resident_r<2, 4, false>(a, model, st);
+        case 26: return open ? launch_resident_r<2, 6, true>(a, model, st) : launch_resident_r<2, 6, false>(a, model, st);
+        case 32: return open ? launch_resident_r<3, 2, true>(a, model, st) : launch_resident_r<3, 2, false>(a, model, st);
+        case 33: return open ? launch_resident_r<3, 3, true>(a, model, st) : launch_resident_r<3, 3, false>(a, model, st);
+        case 34: return open ? hipErrorInvalidValue : launch_resident_r<3, 4, false>(a, model, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -5,9 +5,10 @@ Both collide every cell with the same arithmetic on the same FP32 inputs, so sta
 equal bit for bit: the tolerance is zero.  Sizes sit where the cutting can go wrong: widths around the
 128 columns of a wave and odd ones (a last lane with one cell), one to eight waves per row, heights
 that end inside a wave's rows, workgroups beside one another within and across members, squares across
-wave and row seams and beside the walls and the periodic edge, every number of rows per wave, more
-members than one launch holds, chunks of one step up to the longest, and inactive members.  With a wait limit below zero every member of more
-than one workgroup is given up and stepped by the kernel that waits for nothing.
+wave and row seams and beside the walls and the periodic edge, every number of columns per lane and
+rows per wave, more members than one launch holds, runs of lattices cut alike or each its own way,
+chunks of one step up to the longest, and inactive members.  With a wait limit below zero every member
+of more than one workgroup is given up and stepped by the kernel that waits for nothing.
 """
 import pytest
 import torch
@@ -31,6 +32,10 @@ LATTICES = {
     "four_rows": [_m(512, 131, (250, 60, 9))] * 12,
     "several_launches": [_m(512, 128, (250, 60, 9))] * 25 + [_m(130, 40, (124, 20, 5))] * 3,
     "six_rows": [_m(256, 203, (124, 100, 13))] * 28,
+    "three_columns_two_rows": [_m(575, 101, (190, 40, 9))] * 13,
+    "three_columns_three_rows": [_m(331, 110, (188, 60, 9))] * 24,
+    "three_columns_four_rows": [_m(701, 200, (187, 100, 13))] * 8,
+    "runs_apart": [_m(332, 109, (321, 2, 9))] * 22 + [_m(201, 75, (99, 30, 9))] * 35,
 }
 
 
@@ -44,6 +49,9 @@ OPEN = {
     "four_rows": ([_m(513, 129, (250, 60, 9))] * 8, (31, 5, 300, 0)),
     "six_rows": ([_m(256, 203, (124, 100, 13))] * 28, (100, 7, 200, 1)),
     "several_launches": ([_m(512, 128, (250, 60, 9))] * 25 + [_m(130, 40, (122, 20, 5))] * 3, (9, 4, 100, 0)),
+    "three_columns_two_rows": ([_m(640, 100, (190, 40, 9))] * 10, (62, 5, 300, 1)),
+    "three_columns_three_rows": ([_m(512, 129, (188, 60, 9))] * 11, (31, 5, 300, 0)),
+    "three_columns_odd": ([_m(514, 129, (500, 60, 9))] * 11, (31, 5, 190, 1)),
 }
 
 
