@@ -397,38 +397,42 @@ __device__ void stage_cm(const unsigned short* __restrict__ act, unsigned short*
 __device__ void cm_to_pm(unsigned short* t, int tid) {
     const int c8 = tid & 3, kp = tid >> 2;
     uint4 v[8], o[8];
+    if (tid < 128)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = *(const uint4*)(t + cm_idx(8 * c8 + j, 8 * kp));
+        for (int j = 0; j < 8; ++j) v[j] = *(const uint4*)(t + cm_idx(8 * c8 + j, 8 * kp));
     __syncthreads();
+    if (tid >= 128) return;
     tr8x8(v, o);
 #pragma unroll
     for (int q = 0; q < 8; ++q) *(uint4*)(t + pm_idx(8 * kp + q, 8 * c8)) = o[q];
 }
 
-// Weight gradient of a 32 -> 32 layer, the wave's input-channel tile nt:
-// all nine taps (3 x 3 x 2 accumulator tiles), added to out (the partial
+// Weight gradient of a 32 -> 32 layer, the wave's input-channel tile nt and
+// output-channel tiles mt0 .. mt0 + MT - 1: all nine taps (3 x 3 x MT
+// accumulator tiles), added to out (the partial
 // layout: per tap and tile, each lane's four values), which the first image
 // of a workgroup (first) writes instead.
+template <int MT>
 __device__ void bwd_wgrad32(const unsigned short* dzc, const unsigned short* xc, float* __restrict__ out, bool first,
-                            int lane, int nt) {
+                            int lane, int nt, int mt0) {
     const int col = lane & 15, g = lane >> 4;
     const bool left = (g & 1) == 0;
     const int c = 16 * nt + col;
     __asm__ volatile("" ::: "memory");  // the partial loads below stay here
-    f32x4 acc[3][3][2];
+    f32x4 acc[3][3][MT];
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
+        for (int mt = 0; mt < MT; ++mt) {
             // loaded either way (workspace memory; a branch per load would split the code)
-            const f32x4 v = *(const f32x4*)(out + (((t * 2 + mt) * 2 + nt) * 64 + lane) * 4);
+            const f32x4 v = *(const f32x4*)(out + (((t * 2 + mt0 + mt) * 2 + nt) * 64 + lane) * 4);
             acc[t / 3][t % 3][mt] = first ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : v;
         }
 #pragma unroll 2
     for (int ks = 0; ks < 8; ++ks) {
-        bf16x8 av[2];
+        bf16x8 av[MT];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) av[mt] = lds_b8(dzc + cm_idx(16 * mt + col, 32 * ks + 8 * g));
+        for (int mt = 0; mt < MT; ++mt) av[mt] = lds_b8(dzc + cm_idx(16 * (mt0 + mt) + col, 32 * ks + 8 * g));
         const int y = 2 * ks + (g >> 1);  // the lane's K row
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy) {
@@ -442,38 +446,39 @@ __device__ void bwd_wgrad32(const unsigned short* dzc, const unsigned short* xc,
             for (int dx = 0; dx < 3; ++dx) {
                 const bf16x8 bv = __builtin_bit_cast(bf16x8, row_window(h0, h1, left, dx - 1));
 #pragma unroll
-                for (int mt = 0; mt < 2; ++mt) acc[dy][dx][mt] = mfma32(av[mt], bv, acc[dy][dx][mt]);
+                for (int mt = 0; mt < MT; ++mt) acc[dy][dx][mt] = mfma32(av[mt], bv, acc[dy][dx][mt]);
             }
         }
     }
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) *(f32x4*)(out + (((t * 2 + mt) * 2 + nt) * 64 + lane) * 4) = acc[t / 3][t % 3][mt];
+        for (int mt = 0; mt < MT; ++mt) *(f32x4*)(out + (((t * 2 + mt0 + mt) * 2 + nt) * 64 + lane) * 4) = acc[t / 3][t % 3][mt];
 }
 
 // Weight gradient of the first layer (3 input channels), the wave's column
-// tile nt: columns n = 3 tap + c (27 of 32, the others zero), each lane's
+// tile nt and row tiles mt0 .. mt0 + MT - 1: columns n = 3 tap + c (27 of 32, the others zero), each lane's
 // column with its own tap; added to out in the partial layout (written by
 // the first image).
+template <int MT>
 __device__ void bwd_wgrad1(const unsigned short* dzc, const unsigned short* xc, float* __restrict__ out, bool first,
-                           int lane, int nt) {
+                           int lane, int nt, int mt0) {
     const int col = lane & 15, g = lane >> 4;
     const bool left = (g & 1) == 0;
     const int n = 16 * nt + col;
     const int tap = n / 3, c = n - 3 * (n / 3);
     const int dy = tap / 3 - 1, dx = tap - 3 * (tap / 3) - 1;
     __asm__ volatile("" ::: "memory");  // the partial loads below stay here
-    f32x4 acc[2];
+    f32x4 acc[MT];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-        const f32x4 v = *(const f32x4*)(out + ((mt * 2 + nt) * 64 + lane) * 4);
+    for (int mt = 0; mt < MT; ++mt) {
+        const f32x4 v = *(const f32x4*)(out + (((mt0 + mt) * 2 + nt) * 64 + lane) * 4);
         acc[mt] = first ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : v;
     }
     for (int ks = 0; ks < 8; ++ks) {
-        bf16x8 av[2];
+        bf16x8 av[MT];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) av[mt] = lds_b8(dzc + cm_idx(16 * mt + col, 32 * ks + 8 * g));
+        for (int mt = 0; mt < MT; ++mt) av[mt] = lds_b8(dzc + cm_idx(16 * (mt0 + mt) + col, 32 * ks + 8 * g));
         const int y = 2 * ks + (g >> 1);
         const int yr = y + dy;
         const bool rok = n < 27 && yr >= 0 && yr < 16;
@@ -485,10 +490,10 @@ __device__ void bwd_wgrad1(const unsigned short* dzc, const unsigned short* xc, 
                     wp = row_window(h0, h1, left, 1);
         const bf16x8 bv = __builtin_bit_cast(bf16x8, dx < 0 ? wm : (dx == 0 ? w0 : wp));
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) acc[mt] = mfma32(av[mt], bv, acc[mt]);
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma32(av[mt], bv, acc[mt]);
     }
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) *(f32x4*)(out + ((mt * 2 + nt) * 64 + lane) * 4) = acc[mt];
+    for (int mt = 0; mt < MT; ++mt) *(f32x4*)(out + (((mt0 + mt) * 2 + nt) * 64 + lane) * 4) = acc[mt];
 }
 
 // One row of a data gradient's output: lane (col, g) holds dX of channel
@@ -513,46 +518,47 @@ __device__ __forceinline__ void bwd_row_out(f32x4 acc, unsigned short* xz, int y
     __asm__ volatile("" : "+v"(bs));
 }
 
-// Data gradient of a 32 -> 32 layer, the wave's output-channel tile nt, from
-// dZ (pixel-major, dzp) into xz (the activation of the layer below,
+// Data gradient of a 32 -> 32 layer, the wave's output-channel tile nt and
+// rows y0 .. y0 + ROWS - 1, from dZ (pixel-major, dzp) into xz (the activation of the layer below,
 // channel-major: its mask, replaced by its dZ): a sweep over the rows of dZ as
 // in the forward, each row read once and shifted a pixel either way between
 // lanes, feeding the output rows above, on and below it; output row y is
 // written once dZ row y + 2 has been swept.
+template <int ROWS>
 __device__ void bwd_dgrad32(const unsigned short* dzp, unsigned short* xz, const unsigned short* __restrict__ ft,
-                            float& bs, int lane, int nt) {
+                            float& bs, int lane, int nt, int y0) {
     const int col = lane & 15, g = lane >> 4;
     bf16x8 w[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) w[t] = __builtin_bit_cast(bf16x8, *(const uint4*)(ft + ((t * 2 + nt) * 64 + lane) * 8));
     f32x4 acc[4];
-    acc[0] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    bf16x8 next = lds_b8(dzp + pm_idx(col, 8 * g));
+    bf16x8 next = lds_b8(dzp + pm_idx(max(y0 - 1, 0) * 16 + col, 8 * g));
 #pragma unroll
-    for (int ys = 0; ys < 16; ++ys) {
+    for (int r = -1; r <= ROWS; ++r) {  // dZ row y0 + r
         const bf16x8 v0 = next;
-        if (ys < 15) next = lds_b8(dzp + pm_idx((ys + 1) * 16 + col, 8 * g));
-        // output pixel x reads dZ pixel x - dx: dx = -1, 0, 1
-        const bf16x8 vl = dpp_shift<DPP_ROW_SHL1>(v0), vr = dpp_shift<DPP_ROW_SHR1>(v0);  // pixels x + 1, x - 1
-        if (ys < 15) acc[(ys + 1) & 3] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (r < ROWS) next = lds_b8(dzp + pm_idx(min(y0 + r + 1, 15) * 16 + col, 8 * g));
+        if (r + 1 < ROWS) acc[(r + 1) & 3] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if ((r >= 0 || y0 > 0) && (r < ROWS || y0 + ROWS < 16)) {
+            // output pixel x reads dZ pixel x - dx: dx = -1, 0, 1
+            const bf16x8 vl = dpp_shift<DPP_ROW_SHL1>(v0), vr = dpp_shift<DPP_ROW_SHR1>(v0);  // pixels x + 1, x - 1
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx)
+            for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-            for (int dy = 0; dy < 3; ++dy) {  // output row ys + dy - 1 reads this row through tap (dy, dx)
-                const int y = ys + dy - 1;
-                if (y < 0 || y > 15) continue;
-                const bf16x8 v = dx == 0 ? vl : (dx == 1 ? v0 : vr);
-                acc[y & 3] = mfma32(v, w[dy * 3 + dx], acc[y & 3]);
-            }
-        if (ys >= 2) bwd_row_out(acc[(ys - 2) & 3], xz, ys - 2, col, g, nt, bs);
+                for (int dy = 0; dy < 3; ++dy) {  // output row r + dy - 1 reads this row through tap (dy, dx)
+                    const int y = r + dy - 1;
+                    if (y < 0 || y >= ROWS) continue;
+                    const bf16x8 v = dx == 0 ? vl : (dx == 1 ? v0 : vr);
+                    acc[y & 3] = mfma32(v, w[dy * 3 + dx], acc[y & 3]);
+                }
+        }
+        if (r >= 2) bwd_row_out(acc[(r - 2) & 3], xz, y0 + r - 2, col, g, nt, bs);
     }
-    bwd_row_out(acc[14 & 3], xz, 14, col, g, nt, bs);
-    bwd_row_out(acc[15 & 3], xz, 15, col, g, nt, bs);
+    bwd_row_out(acc[(ROWS - 1) & 3], xz, y0 + ROWS - 1, col, g, nt, bs);
 }
 
 // Per-channel total of bs (channel 16 nt + lane % 16) over the four lanes of
 // the channel, in a fixed order, into out[channel].
-__device__ __forceinline__ void bsum_out(float bs, float* __restrict__ out, int lane, int nt) {
+__device__ __forceinline__ void bsum_out(float bs, float* out, int lane, int nt) {
     bs += __shfl_xor(bs, 16, 64);
     bs += __shfl_xor(bs, 32, 64);
     if (lane < 16) out[16 * nt + lane] = bs;
@@ -562,10 +568,22 @@ __device__ __forceinline__ void bsum_out(float bs, float* __restrict__ out, int 
 // saved activations, one after the other; their parameter gradients are
 // summed into partial row k (each lane adds into its own pieces of the row,
 // which stays in the caches between images).
-__global__ __launch_bounds__(128, 2) void cnn_backward_kernel(CnnArgs a) {
+//
+// Bound by the chain of an image's phases (stage, weight gradient, transpose,
+// data gradient, twice), a barrier after each.  Two waves per image (one per
+// 16 channels) leave half of the SIMDs idle while there are fewer images than
+// two per compute unit; four split the weight gradients by their output
+// channels and the data gradients by their rows: 26.7 -> 22.1 us for 256 images
+// (a training step 50 -> 46.5; 512 images 61 -> 57).  With more images the
+// SIMDs are full either way and the second copy of the windows costs: 1024
+// images 85 us with two waves, 90 with four; 4096 288 and 303.
+constexpr int BWD_TWO_WAVES = 1024;
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void cnn_backward_kernel(CnnArgs a) {
+    constexpr int H = WAVES / 2;  // parts of the output channels (weight gradients) or rows (data gradients)
     __shared__ uint4 tile_p[256 * NC / 8];
     __shared__ uint4 tile_q[256 * NC / 8];
-    __shared__ float bred[2][NC];
+    __shared__ float bred[2][NC], b2red[H][NC], b1red[H][NC];
     unsigned short* const P = (unsigned short*)tile_p;
     unsigned short* const Q = (unsigned short*)tile_q;
     const float* p = a.params;
@@ -582,8 +600,10 @@ __global__ __launch_bounds__(128, 2) void cnn_backward_kernel(CnnArgs a) {
         // hoisted out of the loop to hold registers through every image
         int tid = (int)threadIdx.x;
         __asm__ volatile("" : "+v"(tid) :: "memory");
-        const int lane = tid & 63, wv = tid >> 6;
-        const int c8 = tid & 3, kp = tid >> 2;  // the thread's 8 x 8 block of a tile
+        const int lane = tid & 63, nt = (tid >> 6) & 1;
+        const int h = H == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 7);
+        const int c8 = tid & 3, kp = (tid & 127) >> 2;  // the thread's 8 x 8 block of a tile
+        const bool one = tid < 128, two = H == 1 || tid >= 128;  // the threads of the first tile, and of the second
         const unsigned short* act = a.act + (long long)b * 3 * 256 * NC;  // a1, a2, a3
         // dL/dy for the mean squared error, then through the read-out and the average
         const float gy = 2.0f * (a.y[b] - a.labels[b]) / (float)a.batch;
@@ -592,52 +612,58 @@ __global__ __launch_bounds__(128, 2) void cnn_backward_kernel(CnnArgs a) {
         {
             const unsigned short* a3 = act + 2 * 256 * NC;
             uint4 va[8], vx[8];  // every load in flight before the first is used
+            if (one)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) va[q] = *(const uint4*)(a3 + (8 * kp + q) * NC + 8 * c8);
+                for (int q = 0; q < 8; ++q) va[q] = *(const uint4*)(a3 + (8 * kp + q) * NC + 8 * c8);
+            if (two)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) vx[q] = *(const uint4*)(act + 256 * NC + (8 * kp + q) * NC + 8 * c8);
+                for (int q = 0; q < 8; ++q) vx[q] = *(const uint4*)(act + 256 * NC + (8 * kp + q) * NC + 8 * c8);
+            if (one) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float dg = gy * p[CNN_OFF_W4 + 8 * c8 + j] * (1.0f / 256.0f);
-                float d[8];
-                int n = 0;  // pixels where channel j is active: its bias gradient is n dg
+                for (int j = 0; j < 8; ++j) {
+                    const float dg = gy * p[CNN_OFF_W4 + 8 * c8 + j] * (1.0f / 256.0f);
+                    float d[8];
+                    int n = 0;  // pixels where channel j is active: its bias gradient is n dg
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const uint4 v = va[q];
-                    const unsigned w = (j >> 1) == 0 ? v.x : (j >> 1) == 1 ? v.y : (j >> 1) == 2 ? v.z : v.w;
-                    const bool on = bf2f((unsigned short)(w >> (16 * (j & 1)))) > 0.0f;
-                    d[q] = on ? dg : 0.0f;
-                    n += on;
+                    for (int q = 0; q < 8; ++q) {
+                        const uint4 v = va[q];
+                        const unsigned w = (j >> 1) == 0 ? v.x : (j >> 1) == 1 ? v.y : (j >> 1) == 2 ? v.z : v.w;
+                        const bool on = bf2f((unsigned short)(w >> (16 * (j & 1)))) > 0.0f;
+                        d[q] = on ? dg : 0.0f;
+                        n += on;
+                    }
+                    bs8[j] += (float)n * dg;
+                    *(uint4*)(Q + cm_idx(8 * c8 + j, 8 * kp)) =
+                        uint4{pk_bf16(d[0], d[1]), pk_bf16(d[2], d[3]), pk_bf16(d[4], d[5]), pk_bf16(d[6], d[7])};
                 }
-                bs8[j] += (float)n * dg;
-                *(uint4*)(Q + cm_idx(8 * c8 + j, 8 * kp)) =
-                    uint4{pk_bf16(d[0], d[1]), pk_bf16(d[2], d[3]), pk_bf16(d[4], d[5]), pk_bf16(d[6], d[7])};
             }
-            uint4 t[8];
-            tr8x8(vx, t);
+            if (two) {
+                uint4 t[8];
+                tr8x8(vx, t);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) *(uint4*)(P + cm_idx(8 * c8 + j, 8 * kp)) = t[j];
+                for (int j = 0; j < 8; ++j) *(uint4*)(P + cm_idx(8 * c8 + j, 8 * kp)) = t[j];
+            }
         }
         __syncthreads();
-        bwd_wgrad32(Q, P, part + CNN_PART_W3, b == b0, lane, wv);
+        bwd_wgrad32<2 / H>(Q, P, part + CNN_PART_W3, b == b0, lane, nt, h);
         __syncthreads();
         cm_to_pm(Q, tid);
         __syncthreads();
-        bwd_dgrad32(Q, P, a.wt + CNN_FRAGT3_OFF, bs2, lane, wv);  // P: a2 -> dZ2
+        bwd_dgrad32<16 / H>(Q, P, a.wt + CNN_FRAGT3_OFF, bs2, lane, nt, 16 / H * h);  // P: a2 -> dZ2
         __syncthreads();
-        stage_cm(act, Q, tid);  // a1, the input of layer 2
+        if (one) stage_cm(act, Q, tid);  // a1, the input of layer 2
         __syncthreads();
-        bwd_wgrad32(P, Q, part + CNN_PART_W2, b == b0, lane, wv);
+        bwd_wgrad32<2 / H>(P, Q, part + CNN_PART_W2, b == b0, lane, nt, h);
         __syncthreads();
         cm_to_pm(P, tid);
         __syncthreads();
-        bwd_dgrad32(P, Q, a.wt + CNN_FRAGT2_OFF, bs1, lane, wv);  // Q: a1 -> dZ1
+        bwd_dgrad32<16 / H>(P, Q, a.wt + CNN_FRAGT2_OFF, bs1, lane, nt, 16 / H * h);  // Q: a1 -> dZ1
         __syncthreads();
         // the picture in BF16, channel-major (rows 0..2 of P)
         const float* x = a.x + (long long)b * 3 * 256;
-        for (int q = tid; q < 3 * 256; q += 128) P[cm_idx(q >> 8, q & 255)] = f2bf(x[q]);
+        for (int q = tid; q < 3 * 256; q += 64 * WAVES) P[cm_idx(q >> 8, q & 255)] = f2bf(x[q]);
         __syncthreads();
-        bwd_wgrad1(Q, P, part + CNN_PART_W1, b == b0, lane, wv);
+        bwd_wgrad1<2 / H>(Q, P, part + CNN_PART_W1, b == b0, lane, nt, h);
         __syncthreads();  // the next image overwrites both tiles
     }
 #pragma unroll
@@ -645,13 +671,15 @@ __global__ __launch_bounds__(128, 2) void cnn_backward_kernel(CnnArgs a) {
         float v = bs8[j];
 #pragma unroll
         for (int m = 4; m < 64; m <<= 1) v += __shfl_xor(v, m, 64);
-        if (lane < 4) bred[wv][8 * c8 + j] = v;
+        if (lane < 4 && wv < 2) bred[wv][8 * c8 + j] = v;
     }
-    bsum_out(bs2, part + CNN_PART_B2, lane, wv);
-    bsum_out(bs1, part + CNN_PART_B1, lane, wv);
+    bsum_out(bs2, b2red[wv >> 1], lane, wv & 1);
+    bsum_out(bs1, b1red[wv >> 1], lane, wv & 1);
     __syncthreads();
     if (tid < NC) {
         part[CNN_PART_B3 + tid] = bred[0][tid] + bred[1][tid];
+        part[CNN_PART_B2 + tid] = H == 1 ? b2red[0][tid] : b2red[0][tid] + b2red[H - 1][tid];
+        part[CNN_PART_B1 + tid] = H == 1 ? b1red[0][tid] : b1red[0][tid] + b1red[H - 1][tid];
         float s = 0.0f;  // the read-out: sum over the images of gy times the averages
         for (int b = b0; b < b1; ++b) s += 2.0f * (a.y[b] - a.labels[b]) / (float)a.batch * a.gap[(long long)b * NC + tid];
         part[CNN_PART_W4 + tid] = s;
@@ -840,7 +868,8 @@ hipError_t launch_cnn_forward(const CnnArgs& a, hipStream_t st) {
 }
 hipError_t launch_cnn_backward(const CnnArgs& a, hipStream_t st) {
     const int rows = cnn_partial_rows(a.batch);
-    hipLaunchKernelGGL(cnn_backward_kernel, dim3(rows), dim3(128), 0, st, a);
+    if (a.batch >= BWD_TWO_WAVES) hipLaunchKernelGGL(cnn_backward_kernel<2>, dim3(rows), dim3(128), 0, st, a);
+    else hipLaunchKernelGGL(cnn_backward_kernel<4>, dim3(rows), dim3(256), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const unsigned chunks = (unsigned)((rows + red_chunk(rows) - 1) / red_chunk(rows));

@@ -388,7 +388,6 @@ static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps,
     }
     for (int k = 0; k < p.passes; ++k) {
         ResidentArgs& a = p.pass[k].args;
-
         a.n_steps = steps;
         a.flip = flip;
         const hipError_t e = launch_resident(p.pass[k].cells, p.pass[k].rows, c->open, a, c->model, st);
