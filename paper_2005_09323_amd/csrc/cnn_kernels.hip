@@ -138,18 +138,18 @@ constexpr int FWD_ONE_WAVE = 2048;
 
 // ReLU and BF16 of a lane's output values of one row of one output tile (bias
 // already in the accumulators; channels 16 mt + 4 (lane / 16) + j of pixel
-// lane % 16); into the pixel-major tile (or, for the last layer, the channel
-// sums cs instead) and the saved activation, 8 bytes each.
+// lane % 16); into the pixel-major tile (or, for the last layer, vs instead)
+// and the saved activation, 8 bytes each.
 template <bool LAST>
 __device__ __forceinline__ void fwd_row_out(f32x4 acc, int mt, int y, int col, int g, unsigned short* tile,
-                                            unsigned short* __restrict__ act, f32x4& cs) {
+                                            unsigned short* __restrict__ act, f32x4& vs) {
     f32x4 v;
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = fmaxf(acc[j], 0.0f);
     const uint2 o = uint2{pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])};
     const int c0 = 16 * mt + 4 * g, px = y * 16 + col;
     if (LAST)
-        cs += v;
+        vs = v;
     else
         *(uint2*)(tile + pm_idx(px, c0)) = o;
     if (act) *(uint2*)(act + px * NC + c0) = o;
@@ -164,12 +164,13 @@ __device__ __forceinline__ void fwd_row_out(f32x4 acc, int mt, int y, int col, i
 // In place (src = dst, all rows, both tiles): output row y is complete once
 // input row y + 1 has been swept and is written one row later, over input row
 // y, which no remaining output reads (a wave's LDS accesses complete in program
-// order).  The last layer keeps its outputs out of the tile and sums them per
-// channel, in order within each half of the rows (cs[half]).
+// order).  The last layer keeps its outputs out of the tile: all 16 rows are
+// summed per channel (cs[tile]), eight rows are handed out (cs[row]), for a sum
+// in the same order.
 template <bool LAST, int NMT, int ROWS>
 __device__ __forceinline__ void fwd_layer32(const unsigned short* src, unsigned short* dst,
                                             const unsigned short* __restrict__ frag, const float* __restrict__ bias_p,
-                                            unsigned short* __restrict__ act, f32x4 (*cs)[NMT], int lane, int mt0,
+                                            unsigned short* __restrict__ act, f32x4* cs, int lane, int mt0,
                                             int row0) {
     const int col = lane & 15, g = lane >> 4;
     bf16x8 w[9][NMT];
@@ -192,9 +193,12 @@ __device__ __forceinline__ void fwd_layer32(const unsigned short* src, unsigned 
     };
     auto out_row = [&](int o) {
 #pragma unroll
-        for (int mt = 0; mt < NMT; ++mt)
-            fwd_row_out<LAST>(acc[o & 3][mt], mt0 + mt, row0 + o, col, g, dst, act,
-                              cs[LAST && ROWS == 16 ? o / 8 : 0][mt]);
+        for (int mt = 0; mt < NMT; ++mt) {
+            f32x4 v;
+            fwd_row_out<LAST>(acc[o & 3][mt], mt0 + mt, row0 + o, col, g, dst, act, v);
+            if (LAST && ROWS == 16) cs[mt] += v;
+            else if (LAST) cs[o] = v;
+        }
     };
     bf16x8 next = row_in(0);
 #pragma unroll
@@ -274,7 +278,7 @@ __device__ __forceinline__ void fwd_layer1(const uint2* in2, unsigned short* til
 }
 
 // Per-channel sums of cs over the 16 pixel columns (the lanes of one row of
-// 16, fixed order) into gs[channel] of a half of the rows.
+// 16, fixed order) into gs[channel].
 __device__ __forceinline__ void fwd_channel_sums(f32x4 cs, int mt, int col, int g, float* gs) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -285,12 +289,12 @@ __device__ __forceinline__ void fwd_channel_sums(f32x4 cs, int mt, int col, int 
     }
 }
 
-// The average over both halves of the rows and the read-out.
-__device__ __forceinline__ void fwd_read_out(const CnnArgs& a, int b, const float (*gs)[NC]) {
+// The averages and the read-out.
+__device__ __forceinline__ void fwd_read_out(const CnnArgs& a, int b, const float* gs) {
     const float* p = a.params;
     float y = p[CNN_OFF_B4];
     for (int o = 0; o < NC; ++o) {
-        const float gm = (gs[0][o] + gs[1][o]) * (1.0f / 256.0f);
+        const float gm = gs[o] * (1.0f / 256.0f);
         if (a.gap) a.gap[(long long)b * NC + o] = gm;
         y += gm * p[CNN_OFF_W4 + o];
     }
@@ -305,7 +309,8 @@ __global__ __launch_bounds__(64 * WAVES) void cnn_forward_kernel(CnnArgs a) {
     constexpr int TILES = WAVES == 1 ? 1 : 2, NMT = WAVES == 1 ? 2 : 1, ROWS = WAVES == 1 ? 16 : 8;
     __shared__ uint4 tile4[TILES][256 * NC / 8];  // activation tiles, pixel-major
     __shared__ uint2 in2[256];                    // the input picture: 16 x 16 pixels x 4 channel slots
-    __shared__ float gs[2][NC];
+    __shared__ float gs[NC];
+    __shared__ f32x4 half[2][64];  // four waves: the sums over the first eight rows
     unsigned short* const tile = (unsigned short*)tile4[0];
     unsigned short* const other = (unsigned short*)tile4[TILES - 1];
     const int b = (int)blockIdx.x;
@@ -320,23 +325,31 @@ __global__ __launch_bounds__(64 * WAVES) void cnn_forward_kernel(CnnArgs a) {
     __syncthreads();
     fwd_layer1<NMT, ROWS>(in2, tile, a.wt + CNN_FRAG1_OFF, p + CNN_OFF_B1, act, lane, mt0, row0);
     __syncthreads();
-    f32x4 cs[2][NMT];
+    f32x4 cs[WAVES == 1 ? NMT : ROWS];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) cs[h][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int q = 0; q < (WAVES == 1 ? NMT : ROWS); ++q) cs[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     fwd_layer32<false, NMT, ROWS>(tile, other, a.wt + CNN_FRAG2_OFF, p + CNN_OFF_B2, act ? act + 256 * NC : nullptr, cs,
                                   lane, mt0, row0);
     __syncthreads();
     fwd_layer32<true, NMT, ROWS>(other, nullptr, a.wt + CNN_FRAG3_OFF, p + CNN_OFF_B3, act ? act + 2 * 256 * NC : nullptr,
                                  cs, lane, mt0, row0);
+    if constexpr (WAVES == 1) {
 #pragma unroll
-    for (int mt = 0; mt < NMT; ++mt) {
-        if (WAVES == 1)
+        for (int mt = 0; mt < NMT; ++mt) fwd_channel_sums(cs[mt], mt, col, g, gs);
+    } else {  // rows 0 to 15 in order, as one wave sums them
+        f32x4 sum = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (row0 == 0) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) fwd_channel_sums(cs[h][mt], mt, col, g, gs[h]);
-        else
-            fwd_channel_sums(cs[0][mt], mt0, col, g, gs[wv >> 1]);
+            for (int o = 0; o < ROWS; ++o) sum += cs[o];
+            half[mt0][lane] = sum;
+        }
+        __syncthreads();
+        if (row0 != 0) {
+            sum = half[mt0][lane];
+#pragma unroll
+            for (int o = 0; o < ROWS; ++o) sum += cs[o];
+            fwd_channel_sums(sum, mt0, col, g, gs);
+        }
     }
     __syncthreads();
     if (tid == 0) fwd_read_out(a, b, gs);
@@ -499,9 +512,10 @@ __device__ void bwd_wgrad1(const unsigned short* dzc, const unsigned short* xc, 
 // One row of a data gradient's output: lane (col, g) holds dX of channel
 // 16 nt + col at pixels 4 g .. 4 g + 3 of row y.  dZ of the layer below =
 // [a > 0] dX (a: that layer's activation, held channel-major in xz) replaces
-// a in xz; bs sums it.
+// a in xz; bs sums it, and keep takes its addends (KEEP).
+template <bool KEEP>
 __device__ __forceinline__ void bwd_row_out(f32x4 acc, unsigned short* xz, int y, int col, int g, int nt,
-                                            float& bs) {
+                                            float& bs, float* keep) {
     uint2* const q = (uint2*)(xz + cm_idx(16 * nt + col, y * 16 + 4 * g));
     const uint2 m = *q;
     const unsigned short mb[4] = {(unsigned short)m.x, (unsigned short)(m.x >> 16), (unsigned short)m.y,
@@ -511,6 +525,7 @@ __device__ __forceinline__ void bwd_row_out(f32x4 acc, unsigned short* xz, int y
     for (int j = 0; j < 4; ++j) {
         d[j] = bf2f(mb[j]) > 0.0f ? acc[j] : 0.0f;
         bs += d[j];
+        if (KEEP) keep[j] = d[j];
     }
     *q = uint2{pk_bf16(d[0], d[1]), pk_bf16(d[2], d[3])};
     // the row's sum taken now: left to the scheduler, the additions sink to
@@ -526,7 +541,8 @@ __device__ __forceinline__ void bwd_row_out(f32x4 acc, unsigned short* xz, int y
 // written once dZ row y + 2 has been swept.
 template <int ROWS>
 __device__ void bwd_dgrad32(const unsigned short* dzp, unsigned short* xz, const unsigned short* __restrict__ ft,
-                            float& bs, int lane, int nt, int y0) {
+                            float& bs, int lane, int nt, int y0, float* keep) {
+    constexpr bool KEEP = ROWS < 16;
     const int col = lane & 15, g = lane >> 4;
     bf16x8 w[9];
 #pragma unroll
@@ -551,9 +567,9 @@ __device__ void bwd_dgrad32(const unsigned short* dzp, unsigned short* xz, const
                     acc[y & 3] = mfma32(v, w[dy * 3 + dx], acc[y & 3]);
                 }
         }
-        if (r >= 2) bwd_row_out(acc[(r - 2) & 3], xz, y0 + r - 2, col, g, nt, bs);
+        if (r >= 2) bwd_row_out<KEEP>(acc[(r - 2) & 3], xz, y0 + r - 2, col, g, nt, bs, keep + (KEEP ? 4 * (r - 2) : 0));
     }
-    bwd_row_out(acc[(ROWS - 1) & 3], xz, y0 + ROWS - 1, col, g, nt, bs);
+    bwd_row_out<KEEP>(acc[(ROWS - 1) & 3], xz, y0 + ROWS - 1, col, g, nt, bs, keep + (KEEP ? 4 * (ROWS - 1) : 0));
 }
 
 // Per-channel total of bs (channel 16 nt + lane % 16) over the four lanes of
@@ -573,7 +589,8 @@ __device__ __forceinline__ void bsum_out(float bs, float* out, int lane, int nt)
 // data gradient, twice), a barrier after each.  Two waves per image (one per
 // 16 channels) leave half of the SIMDs idle while there are fewer images than
 // two per compute unit; four split the weight gradients by their output
-// channels and the data gradients by their rows: 26.7 -> 22.1 us for 256 images
+// channels and the data gradients by their rows (every
+// sum in the order that two waves have): 26.7 -> 22.1 us for 256 images
 // (a training step 50 -> 46.5; 512 images 61 -> 57).  With more images the
 // SIMDs are full either way and the second copy of the windows costs: 1024
 // images 85 us with two waves, 90 with four; 4096 288 and 303.
@@ -583,7 +600,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void cnn_backward_kernel(CnnArgs a) 
     constexpr int H = WAVES / 2;  // parts of the output channels (weight gradients) or rows (data gradients)
     __shared__ uint4 tile_p[256 * NC / 8];
     __shared__ uint4 tile_q[256 * NC / 8];
-    __shared__ float bred[2][NC], b2red[H][NC], b1red[H][NC];
+    __shared__ float bred[2][NC], bhalf[2][64];
+    float keep[H == 1 ? 1 : 32];
     unsigned short* const P = (unsigned short*)tile_p;
     unsigned short* const Q = (unsigned short*)tile_q;
     const float* p = a.params;
@@ -649,16 +667,28 @@ __global__ __launch_bounds__(64 * WAVES, 2) void cnn_backward_kernel(CnnArgs a) 
         __syncthreads();
         cm_to_pm(Q, tid);
         __syncthreads();
-        bwd_dgrad32<16 / H>(Q, P, a.wt + CNN_FRAGT3_OFF, bs2, lane, nt, 16 / H * h);  // P: a2 -> dZ2
+        bwd_dgrad32<16 / H>(Q, P, a.wt + CNN_FRAGT3_OFF, bs2, lane, nt, 16 / H * h, keep);  // P: a2 -> dZ2
+        if (H > 1 && h == 0) bhalf[nt][lane] = bs2;
         __syncthreads();
+        if (H > 1 && h == 1) {  // the sum goes on where the first half of the rows ended: the order of two waves
+            bs2 = bhalf[nt][lane];
+#pragma unroll
+            for (int q = 0; q < (H == 1 ? 1 : 32); ++q) bs2 += keep[q];
+        }
         if (one) stage_cm(act, Q, tid);  // a1, the input of layer 2
         __syncthreads();
         bwd_wgrad32<2 / H>(P, Q, part + CNN_PART_W2, b == b0, lane, nt, h);
         __syncthreads();
         cm_to_pm(P, tid);
         __syncthreads();
-        bwd_dgrad32<16 / H>(P, Q, a.wt + CNN_FRAGT2_OFF, bs1, lane, nt, 16 / H * h);  // Q: a1 -> dZ1
+        bwd_dgrad32<16 / H>(P, Q, a.wt + CNN_FRAGT2_OFF, bs1, lane, nt, 16 / H * h, keep);  // Q: a1 -> dZ1
+        if (H > 1 && h == 0) bhalf[nt][lane] = bs1;
         __syncthreads();
+        if (H > 1 && h == 1) {  // the sum goes on where the first half of the rows ended: the order of two waves
+            bs1 = bhalf[nt][lane];
+#pragma unroll
+            for (int q = 0; q < (H == 1 ? 1 : 32); ++q) bs1 += keep[q];
+        }
         // the picture in BF16, channel-major (rows 0..2 of P)
         const float* x = a.x + (long long)b * 3 * 256;
         for (int q = tid; q < 3 * 256; q += 64 * WAVES) P[cm_idx(q >> 8, q & 255)] = f2bf(x[q]);
@@ -673,13 +703,13 @@ __global__ __launch_bounds__(64 * WAVES, 2) void cnn_backward_kernel(CnnArgs a) 
         for (int m = 4; m < 64; m <<= 1) v += __shfl_xor(v, m, 64);
         if (lane < 4 && wv < 2) bred[wv][8 * c8 + j] = v;
     }
-    bsum_out(bs2, b2red[wv >> 1], lane, wv & 1);
-    bsum_out(bs1, b1red[wv >> 1], lane, wv & 1);
+    if (wv >= WAVES - 2) {
+        bsum_out(bs2, part + CNN_PART_B2, lane, wv & 1);
+        bsum_out(bs1, part + CNN_PART_B1, lane, wv & 1);
+    }
     __syncthreads();
     if (tid < NC) {
         part[CNN_PART_B3 + tid] = bred[0][tid] + bred[1][tid];
-        part[CNN_PART_B2 + tid] = H == 1 ? b2red[0][tid] : b2red[0][tid] + b2red[H - 1][tid];
-        part[CNN_PART_B1 + tid] = H == 1 ? b1red[0][tid] : b1red[0][tid] + b1red[H - 1][tid];
         float s = 0.0f;  // the read-out: sum over the images of gy times the averages
         for (int b = b0; b < b1; ++b) s += 2.0f * (a.y[b] - a.labels[b]) / (float)a.batch * a.gap[(long long)b * NC + tid];
         part[CNN_PART_W4 + tid] = s;
