@@ -109,6 +109,7 @@ struct ResidentArgs {
     int n_steps;
     int flip;                // as StepArgs::flip
     int pass;
+    int full;                // every member's width is a multiple of 64 cells per lane
     int total_blocks;
     int block_waves;
     int nseg;

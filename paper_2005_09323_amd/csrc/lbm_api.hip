@@ -304,6 +304,7 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
                     p.rows = rc.rows;
                     p.args.nseg = 0;
                     p.args.block_waves = block_waves;
+                    p.args.full = 1;
                     blocks = sides = words = 0;
                 }
                 ResidentArgs& a = q.pass[q.passes - 1].args;
@@ -312,6 +313,7 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
                 g.member_begin = m;
                 g.halo_begin = words;
                 a.seg[a.nseg++] = g;
+                if (d.nx % (64 * rc.cells)) a.full = 0;
                 blocks += (long long)here * g.ranges;
                 sides += 2LL * here * (g.ranges - 1) * g.waves;
                 words += (long long)here * g.ranges * (12LL * rc.cells * lanes + (c->open ? 4 * RESIDENT_OUTLET_WORDS : 0));

@@ -54,7 +54,9 @@ __device__ __forceinline__ unsigned long long get_word(const unsigned long long*
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int C, int R, int MODEL, bool OPEN>
+// FULL: every member's width is a multiple of 64 C (no lane or cell of a wave is beyond it, and no choice of its end
+// is made in each row: us per step 1 x 256 x 64 2.2 -> 2.1, 16 x 512 x 128 7.2 -> 7.0, 4 x 1024 x 256 7.0 -> 6.7).
+template <int C, int R, int MODEL, bool OPEN, bool FULL>
 __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void resident_kernel(ResidentArgs a) {
     // columns beside a wave: [slot][wave][row][side]: side 0 its first cell (3, 6, 7), side 1 its last (1, 5, 8)
     __shared__ f4 xe[2][SWEEP_WAVES][R][2];
@@ -100,8 +102,8 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const int base = w * sg.lanes * C;
     const int x0 = base + C * lane;
     const bool last_wave = w == W - 1;
-    const int lastl = last_wave ? (nx - base + C - 1) / C - 1 : sg.lanes - 1;
-    const int lastk = last_wave ? nx - base - C * lastl - 1 : C - 1;  // the last cell of the wave's last lane
+    const int lastl = FULL ? 63 : last_wave ? (nx - base + C - 1) / C - 1 : sg.lanes - 1;
+    const int lastk = FULL ? C - 1 : last_wave ? nx - base - C * lastl - 1 : C - 1;  // the last cell of the wave's last lane
     auto last_cell = [&](const float (&v)[C]) {
         float e = v[C - 1];
 #pragma unroll
@@ -267,7 +269,10 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     auto left = [&](const float (&v)[C], float in, float (&o)[C]) {  // -x movers
         const float sh = wave_shl1_in(v[0], in);
 #pragma unroll
-        for (int k = 0; k < C; ++k) o[k] = pick(lane == lastl && lastk == k, in, k + 1 < C ? v[k + 1 < C ? k + 1 : k] : sh);
+        for (int k = 0; k < C; ++k) {
+            const float e = k + 1 < C ? v[k + 1 < C ? k + 1 : k] : sh;
+            o[k] = FULL ? e : pick(lane == lastl && lastk == k, in, e);  // (lane 63's shifted value is `in`)
+        }
     };
 #pragma unroll 1
     for (int t = 0; t < a.n_steps; ++t) {
@@ -315,7 +320,8 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                 for (int i = 1; i < 9; ++i)
 #pragma unroll
                     for (int k = 0; k < C; ++k) {
-                        const unsigned back = (unsigned)((int)(mark[k] << (32 - i)) >> 31);  // all ones or zero
+                        unsigned back;  // all ones or zero (the compiler would make a comparison and a choice of it)
+                        __asm__("v_bfe_i32 %0, %1, %2, 1" : "=v"(back) : "v"(mark[k]), "n"(i - 1));
                         p[i][k] = pinned(__uint_as_float((back & __float_as_uint(f[r][OPP[i]][k])) | (~back & __float_as_uint(p[i][k]))));
                     }
             }
@@ -531,13 +537,20 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     }
 }
 
+template <int C, int R, bool OPEN, bool FULL>
+static hipError_t launch_resident_f(const ResidentArgs& a, int model, hipStream_t st) {
+    const dim3 grid(a.total_blocks), block(64 * a.block_waves);
+    if (model == 2) hipLaunchKernelGGL((resident_kernel<C, R, 2, OPEN, FULL>), grid, block, 0, st, a);
+    else if (model == 1) hipLaunchKernelGGL((resident_kernel<C, R, 1, OPEN, FULL>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((resident_kernel<C, R, 0, OPEN, FULL>), grid, block, 0, st, a);
+    return hipGetLastError();
+}
+
 template <int C, int R, bool OPEN>
 static hipError_t launch_resident_r(const ResidentArgs& a, int model, hipStream_t st) {
-    const dim3 grid(a.total_blocks), block(64 * a.block_waves);
-    if (model == 2) hipLaunchKernelGGL((resident_kernel<C, R, 2, OPEN>), grid, block, 0, st, a);
-    else if (model == 1) hipLaunchKernelGGL((resident_kernel<C, R, 1, OPEN>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((resident_kernel<C, R, 0, OPEN>), grid, block, 0, st, a);
-    return hipGetLastError();
+    if constexpr (C == 2)
+        if (a.full) return launch_resident_f<C, R, OPEN, true>(a, model, st);
+    return launch_resident_f<C, R, OPEN, false>(a, model, st);
 }
 
 hipError_t launch_resident(int cells, int rows, bool open, const ResidentArgs& a, int model, hipStream_t st) {
