@@ -355,7 +355,7 @@ __global__ __launch_bounds__(64 * WAVES) void cnn_forward_kernel(CnnArgs a) {
     if (tid == 0) fwd_read_out(a, b, gs);
 }
 
-// ---- backward: two waves per image ----------------------------------------
+// ---- backward: two or four waves per image ---------------------------------
 //
 // LDS of the image: two 16 KB tiles of 256 pixels x 32 channels (BF16)
 // (32 KB: five images per compute unit).  A tile is channel-major (rows of

@@ -88,7 +88,7 @@ struct ResidentSegment {
 };
 
 // A word's tag: the launch's number (below RESIDENT_EPOCHS), its pass and the step it is for.
-constexpr int RESIDENT_STEP_BITS = 7, RESIDENT_PASS_BITS = 5;
+constexpr int RESIDENT_STEP_BITS = 7, RESIDENT_PASS_BITS = 6;
 constexpr int RESIDENT_EPOCHS = 1 << (32 - RESIDENT_STEP_BITS - RESIDENT_PASS_BITS);
 
 constexpr int RESIDENT_WIDEST = 1024;         // columns
