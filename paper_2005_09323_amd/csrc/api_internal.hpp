@@ -52,6 +52,8 @@ struct SweepPlan {
     SweepPlan() { memset((void*)this, 0, sizeof *this); }  // compared byte by byte
 };
 
+constexpr int RESIDENT_REST = 64;
+
 // The resident launches of a batch: each holds some of the members (all of
 // their rows) for the whole chunk.
 constexpr int RESIDENT_PASSES = 1 << lbm::RESIDENT_PASS_BITS;
@@ -111,6 +113,8 @@ struct lbm_ctx {
     int* d_epoch = nullptr;
     int* d_given_up = nullptr;
     long long wait_ticks = 2000000;  // 20 ms
+    int* gave_up = nullptr;  // pinned: a chunk was given up; the next RESIDENT_REST batches go another way
+    int resident_rest = 0;
     int resident_blocks = 0, resident_places = 1, resident_chunks = 0;
     hipEvent_t resident_done = nullptr;
     int device = 0;

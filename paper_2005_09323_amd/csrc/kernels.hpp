@@ -154,6 +154,7 @@ struct FinalizeArgs {
     // which is stepped again here first, from the buffers below
     int* epoch;
     const int* given_up; // null: the chunk was not a resident one
+    int* gave_up_host;   // pinned: set when a chunk is stepped again
     float* pop0;
     float* pop1;
     double* redo_partial;

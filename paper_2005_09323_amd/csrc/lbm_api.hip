@@ -255,7 +255,11 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
     for (int r : c->run_rows)
         if (r >= 0) return false;  // row ranges given by the caller: the sweep's
     hipStreamCaptureStatus captured;  // a replay would not be known to the other contexts' launches
-    if (hipStreamIsCapturing(c->stream, &captured) != hipSuccess || captured != hipStreamCaptureStatusNone) return false;
+    if (hipStreamIsCapturing(c->stream, &captured) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (captured != hipStreamCaptureStatusNone) return false;
     const bool listed = !every_member && c->n_active < c->n && c->uniform_shape;
     double cells = 0.0;
     int widest = 0;
@@ -412,6 +416,13 @@ struct OutsideCapture {
 // False if there is no memory for them (another kernel steps the batch then).
 static bool ensure_halo(lbm_ctx* c, ResidentPlan& p) {
     const OutsideCapture outside;
+    if (!c->gave_up) {
+        if (hipHostMalloc(&c->gave_up, sizeof(int)) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        *c->gave_up = 0;
+    }
     if (p.halo_words > c->halo_words) {
         if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
         hipFree(c->d_halo);
@@ -780,6 +791,7 @@ extern "C" int lbm_destroy(lbm_ctx* c) {
     hipFree(c->d_epoch);
     hipFree(c->d_given_up);
     hipFree(c->d_halo);
+    if (c->gave_up) hipHostFree(c->gave_up);
     if (c->resident_done) {
         ResidentUsers& u = resident_users();
         const std::lock_guard<std::mutex> hold(u.lock);
@@ -819,6 +831,7 @@ static FinalizeArgs finalize_args(lbm_ctx* c, int n, int accumulate, int swap_pa
     f.pop1 = c->pop[1];
     f.redo_partial = c->d_partial;
     f.ghost = c->d_ghost;
+    f.gave_up_host = c->gave_up;
     return f;
 }
 
@@ -913,7 +926,15 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     SweepPlan sweep;
     bool swept;
     bool stays = plan_batch(c, n_steps, resident, sweep, swept, false);
-    if (stays && !ensure_halo(c, resident)) {
+    // A chunk was given up: something else keeps holding part of the device (another process, long
+    // kernels of other streams), and a chunk stepped again costs many times a good one.
+    if (c->gave_up && *(volatile int*)c->gave_up && c->wait_ticks >= 0) {
+        *(volatile int*)c->gave_up = 0;
+        c->resident_rest = RESIDENT_REST;
+    }
+    const bool rests = stays && c->resident_rest > 0;
+    if (rests) --c->resident_rest;
+    if (stays && (rests || !ensure_halo(c, resident))) {
         stays = false;
         swept = plan_sweep(c, sweep, false);
     }

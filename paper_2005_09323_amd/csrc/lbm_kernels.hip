@@ -411,7 +411,10 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
     const MemberDev m = a.members[mi];
     __shared__ double fd[256];
     if (a.given_up) {
-        if (on && a.given_up[mi] == a.epoch[mi]) resident_redo(a, m, a.parity[mi]);
+        if (on && a.given_up[mi] == a.epoch[mi]) {
+            if (s == 0) *a.gave_up_host = 1;
+            resident_redo(a, m, a.parity[mi]);
+        }
         __syncthreads();
         if (s == 0) a.epoch[mi] += 1;  // every member's: the epochs advance together
     }

@@ -8,7 +8,8 @@ that end inside a wave's rows, workgroups beside one another within and across m
 wave and row seams and beside the walls and the periodic edge, every number of columns per lane and
 rows per wave, more members than one launch holds, runs of lattices cut alike or each its own way,
 chunks of one step up to the longest, and inactive members.  With a wait limit below zero every member
-of more than one workgroup is given up and stepped by the kernel that waits for nothing.
+of more than one workgroup is given up and stepped by the kernel that waits for nothing; with a limit of
+zero a chunk may be given up anywhere in it.
 """
 import pytest
 import torch
@@ -88,7 +89,7 @@ def _run(members, tile, collision, wait=None, opened=None):
 def test_resident_bit_identical_to_one_step(lattices, collision):
     members = LATTICES[lattices]
     drag0, states0, accum0 = _run(members, 0, collision)
-    for wait in (None, -1) if len(members) < 8 else (None,):
+    for wait in (None, -1, 0) if len(members) < 8 else (None,):
         drag, states, accum = _run(members, 20, collision, wait)
         assert torch.equal(drag, drag0) and torch.equal(accum, accum0), wait
         for i, (a, b) in enumerate(zip(states, states0)):
@@ -100,7 +101,7 @@ def test_resident_bit_identical_to_one_step(lattices, collision):
 def test_open_resident_bit_identical_to_one_step(lattices, collision):
     members, opened = OPEN[lattices]
     drag0, states0, accum0 = _run(members, 0, collision, None, opened)
-    for wait in (None, -1) if len(members) < 8 else (None,):
+    for wait in (None, -1, 0) if len(members) < 8 else (None,):
         drag, states, accum = _run(members, 20, collision, wait, opened)
         assert torch.equal(drag, drag0) and torch.equal(accum, accum0), wait
         for i, (a, b) in enumerate(zip(states, states0)):
