@@ -613,7 +613,7 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
 // Which kernel steps the next batch of n_steps with the adaptive shape:
 // resident launches (true), sweeps (`swept`) or neither, by the estimated
 // times.  us per step in long batches, resident launches and the others:
-// 1 x 256 x 64 2.3 and 6.8, 16 x 512 x 128 7.0 and 15.6, 64 x 512 x 128 26.5 and
+// 1 x 256 x 64 2.1 and 6.8, 16 x 512 x 128 6.7 and 15.6, 64 x 512 x 128 26.5 and
 // 44, 20 x 1024 x 256 31.6 and 48.5, 32 x 1024 x 256 52.1 and 51.0, 256 x 512 x
 // 128 106 and 80 (the sweep's estimate is 10 % low where the two are close); open
 // channels of 16, 64 and 512 x 512 x 128 7.4 and 25.4, 28.5 and 51, 226 and 321.

@@ -29,9 +29,9 @@
 // depends on what ran beside.
 //
 // What bounds it: with few waves, a step's chain: a row's collision by a lone
-// wave (0.8 us) and the words' way to memory and back (1 x 256 x 64: 2.3 us
+// wave (0.8 us) and the words' way to memory and back (1 x 256 x 64: 2.1 us
 // per step, 6.8 with one launch per step); with the registers full, the FP64
-// units (16 x 512 x 128, four rows per wave, two waves per SIMD: 7.0 us, 3.5 of
+// units (16 x 512 x 128, four rows per wave, two waves per SIMD: 6.7 us, 3.5 of
 // them the 204 FP64 instructions of a wave's row at 5.2 cycles of 2.4 GHz; 15.6
 // us with one launch per step).  Six rows of two cells per lane, or four
 // of three, are the most that 256 registers hold (eight spill 73, two of five
