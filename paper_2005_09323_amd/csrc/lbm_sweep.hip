@@ -103,12 +103,15 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     // the wave's last lane with cells, and how many of its cells exist
     const int lastl = FULL ? 63 : last_wave ? (nx - base + C - 1) / C - 1 : sg.lanes - 1;
     const int rem = RAG && last_wave ? nx - base - C * lastl : C;
+    // A wave of fewer than 64 lanes works out some columns of the next wave too, the last of them wrongly (nothing
+    // enters beside lane 63; one column more with each stage): its surplus lanes write no cell and no drag.
+    const bool owns = FULL || lane <= lastl;
     // a short last lane loads the row's last C cells and moves them down
     const unsigned voff = 4u * (unsigned)min(x0, nx - C);
     const unsigned vl = 4u * (unsigned)((w == 0 ? nx : base) - 1);     // the column left of the wave (periodic)
     const unsigned vr = 4u * (unsigned)(last_wave ? 0 : base + sg.lanes * C);  // the column right of it
     // stores of the lanes beyond the row go beyond the buffer, which the hardware drops
-    const unsigned vstore = (!FULL && lane > lastl) || (RAG && lane == lastl && rem != C) ? 0x80000000u : voff;
+    const unsigned vstore = !owns || (RAG && lane == lastl && rem != C) ? 0x80000000u : voff;
     const bool sq_cols = m.ss > 0 && base <= m.sx0 + m.ss && base + sg.lanes * C - 1 >= m.sx0 - 1;
     unsigned sqc = 0;                                // bit j: column x0 - 1 + j crosses the square
     if (sq_cols)
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                         float dl[9];
 #pragma unroll
                         for (int i = 0; i < 9; ++i) dl[i] = pinned(p[i][k]);
-                        const int ri = ring_row && !in_square(m, x0 + k, r) ? ring_index(m, x0 + k, r) : -1;
+                        const int ri = ring_row && owns && !in_square(m, x0 + k, r) ? ring_index(m, x0 + k, r) : -1;
                         const unsigned links = ri >= 0 ? square_links(m, x0 + k, r) : 0u;
                         const double drag = collide_cell<MODEL>(m, dl, links, ring_row);
 #pragma unroll
@@ -277,7 +280,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                     const unsigned so = skip == 0u ? vs : 0x80000000u;
 #pragma unroll
                     for (int i = 0; i < 9; ++i) store_cells<C>(rd, so, 4u * ((unsigned)i * plane + rowoff), p[i]);
-                    if (C > 1 && mine && skip != 0u && skip != (1u << C) - 1u) {
+                    if (C > 1 && mine && owns && skip != 0u && skip != (1u << C) - 1u) {
 #pragma unroll
                         for (int k = 0; k < C; ++k)
                             if (!((skip >> k) & 1u) && x0 + k < nx) {
