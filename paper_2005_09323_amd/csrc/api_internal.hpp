@@ -69,6 +69,15 @@ struct ResidentPlan {
     ResidentPass pass[RESIDENT_PASSES];
 };
 
+// What the adaptive shape may step a batch with, whatever its length: worked out when a batch first needs it
+// after the tables, the collision, the channel or the active members have changed.
+struct BatchPlans {
+    bool resident_known = false, resident_found = false;
+    bool sweep_known = false, sweep_found = false;
+    ResidentPlan resident;
+    SweepPlan sweep;
+};
+
 // What a captured chunk of lbm_step_batch depends on besides device memory:
 // a replay is valid while all of it is unchanged.
 struct ChunkGraphKey {
@@ -149,6 +158,7 @@ struct lbm_ctx {
     int nseg2 = 0;
     int total_blocks2 = 0;
     lbm::Segment seg2[lbm::MAX_SEGMENTS];
+    BatchPlans plans;
     RareScratch rare;
     // GKTL cloning by relabelling member blocks (1, the default) or by gathering
     // every copy into the other buffer (0); both give the same states

@@ -240,7 +240,7 @@ static double resident_cost(const ResidentCut& cut, bool two, bool open, double 
     return std::max(open ? cut.opened : two ? cut.both : cut.lone, 0.75e-3 * cut.cells * sides) + 0.75e-4 * cut.cells * sides;
 }
 
-// The resident launches of the next batch, if the adaptive shape may have any: a
+// The resident launches of a batch, if the adaptive shape may have any: a
 // whole chunk of steps per launch with the populations in registers (channels
 // of up to 1024 columns, all workgroups of a launch side by side on
 // the device: two waves per SIMD at most), as many launches as the members
@@ -254,12 +254,6 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
     if (!TILE_SHAPES[c->tile_id].adaptive) return false;
     for (int r : c->run_rows)
         if (r >= 0) return false;  // row ranges given by the caller: the sweep's
-    hipStreamCaptureStatus captured;  // a replay would not be known to the other contexts' launches
-    if (hipStreamIsCapturing(c->stream, &captured) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (captured != hipStreamCaptureStatusNone) return false;
     const bool listed = !every_member && c->n_active < c->n && c->uniform_shape;
     double cells = 0.0;
     int widest = 0;
@@ -374,11 +368,8 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
         a.pop0 = c->pop[0];
         a.pop1 = c->pop[1];
         a.partial = c->d_partial;
-        a.halo = c->d_halo;
         a.epoch = c->d_epoch;
         a.given_up = c->d_given_up;
-        a.wait_ticks = c->wait_ticks;
-        a.flip = 0;
         a.pass = k;
     }
     return true;
@@ -394,6 +385,8 @@ static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps,
     }
     for (int k = 0; k < p.passes; ++k) {
         ResidentArgs& a = p.pass[k].args;
+        a.halo = c->d_halo;
+        a.wait_ticks = c->wait_ticks;
         a.n_steps = steps;
         a.flip = flip;
         const hipError_t e = launch_resident(p.pass[k].cells, p.pass[k].rows, c->open, a, c->model, st);
@@ -414,7 +407,7 @@ struct OutsideCapture {
 // launch's).  Later launches find older launches' words, whoever wrote them:
 // the members' epochs advance together, so no old word passes for a new one.
 // False if there is no memory for them (another kernel steps the batch then).
-static bool ensure_halo(lbm_ctx* c, ResidentPlan& p) {
+static bool ensure_halo(lbm_ctx* c, const ResidentPlan& p) {
     const OutsideCapture outside;
     if (!c->gave_up) {
         if (hipHostMalloc(&c->gave_up, sizeof(int)) != hipSuccess) {
@@ -435,7 +428,6 @@ static bool ensure_halo(lbm_ctx* c, ResidentPlan& p) {
         if (fill_int((int*)c->d_halo, (int)(2 * p.halo_words), 0, c->stream) != hipSuccess) return false;
         c->halo_words = p.halo_words;
     }
-    for (int k = 0; k < p.passes; ++k) p.pass[k].args.halo = c->d_halo;
     return true;
 }
 
@@ -502,23 +494,23 @@ static int sweep_rows(const lbm_ctx* c, int run, int ny, int rows) {
 // fewer than 32 rows take longer than that (us per launch of four steps, 12, 20
 // and 32 x 1024 x 256 in units of 13, 22 and 32 rows: 148, 194 and 204, without
 // the last factor 92, 130 and 184).
-static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int rows, const int* members) {
+static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int steps, int rows, const int* members) {
     const double slots = (double)c->cu_count * (SWEEP_WAVES / p.args.block_waves);
     double load = 0.0, longest = 0.0, blocks = 0.0, bytes = 0.0;
     for (int s = 0; s < c->nseg; ++s) {
         const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
         const int h = sweep_rows(c, s, d.ny, rows), ranges = (d.ny + h - 1) / h;
-        const double len = h + 2.0 * (p.steps - 1) + 3.0;
+        const double len = h + 2.0 * (steps - 1) + 3.0;
         const int per = p.args.block_waves / p.args.seg[s].waves;
         const double nb = std::ceil((double)members[s] * ranges / per);
         blocks += nb;
         load += nb * len;
         longest = std::max(longest, len);
-        bytes += (double)members[s] * d.nx * (72.0 * d.ny + 72.0 * (p.steps - 1) * (ranges - 1));
+        bytes += (double)members[s] * d.nx * (72.0 * d.ny + 72.0 * (steps - 1) * (ranges - 1));
     }
     const double rounds = c->nseg == 1 ? std::ceil(blocks / slots) * longest : std::max(longest, load / slots + 0.5 * longest);
     const double fill = std::min(1.0, blocks / slots);
-    const double iteration = (1.2 + 0.8 * p.steps) * (fill > 0.5 ? 0.2 + 0.8 * fill : 0.6);
+    const double iteration = (1.2 + 0.8 * steps) * (fill > 0.5 ? 0.2 + 0.8 * fill : 0.6);
     return std::max(rounds * iteration, bytes / 4.8e6) * (1.0 + 0.03 * std::max(0, 32 - rows)) + 4.0;
 }
 
@@ -533,7 +525,7 @@ static double others_cost(const lbm_ctx* c, double cells) {
     return cells / (four ? 80e3 : 50e3) + (c->open ? 13.0 : 6.0);
 }
 
-// The sweep launch of the next batch (steps per launch and the table of units); false if another kernel should step it.  The sweep takes
+// The sweep launch of a batch (steps per launch and the table of units); false if another kernel should step it.  The sweep takes
 // lattices of up to 64 SWEEP_WAVES SWEEP_CELLS = 1024 columns in periodic channels; the
 // adaptive shape chooses it where its estimated time per step is below that of
 // the kernels it would use otherwise.
@@ -564,18 +556,18 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     }
     double best = 1e300;
     int rows = tallest;
+    // every height that cuts the tallest lattice into equal parts, from the whole of it down (some 2 sqrt(ny) of them)
     for (int steps : {4, 2})
-        for (int parts = 1; parts <= tallest; ++parts) {
-            const int h = (tallest + parts - 1) / parts;
-            if (parts > 1 && h == (tallest + parts - 2) / (parts - 1)) continue;  // seen
-            SweepPlan q = p;
-            q.steps = steps;
-            const double t = sweep_cost(c, q, h, members) / steps;
+        for (int h = tallest;;) {
+            const double t = sweep_cost(c, p, steps, h, members) / steps;
             if (t < best) {
                 best = t;
                 rows = h;
                 p.steps = steps;
             }
+            if (h == 1) break;
+            const int parts = (tallest + h - 2) / (h - 1);  // the fewest that are lower
+            h = (tallest + parts - 1) / parts;
         }
     bool chosen = false;  // row ranges given by the caller: sweep them
     for (int r : c->run_rows) chosen = chosen || r >= 0;
@@ -620,21 +612,38 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
 // A resident launch also takes 8 us and a copy of the state to begin and end:
 // calls of one step 19.5 and 14.9, 37 and 24, of two 21 and 22, 43 and 41, of
 // four 26 and 38, 55 and 75 for the first two sizes.
-static bool plan_batch(const lbm_ctx* c, int n_steps, ResidentPlan& resident, SweepPlan& sweep, bool& swept, bool every_member) {
-    const bool stays = plan_resident(c, resident, every_member);
+static bool plan_batch(const lbm_ctx* c, int n_steps, BatchPlans& p, bool& swept, bool every_member) {
+    if (!p.resident_known) p.resident_found = plan_resident(c, p.resident, every_member);
+    p.resident_known = true;
+    const ResidentPlan& resident = p.resident;
+    bool stays = p.resident_found;
+    if (stays) {
+        hipStreamCaptureStatus captured;  // a replay would not be known to the other contexts' launches
+        if (hipStreamIsCapturing(c->stream, &captured) != hipSuccess) {
+            (void)hipGetLastError();
+            stays = false;
+        } else if (captured != hipStreamCaptureStatusNone) {
+            stays = false;
+        }
+    }
     swept = false;
     if (stays && resident.passes == 1 && n_steps >= 4) return true;
-    swept = plan_sweep(c, sweep, every_member);
-    if (c->open && stays) sweep.us = others_cost(c, resident.bytes / 72.0);
+    if (!p.sweep_known) p.sweep_found = plan_sweep(c, p.sweep, every_member);
+    p.sweep_known = true;
+    swept = p.sweep_found;
     bool chosen = false;  // row ranges given by the caller: sweep them
     for (int r : c->run_rows) chosen = chosen || r >= 0;
     if (swept && n_steps < 4 && !chosen) swept = false;  // (64 x 512 x 128, calls of one step 93 and 66 us, of two 115 and 92)
     if (!stays) return false;
+    const double other = c->open ? others_cost(c, resident.bytes / 72.0) : p.sweep.us;
     const double start = n_steps < c->chunk ? 8.0 * resident.passes + resident.bytes / 5.2e6 : 0.0;  // (part of us, over a chunk)
-    if (start + resident.us * n_steps >= (swept ? 1.1 : 1.0) * sweep.us * n_steps) return false;
+    if (start + resident.us * n_steps >= (swept ? 1.1 : 1.0) * other * n_steps) return false;
     swept = false;
     return true;
 }
+
+// The tables, the collision, the channel or the active members have changed.
+static void forget_plans(lbm_ctx* c) { c->plans.resident_known = c->plans.sweep_known = false; }
 
 // Tables of the current tile shape.  A two-step shape applies when every
 // member's width is a multiple of 256 and its block fits 32-bit byte
@@ -643,6 +652,7 @@ static bool plan_batch(const lbm_ctx* c, int n_steps, ResidentPlan& resident, Sw
 static int build_segments(lbm_ctx* c) {
     const TileShape ts = TILE_SHAPES[c->tile_id];
     ++c->table_gen;
+    forget_plans(c);
     c->two_step = false;
     c->one_tile = c->tile_id;
     if (ts.steps == 2) {
@@ -854,6 +864,7 @@ extern "C" int lbm_init_flow(lbm_ctx* c, uint64_t seed, double noise_amp, double
     std::fill(c->h_parity.begin(), c->h_parity.end(), 0);
     std::fill(c->h_active.begin(), c->h_active.end(), 1);
     c->n_active = c->n;
+    forget_plans(c);
     InitArgs a;
     a.members = c->d_members;
     a.pop0 = c->pop[0];
@@ -888,6 +899,7 @@ extern "C" int lbm_set_active(lbm_ctx* c, const int32_t* active_host) {
         c->n_active += on;
         if (on) bits.w[m >> 5] |= 1u << (m & 31);
     }
+    forget_plans(c);
     hipError_t e = set_bits(c->d_active, c->d_active_list, c->n, bits, c->stream);
     return e == hipSuccess ? LBM_OK : lbm_hip_fail(e, "active mask upload");
 }
@@ -922,10 +934,9 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     }
     const int waves2 = TILE_SHAPES[c->tile_id].tyt;
     const bool two = two_step_now(c);
-    ResidentPlan resident;
-    SweepPlan sweep;
     bool swept;
-    bool stays = plan_batch(c, n_steps, resident, sweep, swept, false);
+    bool stays = plan_batch(c, n_steps, c->plans, swept, false);
+    ResidentPlan& resident = c->plans.resident;
     // A chunk was given up: something else keeps holding part of the device (another process, long
     // kernels of other streams), and a chunk stepped again costs many times a good one.
     if (c->gave_up && *(volatile int*)c->gave_up && c->wait_ticks >= 0) {
@@ -936,8 +947,11 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     if (rests) --c->resident_rest;
     if (stays && (rests || !ensure_halo(c, resident))) {
         stays = false;
-        swept = plan_sweep(c, sweep, false);
+        if (!c->plans.sweep_known) c->plans.sweep_found = plan_sweep(c, c->plans.sweep, false);
+        c->plans.sweep_known = true;
+        swept = c->plans.sweep_found && n_steps >= 4;
     }
+    SweepPlan& sweep = c->plans.sweep;
     a.active_list = nullptr;
     a2.active_list = nullptr;
     a.ghost = c->open ? c->d_ghost : nullptr;
@@ -1132,6 +1146,7 @@ extern "C" int lbm_set_collision(lbm_ctx* c, int32_t model, double s_bulk, doubl
     // unit bulk, third- and fourth-order rates: the shorter evaluation of the same collision
     const int internal = model == 1 && s_bulk == 1.0 && s_third == 1.0 && s_fourth == 1.0 ? 2 : model;
     c->model = internal;
+    forget_plans(c);
     for (auto& m : c->h_members) {
         m.model = internal;
         if (model == 1) {
@@ -1316,11 +1331,12 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         if (build_segments(c) != LBM_OK) return LBM_OK;
         const TileShape ts = TILE_SHAPES[t];
         if (ts.steps == 2 && !ts.adaptive && !c->two_step) return LBM_OK;  // it would run shape 0
-        SweepPlan sweep;
         // the adaptive shape: where it stays in registers or sweeps (it runs shape 16 or 0 otherwise)
-        ResidentPlan resident;
+        BatchPlans plans;
+        ResidentPlan& resident = plans.resident;
+        SweepPlan& sweep = plans.sweep;
         bool swept = false;
-        const bool stays = ts.adaptive && plan_batch(c, c->chunk, resident, sweep, swept, true) && ensure_halo(c, resident);
+        const bool stays = ts.adaptive && plan_batch(c, c->chunk, plans, swept, true) && ensure_halo(c, resident);
         if (ts.adaptive && !stays && !swept) return LBM_OK;
         const bool two = ts.steps == 2;
         a.total_blocks = two ? c->total_blocks2 : c->total_blocks;

@@ -1,0 +1,79 @@
+"""The host side of lbm_step_batch with the default shape: what it works out and allocates per call."""
+import time
+
+import pytest
+import torch
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _ensemble(members, capacity=90, tile=20):
+    from paper_2005_09323_amd.ensemble import Ensemble
+    ens = Ensemble(members, series_capacity=capacity)
+    ens.pop_a.zero_()  # solid cells are never written
+    ens.pop_b.zero_()
+    ens.set_tile(tile)
+    return ens
+
+
+def test_short_batches_of_a_tall_channel_cost_the_host_little():
+    """How a batch is stepped is worked out once for a set of members, not in each call, and not by trying
+    every height of a tall channel: ten batches of one step are enqueued in far less than the tenth of a
+    second each took with three million rows."""
+    ens = _ensemble([workloads.Member(4, 3_000_000, 0.6, 1e-6, None)], capacity=20)
+    ens.init(7, 1e-3)
+    ens.step(1)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(10):
+        ens.step(1)
+    spent = time.perf_counter() - t0
+    torch.cuda.synchronize()
+    ens.close()
+    assert spent < 0.2, spent
+
+
+@pytest.mark.parametrize("change", ["active", "collision", "tile", "open", "rows", "init"])
+def test_a_plan_is_worked_out_afresh_after_a_change(change):
+    """Batches before and after each call that decides how members are stepped, against the one-step shape 0
+    (bit for bit: the arithmetic of a cell is the same in every kernel)."""
+    members = [workloads.Member(257, 40, 0.56, 2e-5, (120, 12, 9))] * 6
+
+    def run(tile):
+        ens = _ensemble(members, 120, tile)
+        ens.init(7, 1e-2)
+        ens.step(9)
+        if change == "active":
+            ens.set_active([1, 0, 0, 1, 0, 0])
+        elif change == "collision":
+            ens.set_collision("central", 1.2, 0.9, 1.4)
+        elif change == "tile":
+            ens.set_tile(0)
+            ens.step(5)
+            ens.set_tile(tile)
+        elif change == "open":
+            ens.set_open_channel(0.05, 20, 3, 200, 0.9)
+            ens.init(3, 1e-2)
+        elif change == "rows":
+            ens.set_run_rows([7] * ens.run_count())
+            ens.step(5)
+            ens.set_run_rows(None)
+        else:
+            ens.set_active([1, 0, 0, 1, 0, 0])
+            ens.step(9)
+            ens.init(5, 1e-2)
+        ens.step(9)
+        ens.set_active(None)
+        ens.step(70)
+        torch.cuda.synchronize()
+        out = ens.series.clone(), [ens.state(i).clone() for i in range(len(members))]
+        ens.close()
+        return out
+
+    drag0, states0 = run(0)
+    drag, states = run(20)
+    assert torch.equal(drag, drag0)
+    for i, (a, b) in enumerate(zip(states, states0)):
+        assert torch.equal(a, b), i
