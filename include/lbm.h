@@ -50,7 +50,9 @@
  * - Memory: every large buffer is owned by the caller and passed as a
  *   device pointer; the library never frees caller memory.  The library
  *   allocates its own small device scratch (per-member bookkeeping, drag
- *   partial sums) in lbm_create and frees it in lbm_destroy.
+ *   partial sums, the words that workgroups hand one another in
+ *   lbm_step_batch: at most some 26 MB, or 51 for members of several
+ *   widths) in lbm_create and frees it in lbm_destroy.
  * - Errors: every call returns LBM_OK (0) or a negative code; the message
  *   of the last failure on the calling thread is lbm_last_error().  Argument
  *   errors are detected before any work is enqueued.

@@ -114,7 +114,7 @@ struct lbm_ctx {
     int* d_active_list = nullptr;  // the n_active active members in ascending order
     int n_active = 0;
     int* d_flags = nullptr;
-    // resident chunks: words between workgroups (allocated when first needed), per member the chunks
+    // resident chunks: words between workgroups (for any plan), per member the chunks
     // stepped so far and the one given up, the bound of a wait; the last batch's workgroups, how many of
     // them a compute unit holds and the batch's end
     unsigned long long* d_halo = nullptr;

@@ -359,6 +359,7 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
     } else if (!own[c->nseg] || !cut(*own[c->nseg], waves[c->nseg], 0, c->nseg, p)) {
         return false;
     }
+    if (p.halo_words > c->halo_words) return false;  // (no memory for them: allocate_resident)
     for (int k = 0; k < p.passes; ++k) {
         ResidentArgs& a = p.pass[k].args;
         a.members = c->d_members;
@@ -368,11 +369,51 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
         a.pop0 = c->pop[0];
         a.pop1 = c->pop[1];
         a.partial = c->d_partial;
+        a.halo = c->d_halo;
         a.epoch = c->d_epoch;
         a.given_up = c->d_given_up;
         a.pass = k;
     }
     return true;
+}
+
+// The most words between workgroups that a plan for any of the context's members can need (at most some
+// 26 MB, 51 for several widths): for each cut the workgroups that the device or all members have, whichever are
+// fewer, of the widest member.  0: no plan.
+static size_t resident_words(const lbm_ctx* c) {
+    size_t most = 0;
+    for (int waves : {4, 8})
+        for (const ResidentCut& rc : RESIDENT_CUTS) {
+            long long units = 0, words = 0;
+            int block_waves = SWEEP_WAVES;  // the fewest
+            for (const lbm_member_desc& d : c->desc) {
+                if (d.nx > RESIDENT_WIDEST) return 0;
+                const int lanes = (d.nx + rc.cells - 1) / rc.cells, w = (lanes + 63) / 64, groups = std::max(1, waves / w);
+                if (w > SWEEP_WAVES) continue;
+                block_waves = std::min(block_waves, w * groups);
+                units += (d.ny + groups * rc.rows - 1) / (groups * rc.rows);
+                words = std::max(words, 12LL * rc.cells * lanes + 4 * RESIDENT_OUTLET_WORDS);
+            }
+            const long long places = (long long)c->cu_count * (SWEEP_WAVES / block_waves);
+            most = std::max(most, (size_t)(std::min(units, places) * words));
+        }
+    return most;
+}
+
+// The words between workgroups, cleared (no launch's), for every plan to come: a batch allocates nothing.  Later
+// launches find older launches' words, whoever wrote them: the members' epochs advance together, so no old word
+// passes for a new one.  Without memory for them there is no plan (another kernel steps the batches then).
+static void allocate_resident(lbm_ctx* c) {
+    const size_t words = resident_words(c);
+    if (words == 0) return;
+    if (hipHostMalloc(&c->gave_up, sizeof(int)) == hipSuccess &&
+        hipEventCreateWithFlags(&c->resident_done, hipEventDisableTiming) == hipSuccess &&
+        hipMalloc(&c->d_halo, sizeof(unsigned long long) * words) == hipSuccess &&
+        fill_int((int*)c->d_halo, (int)(2 * words), 0, c->stream) == hipSuccess) {
+        *c->gave_up = 0;
+        c->halo_words = words;
+    }
+    (void)hipGetLastError();
 }
 
 static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps, int flip, hipStream_t st) {
@@ -385,7 +426,6 @@ static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps,
     }
     for (int k = 0; k < p.passes; ++k) {
         ResidentArgs& a = p.pass[k].args;
-        a.halo = c->d_halo;
         a.wait_ticks = c->wait_ticks;
         a.n_steps = steps;
         a.flip = flip;
@@ -402,34 +442,6 @@ struct OutsideCapture {
     OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
     ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
-
-// The words between workgroups, grown to the plan's need and cleared (no
-// launch's).  Later launches find older launches' words, whoever wrote them:
-// the members' epochs advance together, so no old word passes for a new one.
-// False if there is no memory for them (another kernel steps the batch then).
-static bool ensure_halo(lbm_ctx* c, const ResidentPlan& p) {
-    const OutsideCapture outside;
-    if (!c->gave_up) {
-        if (hipHostMalloc(&c->gave_up, sizeof(int)) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
-        *c->gave_up = 0;
-    }
-    if (p.halo_words > c->halo_words) {
-        if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
-        hipFree(c->d_halo);
-        c->d_halo = nullptr;
-        c->halo_words = 0;
-        if (hipMalloc(&c->d_halo, sizeof(unsigned long long) * p.halo_words) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
-        if (fill_int((int*)c->d_halo, (int)(2 * p.halo_words), 0, c->stream) != hipSuccess) return false;
-        c->halo_words = p.halo_words;
-    }
-    return true;
-}
 
 // The contexts of this process that have made resident launches.  Workgroups
 // of a resident launch wait for one another, so two launches that do not fit
@@ -450,10 +462,7 @@ static ResidentUsers& resident_users() {
 static hipError_t admit_resident(lbm_ctx* c, ResidentUsers& u, const ResidentPlan& p) {
     const OutsideCapture outside;
     hipError_t e;
-    if (!c->resident_done) {
-        if ((e = hipEventCreateWithFlags(&c->resident_done, hipEventDisableTiming)) != hipSuccess) return e;
-        u.users.push_back(c);
-    }
+    if (std::find(u.users.begin(), u.users.end(), c) == u.users.end()) u.users.push_back(c);
     c->resident_places = 0;  // (its launches differ: beside no other's)
     c->resident_blocks = 0;
     bool fit = true;
@@ -784,6 +793,7 @@ extern "C" int lbm_create(lbm_ctx** out, const lbm_member_desc* members, int32_t
         lbm_destroy(c);
         return lbm_hip_fail(e, "initialising bookkeeping");
     }
+    allocate_resident(c);
     c->n_active = n_members;
     *out = c;
     return LBM_OK;
@@ -805,7 +815,8 @@ extern "C" int lbm_destroy(lbm_ctx* c) {
     if (c->resident_done) {
         ResidentUsers& u = resident_users();
         const std::lock_guard<std::mutex> hold(u.lock);
-        u.users.erase(std::find(u.users.begin(), u.users.end(), c));
+        const auto at = std::find(u.users.begin(), u.users.end(), c);
+        if (at != u.users.end()) u.users.erase(at);
         hipEventDestroy(c->resident_done);
     }
     hipFree(c->d_partial);
@@ -945,7 +956,7 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     }
     const bool rests = stays && c->resident_rest > 0;
     if (rests) --c->resident_rest;
-    if (stays && (rests || !ensure_halo(c, resident))) {
+    if (stays && rests) {
         stays = false;
         if (!c->plans.sweep_known) c->plans.sweep_found = plan_sweep(c, c->plans.sweep, false);
         c->plans.sweep_known = true;
@@ -1336,7 +1347,7 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         ResidentPlan& resident = plans.resident;
         SweepPlan& sweep = plans.sweep;
         bool swept = false;
-        const bool stays = ts.adaptive && plan_batch(c, c->chunk, plans, swept, true) && ensure_halo(c, resident);
+        const bool stays = ts.adaptive && plan_batch(c, c->chunk, plans, swept, true);
         if (ts.adaptive && !stays && !swept) return LBM_OK;
         const bool two = ts.steps == 2;
         a.total_blocks = two ? c->total_blocks2 : c->total_blocks;

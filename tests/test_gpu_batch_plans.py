@@ -77,3 +77,29 @@ def test_a_plan_is_worked_out_afresh_after_a_change(change):
     assert torch.equal(drag, drag0)
     for i, (a, b) in enumerate(zip(states, states0)):
         assert torch.equal(a, b), i
+
+
+def test_batches_allocate_nothing():
+    """lbm_step_batch enqueues: what it needs on the device is allocated with the context, for every set of
+    active members (24 x 512 x 128 needs 25 MB of words between workgroups)."""
+    members = [workloads.Member(512, 128, 0.56, 2e-5, (250, 60, 9))] * 24
+
+    def steps(ens):
+        ens.init(7, 1e-3)
+        ens.set_active([j == 0 for j in range(24)])
+        ens.step(8)
+        ens.set_active(None)
+        ens.step(64)
+        ens.set_active([j % 2 == 0 for j in range(24)])
+        ens.step(7)
+        torch.cuda.synchronize()
+
+    ens = _ensemble(members)
+    steps(ens)  # (every kernel loaded)
+    ens.close()
+    ens = _ensemble(members)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    steps(ens)
+    assert abs(free - torch.cuda.mem_get_info()[0]) < 4 << 20
+    ens.close()
