@@ -169,8 +169,9 @@ int lbm_set_graphs(lbm_ctx* ctx, int32_t on);
  * shape keeps a small ensemble's populations in registers for a whole chunk of
  * steps (20 000 unless set; below 0: no wait).  A chunk whose workgroups wait
  * longer for one another (kernels of other streams hold part of the device) is
- * stepped again by a kernel that waits for nothing: slower, the same results;
- * the next 64 batches then go another way.
+ * stepped again by workgroups that need not run side by side: slower, the
+ * same results.  The batch's later chunks then wait for 200 us at most, and
+ * the next 64 batches go another way.
  */
 int lbm_set_wait_limit(lbm_ctx* ctx, int32_t us);
 

@@ -21,7 +21,6 @@ struct MaskBits {
 hipError_t fill_int(int* p, int n, int v, hipStream_t st);
 hipError_t fill_double(double* p, int n, double v, hipStream_t st);
 hipError_t set_int(int* p, int v, hipStream_t st);
-hipError_t add_int(int* p, int n, int v, hipStream_t st);  // p[i] += v
 // p[m] = bit m; list (if non-null) = the set members in increasing order
 hipError_t set_bits(int* p, int* list, int n, const MaskBits& bits, hipStream_t st);
 hipError_t fill_iota(int* p, int n, hipStream_t st);  // p[i] = i
@@ -66,6 +65,8 @@ struct ResidentPlan {
     double us = 0.0;        // estimated time per step
     double bytes = 0.0;     // of the state, read and written once
     size_t halo_words = 0;  // the most of a pass
+    int slots = 0;          // members of the launches, active or not
+    bool listed = false;    // the active ones only
     ResidentPass pass[RESIDENT_PASSES];
 };
 
@@ -114,17 +115,18 @@ struct lbm_ctx {
     int* d_active_list = nullptr;  // the n_active active members in ascending order
     int n_active = 0;
     int* d_flags = nullptr;
-    // resident chunks: words between workgroups (for any plan), per member the chunks
-    // stepped so far and the one given up, the bound of a wait; the last batch's workgroups, how many of
-    // them a compute unit holds and the batch's end
+    // resident chunks: words between workgroups (for any plan), per member (and of any) the chunk given up, the
+    // counts of one stepped again, the bound of a wait; the last chunk's number and that of its batch's first;
+    // the last batch's workgroups, how many of them a compute unit holds and the batch's end
     unsigned long long* d_halo = nullptr;
     size_t halo_words = 0;
-    int* d_epoch = nullptr;
-    int* d_given_up = nullptr;
+    int* d_given_up = nullptr;  // [n + 1]
+    int* d_redo = nullptr;      // [max(n, REDO_TASKS) + 2]: RedoArgs::done, RedoArgs::ticket
     long long wait_ticks = 2000000;  // 20 ms
     int* gave_up = nullptr;  // pinned: a chunk was given up; the next RESIDENT_REST batches go another way
     int resident_rest = 0;
-    int resident_blocks = 0, resident_places = 1, resident_chunks = 0;
+    int resident_launch = 0, resident_first = 0;
+    int resident_blocks = 0, resident_places = 1;
     hipEvent_t resident_done = nullptr;
     int device = 0;
     std::vector<int> h_parity, h_cursor, h_active;

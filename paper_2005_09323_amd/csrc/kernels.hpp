@@ -87,9 +87,11 @@ struct ResidentSegment {
     long long halo_begin;  // first halo word of the segment: [unit]{[side 2][slot 2][3 cells][lanes of the width], open: [side][slot][36]}
 };
 
-// A word's tag: the launch's number (below RESIDENT_EPOCHS), its pass and the step it is for.
+// A word's tag: the chunk's number, its pass and the step it is for.
 constexpr int RESIDENT_STEP_BITS = 7, RESIDENT_PASS_BITS = 6;
-constexpr int RESIDENT_EPOCHS = 1 << (32 - RESIDENT_STEP_BITS - RESIDENT_PASS_BITS);
+constexpr int RESIDENT_LAUNCHES = 1 << (32 - RESIDENT_STEP_BITS - RESIDENT_PASS_BITS);
+// Bound of a wait in the chunks of a batch after one was given up in it (0.2 ms: some 30 steps).
+constexpr long long RESIDENT_SHORT_WAIT = 20000;
 
 constexpr int RESIDENT_WIDEST = 1024;         // columns
 constexpr int RESIDENT_OUTLET_WORDS = 36;  // open channels: two rows of the last two columns
@@ -103,8 +105,10 @@ struct ResidentArgs {
     float* pop1;
     double* partial;
     unsigned long long* halo;
-    const int* epoch;        // per member: the launch's number (all alike; finalize counts it)
-    int* given_up;           // per member: the epoch whose chunk was given up
+    int launch;              // the chunk's number (1 .. RESIDENT_LAUNCHES - 1)
+    int first;               // that of the batch's first chunk
+    int* given_up;           // per member: the number of the chunk given up; then that of the last one of any member
+    int n_members;
     long long wait_ticks;    // bound of a wait (100 MHz clock); below 0: give up at the first
     int n_steps;
     int flip;                // as StepArgs::flip
@@ -150,15 +154,29 @@ struct FinalizeArgs {
     int swap_parity;     // parity of the number of buffer swaps in this chunk (one per kernel launch)
     double mu;
     double inv_sigma_dt; // dt / sigma
-    // resident chunks: per member the launch's number (counted here) and that of a chunk given up,
-    // which is stepped again here first, from the buffers below
-    int* epoch;
-    const int* given_up; // null: the chunk was not a resident one
-    int* gave_up_host;   // pinned: set when a chunk is stepped again
+};
+
+// The reduction of a resident chunk: block b's member is active_list[b], or b.
+// Members whose chunk was given up are stepped again first, by every block of
+// the launch (lbm_kernels.hip).
+constexpr int REDO_TASKS = 512;   // bands of rows, of all members together, that a step is cut into
+constexpr int REDO_STEPS = 1 << 9;  // above every chunk's steps: the counts of launch n start at n REDO_STEPS
+struct RedoArgs {
+    int launch;              // as ResidentArgs
+    const int* given_up;
+    int n_members;
+    const int* active_list;
+    int slots;               // members of the launch, active or not
+    int bands;               // per member
+    int flip;                // as ResidentArgs
+    int states_only;         // 1: no reduction (an untracked chunk)
+    int* done;               // [slots][bands]: launch REDO_STEPS + steps made
+    int* ticket;             // [2]: tasks taken, blocks that have found none left (both 0 between launches)
+    int* gave_up_host;       // pinned: set when a chunk is stepped again
     float* pop0;
     float* pop1;
-    double* redo_partial;
-    float* ghost;        // open channels, as GhostArgs::ghost
+    double* partial;
+    float* ghost;            // open channels, as GhostArgs::ghost
 };
 
 struct TileShape {
@@ -187,5 +205,6 @@ hipError_t launch_init(const InitArgs& a, int n_members, long long max_cells, hi
 // the outlet ghost columns of the open-channel members for the next one-step launch
 hipError_t launch_outlet_ghost(const GhostArgs& a, int n_members, int max_ny, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs& a, int n_members, hipStream_t st);
+hipError_t launch_finalize_resident(const FinalizeArgs& a, const RedoArgs& r, hipStream_t st);
 
 }  // namespace lbm

@@ -49,10 +49,6 @@ __global__ void fill_double_kernel(double* p, int n, double v) {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (i < n) p[i] = v;
 }
-__global__ void add_int_kernel(int* p, int n, int v) {
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i < n) p[i] += v;
-}
 __global__ void set_int_kernel(int* p, int v) { *p = v; }
 __global__ void iota_kernel(int* p, int n) {
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -73,10 +69,6 @@ __global__ void set_bits_kernel(int* p, int* list, int n, MaskBits bits) {
 hipError_t fill_int(int* p, int n, int v, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_int_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n, v);
-    return hipGetLastError();
-}
-hipError_t add_int(int* p, int n, int v, hipStream_t st) {
-    hipLaunchKernelGGL(add_int_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n, v);
     return hipGetLastError();
 }
 hipError_t fill_double(double* p, int n, double v, hipStream_t st) {
@@ -353,6 +345,8 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
     p.us = 0.0;
     p.bytes = 72.0 * cells;
     p.halo_words = 0;
+    p.listed = listed;
+    p.slots = listed ? c->n_active : c->n;
     if (c->nseg > 1 && each < all) {
         for (int s = 0; s < c->nseg; ++s)
             if (!cut(*own[s], waves[s], s, s + 1, p)) return false;
@@ -370,8 +364,8 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
         a.pop1 = c->pop[1];
         a.partial = c->d_partial;
         a.halo = c->d_halo;
-        a.epoch = c->d_epoch;
         a.given_up = c->d_given_up;
+        a.n_members = c->n;
         a.pass = k;
     }
     return true;
@@ -401,7 +395,7 @@ static size_t resident_words(const lbm_ctx* c) {
 }
 
 // The words between workgroups, cleared (no launch's), for every plan to come: a batch allocates nothing.  Later
-// launches find older launches' words, whoever wrote them: the members' epochs advance together, so no old word
+// launches find older launches' words, whoever wrote them: each chunk has its own number, so no old word
 // passes for a new one.  Without memory for them there is no plan (another kernel steps the batches then).
 static void allocate_resident(lbm_ctx* c) {
     const size_t words = resident_words(c);
@@ -416,16 +410,22 @@ static void allocate_resident(lbm_ctx* c) {
     (void)hipGetLastError();
 }
 
+static hipError_t clear_redo(const lbm_ctx* c, hipStream_t st) {
+    return fill_int(c->d_redo, std::max(c->n, REDO_TASKS) + 2, 0, st);
+}
+
 static hipError_t launch_resident_passes(lbm_ctx* c, ResidentPlan& p, int steps, int flip, hipStream_t st) {
-    if (++c->resident_chunks >= RESIDENT_EPOCHS) {  // the words' tags would repeat: from the start again
+    if (++c->resident_launch >= RESIDENT_LAUNCHES) {  // the words' tags would repeat: from the start again
         hipError_t e;
-        if ((e = fill_int(c->d_epoch, c->n, 1, st)) != hipSuccess || (e = fill_int(c->d_given_up, c->n, 0, st)) != hipSuccess ||
+        if ((e = fill_int(c->d_given_up, c->n + 1, 0, st)) != hipSuccess || (e = clear_redo(c, st)) != hipSuccess ||
             (e = fill_int((int*)c->d_halo, (int)(2 * c->halo_words), 0, st)) != hipSuccess)
             return e;
-        c->resident_chunks = 0;
+        c->resident_launch = c->resident_first = 1;
     }
     for (int k = 0; k < p.passes; ++k) {
         ResidentArgs& a = p.pass[k].args;
+        a.launch = c->resident_launch;
+        a.first = c->resident_first;
         a.wait_ticks = c->wait_ticks;
         a.n_steps = steps;
         a.flip = flip;
@@ -770,8 +770,8 @@ extern "C" int lbm_create(lbm_ctx** out, const lbm_member_desc* members, int32_t
         (e = hipMalloc(&c->d_active, sizeof(int) * n_members)) != hipSuccess ||
         (e = hipMalloc(&c->d_active_list, sizeof(int) * n_members)) != hipSuccess ||
         (e = hipMalloc(&c->d_flags, sizeof(int) * n_members)) != hipSuccess ||
-        (e = hipMalloc(&c->d_epoch, sizeof(int) * n_members)) != hipSuccess ||
-        (e = hipMalloc(&c->d_given_up, sizeof(int) * n_members)) != hipSuccess ||
+        (e = hipMalloc(&c->d_given_up, sizeof(int) * (n_members + 1))) != hipSuccess ||
+        (e = hipMalloc(&c->d_redo, sizeof(int) * (std::max(n_members, REDO_TASKS) + 2))) != hipSuccess ||
         (e = hipMalloc(&c->d_partial, sizeof(double) * c->partial_floats)) != hipSuccess ||
         (e = hipMalloc(&c->d_scratch, sizeof(double) * (4 * (size_t)n_members + 64))) != hipSuccess ||
         (e = hipMalloc(&c->d_iscratch, sizeof(int) * (4 * (size_t)n_members + 64))) != hipSuccess) {
@@ -787,8 +787,8 @@ extern "C" int lbm_create(lbm_ctx** out, const lbm_member_desc* members, int32_t
         (e = fill_int(c->d_cursor, n_members, 0, c->stream)) != hipSuccess ||
         (e = fill_int(c->d_active, n_members, 1, c->stream)) != hipSuccess ||
         (e = fill_iota(c->d_active_list, n_members, c->stream)) != hipSuccess ||
-        (e = fill_int(c->d_epoch, n_members, 1, c->stream)) != hipSuccess ||
-        (e = fill_int(c->d_given_up, n_members, 0, c->stream)) != hipSuccess ||
+        (e = fill_int(c->d_given_up, n_members + 1, 0, c->stream)) != hipSuccess ||
+        (e = clear_redo(c, c->stream)) != hipSuccess ||
         (e = fill_int(c->d_flags, n_members, 0, c->stream)) != hipSuccess) {
         lbm_destroy(c);
         return lbm_hip_fail(e, "initialising bookkeeping");
@@ -808,8 +808,8 @@ extern "C" int lbm_destroy(lbm_ctx* c) {
     hipFree(c->d_active);
     hipFree(c->d_active_list);
     hipFree(c->d_flags);
-    hipFree(c->d_epoch);
     hipFree(c->d_given_up);
+    hipFree(c->d_redo);
     hipFree(c->d_halo);
     if (c->gave_up) hipHostFree(c->gave_up);
     if (c->resident_done) {
@@ -846,14 +846,28 @@ static FinalizeArgs finalize_args(lbm_ctx* c, int n, int accumulate, int swap_pa
     f.swap_parity = swap_parity;
     f.mu = c->mu;
     f.inv_sigma_dt = c->dt / c->sigma;
-    f.epoch = c->d_epoch;
-    f.given_up = nullptr;
-    f.pop0 = c->pop[0];
-    f.pop1 = c->pop[1];
-    f.redo_partial = c->d_partial;
-    f.ghost = c->d_ghost;
-    f.gave_up_host = c->gave_up;
     return f;
+}
+
+// The reduction of the last chunk of resident launches (states_only: an untracked one, of `flip`).
+static hipError_t finalize_resident(lbm_ctx* c, const ResidentPlan& p, int n, int flip, bool states_only, hipStream_t st) {
+    RedoArgs r;
+    r.launch = c->resident_launch;
+    r.given_up = c->d_given_up;
+    r.n_members = c->n;
+    r.active_list = p.listed ? c->d_active_list : nullptr;
+    r.slots = p.slots;
+    r.bands = std::max(1, std::min(REDO_TASKS / p.slots, (c->max_ny + 3) / 4));
+    r.flip = flip;
+    r.states_only = states_only ? 1 : 0;
+    r.done = c->d_redo;
+    r.ticket = c->d_redo + std::max(c->n, REDO_TASKS);
+    r.gave_up_host = c->gave_up;
+    r.pop0 = c->pop[0];
+    r.pop1 = c->pop[1];
+    r.partial = c->d_partial;
+    r.ghost = c->d_ghost;
+    return launch_finalize_resident(finalize_args(c, n, 1, 1), r, st);
 }
 
 extern "C" int lbm_init(lbm_ctx* c, uint64_t seed, double noise_amp) { return lbm_init_flow(c, seed, noise_amp, 0.0); }
@@ -949,11 +963,12 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     bool stays = plan_batch(c, n_steps, c->plans, swept, false);
     ResidentPlan& resident = c->plans.resident;
     // A chunk was given up: something else keeps holding part of the device (another process, long
-    // kernels of other streams), and a chunk stepped again costs many times a good one.
+    // kernels of other streams), and a chunk stepped again costs several times a good one.
     if (c->gave_up && *(volatile int*)c->gave_up && c->wait_ticks >= 0) {
         *(volatile int*)c->gave_up = 0;
         c->resident_rest = RESIDENT_REST;
     }
+    c->resident_first = c->resident_launch + 1;
     const bool rests = stays && c->resident_rest > 0;
     if (rests) --c->resident_rest;
     if (stays && rests) {
@@ -994,9 +1009,7 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
         if (stays) {
             launches = 1;  // every member's buffers swap once
             if ((e = launch_resident_passes(c, resident, chunk, 0, st)) != hipSuccess) return e;
-            FinalizeArgs f = finalize_args(c, chunk, 1, 1);
-            f.given_up = c->d_given_up;
-            return launch_finalize(f, c->n, st);
+            return finalize_resident(c, resident, chunk, 0, false, st);
         }
         if (swept)
             for (int t; s < chunk; s += t, ++launches) {
@@ -1365,7 +1378,7 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
             }
             if (stays) {
                 const hipError_t re = launch_resident_passes(c, resident, c->chunk, flip, c->stream);
-                return re == hipSuccess ? add_int(c->d_epoch, c->n, 1, c->stream) : re;
+                return re == hipSuccess ? finalize_resident(c, resident, c->chunk, flip, true, c->stream) : re;
             }
             if (ts.adaptive) {
                 sweep.args.flip = flip;
@@ -1379,6 +1392,7 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
             hold = std::unique_lock<std::mutex>(u.lock);
             if (admit_resident(c, u, resident) != hipSuccess) return lbm_fail(LBM_EHIP, "resident launch");
         }
+        c->resident_first = c->resident_launch + 1;
         const int steps_per_launch = stays ? c->chunk : ts.adaptive ? sweep.steps : ts.steps;
         // warm-up pair
         launch(0);

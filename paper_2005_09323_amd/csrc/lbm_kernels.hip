@@ -350,13 +350,11 @@ __device__ __forceinline__ OutletVel outlet_velocities(const MemberDev& m, const
     return v;
 }
 
-// A resident chunk that was given up (lbm_resident.hip), stepped again by the
-// member's workgroup alone, cell by cell, from the source buffer that the
-// resident kernel only read; the last step's state ends in the other buffer.
+// Rows y0 .. y1 - 1 of one step of a member, cell by cell.
 template <bool OPEN>
-__device__ __forceinline__ void redo_step(const MemberDev& m, const float* src, float* dst, double* part, float* g) {
-    if (OPEN) {  // the ghost columns first (every row's neighbours anew: no table of ny rows)
-        for (int y = (int)threadIdx.x; y < m.ny; y += (int)blockDim.x) {
+__device__ __forceinline__ void redo_rows(const MemberDev& m, const float* src, float* dst, double* part, float* g, int y0, int y1) {
+    if (OPEN) {  // the ghost columns that the rows pull first (every row's neighbours anew: no table of rows)
+        for (int y = max(y0 - 1, 0) + (int)threadIdx.x; y < min(y1 + 1, m.ny); y += (int)blockDim.x) {
             float d1[9], d2[9];
             const OutletVel va = outlet_velocities(m, src, y > 0 ? y - 1 : 0, d1, d2);
             const OutletVel vb = outlet_velocities(m, src, y + 1 < m.ny ? y + 1 : m.ny - 1, d1, d2);
@@ -370,33 +368,99 @@ __device__ __forceinline__ void redo_step(const MemberDev& m, const float* src, 
         }
         __syncthreads();
     }
-    for (int c = (int)threadIdx.x; c < m.nx * m.ny; c += (int)blockDim.x) {
+    for (int c = y0 * m.nx + (int)threadIdx.x; c < y1 * m.nx; c += (int)blockDim.x) {
         const int y = c / m.nx, x = c - y * m.nx;
         if (m.model == 2) scalar_cell<2, OPEN>(m, src, dst, part, g, x, y);
         else if (m.model == 1) scalar_cell<1, OPEN>(m, src, dst, part, g, x, y);
         else scalar_cell<0, OPEN>(m, src, dst, part, g, x, y);
     }
-    __syncthreads();
 }
 
-__device__ __noinline__ void resident_redo(const FinalizeArgs& a, const MemberDev& m, int par) {
-    float* const from = (par ? a.pop1 : a.pop0) + m.off;
-    float* const to = (par ? a.pop0 : a.pop1) + m.off;
-    const int cells = m.nx * m.ny;
-    for (int t = 0; t < a.n; ++t) {
-        const float* src = t & 1 ? to : from;
-        float* dst = t & 1 ? from : to;
-        double* part = a.redo_partial + m.part_off + (long long)t * m.ring;
-        if (m.open) redo_step<true>(m, src, dst, part, a.ghost + m.ghost_off);
-        else redo_step<false>(m, src, dst, part, nullptr);
-    }
-    if (a.n % 2 == 0)
-        for (int c = (int)threadIdx.x; c < cells; c += (int)blockDim.x) {
-            const int y = c / m.nx, x = c - y * m.nx;
-            if (in_solid(m, x, y)) continue;
-            for (int i = 0; i < 9; ++i) to[(long long)i * cells + c] = from[(long long)i * cells + c];
+// Resident chunks that were given up (lbm_resident.hip), stepped again from the
+// source buffers, which the resident kernel only read; the last step's state
+// ends in the other buffer.
+//
+// A step of a member is cut into bands of rows (four at least).  The tasks
+// (step, member, band) are taken in this order from a counter by whichever
+// blocks run, and a task waits for the step before of its own band and of those
+// beside it: all that its rows pull, the outlet's rows two further on included,
+// and all that still pulls what it overwrites.  Those were taken earlier, by
+// blocks that run, so the earliest unfinished task never waits and every wait
+// ends, however few blocks the device holds at a time.  Bands beside each other
+// are at most one step apart: a ghost row that both form is formed for the same
+// step, to the same values.
+__device__ __forceinline__ void resident_redo(const FinalizeArgs& a, const RedoArgs& r) {
+    __shared__ int taken;
+    const int t0 = (int)threadIdx.x;
+    const int per = r.slots * r.bands, base = r.launch * REDO_STEPS;
+    const int steps = a.n + (a.n % 2 == 0 ? 1 : 0);  // an even number of steps ends in the source buffer: then a copy
+    auto seen = [&](int at) { return __hip_atomic_load(r.done + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (blockIdx.x == 0 && t0 == 0 && !r.states_only) *r.gave_up_host = 1;
+    // The last task's end and the next one's taking are one block of thread 0's between two barriers: with such a
+    // block at either end of the loop the compiler joins them across it, and the other lanes of the wave meet the
+    // barriers without lane 0.
+    int ended = -1, made = 0;
+#pragma unroll 1
+    for (;;) {
+        __syncthreads();  // (the last task's rows are written, and its number read by all)
+        if (t0 == 0) {
+            if (ended >= 0) __hip_atomic_store(r.done + ended, made, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            taken = atomicAdd(r.ticket, 1);
         }
+        __syncthreads();
+        const int k = __builtin_amdgcn_readfirstlane(taken);
+        ended = -1;
+        if (k >= per * steps) break;
+        const int t = k / per, slot = (k - t * per) / r.bands, band = k - t * per - slot * r.bands;
+        const int mi = __builtin_amdgcn_readfirstlane(r.active_list ? r.active_list[slot] : slot);
+        if (!a.active[mi] || r.given_up[mi] != r.launch) continue;
+        const MemberDev m = a.members[mi];
+        const int high = max((m.ny + r.bands - 1) / r.bands, 4), y0 = band * high, y1 = min(y0 + high, m.ny);
+        if (y0 >= m.ny) continue;
+        const int at = slot * r.bands + band;
+        if (t > 0) {
+            if (t0 < 3 && (t0 > 0 || band > 0) && (t0 < 2 || y1 < m.ny))
+                while (seen(at - 1 + t0) < base + t) __builtin_amdgcn_s_sleep(2);
+            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        const int par = a.parity[mi] ^ r.flip;
+        float* const from = (par ? r.pop1 : r.pop0) + m.off;
+        float* const to = (par ? r.pop0 : r.pop1) + m.off;
+        const float* const src = t & 1 ? to : from;
+        float* const dst = t & 1 ? from : to;
+        if (t < a.n) {
+            double* const part = r.partial + m.part_off + (long long)t * m.ring;
+            if (m.open) redo_rows<true>(m, src, dst, part, r.ghost + m.ghost_off, y0, y1);
+            else redo_rows<false>(m, src, dst, part, nullptr, y0, y1);
+        } else {
+            const int cells = m.nx * m.ny;
+            for (int c = y0 * m.nx + t0; c < y1 * m.nx; c += (int)blockDim.x) {
+                const int y = c / m.nx, x = c - y * m.nx;
+                if (in_solid(m, x, y)) continue;
+                for (int i = 0; i < 9; ++i) dst[(long long)i * cells + c] = src[(long long)i * cells + c];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        ended = at;
+        made = base + t + 1;
+    }
+    if (t0 == 0 && atomicAdd(r.ticket + 1, 1) == (int)gridDim.x - 1) {  // no block takes a task any more
+        r.ticket[0] = 0;
+        r.ticket[1] = 0;
+    }
+    // this block's own member, wherever its bands were made
+    const int slot = (int)blockIdx.x;
+    if (slot < r.slots) {
+        const int mi = r.active_list ? r.active_list[slot] : slot;
+        if (a.active[mi] && r.given_up[mi] == r.launch) {
+            const int ny = a.members[mi].ny, high = max((ny + r.bands - 1) / r.bands, 4);
+            for (int band = t0; band * high < ny; band += (int)blockDim.x)
+                while (seen(slot * r.bands + band) < base + steps) __builtin_amdgcn_s_sleep(2);
+        }
+    }
     __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
 // Reduce the drag partials of a chunk of n steps for one member per block:
@@ -404,20 +468,11 @@ __device__ __noinline__ void resident_redo(const FinalizeArgs& a, const MemberDe
 // the member's cursor; then, in step order, accum += (f_d - mu)/sigma * dt.
 // The member's parity flips n times (not for step 0, which init wrote in
 // place) and its cursor advances by n.
-__global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
-    const int mi = (int)blockIdx.x;
+__device__ __forceinline__ void finalize_member(const FinalizeArgs& a, int mi) {
     const int s = (int)threadIdx.x;
     const bool on = a.active[mi];
     const MemberDev m = a.members[mi];
     __shared__ double fd[256];
-    if (a.given_up) {
-        if (on && a.given_up[mi] == a.epoch[mi]) {
-            if (s == 0) *a.gave_up_host = 1;
-            resident_redo(a, m, a.parity[mi]);
-        }
-        __syncthreads();
-        if (s == 0) a.epoch[mi] += 1;  // every member's: the epochs advance together
-    }
     if (!on) return;
     const int cur = a.cursor[mi];
     if (s < a.n) {
@@ -445,6 +500,15 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
         a.parity[mi] ^= a.swap_parity;
         a.cursor[mi] = cur + a.n;
     }
+}
+
+__global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) { finalize_member(a, (int)blockIdx.x); }
+
+__global__ __launch_bounds__(256) void finalize_resident_kernel(FinalizeArgs a, RedoArgs r) {
+    if (r.given_up[r.n_members] == r.launch) resident_redo(a, r);
+    const int slot = (int)blockIdx.x;
+    if (r.states_only || slot >= r.slots) return;
+    finalize_member(a, r.active_list ? r.active_list[slot] : slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -508,6 +572,12 @@ hipError_t launch_init(const InitArgs& a, int n_members, long long max_cells, hi
 
 hipError_t launch_finalize(const FinalizeArgs& a, int n_members, hipStream_t st) {
     hipLaunchKernelGGL(finalize_kernel, dim3(n_members), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+// (blocks beyond the members' have nothing to do unless a chunk is stepped again)
+hipError_t launch_finalize_resident(const FinalizeArgs& a, const RedoArgs& r, hipStream_t st) {
+    hipLaunchKernelGGL(finalize_resident_kernel, dim3(max(r.slots, min(r.slots * r.bands, 256))), dim3(256), 0, st, a, r);
     return hipGetLastError();
 }
 

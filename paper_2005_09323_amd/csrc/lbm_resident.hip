@@ -22,10 +22,11 @@
 // The wait for a neighbour is bounded: workgroups of a member run side by side
 // when the device is free (the host launches at most as many as fit), but
 // kernels of other streams may hold part of it.  A wave that waits longer than
-// its limit (lbm_set_wait_limit) gives the member's chunk up: it marks it and
+// its limit (lbm_set_wait_limit; a short one once a chunk of the same batch was
+// given up) gives the member's chunk up: it marks it and
 // leaves, every other wave of the member that waits leaves too, and the
 // chunk's drag reduction steps the member again from the untouched source
-// buffer, by itself (resident_redo).  So every wave ends, and the result never
+// buffer (resident_redo).  So every wave ends, and the result never
 // depends on what ran beside.
 //
 // What bounds it: with few waves, a step's chain: a row's collision by a lone
@@ -91,8 +92,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const int on = a.active[mi];
     const MemberDev m = a.members[mi];
     const int par = a.parity[mi] ^ a.flip;
-    const int epoch = a.epoch[mi];
-    const unsigned tag0 = ((unsigned)epoch << RESIDENT_PASS_BITS | (unsigned)a.pass) << RESIDENT_STEP_BITS;  // tag of step t: + t + 1
+    const unsigned tag0 = ((unsigned)a.launch << RESIDENT_PASS_BITS | (unsigned)a.pass) << RESIDENT_STEP_BITS;  // tag of step t: + t + 1
     if (!on) return;
     const float* __restrict__ src = (par ? a.pop1 : a.pop0) + m.off;
     float* __restrict__ dst = (par ? a.pop0 : a.pop1) + m.off;
@@ -254,8 +254,12 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     publish_side(0, 0, 4, 7, 8, 0, tag0 + 1u);
     publish_side(1, R - 1, 2, 5, 6, 0, tag0 + 1u);
     publish_outlet(0, tag0 + 1u);
+    auto give_up = [&] {
+        __hip_atomic_store(&a.given_up[mi], a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&a.given_up[a.n_members], a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     if (a.wait_ticks < 0 && (low_mem || high_mem)) {  // no wait at all (the giving up is tested so)
-        __hip_atomic_store(&a.given_up[mi], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        give_up();
         return;
     }
     lds_barrier();
@@ -371,9 +375,11 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                 if ((spin & 63) == 63) {
                     const long long now = wall_clock64();
                     if (!began) began = now;
-                    const bool late = now - began > a.wait_ticks;
-                    if (late) __hip_atomic_store(&a.given_up[mi], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (late || __hip_atomic_load(&a.given_up[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == epoch) return false;
+                    const int any = __hip_atomic_load(&a.given_up[a.n_members], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const long long limit = any >= a.first ? min(a.wait_ticks, RESIDENT_SHORT_WAIT) : a.wait_ticks;
+                    const bool late = now - began > limit;
+                    if (late) give_up();
+                    if (late || __hip_atomic_load(&a.given_up[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.launch) return false;
                 }
             }
         };
