@@ -8,6 +8,7 @@
 
 #include "../../include/lbm.h"
 #include "kernels.hpp"
+#include "resident_admission.hpp"
 
 namespace lbm {
 
@@ -117,7 +118,7 @@ struct lbm_ctx {
     int* d_flags = nullptr;
     // resident chunks: words between workgroups (for any plan), per member (and of any) the chunk given up, the
     // counts of one stepped again, the bound of a wait; the last chunk's number and that of its batch's first;
-    // the last batch's workgroups, how many of them a compute unit holds and the batch's end
+    // what its launches take of the device and the end of the last of them
     unsigned long long* d_halo = nullptr;
     size_t halo_words = 0;
     int* d_given_up = nullptr;  // [n + 1]
@@ -126,7 +127,7 @@ struct lbm_ctx {
     int* gave_up = nullptr;  // pinned: a chunk was given up; the next RESIDENT_REST batches go another way
     int resident_rest = 0;
     int resident_launch = 0, resident_first = 0;
-    int resident_blocks = 0, resident_places = 1;
+    lbm::ResidentUse resident_use;  // of the launches since resident_done was last found to have passed
     hipEvent_t resident_done = nullptr;
     int device = 0;
     std::vector<int> h_parity, h_cursor, h_active;

@@ -456,35 +456,35 @@ static ResidentUsers& resident_users() {
     return *u;
 }
 
-// Before a resident launch of `c` (under the lock): its stream waits for the
-// other contexts' launches that are still running, if all of them together
-// are more than the device holds.
+// Before resident launches of `c` (under the lock, until leave_resident): its stream waits for the other
+// contexts' launches that are still running, if all of them together are more than the device holds.
 static hipError_t admit_resident(lbm_ctx* c, ResidentUsers& u, const ResidentPlan& p) {
     const OutsideCapture outside;
     hipError_t e;
     if (std::find(u.users.begin(), u.users.end(), c) == u.users.end()) u.users.push_back(c);
-    c->resident_places = 0;  // (its launches differ: beside no other's)
-    c->resident_blocks = 0;
-    bool fit = true;
+    ResidentUse now;
     for (int k = 0; k < p.passes; ++k) {
         const ResidentArgs& a = p.pass[k].args;
-        fit = fit && a.block_waves == p.pass[0].args.block_waves;
-        c->resident_blocks = std::max(c->resident_blocks, a.total_blocks);
+        const ResidentUse one{a.total_blocks, SWEEP_WAVES / a.block_waves};
+        now = k == 0 ? one : either_of(now, one);
     }
-    if (fit) c->resident_places = SWEEP_WAVES / p.pass[0].args.block_waves;
-    int others = 0;
-    long long blocks = c->resident_blocks;
+    auto running = [](const lbm_ctx* o) { return hipEventQuery(o->resident_done) == hipErrorNotReady; };
+    c->resident_use = running(c) ? either_of(c->resident_use, now) : now;
+    std::vector<ResidentUse> uses{c->resident_use};
     for (const lbm_ctx* o : u.users)
-        if (o != c && o->device == c->device && hipEventQuery(o->resident_done) == hipErrorNotReady) {
-            ++others;
-            blocks += o->resident_blocks;
-            fit = fit && o->resident_places == c->resident_places;
-        }
+        if (o != c && o->device == c->device && running(o)) uses.push_back(o->resident_use);
     (void)hipGetLastError();  // (not ready)
-    if (!others || (fit && blocks <= (long long)c->cu_count * c->resident_places)) return hipSuccess;
+    if (side_by_side(uses, c->cu_count)) return hipSuccess;
     for (const lbm_ctx* o : u.users)
         if (o != c && o->device == c->device && (e = hipStreamWaitEvent(c->stream, o->resident_done, 0)) != hipSuccess) return e;
     return hipSuccess;
+}
+
+// After them: where the other contexts' launches would wait.
+static hipError_t leave_resident(lbm_ctx* c, std::unique_lock<std::mutex>& hold) {
+    const hipError_t e = hipEventRecord(c->resident_done, c->stream);
+    hold.unlock();
+    return e;
 }
 
 // Rows per unit of a sweep: the run's own choice (lbm_set_run_rows) or `rows`.
@@ -1041,15 +1041,18 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     };
     hipError_t e;
     int done = 0;
+    // Resident chunks are enqueued a few at a time under the users' lock, so that another thread's context waits for
+    // these at most and not for a whole long batch.
+    constexpr int CHUNKS_HELD = 8;
+    ResidentUsers* const users = stays ? &resident_users() : nullptr;
     std::unique_lock<std::mutex> hold;
-    if (stays) {
-        ResidentUsers& u = resident_users();
-        hold = std::unique_lock<std::mutex>(u.lock);
-        if ((e = admit_resident(c, u, resident)) != hipSuccess) return lbm_hip_fail(e, "resident launch");
-    }
     while (done < n_steps) {
         const int chunk = std::min(n_steps - done, c->chunk);
         int launches = 0;
+        if (stays && !hold.owns_lock()) {
+            hold = std::unique_lock<std::mutex>(users->lock);
+            if ((e = admit_resident(c, *users, resident)) != hipSuccess) return lbm_hip_fail(e, "resident launch");
+        }
         if (c->graphs && chunk == c->chunk && !stays) {  // (a resident chunk is two launches)
             ChunkGraphKey key{c->tile_id, c->one_tile, two ? 1 : 0, waves2, c->model, c->open ? 1 : 0, chunk,
                               c->table_gen, a.total_blocks, a2.total_blocks, a.active_list ? 1 : 0, c->mu, c->dt / c->sigma,
@@ -1084,6 +1087,7 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
             if ((e = hipGraphLaunch(c->graph_exec, c->stream)) != hipSuccess) return lbm_hip_fail(e, "graph launch");
             launches = c->graph_launches;
         } else if ((e = enqueue(chunk, c->stream, launches)) != hipSuccess) {
+            if (stays) (void)leave_resident(c, hold);  // (what was launched still runs)
             return lbm_hip_fail(e, "lattice step launches");
         }
         for (int m = 0; m < c->n; ++m)
@@ -1092,8 +1096,9 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
                 c->h_cursor[m] += chunk;
             }
         done += chunk;
+        if (stays && (done == n_steps || done % (CHUNKS_HELD * c->chunk) == 0) && (e = leave_resident(c, hold)) != hipSuccess)
+            return lbm_hip_fail(e, "resident launch");
     }
-    if (stays && (e = hipEventRecord(c->resident_done, c->stream)) != hipSuccess) return lbm_hip_fail(e, "resident launch");
     return LBM_OK;
 }
 

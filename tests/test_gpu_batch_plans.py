@@ -103,3 +103,58 @@ def test_batches_allocate_nothing():
     steps(ens)
     assert abs(free - torch.cuda.mem_get_info()[0]) < 4 << 20
     ens.close()
+
+
+def test_contexts_of_two_threads_take_turns():
+    """Two contexts that do not fit on the device together, each stepped by its own thread on its own stream:
+    a long batch, then a smaller plan while the larger one's launches are still queued, against the same
+    batches alone (bit for bit)."""
+    import threading
+
+    members = [workloads.Member(256, 203, 0.56, 2e-5, (124, 100, 13))] * 28
+    few = [j < 3 for j in range(28)]
+
+    def batches(ens):
+        ens.step(64 * 20 + 9)
+        ens.set_active(few)
+        ens.step(64)
+        ens.set_active(None)
+        ens.step(130)
+
+    def made():
+        ens = _ensemble(members, 1600)
+        ens.init(7, 1e-2)
+        return ens
+
+    ens = made()
+    batches(ens)
+    torch.cuda.synchronize()
+    want = [ens.series.clone()] + [ens.state(i).clone() for i in (0, 27)]
+    ens.close()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    pair = []
+    for st in streams:
+        with torch.cuda.stream(st):
+            pair.append(made())
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(st, e):
+        try:
+            with torch.cuda.stream(st):
+                batches(e)
+        except Exception as err:  # noqa: BLE001 (reported below)
+            failed.append(err)
+
+    threads = [threading.Thread(target=work, args=a) for a in zip(streams, pair)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for e in pair:
+        got = [e.series] + [e.state(i) for i in (0, 27)]
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+        e.close()
