@@ -55,6 +55,17 @@ __device__ __forceinline__ unsigned long long get_word(const unsigned long long*
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ void give_up(int* given_up, int mi, int n_members, int launch) {
+    __hip_atomic_store(given_up + mi, launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(given_up + n_members, launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The kernel's arguments by their address: what only a long wait reads is loaded there and holds no scalar
+// registers in the rows' loop, which spills them (us, 64 steps: 512 x 512 x 128 open 13.94 -> 13.86 ms, 64 x 513 x 129
+// open 2849 -> 2839, 1 x 256 x 64 142.8 -> 137.5).
+typedef const __attribute__((address_space(4))) ResidentArgs* KernelArgs;
+__device__ __forceinline__ KernelArgs kernel_args() { return (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr(); }
+
 // FULL: every member's width is a multiple of 64 C (no lane or cell of a wave is beyond it, and no choice of its end
 // is made in each row: us per step 1 x 256 x 64 2.2 -> 2.1, 16 x 512 x 128 7.2 -> 7.0, 4 x 1024 x 256 7.0 -> 6.7).
 template <int C, int R, int MODEL, bool OPEN, bool FULL>
@@ -254,12 +265,8 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     publish_side(0, 0, 4, 7, 8, 0, tag0 + 1u);
     publish_side(1, R - 1, 2, 5, 6, 0, tag0 + 1u);
     publish_outlet(0, tag0 + 1u);
-    auto give_up = [&] {
-        __hip_atomic_store(&a.given_up[mi], a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&a.given_up[a.n_members], a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
     if (a.wait_ticks < 0 && (low_mem || high_mem)) {  // no wait at all (the giving up is tested so)
-        give_up();
+        give_up(a.given_up, mi, a.n_members, a.launch);
         return;
     }
     lds_barrier();
@@ -375,11 +382,13 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                 if ((spin & 63) == 63) {
                     const long long now = wall_clock64();
                     if (!began) began = now;
-                    const int any = __hip_atomic_load(&a.given_up[a.n_members], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const long long limit = any >= a.first ? min(a.wait_ticks, RESIDENT_SHORT_WAIT) : a.wait_ticks;
+                    const KernelArgs k = kernel_args();
+                    int* const up = k->given_up;
+                    const int any = __hip_atomic_load(up + k->n_members, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const long long limit = any >= k->first ? min(k->wait_ticks, RESIDENT_SHORT_WAIT) : k->wait_ticks;
                     const bool late = now - began > limit;
-                    if (late) give_up();
-                    if (late || __hip_atomic_load(&a.given_up[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.launch) return false;
+                    if (late) give_up(up, mi, k->n_members, k->launch);
+                    if (late || __hip_atomic_load(up + mi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == k->launch) return false;
                 }
             }
         };
