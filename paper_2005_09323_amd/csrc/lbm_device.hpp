@@ -51,6 +51,11 @@ __device__ __forceinline__ double link_momentum(unsigned links, double o1, doubl
 // written in one expression may become one FMA, nothing across statements),
 // so that every kernel that inlines this function computes the same bits
 // whatever the optimizer does around it.
+//
+// FEW: the axes' coefficients are four times the diagonals', an exact factor, so the axes can do with the diagonals'
+// four for two more multiplications per cell and the same bits.  The one-step kernel, whose scalar registers are full,
+// takes this form; the sweep and resident kernels, bound by the FP64 units, do not.
+template <bool FEW>
 __device__ __forceinline__ double bgk_guo(const MemberDev& m, float d[9], unsigned links, bool ring) {
 #pragma clang fp contract(on)
     const double d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3], d4 = d[4];
@@ -70,7 +75,8 @@ __device__ __forceinline__ double bgk_guo(const MemberDev& m, float d[9], unsign
     const double ux = jx * inv;
     const double uy = jy * inv;
     const double keep = m.keep;
-    const double ba = fma(m.a1, fma(-1.5, fma(jy, uy, jx * ux), drho), -(m.ag * ux));  // b / 9
+    const double ux4 = 4.0 * ux, uy4 = 4.0 * uy;
+    const double ba = fma(m.a1, fma(-1.5, fma(jy, uy, jx * ux), drho), FEW ? -(m.qg * ux4) : -(m.ag * ux));  // b / 9
     const double bq = 0.25 * ba;                                                        // b / 36
     // e = c.J, v = c.u of the positive direction of a pair
     auto pair = [&](int ip, int im, double dp, double dm, double even, double odd, double& op, double& on) {
@@ -81,8 +87,20 @@ __device__ __forceinline__ double bgk_guo(const MemberDev& m, float d[9], unsign
     };
     double o1, o3, o2, o4, o5, o7, o8, o6;
     d[0] = (float)fma(4.0, ba, keep * d0);
-    pair(1, 3, d1, d3, fma(fma(m.a45, jx, m.a9), ux, ba), fma(m.a3, jx, m.ag), o1, o3);
-    pair(2, 4, d2, d4, fma(m.a45 * jy, uy, ba), m.a3 * jy, o2, o4);
+    if constexpr (FEW) {
+        // (odd: a fourth of the pair's)
+        auto axis = [&](int ip, int im, double dp, double dm, double even, double odd, double& op, double& on) {
+            op = fma(keep, dp, fma(4.0, odd, even));
+            on = fma(keep, dm, fma(-4.0, odd, even));
+            d[ip] = (float)op;
+            d[im] = (float)on;
+        };
+        axis(1, 3, d1, d3, fma(fma(m.q45, jx, m.q9), ux4, ba), fma(m.q3, jx, m.qg), o1, o3);
+        axis(2, 4, d2, d4, fma(m.q45 * jy, uy4, ba), m.q3 * jy, o2, o4);
+    } else {
+        pair(1, 3, d1, d3, fma(fma(m.a45, jx, m.a9), ux, ba), fma(m.a3, jx, m.ag), o1, o3);
+        pair(2, 4, d2, d4, fma(m.a45 * jy, uy, ba), m.a3 * jy, o2, o4);
+    }
     const double ep = jx + jy, em = jx - jy;
     pair(5, 7, d5, d7, fma(fma(m.q45, ep, m.q9), ux + uy, bq), fma(m.q3, ep, m.qg), o5, o7);
     pair(8, 6, d8, d6, fma(fma(m.q45, em, m.q9), ux - uy, bq), fma(m.q3, em, m.qg), o8, o6);
@@ -241,16 +259,16 @@ __device__ __forceinline__ double cm1_guo(const MemberDev& m, float d[9], unsign
 // register allocation.
 // ring: whether any cell of the wave's row has links (wave-uniform; the drag
 // is not formed otherwise).
-template <int MODEL>
+template <int MODEL, bool FEW = false>
 __device__ __forceinline__ double collide_cell(const MemberDev& m, float d[9], unsigned links, bool ring) {
     if constexpr (MODEL == 2) return cm1_guo(m, d, links, ring);
     else if constexpr (MODEL == 1) return cm_guo(m, d, links, ring);
-    else return bgk_guo(m, d, links, ring);
+    else return bgk_guo<FEW>(m, d, links, ring);
 }
 
 // The member's own model, decided at run time (the one-off initial step).
 __device__ __forceinline__ double collide_member(const MemberDev& m, float d[9], unsigned links) {
-    return m.model == 2 ? cm1_guo(m, d, links, true) : (m.model ? cm_guo(m, d, links, true) : bgk_guo(m, d, links, true));
+    return m.model == 2 ? cm1_guo(m, d, links, true) : (m.model ? cm_guo(m, d, links, true) : bgk_guo<false>(m, d, links, true));
 }
 
 // The nine pulled populations of one cell (x, y) from the state at t, with

@@ -43,9 +43,9 @@ __device__ __forceinline__ void scalar_cell(const MemberDev& m, const float* __r
     if (OPEN) {
         MemberDev mc = m;
         sponge_at(mc, x);
-        drag = collide_cell<MODEL>(mc, dl, links, ri >= 0);
+        drag = collide_cell<MODEL, true>(mc, dl, links, ri >= 0);
     } else {
-        drag = collide_cell<MODEL>(m, dl, links, ri >= 0);
+        drag = collide_cell<MODEL, true>(m, dl, links, ri >= 0);
     }
     const long long cell = (long long)y * nx + x;
 #pragma unroll
@@ -170,9 +170,9 @@ __device__ __forceinline__ void vec_row(const MemberDev& m, const float* __restr
         if (OPEN) {
             MemberDev mc = m;
             if (sponge_wave) sponge_at(mc, x0 + k);
-            drag = collide_cell<MODEL>(mc, dl, links, near_sq);
+            drag = collide_cell<MODEL, true>(mc, dl, links, near_sq);
         } else {
-            drag = collide_cell<MODEL>(m, dl, links, near_sq);
+            drag = collide_cell<MODEL, true>(m, dl, links, near_sq);
         }
 #pragma unroll
         for (int i = 0; i < 9; ++i) p[i][k] = dl[i];
@@ -213,9 +213,14 @@ __global__ __launch_bounds__(64 * TYT) __attribute__((amdgpu_waves_per_eu(R == 1
     const int mi = block_to_member(a, b, tx, ty, vec, seg_rows);
     // the three bookkeeping reads are independent: issue them together
     const int on = a.active[mi];
-    const MemberDev m = a.members[mi];
+    MemberDev m = a.members[mi];
     const int par = a.parity[mi] ^ a.flip;
     if (!on) return;
+    // Few coefficients (bgk_guo), and three of them in vector registers: an instruction takes one scalar operand only,
+    // and nine coefficients in scalar registers spill 34 of these (1 x 256 x 64, 64 launches: 441 -> 423 us; open
+    // 16 x 512 x 128 1641 -> 1586).
+    if constexpr (MODEL == 0 && !OPEN)
+        for (double* c : {&m.q9, &m.qg, &m.keep}) __asm__ volatile("" : "+v"(*c));
     const float* __restrict__ src = (par ? a.pop1 : a.pop0) + m.off;
     float* __restrict__ dst = (par ? a.pop0 : a.pop1) + m.off;
     double* __restrict__ part = a.partial + m.part_off + (long long)a.slot * m.ring;
