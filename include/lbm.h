@@ -324,8 +324,10 @@ int32_t lbm_tile_count(void);
    makes more than this says), for the shape in use and the
    members active now. */
 int lbm_launch_steps(const lbm_ctx* ctx, int32_t* steps);
-/* Time every tile shape on this ensemble (n_steps each, on the context's
-   stream, synchronising it) and keep the fastest.  Writes the chosen id.  If
+/* Time every tile shape on this ensemble (n_steps launches each, the default
+   shape n_steps steps or two chunks of 64 if these are more, after a pair of
+   launches to warm up; on the context's stream, synchronising it) and keep the
+   fastest.  Writes the chosen id.  If
    that shape makes two steps per launch and the ensemble has several runs of
    lattice shapes (an uneven batch), each run's row range (whole strips, 128,
    64 or 32 rows per workgroup) is then tuned on its own, one run at a time,

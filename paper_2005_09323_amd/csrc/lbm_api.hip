@@ -1351,7 +1351,6 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         return lbm_fail(LBM_EHIP, "event creation failed");
     float best_ms = 1e30f;  // per step
     int best = c->tile_id;
-    const int pairs = std::max(1, n_steps / 2);
     c->run_rows.clear();  // the shapes first, each with its own row policy
     // time the current tables with shape t; ms per step, or a negative value
     // if the shape does not apply
@@ -1399,6 +1398,7 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         }
         c->resident_first = c->resident_launch + 1;
         const int steps_per_launch = stays ? c->chunk : ts.adaptive ? sweep.steps : ts.steps;
+        const int pairs = std::max(1, n_steps / (ts.adaptive ? 2 * steps_per_launch : 2));
         // warm-up pair
         launch(0);
         launch(1);

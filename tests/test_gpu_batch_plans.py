@@ -158,3 +158,21 @@ def test_contexts_of_two_threads_take_turns():
         for a, b in zip(got, want):
             assert torch.equal(a, b)
         e.close()
+
+
+def test_tuning_makes_about_the_steps_asked_for():
+    """lbm_autotune(n) makes n launches of each shape (of up to two steps), or of the default shape n steps or two
+    chunks of 64 if these are more, and two launches more: with n = 200 at most 404 steps each.  The steps are
+    untracked, but a body force F adds F to every cell's momentum in each of them (the walls take less than a
+    tenth of it back: their layers grow to sqrt(nu T) = 6 of 256 rows)."""
+    force = 1e-9
+    members = [workloads.Member(256, 256, 0.51, force, None)] * 8
+    ens = _ensemble(members)
+    ens.init(7, 0.0)
+    ens.autotune(200)
+    torch.cuda.synchronize()
+    d = ens.state(3).double()
+    jx = (d[1] - d[3] + d[5] - d[6] - d[7] + d[8]).mean().item()
+    shapes = ens.lib.lbm_tile_count()
+    ens.close()
+    assert 16 * 200 * 0.9 < jx / force < shapes * 404, jx / force
