@@ -350,7 +350,8 @@ int lbm_run_count(const lbm_ctx* ctx, int32_t* n_runs);
    changes). */
 int lbm_set_run_rows(lbm_ctx* ctx, const int32_t* rows, int32_t n_runs);
 /* The rows per workgroup each run uses now (0: whole strips; -1 for every
-   run if the shape in use makes one step per launch): writes n_runs and, if
+   run if the shape in use makes one step per launch, except those given for
+   the default shape's sweep): writes n_runs and, if
    rows is not NULL, max_runs >= n_runs entries. */
 int lbm_get_run_rows(const lbm_ctx* ctx, int32_t* rows, int32_t max_runs, int32_t* n_runs);
 /* lbm_autotune with a persisted table: path is a text file of lines

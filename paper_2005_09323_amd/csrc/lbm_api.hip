@@ -534,12 +534,22 @@ static double others_cost(const lbm_ctx* c, double cells) {
     return cells / (four ? 80e3 : 50e3) + (c->open ? 13.0 : 6.0);
 }
 
-// The sweep launch of a batch (steps per launch and the table of units); false if another kernel should step it.  The sweep takes
-// lattices of up to 64 SWEEP_WAVES SWEEP_CELLS = 1024 columns in periodic channels; the
-// adaptive shape chooses it where its estimated time per step is below that of
+// The sweep takes lattices of up to 64 SWEEP_WAVES SWEEP_CELLS = 1024 columns in periodic channels, with the
+// adaptive shape.
+static bool sweep_takes(const lbm_ctx* c) {
+    if (!TILE_SHAPES[c->tile_id].adaptive || c->open) return false;
+    for (int s = 0; s < c->nseg; ++s) {
+        const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
+        if (36LL * d.nx * d.ny >= (1LL << 31) || d.nx > 64 * SWEEP_WAVES * SWEEP_CELLS) return false;
+    }
+    return true;
+}
+
+// The sweep launch of a batch (steps per launch and the table of units); false if another kernel should step it.
+// The adaptive shape chooses it where its estimated time per step is below that of
 // the kernels it would use otherwise.
 static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
-    if (!TILE_SHAPES[c->tile_id].adaptive || c->open) return false;
+    if (!sweep_takes(c)) return false;
     const bool listed = !every_member && c->n_active < c->n && c->uniform_shape;
     p = SweepPlan();
     SweepArgs& a = p.args;
@@ -549,14 +559,12 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     double cells = 0.0;
     for (int s = 0; s < c->nseg; ++s) {
         const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
-        if (36LL * d.nx * d.ny >= (1LL << 31)) return false;
         const int end = s + 1 < c->nseg ? c->seg[s + 1].member_begin : c->n;
         const int lanes = (d.nx + SWEEP_CELLS - 1) / SWEEP_CELLS;
         SweepSegment& g = a.seg[s];
         g.member_begin = c->seg[s].member_begin;
         g.waves = (lanes + 63) / 64;
         g.lanes = (lanes + g.waves - 1) / g.waves;
-        if (g.waves > SWEEP_WAVES) return false;
         a.block_waves = std::max(a.block_waves, g.waves);
         if (d.nx % (64 * SWEEP_CELLS)) a.width = 1;
         members[s] = listed ? c->n_active : end - g.member_begin;
@@ -1314,12 +1322,11 @@ extern "C" int lbm_get_run_rows(const lbm_ctx* c, int32_t* rows, int32_t max_run
     if (rows && max_runs < *n_runs) return lbm_fail(LBM_EINVAL, "room for %d runs, need %d", max_runs, *n_runs);
     if (rows)
         for (int s = 0; s < *n_runs; ++s) {
-            if (!c->two_step) {
-                rows[s] = -1;
-                continue;
-            }
-            const int ny = c->desc[c->seg2[s].member_begin].ny;
-            rows[s] = c->seg2[s].rows >= ny ? 0 : c->seg2[s].rows;
+            // one step per launch: no ranges, but those given for the sweep, which takes any width
+            const int ny = c->desc[(c->two_step ? c->seg2[s] : c->seg[s]).member_begin].ny;
+            const int given = s < (int)c->run_rows.size() && sweep_takes(c) ? c->run_rows[s] : -1;
+            const int used = c->two_step ? c->seg2[s].rows : given;
+            rows[s] = used >= ny ? 0 : used;
         }
     return LBM_OK;
 }

@@ -183,7 +183,8 @@ class Ensemble:
         native.check(self.lib.lbm_set_run_rows(self._ctx, arr, len(rows)))
 
     def run_rows(self) -> list:
-        """The rows per workgroup each run uses now (0: whole strips; -1: one-step launches)."""
+        """The rows per workgroup each run uses now (0: whole strips; -1: one-step launches, or the
+        default shape's own choice)."""
         n = ctypes.c_int32()
         native.check(self.lib.lbm_get_run_rows(self._ctx, None, 0, ctypes.byref(n)))
         arr = (ctypes.c_int32 * max(n.value, 1))()

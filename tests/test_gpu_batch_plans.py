@@ -176,3 +176,32 @@ def test_tuning_makes_about_the_steps_asked_for():
     shapes = ens.lib.lbm_tile_count()
     ens.close()
     assert 16 * 200 * 0.9 < jx / force < shapes * 404, jx / force
+
+
+def test_row_ranges_of_ragged_widths_read_back():
+    """Row ranges given for the default shape's sweep are what run_rows returns, for widths that no two-step
+    shape takes too, and setting what was read changes nothing; where no kernel uses them it returns -1."""
+    members = [workloads.Member(250, 40, 0.56, 2e-5, (116, 12, 9))] * 2 + [workloads.Member(330, 24, 0.56, 2e-5, None)]
+    ens = _ensemble(members)
+    assert ens.run_rows() == [-1, -1]
+    for given, read in (([7, -1], [7, -1]), ([0, 3], [0, 3]), ([40, 25], [0, 0]), ([39, 23], [39, 23])):
+        ens.set_run_rows(given)
+        assert ens.run_rows() == read, given
+        ens.set_run_rows(ens.run_rows())
+        assert ens.run_rows() == read, given
+    ens.set_tile(0)
+    assert ens.run_rows() == [-1, -1]
+    ens.set_tile(20)
+    assert ens.run_rows() == [39, 23]
+    ens.set_open_channel(0.05, 20, 3, 200, 0.9)
+    assert ens.run_rows() == [-1, -1]
+    ens.set_open_channel(None)
+    ens.set_run_rows(None)
+    assert ens.run_rows() == [-1, -1]
+    ens.close()
+    # two-step launches: the ranges in use, given or not
+    ens = _ensemble([workloads.Member(256, 64, 0.56, 2e-5, None)] * 2)
+    assert ens.run_rows() == [32]
+    ens.set_run_rows([16])
+    assert ens.run_rows() == [16]
+    ens.close()
