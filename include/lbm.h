@@ -175,6 +175,26 @@ int lbm_set_graphs(lbm_ctx* ctx, int32_t on);
  */
 int lbm_set_wait_limit(lbm_ctx* ctx, int32_t us);
 
+/*
+ * The kernel that steps a batch with the default shape (20): several steps per
+ * launch with the populations in registers for a whole chunk, the sweep, or
+ * the one- and two-step kernels.  Estimated times choose it (LBM_KERNEL_ESTIMATED);
+ * lbm_set_batch_kernel asks for one, for measurements and tests: it is taken
+ * wherever it can step the ensemble, whatever the estimates and earlier
+ * given-up chunks.  All give bit-identical results.  LBM_EINVAL on another value.
+ */
+#define LBM_KERNEL_ESTIMATED (-1)
+#define LBM_KERNEL_PLAIN 0
+#define LBM_KERNEL_SWEEP 1
+#define LBM_KERNEL_RESIDENT 2
+int lbm_set_batch_kernel(lbm_ctx* ctx, int32_t kernel);
+/* What the next lbm_step_batch of n_steps (of any shape) makes on the context's
+   stream: out[0] the kernel (LBM_KERNEL_PLAIN .. LBM_KERNEL_RESIDENT), out[1] the steps of a
+   full launch, out[2] the launches that share the members (each of out[1] steps), out[3] the
+   columns a lane holds and out[4] the rows per wave (LBM_KERNEL_PLAIN with one
+   step, LBM_KERNEL_RESIDENT) or per unit, each of the first launch or run. */
+int lbm_batch_kernel(lbm_ctx* ctx, int32_t n_steps, int32_t out[5]);
+
 /* The drag on the square (paper Section 2.1: the x-force the flow exerts on
    the obstacle; here by momentum exchange, see the conventions above) of steps
    t0 .. t1-1 of every member: copies drag columns [t0, t1) into out_dev

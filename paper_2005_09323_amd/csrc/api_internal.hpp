@@ -162,6 +162,7 @@ struct lbm_ctx {
     int total_blocks2 = 0;
     lbm::Segment seg2[lbm::MAX_SEGMENTS];
     BatchPlans plans;
+    int batch_kernel = LBM_KERNEL_ESTIMATED;  // lbm_set_batch_kernel
     RareScratch rare;
     // GKTL cloning by relabelling member blocks (1, the default) or by gathering
     // every copy into the other buffer (0); both give the same states

@@ -586,7 +586,7 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
             const int parts = (tallest + h - 2) / (h - 1);  // the fewest that are lower
             h = (tallest + parts - 1) / parts;
         }
-    bool chosen = false;  // row ranges given by the caller: sweep them
+    bool chosen = c->batch_kernel == LBM_KERNEL_SWEEP;  // or row ranges given by the caller: sweep them
     for (int r : c->run_rows) chosen = chosen || r >= 0;
     p.us = best;
     if (!chosen) {
@@ -619,8 +619,8 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     return true;
 }
 
-// Which kernel steps the next batch of n_steps with the adaptive shape:
-// resident launches (true), sweeps (`swept`) or neither, by the estimated
+// Which kernel steps the next batch of n_steps with the adaptive shape
+// (LBM_KERNEL_*): the one asked for (lbm_set_batch_kernel), or by the estimated
 // times.  us per step in long batches, resident launches and the others:
 // 1 x 256 x 64 2.1 and 6.8, 16 x 512 x 128 6.7 and 15.6, 64 x 512 x 128 26.5 and
 // 44, 20 x 1024 x 256 31.6 and 48.5, 32 x 1024 x 256 52.1 and 51.0, 256 x 512 x
@@ -629,11 +629,14 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
 // A resident launch also takes 8 us and a copy of the state to begin and end:
 // calls of one step 19.5 and 14.9, 37 and 24, of two 21 and 22, 43 and 41, of
 // four 26 and 38, 55 and 75 for the first two sizes.
-static bool plan_batch(const lbm_ctx* c, int n_steps, BatchPlans& p, bool& swept, bool every_member) {
+// resting: no resident launches now.
+static int plan_batch(const lbm_ctx* c, int n_steps, BatchPlans& p, bool every_member, bool resting) {
+    const int asked = c->batch_kernel;
+    if (asked == LBM_KERNEL_PLAIN) return LBM_KERNEL_PLAIN;
     if (!p.resident_known) p.resident_found = plan_resident(c, p.resident, every_member);
     p.resident_known = true;
     const ResidentPlan& resident = p.resident;
-    bool stays = p.resident_found;
+    bool stays = p.resident_found && !resting && asked != LBM_KERNEL_SWEEP;
     if (stays) {
         hipStreamCaptureStatus captured;  // a replay would not be known to the other contexts' launches
         if (hipStreamIsCapturing(c->stream, &captured) != hipSuccess) {
@@ -643,20 +646,19 @@ static bool plan_batch(const lbm_ctx* c, int n_steps, BatchPlans& p, bool& swept
             stays = false;
         }
     }
-    swept = false;
-    if (stays && resident.passes == 1 && n_steps >= 4) return true;
+    if (stays && ((resident.passes == 1 && n_steps >= 4) || asked == LBM_KERNEL_RESIDENT)) return LBM_KERNEL_RESIDENT;
     if (!p.sweep_known) p.sweep_found = plan_sweep(c, p.sweep, every_member);
     p.sweep_known = true;
-    swept = p.sweep_found;
-    bool chosen = false;  // row ranges given by the caller: sweep them
+    bool swept = p.sweep_found;
+    bool chosen = asked == LBM_KERNEL_SWEEP;  // or row ranges given by the caller: sweep them
     for (int r : c->run_rows) chosen = chosen || r >= 0;
     if (swept && n_steps < 4 && !chosen) swept = false;  // (64 x 512 x 128, calls of one step 93 and 66 us, of two 115 and 92)
-    if (!stays) return false;
-    const double other = c->open ? others_cost(c, resident.bytes / 72.0) : p.sweep.us;
-    const double start = n_steps < c->chunk ? 8.0 * resident.passes + resident.bytes / 5.2e6 : 0.0;  // (part of us, over a chunk)
-    if (start + resident.us * n_steps >= (swept ? 1.1 : 1.0) * other * n_steps) return false;
-    swept = false;
-    return true;
+    if (stays) {
+        const double other = c->open ? others_cost(c, resident.bytes / 72.0) : p.sweep.us;
+        const double start = n_steps < c->chunk ? 8.0 * resident.passes + resident.bytes / 5.2e6 : 0.0;  // (part of us, over a chunk)
+        if (start + resident.us * n_steps < (swept ? 1.1 : 1.0) * other * n_steps) return LBM_KERNEL_RESIDENT;
+    }
+    return swept ? LBM_KERNEL_SWEEP : LBM_KERNEL_PLAIN;
 }
 
 // The tables, the collision, the channel or the active members have changed.
@@ -967,9 +969,8 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
     }
     const int waves2 = TILE_SHAPES[c->tile_id].tyt;
     const bool two = two_step_now(c);
-    bool swept;
-    bool stays = plan_batch(c, n_steps, c->plans, swept, false);
     ResidentPlan& resident = c->plans.resident;
+    SweepPlan& sweep = c->plans.sweep;
     // A chunk was given up: something else keeps holding part of the device (another process, long
     // kernels of other streams), and a chunk stepped again costs several times a good one.
     if (c->gave_up && *(volatile int*)c->gave_up && c->wait_ticks >= 0) {
@@ -977,15 +978,12 @@ extern "C" int lbm_step_batch(lbm_ctx* c, int32_t n_steps) {
         c->resident_rest = RESIDENT_REST;
     }
     c->resident_first = c->resident_launch + 1;
-    const bool rests = stays && c->resident_rest > 0;
-    if (rests) --c->resident_rest;
-    if (stays && rests) {
-        stays = false;
-        if (!c->plans.sweep_known) c->plans.sweep_found = plan_sweep(c, c->plans.sweep, false);
-        c->plans.sweep_known = true;
-        swept = c->plans.sweep_found && n_steps >= 4;
+    int kernel = plan_batch(c, n_steps, c->plans, false, false);
+    if (kernel == LBM_KERNEL_RESIDENT && c->resident_rest > 0 && c->batch_kernel != LBM_KERNEL_RESIDENT) {
+        --c->resident_rest;
+        kernel = plan_batch(c, n_steps, c->plans, false, true);
     }
-    SweepPlan& sweep = c->plans.sweep;
+    const bool stays = kernel == LBM_KERNEL_RESIDENT, swept = kernel == LBM_KERNEL_SWEEP;
     a.active_list = nullptr;
     a2.active_list = nullptr;
     a.ghost = c->open ? c->d_ghost : nullptr;
@@ -1115,6 +1113,39 @@ void free_chunk_graph(lbm_ctx* c) {
     if (c->graph) hipGraphDestroy(c->graph);
     c->graph_exec = nullptr;
     c->graph = nullptr;
+}
+
+extern "C" int lbm_set_batch_kernel(lbm_ctx* c, int32_t kernel) {
+    if (!c) return lbm_fail(LBM_EINVAL, "NULL context");
+    if (kernel < LBM_KERNEL_ESTIMATED || kernel > LBM_KERNEL_RESIDENT) return lbm_fail(LBM_EINVAL, "kernel %d: -1 to 2", kernel);
+    c->batch_kernel = kernel;
+    forget_plans(c);
+    return LBM_OK;
+}
+
+extern "C" int lbm_batch_kernel(lbm_ctx* c, int32_t n_steps, int32_t* out) {
+    if (!c || !out) return lbm_fail(LBM_EINVAL, "NULL argument");
+    if (n_steps < 1) return lbm_fail(LBM_EINVAL, "n_steps must be >= 1");
+    const bool resting = c->resident_rest > 0 && c->batch_kernel != LBM_KERNEL_RESIDENT;
+    out[0] = plan_batch(c, n_steps, c->plans, false, resting);
+    if (out[0] == LBM_KERNEL_RESIDENT) {
+        const ResidentPlan& p = c->plans.resident;
+        out[1] = std::min(n_steps, c->chunk);
+        out[2] = p.passes;
+        out[3] = p.pass[0].cells;
+        out[4] = p.pass[0].rows;
+    } else if (out[0] == LBM_KERNEL_SWEEP) {
+        out[1] = c->plans.sweep.steps;
+        out[2] = 1;
+        out[3] = SWEEP_CELLS;
+        out[4] = c->plans.sweep.args.seg[0].rows;
+    } else {
+        out[1] = two_step_now(c) ? 2 : 1;
+        out[2] = 1;
+        out[3] = out[1] == 2 || c->seg[0].vec ? 4 : 1;
+        out[4] = out[1] == 2 ? c->seg2[0].rows : TILE_SHAPES[c->one_tile].r;
+    }
+    return LBM_OK;
 }
 
 extern "C" int lbm_set_graphs(lbm_ctx* c, int32_t on) {
@@ -1370,9 +1401,9 @@ extern "C" int lbm_autotune(lbm_ctx* c, int32_t n_steps, int32_t* best_tile) {
         BatchPlans plans;
         ResidentPlan& resident = plans.resident;
         SweepPlan& sweep = plans.sweep;
-        bool swept = false;
-        const bool stays = ts.adaptive && plan_batch(c, c->chunk, plans, swept, true);
-        if (ts.adaptive && !stays && !swept) return LBM_OK;
+        const int kernel = ts.adaptive ? plan_batch(c, c->chunk, plans, true, false) : LBM_KERNEL_PLAIN;
+        const bool stays = kernel == LBM_KERNEL_RESIDENT;
+        if (ts.adaptive && kernel == LBM_KERNEL_PLAIN) return LBM_OK;
         const bool two = ts.steps == 2;
         a.total_blocks = two ? c->total_blocks2 : c->total_blocks;
         a.split = two && c->split2 ? 1 : 0;

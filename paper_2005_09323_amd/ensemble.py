@@ -37,6 +37,8 @@ class MemberSpec:
 
 
 CHECKPOINT_VERSION = 1
+# the kernels of the default shape (LBM_KERNEL_PLAIN, LBM_KERNEL_SWEEP, LBM_KERNEL_RESIDENT)
+KERNELS = ("plain", "sweep", "resident")
 
 
 class Ensemble:
@@ -157,6 +159,19 @@ class Ensemble:
         n = ctypes.c_int32()
         native.check(self.lib.lbm_launch_steps(self._ctx, ctypes.byref(n)))
         return n.value
+
+    def batch_kernel(self, n_steps: int) -> dict:
+        """What steps the next batch of n_steps: the kernel ('plain': one or two steps per launch, 'sweep' or
+        'resident'), the steps of a full launch, the launches that share the members, and of the first of
+        them the columns per lane and the rows per wave or unit."""
+        out = (ctypes.c_int32 * 5)()
+        native.check(self.lib.lbm_batch_kernel(self._ctx, n_steps, out))
+        return dict(kernel=KERNELS[out[0]], steps=out[1], launches=out[2], columns=out[3], rows=out[4])
+
+    def set_batch_kernel(self, kernel: Optional[str]) -> None:
+        """Ask for one of the default shape's kernels wherever it can step the ensemble (measurements and
+        tests; None: by estimated times).  Same results."""
+        native.check(self.lib.lbm_set_batch_kernel(self._ctx, -1 if kernel is None else KERNELS.index(kernel)))
 
     def autotune(self, n_steps: int = 20, table: Optional[str] = None) -> int:
         """Time every launch shape and keep the fastest; with `table`, reuse or extend a persisted table."""

@@ -68,6 +68,8 @@ _SIG = {
     "lbm_set_open_channel": (ctypes.c_int, [_P, _P]),
     "lbm_set_graphs": (ctypes.c_int, [_P, _I]),
     "lbm_set_wait_limit": (ctypes.c_int, [_P, _I]),
+    "lbm_set_batch_kernel": (ctypes.c_int, [_P, _I]),
+    "lbm_batch_kernel": (ctypes.c_int, [_P, _I, _P]),
     "lbm_autotune": (ctypes.c_int, [_P, _I, ctypes.POINTER(_I)]),
     "lbm_autotune_cached": (ctypes.c_int, [_P, _I, ctypes.c_char_p, ctypes.POINTER(_I)]),
     "lbm_run_count": (ctypes.c_int, [_P, ctypes.POINTER(_I)]),
