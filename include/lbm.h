@@ -326,10 +326,10 @@ int lbm_set_open_channel(lbm_ctx* ctx, const lbm_open_channel* oc);
  * rows (the rows next to a cut are collided by both neighbours).  Shape 20,
  * the default, steps channels of up to 1024 columns (any width) with the
  * populations in registers for a whole chunk of steps (lbm_step_batch) where
- * the active members fit in a few such launches, and periodic ones with the
- * sweep kernel (up to four steps per launch, the steps in between held in registers)
- * where they are many enough for it to be the faster, or whenever row ranges
- * are given (lbm_set_run_rows).  Otherwise it
+ * the active members fit in a few such launches (and no row ranges are given:
+ * lbm_set_run_rows), and periodic ones with the sweep kernel (up to four steps
+ * per launch, the steps in between held in registers) where they are many
+ * enough for it to be the faster, with the row ranges given too.  Otherwise it
  * makes two steps per launch with whole strips when there are
  * at least two per compute unit and with strips cut into the tallest row
  * ranges that give four workgroups per compute unit otherwise (32 rows at

@@ -245,7 +245,7 @@ static double resident_cost(const ResidentCut& cut, bool two, bool open, double 
 static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) {
     if (!TILE_SHAPES[c->tile_id].adaptive) return false;
     for (int r : c->run_rows)
-        if (r >= 0) return false;  // row ranges given by the caller: the sweep's
+        if (r >= 0) return false;  // row ranges given by the caller: for the kernels that have such
     const bool listed = !every_member && c->n_active < c->n && c->uniform_shape;
     double cells = 0.0;
     int widest = 0;
@@ -518,7 +518,11 @@ static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int steps, int ro
         bytes += (double)members[s] * d.nx * (72.0 * d.ny + 72.0 * (steps - 1) * (ranges - 1));
     }
     const double rounds = c->nseg == 1 ? std::ceil(blocks / slots) * longest : std::max(longest, load / slots + 0.5 * longest);
-    const double fill = std::min(1.0, blocks / slots);
+    // (five waves and more share their SIMDs however few the workgroups: 128 x 1024 x 256 in whole strips 1175 us per
+    // launch.  Only ranges given by the caller leave workgroups that wide so few: the others are chosen to fill the device.)
+    bool given = false;
+    for (int r : c->run_rows) given = given || r >= 0;
+    const double fill = given && p.args.block_waves > 4 ? 1.0 : std::min(1.0, blocks / slots);
     const double iteration = (1.2 + 0.8 * steps) * (fill > 0.5 ? 0.2 + 0.8 * fill : 0.6);
     return std::max(rounds * iteration, bytes / 4.8e6) * (1.0 + 0.03 * std::max(0, 32 - rows)) + 4.0;
 }
@@ -586,10 +590,8 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
             const int parts = (tallest + h - 2) / (h - 1);  // the fewest that are lower
             h = (tallest + parts - 1) / parts;
         }
-    bool chosen = c->batch_kernel == LBM_KERNEL_SWEEP;  // or row ranges given by the caller: sweep them
-    for (int r : c->run_rows) chosen = chosen || r >= 0;
     p.us = best;
-    if (!chosen) {
+    if (c->batch_kernel != LBM_KERNEL_SWEEP) {
         const double other = others_cost(c, cells);
         p.us = std::min(best, other);
         if (cells < 3e6) p.us = other;
@@ -650,9 +652,7 @@ static int plan_batch(const lbm_ctx* c, int n_steps, BatchPlans& p, bool every_m
     if (!p.sweep_known) p.sweep_found = plan_sweep(c, p.sweep, every_member);
     p.sweep_known = true;
     bool swept = p.sweep_found;
-    bool chosen = asked == LBM_KERNEL_SWEEP;  // or row ranges given by the caller: sweep them
-    for (int r : c->run_rows) chosen = chosen || r >= 0;
-    if (swept && n_steps < 4 && !chosen) swept = false;  // (64 x 512 x 128, calls of one step 93 and 66 us, of two 115 and 92)
+    if (swept && n_steps < 4 && asked != LBM_KERNEL_SWEEP) swept = false;  // (64 x 512 x 128, calls of one step 93 and 66 us, of two 115 and 92)
     if (stays) {
         const double other = c->open ? others_cost(c, resident.bytes / 72.0) : p.sweep.us;
         const double start = n_steps < c->chunk ? 8.0 * resident.passes + resident.bytes / 5.2e6 : 0.0;  // (part of us, over a chunk)

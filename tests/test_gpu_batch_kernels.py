@@ -149,3 +149,21 @@ def test_a_kernel_that_cannot_step_the_ensemble_is_passed_over():
             assert ens.batch_kernel(13)["kernel"] == ("resident" if can else "plain"), asked
             assert ens.lib.lbm_batch_kernel(ens._ctx, 0, None) == native.LBM_EINVAL
             ens.close()
+
+
+@pytest.mark.parametrize("members,rows,swept", [
+    ([_m(256, 64, (124, 20, 9))], 32, False),                # 64 steps: 429 us with one step per launch, 1752 swept
+    ([_m(1024, 256, (500, 100, 32))] * 8, 64, False),        # 1869 and 5273
+    ([_m(512, 128, (250, 60, 9))] * 64, 128, False),         # 3667 and 6209
+    ([_m(1024, 256, (500, 100, 32))] * 128, 0, False),       # two steps per launch 15 852, swept 18 805
+    ([_m(512, 128, (250, 60, 9))] * 64, 32, True),           # 2642 and 2135
+    ([_m(1024, 256, (500, 100, 32))] * 128, 64, True),       # 16 818 and 11 373
+])
+def test_row_ranges_do_not_force_the_sweep(members, rows, swept):
+    """Row ranges given by the caller are the two-step strips' and the sweep's; the faster of these steps the
+    batch, and the sweep never steps batches of one to three."""
+    ens = _ensemble(members, 20)
+    ens.set_run_rows([rows])
+    assert ens.batch_kernel(64)["kernel"] == ("sweep" if swept else "plain")
+    assert [ens.batch_kernel(n)["kernel"] for n in (1, 2, 3)] == ["plain"] * 3
+    ens.close()

@@ -1,4 +1,4 @@
-"""The sweep kernel (the default shape with row ranges given) against the one-step shape 0 where a
+"""The sweep kernel against the one-step shape 0 where a
 width gives a wave fewer than 64 lanes and the square lies over the seam between two waves.
 
 The lanes of a wave beyond its columns run over the next wave's; what they work out there is wrong in
@@ -38,7 +38,9 @@ def _run(members, tile, rows, collision):
     if collision is not None:
         ens.set_collision("central", *collision)
     if rows is not None:
+        ens.set_batch_kernel("sweep")
         ens.set_run_rows([rows] * ens.run_count())
+        assert ens.batch_kernel(13)["kernel"] == "sweep"
     ens.init(7, 1e-2)
     ens.step(13)                      # 4 + 4 + 4 + 1
     ens.step(66)                      # a captured chunk, then 2
