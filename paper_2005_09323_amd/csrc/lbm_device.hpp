@@ -312,7 +312,22 @@ __device__ __forceinline__ void sponge_at(MemberDev& m, int x) {
     om = om * (2.0 - tau * om);
     om = om * (2.0 - tau * om);
     m.omega = om;
-    bgk_coefficients(m);
+}
+
+// The member as column x of an open channel collides (sponge: the column may lie in the sponge).  BGK: the
+// coefficients are formed from the lane's rate in each cell, and the rate is kept out of the compiler's sight.  As
+// values that only the sponge's columns change they are kept through a row's cells, which spilled 59 registers of the
+// two-step kernel (16 steps of 512 x 512 x 128 7.16 ms, 5.03 so, 4.89 while the update had four coefficients); formed
+// once per row they take 5.04, read from the member outside the sponge 5.07.
+template <int MODEL>
+__device__ __forceinline__ MemberDev at_column(const MemberDev& m, int x, bool sponge) {
+    MemberDev mc = m;
+    if (sponge) sponge_at(mc, x);
+    if constexpr (MODEL == 0) {
+        __asm__ volatile("" : "+v"(mc.omega));
+        bgk_coefficients(mc);
+    }
+    return mc;
 }
 
 // Open channel inlet: the ghost column x = -1 holds the equilibrium of

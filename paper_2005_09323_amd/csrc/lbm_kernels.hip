@@ -41,9 +41,7 @@ __device__ __forceinline__ void scalar_cell(const MemberDev& m, const float* __r
     const unsigned links = ri >= 0 ? square_links(m, x, y) : 0u;
     double drag;
     if (OPEN) {
-        MemberDev mc = m;
-        sponge_at(mc, x);
-        drag = collide_cell<MODEL, true>(mc, dl, links, ri >= 0);
+        drag = collide_cell<MODEL, true>(at_column<MODEL>(m, x, true), dl, links, ri >= 0);
     } else {
         drag = collide_cell<MODEL, true>(m, dl, links, ri >= 0);
     }
@@ -168,9 +166,7 @@ __device__ __forceinline__ void vec_row(const MemberDev& m, const float* __restr
         const unsigned links = ri >= 0 ? square_links(m, x0 + k, y) : 0u;
         double drag;
         if (OPEN) {
-            MemberDev mc = m;
-            if (sponge_wave) sponge_at(mc, x0 + k);
-            drag = collide_cell<MODEL, true>(mc, dl, links, near_sq);
+            drag = collide_cell<MODEL, true>(at_column<MODEL>(m, x0 + k, sponge_wave), dl, links, near_sq);
         } else {
             drag = collide_cell<MODEL, true>(m, dl, links, near_sq);
         }
@@ -332,7 +328,10 @@ __global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
     }
     const int ri = ring_index(m, x, y);
     MemberDev mc = m;
-    if (m.open) sponge_at(mc, x);
+    if (m.open) {
+        sponge_at(mc, x);
+        bgk_coefficients(mc);
+    }
     const double drag = collide_member(mc, d, ri >= 0 ? square_links(m, x, y) : 0u);
     float* dst = a.pop0 + m.off;  // step 0 lives in buffer 0 (parity 0)
 #pragma unroll

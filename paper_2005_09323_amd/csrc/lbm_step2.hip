@@ -106,9 +106,7 @@ __device__ __forceinline__ void collide_row(const MemberDev& m, f4 p[9], double*
         const unsigned links = ri >= 0 ? square_links(m, x0 + k, y) : 0u;
         double drag;
         if (OPEN) {
-            MemberDev mc = m;
-            if (sponge) sponge_at(mc, x0 + k);
-            drag = collide_cell<MODEL>(mc, dl, links, near_sq);
+            drag = collide_cell<MODEL, true>(at_column<MODEL>(m, x0 + k, sponge), dl, links, near_sq);
         } else {
             drag = collide_cell<MODEL>(m, dl, links, near_sq);
         }
@@ -363,9 +361,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             // the outside cells (their drag belongs to the neighbouring strip)
             if (own_h) {
                 if (OPEN) {
-                    MemberDev mc = m;
-                    if (sponge || base + 256 > m.sp_x0) sponge_at(mc, xh);
-                    collide_cell<MODEL>(mc, hv, 0u, false);
+                    collide_cell<MODEL, true>(at_column<MODEL>(m, xh, sponge || base + 256 > m.sp_x0), hv, 0u, false);
                 } else {
                     collide_cell<MODEL>(m, hv, 0u, false);
                 }
