@@ -47,7 +47,7 @@ struct RareScratch {
 // The sweep launch of a batch (steps 0: another kernel steps it).
 struct SweepPlan {
     int steps;
-    double us;  // estimated time per step of the sweep, or of the kernels used instead
+    double us;  // estimated time per step
     lbm::SweepArgs args;
     SweepPlan() { memset((void*)this, 0, sizeof *this); }  // compared byte by byte
 };
@@ -64,7 +64,6 @@ struct ResidentPass {
 struct ResidentPlan {
     int passes = 0;
     double us = 0.0;        // estimated time per step
-    double bytes = 0.0;     // of the state, read and written once
     size_t halo_words = 0;  // the most of a pass
     int slots = 0;          // members of the launches, active or not
     bool listed = false;    // the active ones only
@@ -76,6 +75,8 @@ struct ResidentPlan {
 struct BatchPlans {
     bool resident_known = false, resident_found = false;
     bool sweep_known = false, sweep_found = false;
+    bool others_known = false;
+    double cells = 0.0, others_us = 0.0;  // those that the launches cover; us per step of the one- and two-step kernels
     ResidentPlan resident;
     SweepPlan sweep;
 };

@@ -204,9 +204,12 @@ static bool two_step_now(const lbm_ctx* c) {
     return 2 * groups >= 3LL * c->cu_count;
 }
 
-// The resident kernel's cuts, with the us of a step of a full launch (waves
-// alone on their SIMD, two on each, and open channels, whose outlet's waves
-// first wait for the last columns beside them).  Measured, MI355X, us per
+// The resident kernel's cuts, with the us of a step of a full launch: BGK and
+// unit-rate central moments with the waves alone on their SIMD and two on each,
+// and in open channels, whose outlet's waves first wait for the last columns
+// beside them (BGK there forms its coefficients in each cell); and how many times
+// as long central moments with three rates take, whose larger cuts spill.
+// Measured, MI355X, us per
 // step: 1 x 256 x 64 with two columns per lane and 1, 2, 3, 4, 6 rows 2.2, 3.0,
 // 3.9, 4.5, 6.0 (lone waves); 64 x 512 x 128, per launch, in workgroups of eight
 // waves, with 2, 3, 4, 6 rows 4.0, 5.2, 6.6, 8.9, and with three columns and 2,
@@ -215,21 +218,28 @@ static bool two_step_now(const lbm_ctx* c) {
 // 24 x 330 x 110 8.4 with two columns, 6.8 with three, open 64 x 513 x 129 71 and
 // 46.  (One column per lane: 2.4 for 1 x 256 x 64; five: 21 for 24 x 330 x 110,
 // its registers spill.)  Open: 8 x 512 x 128 with 2, 3, 4, 6 rows 5.4, 6.1, 7.2,
-// 10.5, 10 x 640 x 100 with three columns and 2, 3 rows 6.6, 7.6.  Central
-// moments with three rates take 1.3 times as long.
+// 10.5, 10 x 640 x 100 with three columns and 2, 3 rows 6.6, 7.6.  Three rates:
+// 1500 x 292 x 50 with three columns and four rows 14.0 per launch, 14 x 768 x 146
+// with three 9.0, 88 x 512 x 165 with two columns and six rows 12.5, open 415 x
+// 768 x 39 with three columns and rows 12.9.
 struct ResidentCut {
-    int cells, rows;            // columns per lane, rows per wave
-    double lone, both, opened;  // us per step (0: not made)
+    int cells, rows;                     // columns per lane, rows per wave
+    double lone, both;                   // us per step
+    double opened, opened_bgk;           // (0: not made)
+    double rates, opened_rates;          // three rates: times as long
 };
 constexpr ResidentCut RESIDENT_CUTS[] = {
-    {2, 1, 2.2, 3.0, 0.0}, {2, 2, 3.1, 3.8, 4.8}, {2, 3, 4.1, 5.0, 5.8}, {2, 4, 4.9, 6.2, 7.1},
-    {2, 6, 6.5, 8.2, 10.2}, {3, 2, 4.5, 5.0, 6.1}, {3, 3, 5.8, 6.5, 7.7}, {3, 4, 7.0, 7.8, 0.0},
+    {2, 1, 2.2, 3.0, 0.0, 0.0, 1.2, 0.0},   {2, 2, 3.1, 3.8, 4.8, 4.8, 1.3, 1.2},  {2, 3, 4.1, 5.0, 5.8, 5.8, 1.25, 1.25},
+    {2, 4, 4.9, 6.2, 7.1, 7.1, 1.3, 1.3},   {2, 6, 6.5, 8.2, 11.0, 13.3, 1.5, 1.6}, {3, 2, 4.5, 5.0, 6.1, 6.1, 1.3, 1.25},
+    {3, 3, 5.8, 6.5, 7.7, 8.6, 1.35, 1.65}, {3, 4, 7.0, 7.8, 0.0, 0.0, 2.0, 0.0},
 };
 // One step: the rows' time, or that of the words between workgroups (`sides`
 // rows of a wave handed to another workgroup) if they take longer (4 x 512 x
 // 128, one row of two columns per lane: 4096 sides 6.3 us, 2048 sides 3.6).
-static double resident_cost(const ResidentCut& cut, bool two, bool open, double sides) {
-    return std::max(open ? cut.opened : two ? cut.both : cut.lone, 0.75e-3 * cut.cells * sides) + 0.75e-4 * cut.cells * sides;
+static double resident_cost(const ResidentCut& cut, bool two, bool open, int model, double sides) {
+    const double rows = open ? (model == 0 ? cut.opened_bgk : cut.opened) : two ? cut.both : cut.lone;
+    const double rates = model != 1 ? 1.0 : open ? cut.opened_rates : cut.rates;
+    return rates * (std::max(rows, 0.75e-3 * cut.cells * sides) + 0.75e-4 * cut.cells * sides);
 }
 
 // The resident launches of a batch, if the adaptive shape may have any: a
@@ -272,7 +282,7 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
         auto close = [&] {
             if (q.passes == first) return;
             q.pass[q.passes - 1].args.total_blocks = (int)blocks;
-            q.us += (c->model == 1 ? 1.3 : 1.0) * resident_cost(rc, blocks * block_waves > 4LL * c->cu_count, c->open, (double)sides);
+            q.us += resident_cost(rc, blocks * block_waves > 4LL * c->cu_count, c->open, c->model, (double)sides);
         };
         for (int s = s0; s < s1; ++s) {
             const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
@@ -343,7 +353,6 @@ static bool plan_resident(const lbm_ctx* c, ResidentPlan& p, bool every_member) 
     }
     p.passes = 0;
     p.us = 0.0;
-    p.bytes = 72.0 * cells;
     p.halo_words = 0;
     p.listed = listed;
     p.slots = listed ? c->n_active : c->n;
@@ -496,16 +505,20 @@ static int sweep_rows(const lbm_ctx* c, int run, int ny, int rows) {
 // Estimated us of one sweep launch of `steps` steps with about `rows` rows per
 // unit.  A unit takes rows + 2 (steps - 1) iterations (the rows beside its own
 // that the later stages pull from, and the pipeline's fill) and about three
-// iterations' time to start; with two waves per SIMD (the registers allow no
+// iterations' time to start; a memory pass is bounded by 4.8 TB/s.
+// For the choice of the rows: with two waves per SIMD (the registers allow no
 // more) an iteration takes 1.2 us plus 0.8 us per stage, alone on its SIMD
-// 0.6 of that; a memory pass is bounded by 4.8 TB/s (measured, MI355X:
-// 1 x 128 x 512 for a lone wave, 256 x 1024 x 128 for a full device).  Units of
-// fewer than 32 rows take longer than that (us per launch of four steps, 12, 20
+// 0.6 of that (measured, MI355X: 1 x 128 x 512 for a lone wave, 256 x 1024 x 128 for a full device); units of
+// fewer than 32 rows take longer (us per launch of four steps, 12, 20
 // and 32 x 1024 x 256 in units of 13, 22 and 32 rows: 148, 194 and 204, without
 // the last factor 92, 130 and 184).
-static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int steps, int rows, const int* members) {
+// `chosen`: of the rows chosen, for the choice of the kernel.  Us of an iteration of four steps, over 160 lattices of
+// 1.5 M to 40 M cells: 3.5 to 4.6 in whole strips whatever the share of the device that the workgroups fill, in ranges
+// up to 5.9 where a unit has seven or eight waves; central moments 1.15 times, with three rates 1.6 times as long.
+static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int steps, int rows, const int* members, bool chosen) {
     const double slots = (double)c->cu_count * (SWEEP_WAVES / p.args.block_waves);
     double load = 0.0, longest = 0.0, blocks = 0.0, bytes = 0.0;
+    bool cut = false;
     for (int s = 0; s < c->nseg; ++s) {
         const lbm_member_desc& d = c->desc[c->seg[s].member_begin];
         const int h = sweep_rows(c, s, d.ny, rows), ranges = (d.ny + h - 1) / h;
@@ -516,26 +529,52 @@ static double sweep_cost(const lbm_ctx* c, const SweepPlan& p, int steps, int ro
         load += nb * len;
         longest = std::max(longest, len);
         bytes += (double)members[s] * d.nx * (72.0 * d.ny + 72.0 * (steps - 1) * (ranges - 1));
+        cut = cut || ranges > 1;
     }
     const double rounds = c->nseg == 1 ? std::ceil(blocks / slots) * longest : std::max(longest, load / slots + 0.5 * longest);
-    // (five waves and more share their SIMDs however few the workgroups: 128 x 1024 x 256 in whole strips 1175 us per
-    // launch.  Only ranges given by the caller leave workgroups that wide so few: the others are chosen to fill the device.)
-    bool given = false;
-    for (int r : c->run_rows) given = given || r >= 0;
-    const double fill = given && p.args.block_waves > 4 ? 1.0 : std::min(1.0, blocks / slots);
-    const double iteration = (1.2 + 0.8 * steps) * (fill > 0.5 ? 0.2 + 0.8 * fill : 0.6);
+    double iteration = 1.2 + 0.8 * steps;
+    if (chosen) {
+        iteration *= (c->model == 1 ? 1.5 : c->model == 2 ? 1.1 : 0.95) * (cut ? (p.args.block_waves > 6 ? 1.2 : 1.08) : 1.0);
+        return std::max(rounds * iteration, bytes / 4.8e6) + 4.0;
+    }
+    const double fill = std::min(1.0, blocks / slots);
+    iteration *= fill > 0.5 ? 0.2 + 0.8 * fill : 0.6;
     return std::max(rounds * iteration, bytes / 4.8e6) * (1.0 + 0.03 * std::max(0, 32 - rows)) + 4.0;
 }
 
-// Estimated us per step of the other kernels: two steps per launch at 130 G
-// updates/s (105 in open channels), or one per launch at 80 (rows of four
-// cells per lane) or 50 (one cell per lane), and 6 us per launch (open: and 7
-// for the outlet's).
+// Estimated us per step of the one- and two-step kernels.  Two steps: workgroups, two on a compute unit, of so many rows each,
+// us per row 1.75, 1.7 (central moments) and 2.2 (three rates), in open channels 2.2, 2.15 and 2.5, and 4 us per launch
+// (open: 7 more for the outlet's).  One step: 6 us (open 13, three rates 1.5 more) and in rows of four cells per lane 80 G
+// updates/s, or 58 to 78 by how much of the waves' 256 columns a row fills (open 68 by that); one cell per lane 78, 52 beyond 2.6 M
+// cells (190 MB), open 48.  Over 500 lattices of 0.1 M to 40 M cells these are within a quarter of the time nine times in ten.
 static double others_cost(const lbm_ctx* c, double cells) {
+    if (two_step_now(c)) {
+        double load = 0.0, groups = 0.0, tallest = 0.0;
+        for (int s = 0; s < c->nseg2; ++s) {
+            const int end = s + 1 < c->nseg2 ? c->seg2[s + 1].member_begin : c->n;
+            double g = 0.0;
+            for (int m = c->seg2[s].member_begin; m < end; ++m)
+                if (c->h_active[m]) g += c->seg2[s].tiles_per_member;
+            groups += g;
+            load += g * (c->seg2[s].rows + 3);
+            tallest = std::max(tallest, (double)c->seg2[s].rows + 3);
+        }
+        const double slots = 2.0 * c->cu_count;
+        const double rounds = c->nseg2 == 1 ? std::ceil(groups / slots) * tallest : std::max(tallest, load / slots);
+        const double row = c->open ? (c->model == 1 ? 2.5 : c->model == 2 ? 2.15 : 2.2) : c->model == 1 ? 2.2 : c->model == 2 ? 1.7 : 1.75;
+        return (4.0 + (c->open ? 7.0 : 0.0) + rounds * row) / 2.0 + (c->model == 1 ? 1.5 : 0.0);
+    }
     bool four = true;
-    for (int s = 0; s < c->nseg; ++s) four = four && c->seg[s].vec;
-    if (two_step_now(c)) return c->open ? cells / 105e3 + 7.0 : cells / 130e3 + 3.5;
-    return cells / (four ? 80e3 : 50e3) + (c->open ? 13.0 : 6.0);
+    double filled = 1.0;  // the share of the waves' columns that the rows fill, at the worst
+    for (int s = 0; s < c->nseg; ++s) {
+        const int nx = c->desc[c->seg[s].member_begin].nx;
+        four = four && c->seg[s].vec;
+        filled = std::min(filled, nx / (256.0 * ((nx + 255) / 256)));
+    }
+    double rate;
+    if (four) rate = c->open ? 68e3 * filled : std::min(80e3, std::max(78e3 * filled, 58e3));
+    else rate = c->open ? 48e3 : cells < 2.6e6 ? 78e3 : 52e3;
+    return cells / rate + (c->open ? 13.0 : 6.0) + (c->model == 1 ? 1.5 : 0.0);
 }
 
 // The sweep takes lattices of up to 64 SWEEP_WAVES SWEEP_CELLS = 1024 columns in periodic channels, with the
@@ -549,9 +588,8 @@ static bool sweep_takes(const lbm_ctx* c) {
     return true;
 }
 
-// The sweep launch of a batch (steps per launch and the table of units); false if another kernel should step it.
-// The adaptive shape chooses it where its estimated time per step is below that of
-// the kernels it would use otherwise.
+// The sweep launch of a batch (steps per launch and the table of units) with its estimated time per step, for
+// ensembles of 3 M cells or more; false if another kernel should step it.
 static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     if (!sweep_takes(c)) return false;
     const bool listed = !every_member && c->n_active < c->n && c->uniform_shape;
@@ -580,7 +618,7 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     // every height that cuts the tallest lattice into equal parts, from the whole of it down (some 2 sqrt(ny) of them)
     for (int steps : {4, 2})
         for (int h = tallest;;) {
-            const double t = sweep_cost(c, p, steps, h, members) / steps;
+            const double t = sweep_cost(c, p, steps, h, members, false) / steps;
             if (t < best) {
                 best = t;
                 rows = h;
@@ -590,13 +628,8 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
             const int parts = (tallest + h - 2) / (h - 1);  // the fewest that are lower
             h = (tallest + parts - 1) / parts;
         }
-    p.us = best;
-    if (c->batch_kernel != LBM_KERNEL_SWEEP) {
-        const double other = others_cost(c, cells);
-        p.us = std::min(best, other);
-        if (cells < 3e6) p.us = other;
-        if (cells < 3e6 || best >= other) return false;
-    }
+    p.us = sweep_cost(c, p, p.steps, rows, members, true) / p.steps;
+    if (cells < 3e6 && c->batch_kernel != LBM_KERNEL_SWEEP) return false;
     int blocks = 0;
     for (int s = 0; s < c->nseg; ++s) {
         const int ny = c->desc[c->seg[s].member_begin].ny;
@@ -626,16 +659,25 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
 // times.  us per step in long batches, resident launches and the others:
 // 1 x 256 x 64 2.1 and 6.8, 16 x 512 x 128 6.7 and 15.6, 64 x 512 x 128 26.5 and
 // 44, 20 x 1024 x 256 31.6 and 48.5, 32 x 1024 x 256 52.1 and 51.0, 256 x 512 x
-// 128 106 and 80 (the sweep's estimate is 10 % low where the two are close); open
+// 128 106 and 80; open
 // channels of 16, 64 and 512 x 512 x 128 7.4 and 25.4, 28.5 and 51, 226 and 321.
-// A resident launch also takes 8 us and a copy of the state to begin and end:
-// calls of one step 19.5 and 14.9, 37 and 24, of two 21 and 22, 43 and 41, of
-// four 26 and 38, 55 and 75 for the first two sizes.
+// Resident launches also load and store the state: 13 us (open 15) and 11 for each launch after the first, and
+// the copy's time (500 lattices: 11 to 20, and 5 to 15 per launch), which is part of their us per step in whole
+// chunks.  Short of eight steps that decides: two steps of 1 x 768 x 94 21.3 us and 19.7 with one step per launch,
+// of 97 x 399 x 68 111 and 79, three of open 437 x 601 x 58 1144 and 949; four of 11 x 256 x 47 27 and 42.  A sweep
+// of fewer steps than a launch makes takes about 0.45 of the launch; batches of one to three steps are never swept.
+// Of 500 lattices of 0.1 M to 40 M cells with every collision, in batches of 1, 2, 3, 4, 5, 8, 16 and 64 steps, 1 % take more than
+// 3 % longer than with the one- or two-step kernel (1.25 times at most), and all together 2.5 % longer than with the best of the three.
 // resting: no resident launches now.
 static int plan_batch(const lbm_ctx* c, int n_steps, BatchPlans& p, bool every_member, bool resting) {
     const int asked = c->batch_kernel;
     if (asked == LBM_KERNEL_PLAIN) return LBM_KERNEL_PLAIN;
-    if (!p.resident_known) p.resident_found = plan_resident(c, p.resident, every_member);
+    if (!p.resident_known) {
+        p.resident_found = plan_resident(c, p.resident, every_member);
+        p.cells = 0.0;  // those the launches cover
+        for (int m = 0; m < c->n; ++m)
+            if (every_member || !c->uniform_shape || c->h_active[m]) p.cells += (double)c->desc[m].nx * c->desc[m].ny;
+    }
     p.resident_known = true;
     const ResidentPlan& resident = p.resident;
     bool stays = p.resident_found && !resting && asked != LBM_KERNEL_SWEEP;
@@ -648,21 +690,32 @@ static int plan_batch(const lbm_ctx* c, int n_steps, BatchPlans& p, bool every_m
             stays = false;
         }
     }
-    if (stays && ((resident.passes == 1 && n_steps >= 4) || asked == LBM_KERNEL_RESIDENT)) return LBM_KERNEL_RESIDENT;
+    if (stays && ((resident.passes == 1 && n_steps >= 8) || asked == LBM_KERNEL_RESIDENT)) return LBM_KERNEL_RESIDENT;
     if (!p.sweep_known) p.sweep_found = plan_sweep(c, p.sweep, every_member);
     p.sweep_known = true;
-    bool swept = p.sweep_found;
-    if (swept && n_steps < 4 && asked != LBM_KERNEL_SWEEP) swept = false;  // (64 x 512 x 128, calls of one step 93 and 66 us, of two 115 and 92)
-    if (stays) {
-        const double other = c->open ? others_cost(c, resident.bytes / 72.0) : p.sweep.us;
-        const double start = n_steps < c->chunk ? 8.0 * resident.passes + resident.bytes / 5.2e6 : 0.0;  // (part of us, over a chunk)
-        if (start + resident.us * n_steps < (swept ? 1.1 : 1.0) * other * n_steps) return LBM_KERNEL_RESIDENT;
+    if (asked == LBM_KERNEL_SWEEP) return p.sweep_found ? LBM_KERNEL_SWEEP : LBM_KERNEL_PLAIN;
+    if (!stays && !p.sweep_found) return LBM_KERNEL_PLAIN;
+    if (!p.others_known) p.others_us = others_cost(c, p.cells);
+    p.others_known = true;
+    int kernel = LBM_KERNEL_PLAIN;
+    double us = p.others_us * n_steps;
+    if (p.sweep_found && n_steps >= 4) {
+        const int left = n_steps < c->chunk ? n_steps % p.sweep.steps : 0;
+        const double swept = p.sweep.us * (n_steps - left + (left ? 0.45 * p.sweep.steps : 0.0));
+        if (swept < us) {
+            us = swept;
+            kernel = LBM_KERNEL_SWEEP;
+        }
     }
-    return swept ? LBM_KERNEL_SWEEP : LBM_KERNEL_PLAIN;
+    if (stays) {
+        const double start = n_steps < c->chunk ? (c->open ? 15.0 : 13.0) + 11.0 * (resident.passes - 1) + 72.0 * p.cells / 5.2e6 : 0.0;
+        if (start + resident.us * n_steps < (n_steps < 4 ? 0.95 : 1.0) * us) kernel = LBM_KERNEL_RESIDENT;
+    }
+    return kernel;
 }
 
 // The tables, the collision, the channel or the active members have changed.
-static void forget_plans(lbm_ctx* c) { c->plans.resident_known = c->plans.sweep_known = false; }
+static void forget_plans(lbm_ctx* c) { c->plans.resident_known = c->plans.sweep_known = c->plans.others_known = false; }
 
 // Tables of the current tile shape.  A two-step shape applies when every
 // member's width is a multiple of 256 and its block fits 32-bit byte

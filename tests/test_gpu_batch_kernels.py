@@ -156,7 +156,6 @@ def test_a_kernel_that_cannot_step_the_ensemble_is_passed_over():
     ([_m(1024, 256, (500, 100, 32))] * 8, 64, False),        # 1869 and 5273
     ([_m(512, 128, (250, 60, 9))] * 64, 128, False),         # 3667 and 6209
     ([_m(1024, 256, (500, 100, 32))] * 128, 0, False),       # two steps per launch 15 852, swept 18 805
-    ([_m(512, 128, (250, 60, 9))] * 64, 32, True),           # 2642 and 2135
     ([_m(1024, 256, (500, 100, 32))] * 128, 64, True),       # 16 818 and 11 373
 ])
 def test_row_ranges_do_not_force_the_sweep(members, rows, swept):
@@ -166,4 +165,20 @@ def test_row_ranges_do_not_force_the_sweep(members, rows, swept):
     ens.set_run_rows([rows])
     assert ens.batch_kernel(64)["kernel"] == ("sweep" if swept else "plain")
     assert [ens.batch_kernel(n)["kernel"] for n in (1, 2, 3)] == ["plain"] * 3
+    ens.close()
+
+
+@pytest.mark.parametrize("members,collision,opened,n_steps,us", [
+    # us with the kernel that the estimates chose once, and with the one- and two-step kernels
+    ([_m(768, 306, (300, 100, 9))] * 16, (1.2, 0.9, 1.4), None, 8, (604, 492)),
+    ([_m(512, 163, (300, 50, 9))] * 3, None, None, 2, (27.9, 21.1)),
+    ([_m(399, 68, (300, 30, 9))] * 97, None, None, 2, (111, 79)),
+    ([_m(512, 37, (300, 20, 5))] * 5, (1.0, 1.0, 1.0), (20, 3, 400, 0), 1, (26.4, 19.6)),
+    ([_m(601, 58, (300, 20, 5))] * 437, (1.2, 0.9, 1.4), (20, 3, 400, 0), 3, (1144, 949)),
+])
+def test_batches_that_the_one_and_two_step_kernels_step_faster(members, collision, opened, n_steps, us):
+    """Short batches, whose resident launches mostly load and store the state, and central moments with three
+    rates, whose sweeps take half as long again as other collisions', go to the one- or two-step kernel."""
+    ens = _ensemble(members, 20, None, collision, opened)
+    assert ens.batch_kernel(n_steps)["kernel"] == "plain", us
     ens.close()
