@@ -595,6 +595,9 @@ __device__ __forceinline__ void bsum_out(float bs, float* out, int lane, int nt)
 // SIMDs are full either way and the second copy of the windows costs: 1024
 // images 85 us with two waves, 90 with four; 4096 288 and 303.
 constexpr int BWD_TWO_WAVES = 1024;
+// Four waves hand half of a bias sum over through bhalf, from which the second half starts: right for one image per
+// workgroup only (the images of a group grow with the batch).
+static_assert(cnn_images_per_group(BWD_TWO_WAVES - 1) == 1, "four waves take one image");
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void cnn_backward_kernel(CnnArgs a) {
     constexpr int H = WAVES / 2;  // parts of the output channels (weight gradients) or rows (data gradients)
