@@ -67,10 +67,9 @@ struct SweepArgs {
     double* partial;
     int slot;                // chunk step of the launch's first step
     int flip;
-    int xcd;
+    int full;                // every width is a multiple of 64 SWEEP_CELLS
     int total_blocks;
     int block_waves;         // waves per workgroup
-    int width;               // 0: every width is a multiple of 64 SWEEP_CELLS
     int nseg;
     SweepSegment seg[MAX_SEGMENTS];
 };

@@ -596,6 +596,7 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
     p = SweepPlan();
     SweepArgs& a = p.args;
     a.nseg = c->nseg;
+    a.full = 1;
     a.block_waves = 1;
     int members[MAX_SEGMENTS], tallest = 0;
     double cells = 0.0;
@@ -608,7 +609,7 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
         g.waves = (lanes + 63) / 64;
         g.lanes = (lanes + g.waves - 1) / g.waves;
         a.block_waves = std::max(a.block_waves, g.waves);
-        if (d.nx % (64 * SWEEP_CELLS)) a.width = 1;
+        if (d.nx % (64 * SWEEP_CELLS)) a.full = 0;
         members[s] = listed ? c->n_active : end - g.member_begin;
         tallest = std::max(tallest, d.ny);
         cells += (double)members[s] * d.nx * d.ny;
@@ -643,7 +644,6 @@ static bool plan_sweep(const lbm_ctx* c, SweepPlan& p, bool every_member) {
         blocks += (g.units + g.units_per_block - 1) / g.units_per_block;
     }
     a.total_blocks = blocks;
-    a.xcd = 1;
     a.members = c->d_members;
     a.parity = c->d_parity;
     a.active = c->d_active;

@@ -507,16 +507,11 @@ __device__ __forceinline__ void load_cells(__amdgpu_buffer_rsrc_t rs, unsigned v
         typedef unsigned u3 __attribute__((ext_vector_type(3)));
         const u3 q = __builtin_amdgcn_raw_buffer_load_b96(rs, voff, soff, 0);
         v[0] = __uint_as_float(q.x); v[1] = __uint_as_float(q.y); v[2] = __uint_as_float(q.z);
-    } else if constexpr (C == 4) {
-        const f4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    } else if constexpr (C == 2) {
+    } else {
+        static_assert(C == 2, "cells per lane");
         typedef unsigned u2 __attribute__((ext_vector_type(2)));
         const u2 q = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soff, 0);
         v[0] = __uint_as_float(q.x); v[1] = __uint_as_float(q.y);
-    } else {
-        static_assert(C == 1, "cells per lane");
-        v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
     }
 }
 

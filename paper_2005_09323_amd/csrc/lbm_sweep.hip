@@ -45,29 +45,23 @@
 
 namespace lbm {
 
-template <int C>
-__device__ __forceinline__ void store_cells(__amdgpu_buffer_rsrc_t rd, unsigned voff, unsigned soff, const float v[C]) {
-    if constexpr (C == 4) {
-        __builtin_amdgcn_raw_buffer_store_b128(f4{v[0], v[1], v[2], v[3]}, rd, voff, soff, BUFFER_NT);
-    } else if constexpr (C == 2) {
-        typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(u2{__float_as_uint(v[0]), __float_as_uint(v[1])}, rd, voff, soff, BUFFER_NT);
-    } else {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), rd, voff, soff, BUFFER_NT);
-    }
+static_assert(SWEEP_CELLS == 2, "cells are stored in pairs");
+__device__ __forceinline__ void store_cells(__amdgpu_buffer_rsrc_t rd, unsigned voff, unsigned soff, const float v[SWEEP_CELLS]) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(u2{__float_as_uint(v[0]), __float_as_uint(v[1])}, rd, voff, soff, BUFFER_NT);
 }
 
-// WIDTH: 0 a multiple of 64 C (every lane has its cells), 2 any (lanes beyond
+// FULL: a width that is a multiple of 64 SWEEP_CELLS (every lane has its cells); else any (lanes beyond
 // the width, and the row's last lane may have fewer cells).
 // An iteration has two forms: `plain` while no row of the wave touches a wall
 // or the square, and `special` with all the tests otherwise (registers and scalars of the tests would
 // otherwise be live through every row: 68 scalar spills and their reloads).
-template <int C, int T, int MODEL, int WIDTH>
+template <int T, int MODEL, bool FULL>
 __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void sweep_kernel(SweepArgs a) {
-    constexpr bool RAG = WIDTH == 2, FULL = WIDTH == 0;
+    constexpr int C = SWEEP_CELLS;
     // [parity][boundary][wave][side]: side 0 the wave's first cell (3, 6, 7), side 1 its last (1, 5, 8)
     __shared__ f4 edge[2][T > 1 ? T - 1 : 1][SWEEP_WAVES][2];
-    const int b = a.xcd ? xcd_remap((int)blockIdx.x, a.total_blocks) : (int)blockIdx.x;
+    const int b = xcd_remap((int)blockIdx.x, a.total_blocks);
     int s = 0;
 #pragma unroll 1
     while (s + 1 < a.nseg && b >= a.seg[s + 1].block_begin) ++s;
@@ -102,7 +96,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const bool last_wave = w == W - 1;
     // the wave's last lane with cells, and how many of its cells exist
     const int lastl = FULL ? 63 : last_wave ? (nx - base + C - 1) / C - 1 : sg.lanes - 1;
-    const int rem = RAG && last_wave ? nx - base - C * lastl : C;
+    const int rem = !FULL && last_wave ? nx - base - C * lastl : C;
     // A wave of fewer than 64 lanes works out some columns of the next wave too, the last of them wrongly (nothing
     // enters beside lane 63; one column more with each stage): its surplus lanes write no cell and no drag.
     const bool owns = FULL || lane <= lastl;
@@ -111,7 +105,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     const unsigned vl = 4u * (unsigned)((w == 0 ? nx : base) - 1);     // the column left of the wave (periodic)
     const unsigned vr = 4u * (unsigned)(last_wave ? 0 : base + sg.lanes * C);  // the column right of it
     // stores of the lanes beyond the row go beyond the buffer, which the hardware drops
-    const unsigned vstore = !owns || (RAG && lane == lastl && rem != C) ? 0x80000000u : voff;
+    const unsigned vstore = !owns || (!FULL && lane == lastl && rem != C) ? 0x80000000u : voff;
     const bool sq_cols = m.ss > 0 && base <= m.sx0 + m.ss && base + sg.lanes * C - 1 >= m.sx0 - 1;
     unsigned sqc = 0;                                // bit j: column x0 - 1 + j crosses the square
     if (sq_cols)
@@ -150,7 +144,7 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     };
     // cells of a short last lane: those loaded are the row's last C, move them to its first places
     auto settle = [&](float v[C]) {
-        if constexpr (RAG)
+        if constexpr (!FULL)
 #pragma unroll
             for (int sh = 1; sh < C; ++sh)
 #pragma unroll
@@ -166,12 +160,12 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     auto shift_left = [&](float v[C], float in) {
         const float sh = wave_shl1_in(v[0], in);
 #pragma unroll
-        for (int k = 0; k + 1 < C; ++k) v[k] = RAG && lane == lastl && rem == k + 1 ? in : v[k + 1];
+        for (int k = 0; k + 1 < C; ++k) v[k] = !FULL && lane == lastl && rem == k + 1 ? in : v[k + 1];
         v[C - 1] = FULL ? sh : (lane == lastl ? in : sh);
     };
     auto last_cell = [&](const float v[C]) {
         float r = v[C - 1];
-        if constexpr (RAG)
+        if constexpr (!FULL)
 #pragma unroll
             for (int k = 1; k < C; ++k) r = rem == k ? v[k - 1] : r;
         return r;
@@ -279,8 +273,8 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                     const unsigned skip = solid_row(r) ? (sqc >> 1) & ((1u << C) - 1u) : 0u;
                     const unsigned so = skip == 0u ? vs : 0x80000000u;
 #pragma unroll
-                    for (int i = 0; i < 9; ++i) store_cells<C>(rd, so, 4u * ((unsigned)i * plane + rowoff), p[i]);
-                    if (C > 1 && mine && owns && skip != 0u && skip != (1u << C) - 1u) {
+                    for (int i = 0; i < 9; ++i) store_cells(rd, so, 4u * ((unsigned)i * plane + rowoff), p[i]);
+                    if (mine && owns && skip != 0u && skip != (1u << C) - 1u) {
 #pragma unroll
                         for (int k = 0; k < C; ++k)
                             if (!((skip >> k) & 1u) && x0 + k < nx) {
@@ -290,9 +284,9 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
                     }
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 9; ++i) store_cells<C>(rd, vs, 4u * ((unsigned)i * plane + rowoff), p[i]);
+                    for (int i = 0; i < 9; ++i) store_cells(rd, vs, 4u * ((unsigned)i * plane + rowoff), p[i]);
                 }
-                if constexpr (RAG && C > 1) {  // the short last lane (never next to the square: a fluid column is between)
+                if constexpr (!FULL) {  // the short last lane (never next to the square: a fluid column is between)
 #pragma unroll
                     for (int k = 0; k < C - 1; ++k) {
                         const unsigned so = mine && lane == lastl && rem != C && k < rem ? 4u * (unsigned)(x0 + k) : 0x80000000u;
@@ -401,19 +395,18 @@ __global__ __launch_bounds__(64 * SWEEP_WAVES) __attribute__((amdgpu_waves_per_e
     }
 }
 
-template <int T, int WIDTH>
+template <int T, bool FULL>
 static hipError_t launch_sweep_w(const SweepArgs& a, int model, hipStream_t st) {
-    constexpr int C = SWEEP_CELLS;
     const dim3 grid(a.total_blocks), block(64 * a.block_waves);
-    if (model == 2) hipLaunchKernelGGL((sweep_kernel<C, T, 2, WIDTH>), grid, block, 0, st, a);
-    else if (model == 1) hipLaunchKernelGGL((sweep_kernel<C, T, 1, WIDTH>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((sweep_kernel<C, T, 0, WIDTH>), grid, block, 0, st, a);
+    if (model == 2) hipLaunchKernelGGL((sweep_kernel<T, 2, FULL>), grid, block, 0, st, a);
+    else if (model == 1) hipLaunchKernelGGL((sweep_kernel<T, 1, FULL>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((sweep_kernel<T, 0, FULL>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
 template <int T>
 static hipError_t launch_sweep_t(const SweepArgs& a, int model, hipStream_t st) {
-    return a.width == 0 ? launch_sweep_w<T, 0>(a, model, st) : launch_sweep_w<T, 2>(a, model, st);
+    return a.full ? launch_sweep_w<T, true>(a, model, st) : launch_sweep_w<T, false>(a, model, st);
 }
 
 hipError_t launch_sweep(int steps, const SweepArgs& a, int model, hipStream_t st) {
