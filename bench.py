@@ -149,6 +149,23 @@ def _timed(fn, reps=1):
     return e0.elapsed_time(e1) / reps
 
 
+def pass_pricing(kernel: dict, collision: str):
+    """Steps that share one read and one write of the state, and what bounds them if it is not HBM.
+
+    `kernel` is Ensemble.batch_kernel's description of the timed batch.  A resident batch holds the
+    state in registers for a whole chunk, whatever the number of launches that share the members."""
+    note = None
+    if kernel["kernel"] == "resident":
+        note = ("%d steps per pass over the state: FP64 issue and the exchange between workgroups bound it, "
+                "not HBM" % kernel["steps"])
+    elif kernel["kernel"] == "sweep":
+        note = "%d steps per pass over the state: the FP64 units bound it" % kernel["steps"]
+        if kernel["steps"] == 4 and collision == "bgk":
+            note += " (4.0 of 4.4 us per row of four stages)"
+        note += ", not HBM"
+    return kernel["steps"], note
+
+
 KERNEL_SOURCES = ("common.hpp", "kernels.hpp", "lbm_device.hpp", "lbm_kernels.hip", "lbm_step2.hip", "lbm_sweep.hip", "lbm_resident.hip")
 
 
@@ -231,27 +248,33 @@ def legs():
     torch.cuda.synchronize()
     t_mixed = _timed(lambda: ens.step(256)) / 256
     fluid = sum(m.fluid_cells for m in wl.members)
-    out["mixed_sizes"] = {"workload": wl.name, "steps_per_launch": ens.launch_steps(),
+    kernel = ens.batch_kernel(256)
+    out["mixed_sizes"] = {"workload": wl.name, "kernel": kernel["kernel"], "steps_per_launch": kernel["steps"],
+                          "launches_per_pass": kernel["launches"],
                           "ms_per_step": round(t_mixed, 4), "MLUPS": round(wl.cells / t_mixed / 1e3, 1),
                           "GBs_72B_per_update": round(BYTES_PER_LUP * fluid / t_mixed / 1e6, 1),
                           "nonfinite_members": int(ens.flags().sum().item())}
     ens.close()
     del ens
     torch.cuda.empty_cache()
-    # the same batch with its launch shape tuned, and a row range per lattice size
+    # the same batch with its launch shape tuned, and a row range per lattice size where the kernel has any
     ens = Ensemble(wl.members, series_capacity=300)
     tile = ens.autotune(16)
     ens.init(wl.seed, wl.noise_amp)
     ens.step(20)
     torch.cuda.synchronize()
     t_tuned = _timed(lambda: ens.step(256)) / 256
-    out["mixed_sizes"]["tuned"] = {"tile": tile, "rows_per_workgroup_per_size": ens.run_rows(),
+    kernel = ens.batch_kernel(256)
+    rows = None if kernel["kernel"] == "resident" else ens.run_rows()
+    out["mixed_sizes"]["tuned"] = {"tile": tile, "kernel": kernel["kernel"], "steps_per_launch": kernel["steps"],
+                                   "rows_per_workgroup_per_size": rows,
                                    "ms_per_step": round(t_tuned, 4), "MLUPS": round(wl.cells / t_tuned / 1e3, 1)}
     ens.close()
     del ens
     torch.cuda.empty_cache()
-    # launch-bound batches (an AMS branch re-simulates a handful of members): full 64-step chunks
-    # replayed from a captured HIP graph against launching every kernel of every chunk
+    # small batches (an AMS branch re-simulates a handful of members): full 64-step chunks replayed
+    # from a captured HIP graph, where the kernel is one that is launched for every step or two
+    # (resident launches, one per chunk, are never captured), against launching every kernel
     m = workloads.ams_ensemble().members[0]
     small = {}
     for graphs in (True, False):
@@ -260,14 +283,15 @@ def legs():
         ens.init(1, 1e-3)
         ens.step(64)
         torch.cuda.synchronize()
+        small["kernel"] = ens.batch_kernel(1024)["kernel"]
         small["graphs" if graphs else "launches"] = _timed(lambda: ens.step(1024)) / 1024
         ens.close()
-    out["small_batch"] = {"workload": "16 x 512x128 (AMS branch size)", "ms_per_step_graphs": round(small["graphs"], 5),
+    out["small_batch"] = {"workload": "16 x 512x128 (AMS branch size)", "kernel": small["kernel"],
+                          "ms_per_step_graphs": round(small["graphs"], 5),
                           "ms_per_step_launches": round(small["launches"], 5),
                           "MLUPS_graphs": round(16 * m.cells / small["graphs"] / 1e3, 1),
                           "MLUPS_launches": round(16 * m.cells / small["launches"] / 1e3, 1)}
-    # the paper's open channel (inlet, grid, sponge, outlet ghost column), central moments:
-    # one step per launch plus the small ghost-column launch
+    # the paper's open channel (inlet, grid, sponge, outlet ghost column), central moments
     wl = workloads.open_channel()
     op = wl.extra["open"]
     ens = Ensemble(wl.members, series_capacity=301)
@@ -278,11 +302,13 @@ def legs():
     torch.cuda.synchronize()
     t_open = _timed(lambda: ens.step(256))
     fluid = sum(m.fluid_cells for m in wl.members) - len(wl.members) * _grid_cells(wl.members[0], op)
-    gbs = BYTES_PER_LUP * fluid * 256 / (t_open / 1e3) / 1e9
+    kernel = ens.batch_kernel(256)
     out["open_channel"] = {"workload": wl.name, "collision": "central", "steps": 256,
+                           "kernel": kernel["kernel"], "steps_per_launch": kernel["steps"],
+                           "launches_per_pass": kernel["launches"],
                            "ms_per_step": round(t_open / 256, 4),
                            "MLUPS": round(wl.cells * 256 / (t_open / 1e3) / 1e6, 1),
-                           "GBs_per_step_72B": round(gbs, 1), "frac_of_peak": round(gbs / HBM_PEAK_GBS, 4),
+                           "GBs_72B_per_update": round(BYTES_PER_LUP * fluid * 256 / t_open / 1e6, 1),
                            "nonfinite_members": int(ens.flags().sum().item())}
     ens.close()
     return out
@@ -375,7 +401,7 @@ def main():
     ap.add_argument("--workload", default="ensemble", choices=["ensemble", "mixed", "single", "open"])
     ap.add_argument("--tile", type=int, default=None,
                     help="lattice launch shape (-1: autotune; default: 20, the library's own choice, for the ensemble "
-                         "workload, whose launches make a known number of steps; 16 for the others)")
+                         "workload; 16, two steps per launch or one, for the others)")
     ap.add_argument("--cpu-steps", type=int, default=800, help="oracle steps for the CPU baseline (0: skip)")
     ap.add_argument("--traffic-json", default=os.path.join(ROOT, "profiles", "sweep_kernel_ensemble1024_traffic.json"))
     ap.add_argument("--mode", default="bench", choices=["bench", "copy", "score-scaling", "open-parts"],
@@ -448,13 +474,11 @@ def main():
     if op is not None:
         fluid -= len(wl.members) * _grid_cells(wl.members[0], op)
     mlups = cells * args.steps / sec / 1e6
-    # the dominant kernel moves the state through HBM once per launch (72 B per
+    # the dominant kernel moves the state through HBM once per pass (72 B per
     # fluid cell) and makes `per_launch` lattice steps doing so
-    # (the default shape steps the ensemble workload with the sweep kernel: four steps per launch, and
-    # launch_steps() says at least how many)
-    swept = tile == 20 and args.workload == "ensemble"
-    per_launch = 4 if swept else ens.launch_steps()
-    launch_s = sec / args.steps * per_launch           # per launch, chunk reductions (0.15 %) included
+    kernel = ens.batch_kernel(args.steps)
+    per_launch, note = pass_pricing(kernel, args.collision)
+    launch_s = sec / args.steps * per_launch           # per pass, chunk reductions (0.15 %) included
     achieved = BYTES_PER_LUP * fluid / launch_s / 1e9  # GB/s
     equiv = BYTES_PER_LUP * fluid * args.steps / sec / 1e9
     flags = int(ens.flags().sum().item())
@@ -466,6 +490,7 @@ def main():
         tj = json.load(open(args.traffic_json))
         same_kernel = kernel_sources_sha256().startswith(tj.get("kernel_sources_sha256_prefix", "-"))
         if (tj.get("workload") == wl.name and same_kernel and tile == tj.get("tile_id")
+                and tj.get("kernel", "").startswith("sweep") == (kernel["kernel"] == "sweep")
                 and args.collision == tj.get("collision", "bgk")):
             traffic = tj.get("bytes_per_launch")
 
@@ -485,13 +510,12 @@ def main():
                 + ("at rest" if op is None else "with the inlet profile"),
         "config": {"workload": wl.name, "members": len(wl.members),
                    "cells_per_step": cells, "fluid_cells_per_step": fluid,
-                   "tile_id": tile, "collision": args.collision, "nonfinite_members": flags,
+                   "tile_id": tile, "kernel": kernel["kernel"], "collision": args.collision, "nonfinite_members": flags,
                    "wall_s": round(wall, 3)},
         "settle": settle,
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                     **({"note": "four steps per pass: the FP64 units bound it (4.0 of 4.4 us per row of four "
-                                 "stages), not HBM"} if swept else {})},
+                     **({"note": note} if note else {})},
         # the same throughput priced at one HBM round trip per lattice step (72 B per fluid-cell update)
         "lup_equivalent": {"steps_per_launch": per_launch, "bytes_per_lup": BYTES_PER_LUP,
                            "GBs": round(equiv, 1), "frac_of_peak": round(equiv / HBM_PEAK_GBS, 4)},
