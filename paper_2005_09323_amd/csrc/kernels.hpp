@@ -183,7 +183,7 @@ struct TileShape {
     int r;      // rows per wave (a tile is 256 columns by tyt * r rows); 1 for two-step shapes
     int xcd;    // 1: remap workgroups so each XCD gets a contiguous range of tiles
     int steps;  // lattice steps per launch: 1, or 2 (a strip of 256 columns swept bottom to top)
-    int adaptive;  // chooses between the sweep, the two-step kernel and shape 0 by the active members
+    int adaptive;  // chooses between the resident kernel, the sweep, the two-step kernel and shape 0 by the active members
     int seg_rows;  // two-step shapes: rows per workgroup (0: whole strips; -1: split only when
                    // the strips alone leave workgroup slots empty)
 };

@@ -537,8 +537,8 @@ static hipError_t launch_step_t(const StepArgs& a, int model, hipStream_t st) {
 // wave, whether workgroups are remapped so each XCD gets contiguous tiles,
 // and steps per launch.  Ids 0-15 are one-step shapes (launch_step switches
 // on id % 8); ids 16-19 are the two-step kernel with TYT rows per iteration;
-// ids 21-23 are shape 16 with shorter strips, and id 20 takes the sweep kernel (up to four steps
-// per launch), shape 16 or shape 0 by what the active members give.
+// ids 21-23 are shape 16 with shorter strips, and id 20 takes the resident kernel (a chunk of steps
+// per launch), the sweep kernel (up to four), shape 16 or shape 0, by estimated times of the active members.
 const TileShape TILE_SHAPES[] = {
     {4, 1, 1, 1, 0}, {4, 2, 1, 1, 0}, {8, 1, 1, 1, 0}, {2, 2, 1, 1, 0},
     {16, 1, 1, 1, 0}, {1, 4, 1, 1, 0}, {4, 4, 1, 1, 0}, {8, 2, 1, 1, 0},
